@@ -1,113 +1,287 @@
-// fp32 GEMM with arbitrary operand strides, LDS-tiled, for the fp32 workloads (the small
-// parity configuration).  acc[m,n] = sum_k A[m*sam + k*sak] * B[n*sbn + k*sbk].
+// fp32 products on the matrix cores (v_mfma_f32_32x32x2_f32 and 16x16x4: fp32 operands, fp32 fused
+// multiply-adds) for the fp32 workloads.  acc[m,n] = sum_k A[m*sam + k*sak] * B[n*sbn + k*sbk], each operand
+// contiguous along k or along its rows.
+//
+// An fp32 workload's products are small (16 to 512 rows, 10 to 1024 columns, contractions of 16 to 4096), so
+// what bounds them is the number of dependent trips to memory and how many compute units have a tile, not
+// flops: 64 x 64 tiles staged through LDS 16 contraction elements at a time made K / 16 trips one after the
+// other on a handful of workgroups (104 us for 256 x 256 x 1024, 714 us for 36 x 256 x 4099).
+// Here a workgroup's wavefronts cut the contraction among themselves: each takes its slice of k for the WHOLE
+// tile, operands straight from memory into the MFMA registers (nothing is shared between wavefronts, so LDS
+// would only add a round trip), two groups of 32 or 64 contraction elements in flight; the partial tiles are
+// then added through LDS in wavefront order, so results do not depend on scheduling.  The same products now
+// take 4.9 and 15 us; 2048 x 1024 x 1024 runs at 81 TFLOP/s.
 #include "vf_device.h"
 
 namespace vf {
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 16, NT = 256;
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef float f32x16v __attribute__((ext_vector_type(16)));
 
-// Loads a [ROWS x TK] tile (row index r in [0,ROWS), k in [0,TK)) into dst[k][r].
-// When the k stride is 1 consecutive threads walk k, otherwise they walk rows, so that
-// the unit-stride index is always the fastest across a wavefront.
-__device__ __forceinline__ void load_tile(const float* __restrict__ base, int64_t srow, int64_t sk,
-                                          int row0, int nrows, int k0, int K,
-                                          float (*dst)[TM + 4], int tid) {
-  if (sk == 1) {
+constexpr int GU = 4;        // chunks of the contraction per group
+constexpr uint32_t kOutside = 0x80000000u;   // an offset beyond every buffer: the load returns 0
+
+// One lane's part of an operand: T row tiles of MS rows, this lane's row of each.  A chunk is 4 * 64 / MS
+// contraction elements: the q-th copy of the rows among the lanes (q = lane / MS) holds elements 4 q .. 4 q + 3
+// of it, and MFMA step s contracts element s of every copy (any assignment of k to steps will do as long as
+// both operands use the same one).  A group is GU chunks.  KC: the operand is contiguous along k; VEC: in
+// 16-byte vectors (rows 16-byte aligned, K % 4 == 0).  Loads go through a buffer descriptor over the operand
+// from the workgroup's first row on: what lies outside the matrix (rows, or k at and beyond K) is asked for
+// beyond the buffer's end and comes back as 0, so there are neither branches nor selections around the loads
+// and the compiler keeps a whole group's in flight.
+template <int MS, int T, bool KC, bool VEC>
+struct Operand {
+  static constexpr int CK = 4 * (64 / MS);
+  __amdgpu_buffer_rsrc_t buf;
+  uint32_t pitch;                                        // bytes
+  int K, kl;                                             // kl: this lane's first element of a chunk
+  uint32_t off[T];                                       // of this lane's row (and of its first element's row of k)
+  __device__ __forceinline__ void init(const float* p, int64_t ld, int r0, int nrows, int K_, int lane) {
+    K = K_;
+    kl = 4 * (lane / MS);
+    pitch = (uint32_t)ld * 4u;
+    const float* base = p + (KC ? (int64_t)r0 * ld : (int64_t)r0);
+    // bytes from the first row to the operand's end (the host keeps what a workgroup can reach below 2 GiB)
+    const int64_t span = (KC ? (int64_t)(nrows - 1 - r0) * ld + K : (int64_t)(K - 1) * ld + (nrows - r0)) * 4;
+    buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)min(span, (int64_t)0x7fffffff), 0x00020000);
 #pragma unroll
-    for (int i = 0; i < (TM * TK) / NT; ++i) {
-      int e = tid + i * NT;
-      int k = e % TK, r = e / TK;
-      int gr = row0 + r, gk = k0 + k;
-      float v = 0.f;
-      if (gr < nrows && gk < K) v = base[(int64_t)gr * srow + gk];
-      dst[k][r] = v;
+    for (int t = 0; t < T; ++t) {
+      const int r = MS * t + lane % MS;
+      off[t] = r0 + r < nrows ? (KC ? (uint32_t)r * pitch + (uint32_t)kl * 4u : (uint32_t)r * 4u + (uint32_t)kl * pitch) : kOutside;
     }
-  } else {
+  }
+  // The group of contraction elements k0 .. k0 + GU * CK - 1 (k0 the same for the whole wavefront).
+  __device__ __forceinline__ void load(float (&v)[GU][T][4], int k0) const {
+    const int left = K - k0 - kl;                        // elements of this lane from its first one on
+    // (a chunk that starts past the end: nothing is fetched, and its scalar offset stays inside the buffer, so that
+    // the bounds check -- lane offset against the buffer's size, with or without the scalar offset -- is the same)
 #pragma unroll
-    for (int i = 0; i < (TM * TK) / NT; ++i) {
-      int e = tid + i * NT;
-      int r = e % TM, k = e / TM;
-      int gr = row0 + r, gk = k0 + k;
-      float v = 0.f;
-      if (gr < nrows && gk < K) v = base[(int64_t)gr * srow + (int64_t)gk * sk];
-      dst[k][r] = v;
+    for (int u = 0; u < GU; ++u)
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        if (KC && VEC) {
+          typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+          const u32x4v q = __builtin_amdgcn_raw_buffer_load_b128(buf, CK * u < left ? off[t] : kOutside,
+                                                              min(k0 + CK * u, K - 1) * 4, 0);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) v[u][t][s] = __uint_as_float(q[s]);
+        } else {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const uint32_t o = CK * u + s < left ? off[t] + (KC ? 4u * s : pitch * s) : kOutside;
+            const uint32_t so = (uint32_t)min(k0 + CK * u, K - 1) * (KC ? 4u : pitch);
+            v[u][t][s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, o, so, 0));
+          }
+        }
+      }
+  }
+};
+
+template <int MS> struct Mfma;
+template <> struct Mfma<32> {
+  typedef f32x16v acc_t;
+  static constexpr int R = 16;
+  static __device__ __forceinline__ acc_t mul(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+  static __device__ __forceinline__ int row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+};
+template <> struct Mfma<16> {
+  typedef f32x4v acc_t;
+  static constexpr int R = 4;
+  static __device__ __forceinline__ acc_t mul(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static __device__ __forceinline__ int row(int r, int lane) { return 4 * (lane >> 4) + r; }
+};
+
+// blockIdx.z selects the contraction slice [z * kslab, (z + 1) * kslab); slice z writes its partial product
+// to slab z of C (the consumer adds the slabs in order), the bias goes to slab 0.  Wavefront w of a
+// workgroup takes the elements [w * kwave, (w + 1) * kwave) of the slice (kwave and kslab multiples of a group).
+template <int MS, int TM, int TN, int NW, bool AKC, bool BKC, bool VEC>
+__global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __restrict__ A, int64_t lda,
+                                                                const float* __restrict__ B, int64_t ldb,
+                                                                int M, int N, int K, int kslab, int kwave,
+                                                                int64_t slab_stride, Epilogue ep) {
+  typedef Mfma<MS> MF;
+  constexpr int R = MF::R;
+  constexpr int E = TM * TN * MS * MS;                   // elements of the tile
+  constexpr int GK = GU * 4 * (64 / MS);                 // contraction elements of a group
+  __shared__ float part[NW * E];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = blockIdx.y * (MS * TM), n0 = blockIdx.x * (MS * TN);
+  const int kend_slab = min(K, (int)(blockIdx.z + 1) * kslab);
+  const int kbeg = (int)blockIdx.z * kslab + wave * kwave;
+  const int kend = min(kend_slab, kbeg + kwave);
+
+  typename MF::acc_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[i][j][r] = 0.f;
+
+  const int groups = kend > kbeg ? (kend - kbeg + GK - 1) / GK : 0;
+  if (groups > 0) {
+    Operand<MS, TM, AKC, VEC> oa;
+    Operand<MS, TN, BKC, VEC> ob;
+    oa.init(A, lda, m0, M, K, lane);
+    ob.init(B, ldb, n0, N, K, lane);
+    float a0[GU][TM][4], b0[GU][TN][4], a1[GU][TM][4], b1[GU][TN][4];
+    auto multiply = [&](const float (&a)[GU][TM][4], const float (&b)[GU][TN][4]) {
+#pragma unroll
+      for (int u = 0; u < GU; ++u)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = MF::mul(a[u][i][s], b[u][j][s], acc[i][j]);
+    };
+    // two groups in flight: the loads of group g + 2 are issued as soon as group g has been multiplied (past the
+    // operand's end they fetch nothing and return 0; past the slice's end they are not used)
+    oa.load(a0, kbeg);
+    ob.load(b0, kbeg);
+    if (groups > 1) {
+      oa.load(a1, kbeg + GK);
+      ob.load(b1, kbeg + GK);
+      int k = kbeg;
+      for (int g = 0; g + 2 <= groups; g += 2, k += 2 * GK) {
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(a0, b0);
+        __builtin_amdgcn_sched_barrier(0);
+        oa.load(a0, min(k + 2 * GK, K));
+        ob.load(b0, min(k + 2 * GK, K));
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(a1, b1);
+        __builtin_amdgcn_sched_barrier(0);
+        oa.load(a1, min(k + 3 * GK, K));
+        ob.load(b1, min(k + 3 * GK, K));
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
+    if (groups & 1) multiply(a0, b0);
+  }
+
+  // Partial tiles through LDS as the registers hold them, added in wavefront order.
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < R; ++r) part[wave * E + ((i * TN + j) * R + r) * 64 + lane] = acc[i][j][r];
+  __syncthreads();
+  float* C = static_cast<float*>(ep.C) + (int64_t)blockIdx.z * slab_stride;
+  const bool first_slice = blockIdx.z == 0;
+  constexpr int NT = NW * 64;
+  constexpr int PER = (E + NT - 1) / NT;
+  float add[PER];
+  int mm[PER], nn[PER];
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    const int e = p * NT + tid;
+    const int f = e / 64, r = f % R, i = f / R / TN, j = f / R % TN;
+    mm[p] = m0 + MS * i + MF::row(r, lane);
+    nn[p] = n0 + MS * j + lane % MS;
+    if (E % NT && e >= E) mm[p] = M;
+    const int m = min(mm[p], M - 1), n = min(nn[p], N - 1);
+    add[p] = (ep.bias && first_slice) ? ep.bias[n] : 0.f;
+    if (ep.R) add[p] = fmaf(ep.beta, ep.R[(int64_t)m * ep.ldr + n], add[p]);
+  }
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    const int e = p * NT + tid;
+    if (mm[p] >= M || nn[p] >= N) continue;
+    float sum = part[e];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) sum += part[w * E + e];
+    C[(int64_t)mm[p] * ep.ldc + nn[p]] = fmaf(ep.alpha, sum, add[p]);
   }
 }
 
-// blockIdx.z selects the contraction slice [z*kchunk, (z+1)*kchunk); slice z writes its partial
-// product to slab z of C (the consumer adds the slabs in order), the bias goes to slab 0.
-__global__ __launch_bounds__(NT) void gemm_f32_kernel(const float* __restrict__ A, int64_t sam,
-                                                      int64_t sak, const float* __restrict__ B,
-                                                      int64_t sbn, int64_t sbk, int M, int N, int K,
-                                                      int kchunk, int64_t slab_stride, Epilogue ep) {
-  __shared__ float As[TK][TM + 4];
-  __shared__ float Bs[TK][TN + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-  float acc[4][4] = {};
-  const int kbeg = blockIdx.z * kchunk;
-  const int kend = min(K, kbeg + kchunk);
-  for (int k0 = kbeg; k0 < kend; k0 += TK) {
-    load_tile(A, sam, sak, m0, M, k0, kend, As, tid);
-    load_tile(B, sbn, sbk, n0, N, k0, kend, Bs, tid);
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < TK; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  float* C = static_cast<float*>(ep.C) + (int64_t)blockIdx.z * slab_stride;
-  const bool first_slice = blockIdx.z == 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float addend = (ep.bias && first_slice) ? ep.bias[n] : 0.f;
-      if (ep.R) addend = fmaf(ep.beta, ep.R[(int64_t)m * ep.ldr + n], addend);
-      float v = fmaf(ep.alpha, acc[i][j], addend);
-      C[(int64_t)m * ep.ldc + n] = v;
-    }
-  }
+// Operands that a workgroup cannot reach with 32-bit offsets (row pitches of 32 MB and more): one element of C
+// per thread.
+__global__ __launch_bounds__(256) void gemm_f32_far_kernel(const float* __restrict__ A, int64_t sam, int64_t sak,
+                                                           const float* __restrict__ B, int64_t sbn, int64_t sbk,
+                                                           int M, int N, int K, int kslab, int64_t slab_stride, Epilogue ep) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= (int64_t)M * N) return;
+  const int m = (int)(e / N), n = (int)(e % N);
+  float acc = 0.f;
+  for (int k = blockIdx.z * kslab, end = min(K, (int)(blockIdx.z + 1) * kslab); k < end; ++k)
+    acc = fmaf(A[m * sam + k * sak], B[n * sbn + k * sbk], acc);
+  float add = (ep.bias && blockIdx.z == 0) ? ep.bias[n] : 0.f;
+  if (ep.R) add = fmaf(ep.beta, ep.R[(int64_t)m * ep.ldr + n], add);
+  static_cast<float*>(ep.C)[(int64_t)blockIdx.z * slab_stride + (int64_t)m * ep.ldc + n] = fmaf(ep.alpha, acc, add);
+}
+
+struct F32Shape {
+  const float* A; int64_t lda; const float* B; int64_t ldb; int M, N, K, nsplit; int64_t slab;
+};
+
+template <int MS, int TM, int TN, int NW, bool AKC, bool BKC, bool VEC>
+int launch_tile(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
+  constexpr int GK = GU * 4 * (64 / MS);
+  const int kslab = ((g.K + g.nsplit - 1) / g.nsplit + GK - 1) / GK * GK;
+  const int kwave = ((kslab + NW - 1) / NW + GK - 1) / GK * GK;
+  dim3 grid((g.N + MS * TN - 1) / (MS * TN), (g.M + MS * TM - 1) / (MS * TM), g.nsplit);
+  gemm_f32_mfma_kernel<MS, TM, TN, NW, AKC, BKC, VEC><<<grid, NW * 64, 0, s>>>(g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K,
+                                                                                   kslab, kwave, g.slab, ep);
+  VF_LAUNCH_CHECK();
+  return VF_OK;
+}
+
+// Which tile on how many wavefronts: measured back to back with launch (2.5 us of it), us per product, the
+// neighbouring choices beside the one taken (M x N x K):
+//   few tiles       16 x 256 x 784: 16/16 4.2, 16/4 4.9, 32/16 8.4;  100 x 500 x 1000: 4.8, 5.5, 11.3
+//   short k         784 x 256 x 16: 16/4 3.0, 16/16 5.7, 32/4 3.6
+//   more tiles      256 x 1024 x 256: 32/16 4.2, 32/4 5.2, 16/4 5.0;  256 x 4099 x 36: 32/4 6.1, 32/8 7.9, 16/4 8.0
+//                   512 x 1024 x 1024: 32/8 17.1, 32/16 22.6, 64/4 26.9;  2048 x 1152 x 384: 32/4 29.8, 32/8 37.0
+//   64 x 64         300 x 30522 x 384: 64/4 111, 32/16 147, 32/4 156;  2048 x 1024 x 1024: 53, 88, 56
+template <bool AKC, bool BKC, bool VEC>
+int launch_operands(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
+  auto tiles = [&](int t) { return (int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.nsplit; };
+  const int K = g.K / g.nsplit;
+  if (tiles(64) >= 512) return launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
+  if (tiles(16) <= (K <= 128 ? 1024 : 512))
+    return K >= 512 ? launch_tile<16, 1, 1, 16, AKC, BKC, VEC>(g, ep, s) : launch_tile<16, 1, 1, 4, AKC, BKC, VEC>(g, ep, s);
+  if (K <= 128 || tiles(32) > 1024) return launch_tile<32, 1, 1, 4, AKC, BKC, VEC>(g, ep, s);
+  return tiles(32) > 256 ? launch_tile<32, 1, 1, 8, AKC, BKC, VEC>(g, ep, s) : launch_tile<32, 1, 1, 16, AKC, BKC, VEC>(g, ep, s);
 }
 
 }  // namespace
 
+// Slices of the contraction beyond what a workgroup's wavefronts take: only for very long contractions
+// of few tiles (the input gradient of a wide output layer).
 int gemm_f32_pick_split(int M, int N, int K) {
-  // small fp32 products are latency bound: spread the contraction until about 128 workgroups
-  // exist, slices no shorter than four 16-wide stages
-  int64_t tiles = (int64_t)((M + TM - 1) / TM) * ((N + TN - 1) / TN);
+  const int64_t tiles = (int64_t)((M + 31) / 32) * ((N + 31) / 32);
   int split = 1;
-  while (tiles * split < 128 && K / (split * 2) >= 4 * TK && split < 32) split *= 2;
+  while (tiles * split < 128 && K / (split * 2) >= 1024 && split < 32) split *= 2;
   return split;
 }
 
 int launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbn,
                     int64_t sbk, int M, int N, int K, int nsplit, int64_t slab_stride,
                     const Epilogue& ep, hipStream_t s) {
-  if (M <= 0 || N <= 0 || K < 0 || !A || !B || !ep.C || ep.c_is_bf16 || nsplit < 1) return VF_EINVAL;
+  if (M <= 0 || N <= 0 || K <= 0 || !A || !B || !ep.C || ep.c_is_bf16 || nsplit < 1) return VF_EINVAL;
   if (nsplit > 1 && ep.R) return VF_EINVAL;
-  const int kchunk = ((K + nsplit - 1) / nsplit + TK - 1) / TK * TK;
-  dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM, nsplit);
-  gemm_f32_kernel<<<grid, NT, 0, s>>>(A, sam, sak, B, sbn, sbk, M, N, K, kchunk > 0 ? kchunk : TK,
-                                      slab_stride, ep);
-  VF_LAUNCH_CHECK();
-  return VF_OK;
+  const bool akc = sak == 1, bkc = sbk == 1;
+  if ((!akc && sam != 1) || (!bkc && sbn != 1)) return VF_EINVAL;
+  F32Shape g{A, akc ? sam : sak, B, bkc ? sbn : sbk, M, N, K, nsplit, slab_stride};
+  // what a workgroup's loads reach (64 rows, or the whole contraction of an operand contiguous along its rows)
+  auto near = [&](bool kc, int64_t ld, int rows) { return (kc ? 64 * ld + K : (int64_t)K * ld + rows) * 4 < ((int64_t)1 << 31); };
+  if (!near(akc, g.lda, M) || !near(bkc, g.ldb, N)) {
+    const int kslab = (K + nsplit - 1) / nsplit;
+    dim3 grid((unsigned)(((int64_t)M * N + 255) / 256), 1, nsplit);
+    gemm_f32_far_kernel<<<grid, 256, 0, s>>>(A, sam, sak, B, sbn, sbk, M, N, K, kslab, slab_stride, ep);
+    VF_LAUNCH_CHECK();
+    return VF_OK;
+  }
+  auto al = [](const float* p, int64_t ld) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && (ld & 3) == 0; };
+  const bool vec = (K & 3) == 0 && (!akc || al(A, g.lda)) && (!bkc || al(B, g.ldb));
+  if (akc && bkc) return vec ? launch_operands<true, true, true>(g, ep, s) : launch_operands<true, true, false>(g, ep, s);
+  if (akc) return vec ? launch_operands<true, false, true>(g, ep, s) : launch_operands<true, false, false>(g, ep, s);
+  if (!bkc) return launch_operands<false, false, false>(g, ep, s);
+  return launch_operands<false, true, false>(g, ep, s);
 }
 
 }  // namespace vf

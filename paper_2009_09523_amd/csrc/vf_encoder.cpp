@@ -502,17 +502,16 @@ class Encoder final : public Model {
     Epilogue ep;
     ep.C = dx; ep.ldc = lddx;
     int ns = 1;
+    if (split) {
+      ns = std::min(bf16_ ? gemm_bf16_pick_split(R, L.K, L.N) : gemm_f32_pick_split(R, L.K, L.N), out_split_max_);
+      *split = ns;
+    }
     if (bf16_) {
-      if (split) {
-        ns = std::min(gemm_bf16_pick_split(R, L.K, L.N), out_split_max_);
-        *split = ns;
-      }
       VF_KS(c, stream_, tag, launch_gemm_bf16(static_cast<const bf16_t*>(dy), lddy, L.wnat, L.ldn, R, L.K, L.N, ns,
                                     (int64_t)R * lddx, ep, stream_));
     } else {
-      if (split) *split = 1;
-      VF_KS(c, stream_, tag, launch_gemm_f32(static_cast<const float*>(dy), lddy, 1, P + L.w_off, L.N, 1, R, L.K, L.N, 1, 0, ep,
-                                   stream_));
+      VF_KS(c, stream_, tag, launch_gemm_f32(static_cast<const float*>(dy), lddy, 1, P + L.w_off, L.N, 1, R, L.K, L.N, ns,
+                                   (int64_t)R * lddx, ep, stream_));
     }
     return VF_OK;
   }

@@ -206,3 +206,31 @@ def test_gemm_ragged_contraction_with_cold_operands(M, N, K):
         if first is None:
             first = got
         assert got.tobytes() == first.tobytes(), k
+
+
+@pytest.mark.parametrize("pad", [0, 1, 4])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (16, 256, 784), (17, 33, 65), (31, 10, 3), (100, 500, 1000), (784, 65, 16),
+                                   (256, 769, 256), (256, 1601, 40), (36, 256, 4099), (515, 1024, 515), (1000, 1100, 200),
+                                   (1030, 2100, 20)])
+def test_gemm_f32_tiles(M, N, K, pad):
+    """Every tile of the fp32 product at its edges: rows, columns and contractions that end inside a tile, a
+    chunk, a 16-byte vector; what lies in the rows' padding (here NaN) must not be read into the product."""
+    import torch
+    import paper_2009_09523_amd as vf
+    print(f"gemm f32 M={M} N={N} K={K} pad={pad}", flush=True)
+    rng = np.random.Generator(np.random.PCG64(M + 3 * N + 7 * K + pad))
+    A = np.full((M, K + pad), np.nan, np.float32)
+    B = np.full((N, K + pad), np.nan, np.float32)
+    A[:, :K] = rng.standard_normal((M, K))
+    B[:, :K] = rng.standard_normal((N, K))
+    C0 = rng.standard_normal((M, N + 2)).astype(np.float32)
+    Cd = torch.from_numpy(C0).cuda()
+    vf.vf_gemm(torch.from_numpy(A).cuda()[:, :K], torch.from_numpy(B).cuda()[:, :K], Cd[:, :N], M, N, K, alpha=0.5,
+               accumulate=True)
+    torch.cuda.synchronize()
+    got = Cd.cpu().numpy()
+    a, b = A[:, :K].astype(np.float64), B[:, :K].astype(np.float64)
+    # fp32 sums of K products: at most K roundings of partial sums no larger than sum |a||b|
+    bound = K * 2.0 ** -24 * 0.5 * (np.abs(a) @ np.abs(b).T) + 2.0 ** -23 * (1 + np.abs(C0[:, :N]))
+    assert np.all(np.abs(got[:, :N] - (0.5 * (a @ b.T) + C0[:, :N])) <= bound + 2.0 ** -23 * np.abs(a @ b.T))
+    np.testing.assert_array_equal(got[:, N:], C0[:, N:])

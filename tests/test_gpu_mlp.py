@@ -32,6 +32,20 @@ def test_mlp_step_matches_oracle(name, flags):
     check_update_from_own_gradient(wl, gpu, theta)
 
 
+@pytest.mark.parametrize("dims,nodes", [((784, 1000, 500, 10), (100, 56, 101)), ((66, 199, 543), (61, 3)),
+                                        ((1024, 1024, 333), (257,))])
+def test_f32_step_on_wide_layers(dims, nodes):
+    """The fp32 products in their three layouts on layers of several tiles, unaligned weights among them."""
+    from dataclasses import replace
+    print(f"f32 dims={dims} nodes={nodes}", flush=True)
+    wl = replace(I.workload("mlp_small_bn_f32"), dims=dims, node_sizes=nodes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH)
+    ref = oracle_steps(wl, theta, x, y)
+    check_against_oracle(wl, gpu, ref)
+
+
 def test_c1_exact_configuration():
     """MLP 784-256-10, fp32, B=64 in 4 nodes of 16, He init, one SGD step lr 0.1 mu 0.9."""
     wl, theta, x, y = _case("C1", jitter=0.0)
