@@ -404,8 +404,9 @@ __global__ __launch_bounds__(NT) void gemm_bf16_pipe_kernel(const bf16_t* __rest
 // (chunk c of row r at position c ^ f(r), f(r) = (r & 7) ^ ((r >> 3) & 1)): the 16-byte reads of
 // the MFMA operands (32 rows, one chunk index) then spread over all banks.  The permutation is
 // applied on the global side: a lane fetches the chunk that belongs at its position.
-// Requires a contraction that is a whole number of 64-element stages per slice (operand rows
-// are clamped into the matrix, their products never stored; nothing is masked).
+// A contraction slice's elements beyond its whole 64-element stages come first, through registers
+// and masked (one stage without overlap, about 1 us); operand rows are clamped into the matrix,
+// their products never stored.
 __device__ __forceinline__ int dl_swizzle(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
 //
@@ -492,7 +493,31 @@ __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restri
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   const int arow = wm * 32 + (lane & 31), brow = wn * 32 + (lane & 31);
   const int asw = dl_swizzle(arow), bsw = dl_swizzle(brow);
+  auto multiply = [&](int slot) {
+    const bf16_t* as = &lds[slot * STAGE];
+    const bf16_t* bs = as + TILE;
+#pragma unroll
+    for (int kk = 0; kk < BK / 16; ++kk) {
+      const int cidx = 2 * kk + (lane >> 5);
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(&as[arow * BK + ((cidx ^ asw) * 8)]);
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(&bs[brow * BK + ((cidx ^ bsw) * 8)]);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+    }
+  };
 
+  const int ktail = kbeg + nstage * BK;
+  if (!CONV && ktail < kend) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int row = (wave * 2 + q) * 8 + (lane >> 3);
+      const int k = ktail + ((lane & 7) ^ dl_swizzle(row)) * 8;
+      *reinterpret_cast<u32x4*>(&lds[row * BK + (lane & 7) * 8]) = load_vec(A, lda, m0 + row, M, k, kend);
+      *reinterpret_cast<u32x4*>(&lds[TILE + row * BK + (lane & 7) * 8]) = load_vec(B, ldb, n0 + row, N, k, kend);
+    }
+    __syncthreads();
+    multiply(0);
+    __syncthreads();
+  }
   if (nstage > 0) {
     // NS-1 stages in flight (indices past the end repeat the last stage into a free slot: never
     // read, they only keep the count of outstanding loads uniform)
@@ -501,21 +526,14 @@ __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restri
     for (int it = 0; it < nstage; ++it) {
       // loads complete in order: stage `it` has landed when at most NS-2 stages are outstanding
       wait_loads_but<(NS - 2) * LPS>();
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (this wave's reads of stage it-1 have returned)
       // every wave's part of stage `it` is in LDS, and every wave is done reading stage it-1,
       // whose slot the next loads overwrite.  (A bare barrier: the loop issues no LDS stores, and
       // __syncthreads would wait for ALL outstanding loads.)
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       issue(min(it + NS - 1, nstage - 1), (it + NS - 1) % NS);
-      const bf16_t* as = &lds[(it % NS) * STAGE];
-      const bf16_t* bs = as + TILE;
-#pragma unroll
-      for (int kk = 0; kk < BK / 16; ++kk) {
-        const int cidx = 2 * kk + (lane >> 5);
-        const bf16x8 a = *reinterpret_cast<const bf16x8*>(&as[arow * BK + ((cidx ^ asw) * 8)]);
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(&bs[brow * BK + ((cidx ^ bsw) * 8)]);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-      }
+      multiply(it % NS);
     }
     wait_loads_but<0>();
   }
@@ -545,8 +563,8 @@ __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restri
 // Workgroup numbering: XCD x (workgroup index modulo 8) takes a contiguous run of the tile order
 // "eight row tiles down, then one column right", so the 32 tiles that run side by side on one
 // XCD form an 8 x 4 block sharing 8 + 4 operand panels on that XCD's L2.
-// Requires whole stages in every contraction slice; operand rows are clamped into the matrix
-// (their products never stored).
+// A slice's elements beyond its whole stages come first, through registers and masked; operand rows
+// are clamped into the matrix (their products never stored).
 // One LDS-direct load of 16 bytes per lane: global address = scalar base + 32-bit lane offset, LDS
 // address (wavefront-uniform; lane l lands 16 l bytes behind it) through M0.  No destination
 // register: the data is in LDS when the wavefront's vmcnt says so.
@@ -637,6 +655,32 @@ __global__ __launch_bounds__(512) void gemm_bf16_wide_kernel(const bf16_t* __res
 #pragma unroll
   for (int j = 0; j < TN; ++j) { brow[j] = wn * (BN / 2) + j * 32 + (lane & 31); bsw[j] = wide_swizzle<KS>(brow[j]); }
 
+  const int ktail = kbeg + nstage * KS;
+  if (ktail < kend) {
+#pragma unroll
+    for (int q = 0; q < LPS; ++q) {
+      const bool of_a = q < AL;
+      const int row = (wave + 8 * (of_a ? q : q - AL)) * RPI + lane / CPR;
+      const int k = ktail + ((lane % CPR) ^ wide_swizzle<KS>(row)) * 8;
+      *reinterpret_cast<u32x4*>(&lds_wide[(of_a ? 0 : ATILE) + row * KS + (lane % CPR) * 8]) =
+          of_a ? load_vec(A, lda, m0 + row, M, k, kend) : load_vec(B, ldb, n0 + row, N, k, kend);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < STEPS; ++kk) {
+      const int cidx = 2 * kk + (lane >> 5);
+      bf16x8 a[2], b[TN];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const bf16x8*>(&lds_wide[arow[i] * KS + ((cidx ^ asw[i]) * 8)]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const bf16x8*>(&lds_wide[ATILE + brow[j] * KS + ((cidx ^ bsw[j]) * 8)]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
   if (nstage > 0) {
     // Schedule.  A step's MFMAs are issued with the step's other instructions between them, one at a
     // time: the two wavefronts of a SIMD run in step (every barrier puts them side by side again), so
@@ -1943,11 +1987,7 @@ int launch_wide(const Shape& g, const Epilogue& ep, hipStream_t s);
 }  // namespace
 static int launch_gemm_bf16_ep(const Shape& g, const Epilogue& ep, hipStream_t s);
 
-// Compute-bound shapes take the big tile; everything else (few rows, or a short contraction
-// whose cost is writing the output) does better with many small workgroups in flight.
-static bool use_big_tile(int M, int N, int K) { return M >= 1024 && N >= 1024 && K >= 512; }
-
-// The wide kernel takes products of more than 128 rows whose contraction slices are whole stages.
+// The wide kernel takes products of more than 128 rows and at least 128 columns.
 // Tuning aid: VF_GEMM_WIDE=0 switches it off, 128 / 256 forces the tile width.
 static int wide_mode() {
   static int cached = -1;
@@ -1970,32 +2010,67 @@ static int wide_tile_n(int M, int N) {
   const int64_t r256 = (t256 + 255) / 256, r128 = (t128 + 255) / 256;
   return (r256 * 185 <= r128 * 100) ? 256 : 128;
 }
-static bool wide_fits(int M, int N, int K, int nsplit) {
-  if (!wide_mode() || M <= 128 || N < 128 || (K % BK)) return false;
-  // (the 256-row kernels address their operands with 32-bit byte offsets: launch_gemm_bf16 checks the spans)
-  const int kchunk = ((K + nsplit - 1) / nsplit + BK - 1) / BK * BK;
-  return (K % kchunk) == 0 || nsplit == 1;
+static bool wide_fits(int M, int N) { return wide_mode() && M > 128 && N >= 128; }
+
+// Which of the two LDS-direct kernels takes a product, by what each needs for it.  The 64 x 64 kernel
+// gives every compute unit a tile where the 256-row kernel leaves most of the chip idle, and loses to it
+// where the operands' way to the compute units is what bounds (64 x 64 moves three times as much per
+// flop).  Microseconds, fitted to products of 240 to 8192 rows launched back to back (launch, stages,
+// result stored at 4 TB/s; the fit and what was measured, 64 x 64 | 256-row):
+//   1600 x 512 x 512    6.4: 6.2 | 11.3: 12.1     1600 x 512 x 2048  12.9: 12.6 | 29: 26.5
+//   1600 x 2048 x 512  13.0: 13.5 | 13.8: 14.2    512 x 4096 x 4096  29.9: 28.3 | 55: 45.5 (4 slices 25: 23.7)
+//   256 x 4096 x 4096  21.7: 21.9 | 54: 44.9      8192 x 768 x 768   27.7: 27.0 | 19.8: 18.9
+//   1024 x 4096 x 4096 71: 59 | 56: 54            4096 x 4096 x 1024 84: 77 | 45: 36.7
+//   768 x 3072 x 8192  85: 87 | 103: 92 (2 slices 57: 58)
+static float tile64_cost(int M, int N, int K, int nsplit) {
+  const float tiles = (float)((M + 63) / 64) * (float)((N + 63) / 64) * nsplit;
+  const float stages = (float)(((K + nsplit - 1) / nsplit + BK - 1) / BK);
+  // two workgroups per compute unit, all of them fed: 0.38 us per stage, more in further rounds and with
+  // operands that pass through the L2s
+  const bool far = ((float)M + N) * K * 2 > 48e6f;
+  const float stage = (far ? 0.55f : tiles > 512 ? 0.5f : 0.38f) / 512 * tiles;
+  return 3.4f + stages * std::max(0.27f, stage) + (float)M * N * nsplit * 1e-6f;
+}
+static float wide_cost(int M, int N, int K, int nsplit) {
+  const bool t256 = (K % BK) == 0 && wide_tile_n(M, N) == 256;
+  const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + (t256 ? 255 : 127)) / (t256 ? 256 : 128)) * nsplit;
+  const float stages = (float)(((K + nsplit - 1) / nsplit + BK - 1) / BK);
+  return 4.5f + (float)((tiles + 255) / 256) * stages * (t256 ? 1.05f : 0.75f) + (float)M * N * nsplit * 1e-6f;
+}
+static bool takes_wide(int M, int N, int K, int nsplit) {
+  return wide_fits(M, N) && wide_cost(M, N, K, nsplit) < tile64_cost(M, N, K, nsplit);
 }
 
+// Slices of the contraction of a product whose consumer adds the slabs: what the product needs with
+// that many slices plus what the consumer needs to read the slabs (the BatchNorm kernels read them at
+// 1.5 TB/s or so).  256 x 4096 x 4096 (a unit of small nodes): two slabs off the 64 x 64 kernel,
+// 17.7 us, where eight off the 256-row kernel took 17.8 us and the kernels behind them 25 and 39 us.
 int gemm_bf16_pick_split(int M, int N, int K) {
-  if (wide_fits(M, N, K, 1)) {
-    // one workgroup per compute unit: slices until about 256 workgroups, each at least 8 stages long
-    const int bn = wide_tile_n(M, N);
-    const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + bn - 1) / bn);
-    int split = 1;
-    while (tiles * split * 2 <= 256 && K / (split * 2) >= 8 * BK && (K / BK) % (split * 2) == 0 && split < 32) split *= 2;
-    return split;
+  if (M > 32 && N > 32) {
+    const bool wide = wide_fits(M, N);
+    const int bn = wide ? wide_tile_n(M, N) : 64, bm = wide ? 256 : 64;
+    const int64_t wtiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+    const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+    int best = 1;
+    float cost = 0.f;
+    for (int split = 1; split <= 32; split *= 2) {
+      // slices of three stages at least (eight for the 256-row kernel) until every compute unit has a
+      // workgroup (two for the 64 x 64 kernel)
+      const bool few64 = split == 1 || (tiles * split <= 512 && K / split >= 3 * BK);
+      const bool few_wide = wide && (split == 1 || (wtiles * split <= 256 && K / split >= 8 * BK && (K / BK) % split == 0));
+      if (!few64 && !few_wide) continue;
+      const float c64 = few64 ? tile64_cost(M, N, K, split) : 1e30f;
+      const float cw = few_wide ? wide_cost(M, N, K, split) : 1e30f;
+      const float c = std::min(c64, cw) + (float)M * N * split * 2.7e-6f;
+      if (split == 1 || c < cost) { best = split; cost = c; }
+    }
+    return best;
   }
-  // Measured on the node-sized products (128 x 4096 x 4096 and relatives) with the
-  // pipelined kernel: about two 64x64 workgroups per compute unit, slices no shorter than
-  // 3 LDS stages.
-  if (use_big_tile(M, N, K)) return 1;
-  int bm = M <= 32 ? 32 : 64;
-  int bn = M <= 32 ? 128 : 64;
-  int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-  static const int target = std::getenv("VF_GEMM_SPLIT_TARGET") ? std::atoi(std::getenv("VF_GEMM_SPLIT_TARGET")) : 256;
+  // a few rows or columns (tiles of 32 x 128): about one workgroup per compute unit, slices no shorter
+  // than 3 LDS stages
+  const int64_t tiles = M <= 32 ? (N + 127) / 128 : (M + 127) / 128;
   int split = 1;
-  while (tiles * split < target && K / (split * 2) >= 3 * BK && split < 32) split *= 2;
+  while (tiles * split < 256 && K / (split * 2) >= 3 * BK && split < 32) split *= 2;
   return split;
 }
 
@@ -2057,7 +2132,8 @@ int wide_variant() {   // tuning aid: VF_GEMM_WIDE_V=1 runs 256-wide tiles on th
   return cached;
 }
 int launch_wide(const Shape& g, const Epilogue& ep, hipStream_t s) {
-  if (wide_tile_n(g.M, g.N) == 256)
+  // (the 256 x 256 kernels take whole stages, as many in every slice)
+  if (wide_tile_n(g.M, g.N) == 256 && g.K % (BK * g.nsplit) == 0)
     return wide_variant() == 1 ? launch_wide_cfg<256, 32, 3>(g, ep, s) : launch_wide_line(g, ep, s);
   return launch_wide_cfg<128, 64, 3>(g, ep, s);
 }
@@ -2072,7 +2148,7 @@ bool gemm_bf16_bn_fwd_takes(const bf16_t* A, int64_t lda, const bf16_t* B, int64
   if ((fa.gamma == nullptr) != (fa.beta == nullptr) || (fa.gamma && (!fa.mean || !fa.rstd || !fa.var || fa.bias))) return false;
   auto al = [](const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; };
   const bool spans32 = (int64_t)M * lda * 2 < ((int64_t)1 << 31) && (int64_t)N * ldb * 2 < ((int64_t)1 << 31);
-  return (M % 256) == 0 && (N % 256) == 0 && (K % 64) == 0 && spans32 && wide_fits(M, N, K, 1) &&
+  return (M % 256) == 0 && (N % 256) == 0 && (K % 64) == 0 && spans32 && wide_fits(M, N) &&
          wide_tile_n(M, N) == 256 && wide_variant() == 0 && !(lda & 7) && !(ldb & 7) && al(A, 16) && al(B, 16) &&
          !(fa.ldz & 3) && !(fa.lda & 3) && !(fa.ldt & 7) && al(fa.z, 16) && al(fa.a, 8) && al(fa.aT, 16) &&
          al(fa.mean, 16) && al(fa.rstd, 16) && al(fa.var, 16) && al(fa.gamma, 16) && al(fa.beta, 16) && al(fa.bias, 16);
@@ -2104,7 +2180,7 @@ bool gemm_bf16_bn_bwd_takes(const bf16_t* A, int64_t lda, const bf16_t* B, int64
   if ((fa.gamma == nullptr) != (fa.beta == nullptr) || (fa.gamma && (!fa.mean || !fa.rstd))) return false;
   auto al = [](const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; };
   const bool spans32 = (int64_t)M * lda * 2 < ((int64_t)1 << 31) && (int64_t)N * ldb * 2 < ((int64_t)1 << 31);
-  return (M % 256) == 0 && (N % 256) == 0 && (K % 64) == 0 && spans32 && wide_fits(M, N, K, 1) &&
+  return (M % 256) == 0 && (N % 256) == 0 && (K % 64) == 0 && spans32 && wide_fits(M, N) &&
          wide_tile_n(M, N) == 256 && wide_variant() == 0 && !(lda & 7) && !(ldb & 7) && al(A, 16) && al(B, 16) &&
          !(fa.ldz & 3) && !(fa.lddz & 3) && !(fa.ldt & 7) && al(fa.z, 16) && al(fa.dz, 8) && al(fa.dzT, 16) &&
          al(fa.sums, 16) && al(fa.mean, 16) && al(fa.rstd, 16) && al(fa.gamma, 16) && al(fa.beta, 16);
@@ -2178,14 +2254,13 @@ static int launch_gemm_bf16_ep(const Shape& g, const Epilogue& ep, hipStream_t s
   }
   // (the 256-row kernels address their operands with 32-bit byte offsets)
   const bool spans32 = (int64_t)M * lda * 2 < ((int64_t)1 << 31) && (int64_t)N * ldb * 2 < ((int64_t)1 << 31);
-  if (spans32 && wide_fits(M, N, K, nsplit)) return launch_wide(g, ep, s);
-  if (use_big_tile(M, N, K)) return launch_cfg<128, 128, 2, 2>(g, ep, s);
+  if (spans32 && takes_wide(M, N, K, nsplit)) return launch_wide(g, ep, s);
   if (M <= 32) return launch_cfg<32, 128, 1, 4>(g, ep, s);
   if (N <= 32) return launch_cfg<128, 32, 4, 1>(g, ep, s);
-  // whole 64-element stages in every slice: operand tiles straight into LDS
+  // operand tiles straight into LDS
   const int kchunk = ((K + nsplit - 1) / nsplit + BK - 1) / BK * BK;
   const int depth = dl_depth();
-  if (depth && (K % BK) == 0 && (K % kchunk) == 0) {
+  if (depth) {
     dim3 grid((N + 63) / 64, (M + 63) / 64, nsplit);
     switch (depth) {
       case 3: gemm_bf16_dl_kernel<3><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, kchunk, slab_stride, ep); break;

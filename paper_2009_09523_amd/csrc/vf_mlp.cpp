@@ -86,8 +86,8 @@ class Mlp final : public Model {
     }
   }
 
-  // split * rows * ld maximised over node sizes up to max_b (the split only changes when the
-  // number of row tiles does)
+  // split * rows * ld maximised over node sizes up to max_b (the split changes with the number of
+  // row tiles)
   int64_t slab_need(int max_b, int N, int K, int64_t ld) const {
     int64_t need = 0;
     auto probe = [&](int m) {
@@ -95,8 +95,8 @@ class Mlp final : public Model {
       int split = bf16_ ? gemm_bf16_pick_split(m, N, K) : gemm_f32_pick_split(m, N, K);
       need = std::max(need, (int64_t)split * m * ld);
     };
-    probe(32); probe(64);
-    for (int m = 128; m < max_b + 128; m += 128) probe(m);
+    probe(32);
+    for (int m = 64; m < max_b + 64; m += 64) probe(m);
     return need;
   }
 

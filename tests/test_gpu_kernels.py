@@ -208,6 +208,30 @@ def test_gemm_ragged_contraction_with_cold_operands(M, N, K):
         assert got.tobytes() == first.tobytes(), k
 
 
+@pytest.mark.parametrize("M,N,K,nsplit", [(70, 131, 193, 1), (64, 66, 63, 1), (200, 130, 1000, 3), (65, 64, 130, 4),
+                                         (300, 1003, 71, 1), (700, 3000, 321, 1), (1030, 4100, 1001, 2),
+                                         (4096, 4100, 211, 1), (515, 2050, 2049, 8)])
+def test_gemm_bf16_contraction_tails(M, N, K, nsplit):
+    """Contraction slices that are no whole number of 64-element stages, on the 64 x 64 and on the 256-row kernel
+    (and slices with no element at all): what lies in the rows' padding (here NaN) must not be read into the product."""
+    import torch
+    import paper_2009_09523_amd as vf
+    print(f"gemm bf16 tail M={M} N={N} K={K} nsplit={nsplit}", flush=True)
+    gen = torch.Generator().manual_seed(M + 3 * N + 7 * K)
+    ld = (K + 7) // 8 * 8 + 8
+    A, B = torch.full((M, ld), float("nan")), torch.full((N, ld), float("nan"))
+    A[:, :K] = torch.randn((M, K), generator=gen)
+    B[:, :K] = torch.randn((N, K), generator=gen)
+    A, B = A.to(torch.bfloat16), B.to(torch.bfloat16)
+    Cd = torch.full((nsplit, M, N), 3.0, device="cuda")
+    vf.vf_gemm(A.cuda()[:, :K], B.cuda()[:, :K], Cd if nsplit > 1 else Cd[0], M, N, K, nsplit=nsplit)
+    torch.cuda.synchronize()
+    a, b = A[:, :K].double(), B[:, :K].double()
+    # exact products, fp32 sums: at most K roundings of partial sums no larger than sum |a||b|
+    bound = K * 2.0 ** -24 * (a.abs() @ b.abs().T)
+    assert torch.all((Cd.double().sum(0).cpu() - a @ b.T).abs() <= bound)
+
+
 @pytest.mark.parametrize("pad", [0, 1, 4])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (16, 256, 784), (17, 33, 65), (31, 10, 3), (100, 500, 1000), (784, 65, 16),
                                    (256, 769, 256), (256, 1601, 40), (36, 256, 4099), (515, 1024, 515), (1000, 1100, 200),
