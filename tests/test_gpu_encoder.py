@@ -1,4 +1,6 @@
 """GPU parity: the encoder workloads through the C ABI against the CPU oracle."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
@@ -32,6 +34,20 @@ def test_encoder_step_matches_oracle(name, flags):
     # gradient is within rounding of zero moves by +lr on one side and -lr on the other)
     check_against_oracle(wl, gpu, ref)
     check_update_from_own_gradient(wl, gpu, theta, tol=1e-4)
+
+
+@pytest.mark.parametrize("T", [1, 17, 33, 95, 100, 128, 130])
+def test_encoder_sequence_lengths(T):
+    """Sequences that do not fill the attention kernel's tiles of 32 tokens (130: the generic kernels)."""
+    print(f"T={T}", flush=True)
+    wl = replace(I.workload("enc_small_bf16"), name=f"enc_T{T}", seq_len=T, n_masked=max(1, int(0.15 * T)))
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    ref = oracle_steps(wl, theta, x, y)
+    base = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH)
+    check_against_oracle(wl, base, ref)
+    two = run_gpu(wl, theta, x, y, flags=FUSED | OVERLAP | NO_GRAPH)
+    assert base["G"].tobytes() == two["G"].tobytes()
 
 
 def test_encoder_fused_and_staged_agree_bitwise():
