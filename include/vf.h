@@ -175,8 +175,8 @@ typedef struct vf_config {
                                     mix of sizes; other nodes go alone (units of 16 or 32 nodes: the
                                     staged fold then differs from the fused one by fp32 rounding in the
                                     BatchNorm scale / shift gradients, and a fold window holds at most
-                                    as many units as a batch has).  Encoder: runs of 2 or 4
-                                    nodes of one size.  The per-node workspace grows by this factor
+                                    as many units as a batch has).  Encoder: up to four
+                                    nodes of any sizes.   The per-node workspace grows by this factor
                                     (not with V). */
   uint32_t flags;                /* VF_FLAG_* */
   void*   stream;                /* hipStream_t; NULL = the default stream */

@@ -98,6 +98,9 @@ class Encoder final : public Model {
   int64_t num_params() const override { return P_; }
   // (the row-chunked reductions of the backward pass take units of up to 8192 tokens)
   int max_group(int) const override { return 4; }
+  // the sequences of a unit are independent, and every masked row carries 1/rows of the unit times the
+  // unit's weight: 1/B of the loss, whatever the sizes of its nodes
+  bool groups_unequal() const override { return true; }
   // the forward part of the fp32 / non-MFMA attention path shares its score scratch with the backward part
   bool supports_overlap() const override { return bf16_ && mfma_attn_; }
 
@@ -248,12 +251,14 @@ class Encoder final : public Model {
     VF_KS(c, st, "softmax_xent", launch_softmax_xent(logits_, 1, 0, ldV_, logits_, ldV_, H.labels, Rm, V_, c.rowloss,
                                                 H.dlogits, ldV_, bf16_, nullptr, 0, w, i, nullptr, nullptr, st));
     // loss bookkeeping per virtual node (Section 5.2), in node order
-    for (int j = 0; j < s.group(i); ++j) {
-      const int node = s.first[i] + j, rows = s.seg[i] * m_;
-      VF_KS(c, st, "loss_reduce", launch_loss_reduce(c.rowloss + (int64_t)j * rows, rows, s.node_w[node], node, c.node_loss,
-                                                     c.loss_total, st));
+    LossNodes ln{};
+    ln.first = s.first[i];
+    ln.count = s.group(i);                   // (at most four: max_group)
+    for (int j = 0, row = 0; j < ln.count; ++j) {
+      ln.off[j] = row; ln.rows[j] = s.rows_of(i)[j] * m_; ln.w[j] = s.node_w[ln.first + j];
+      row += ln.rows[j];
     }
-
+    VF_KS(c, st, "loss_reduce", launch_loss_reduce_nodes(c.rowloss, ln, c.node_loss, c.loss_total, st));
     return VF_OK;
   }
 
