@@ -1547,50 +1547,65 @@ __global__ __launch_bounds__(512) void gemm_bf16_wide_line16_kernel(const bf16_t
 // Rows are stored with the same 16-byte chunk permutation as the other LDS-direct kernels
 // (by stored position for the input, by output channel for the filters).
 // Requires H % (64 / W) == 0 (a stage lies within one image) and rows % 64 == 0.
+// What bounds it is the LDS: a 32x32x16 MFMA takes 32 cycles of a SIMD, and with both operands read
+// from LDS for each one the four SIMDs ask for 64 cycles of reads in that time.  So a wavefront keeps
+// its 32 channels x 576 filters in registers (144 of them; LDS only passes them on, once) and reads the
+// input alone.  Eight wavefronts: two groups of 2 x 2 on alternate stages, so that one group's stores
+// and statistics run beside the other's MFMAs.  Each group has a ring of three input buffers (two where
+// W = 64), the later ones in the space that the filters leave; the loads of the next stage are waited
+// for BEFORE this stage's results are stored (one counter covers both: waiting afterwards would wait
+// for the stores to reach memory in every stage).
 // With `stats` (plain epilogue only: what is stored is the product itself) the workgroup also
 // leaves, per output channel, the mean of the values it stored and their sum of squared
 // deviations from it -- stats[(blockIdx.y * 2 + 0) * N + n] and [.. + 1 ..] -- for a per-channel
 // normalisation over all positions: every lane keeps shifted sums over its own values (shift =
-// its first value), and the four lanes that share a channel are joined in a fixed order.
+// its first value), and the eight lanes that share a channel are joined in a fixed order.
+// 131072 positions of 32 x 32 images, 64 channels: 25.2 us with both operands from LDS, 18.4 now.
+constexpr int CONV_NT = 512;
 template <int W>
-__global__ __launch_bounds__(NT) void conv3x3_lds_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wk,
+struct ConvLds {
+  static constexpr int IR = 64 / W;              // image rows per stage
+  static constexpr int PW = W + 2;               // stored positions per image row
+  static constexpr int XB = (IR + 2) * PW * 64;  // elements of one input buffer
+  static constexpr int FE = 9 * 64 * 64;         // elements of the filters
+  static constexpr int NB = 4 * XB <= FE ? 3 : 2;               // input buffers per group; all but the first share the filters' space
+  static constexpr int TAIL = 2 * (NB - 1) * XB > FE ? 2 * (NB - 1) * XB : FE;
+  static constexpr int BYTES = (2 * XB + TAIL) * 2;
+};
+template <int W>
+__global__ __launch_bounds__(CONV_NT) void conv3x3_lds_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wk,
                                                          int64_t ldb, int H, const bf16_t* __restrict__ zeros,
                                                          int nstages, int stages_per_wg, int N, Epilogue ep,
                                                          float* __restrict__ stats) {
   static_assert(W == 8 || W == 16 || W == 32 || W == 64, "image width");
-  constexpr int IR = 64 / W;                     // image rows per stage
-  constexpr int PW = W + 2;                      // stored positions per image row
-  constexpr int XR = (IR + 2) * PW;              // stored positions per stage
-  constexpr int XB = XR * 64;                    // elements of one input buffer
-  constexpr int FE = 9 * 64 * 64;                // elements of the filters
+  using L = ConvLds<W>;
+  constexpr int IR = L::IR, PW = L::PW, XB = L::XB, NB = L::NB;
   constexpr int NI = (IR + 2) * (W / 8);         // load instructions per stage (8 positions each)
   extern __shared__ __attribute__((aligned(1024))) bf16_t lds_dyn[];
-  bf16_t* F = lds_dyn;
-  bf16_t* X = lds_dyn + FE;
+  bf16_t* F = lds_dyn + 2 * XB;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, hi = lane >> 5, m = lane & 31;
+  const int grp = wave >> 2, gw = wave & 3;
+  const int wm = gw >> 1, wn = gw & 1, hi = lane >> 5, m = lane & 31;
   const int n0 = blockIdx.x * 64;
   const int sbeg = blockIdx.y * stages_per_wg, send = min(nstages, sbeg + stages_per_wg);
+  if (sbeg >= send) return;
+  const int niter = (send - sbeg + 1) / 2;       // iteration j: stages sbeg + 2 j (group 0) and the one after it
 
-  // filters: tile t = tap, 64 rows (output channels) of 64 channels, 8 rows per instruction
-  for (int i = wave; i < 72; i += 4) {
-    const int t = i >> 3, row = (i & 7) * 8 + (lane >> 3);
-    const int chunk = (lane & 7) ^ dl_swizzle(row);
-    const bf16_t* src = Wk + (int64_t)min(n0 + row, N - 1) * ldb + t * 64 + chunk * 8;
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)src,
-                                     (void __attribute__((address_space(3)))*)&F[i * 512], 16, 0, 0);
-  }
-  // the empty positions before and after every stored image row, both buffers (32 dwords each)
-  for (int k = tid; k < 2 * (IR + 2) * 2 * 32; k += NT) {
-    const int dword = k & 31, which = k >> 5;
-    const int side = which & 1, irow = (which >> 1) % (IR + 2), buf = (which >> 1) / (IR + 2);
-    const int pos = irow * PW + (side ? PW - 1 : 0);
-    reinterpret_cast<uint32_t*>(X + buf * XB + pos * 64)[dword] = 0u;
-  }
-
-  auto issue = [&](int stage, int buf) {
-    for (int idx = wave; idx < NI; idx += 4) {
+  // input buffer b of this group (in LDS elements)
+  auto buffer = [&](int b) { return b == 0 ? grp * XB : 2 * XB + ((b - 1) * 2 + grp) * XB; };
+  // the empty positions before and after every stored image row of one buffer (32 dwords each)
+  auto clear_edges = [&](int b) {
+    for (int k = gw * 64 + lane; k < (IR + 2) * 2 * 32; k += 256) {
+      const int dword = k & 31, which = k >> 5;
+      const int pos = (which >> 1) * PW + ((which & 1) ? PW - 1 : 0);
+      reinterpret_cast<uint32_t*>(lds_dyn + buffer(b) + pos * 64)[dword] = 0u;
+    }
+  };
+  // (stages past the end repeat the last one, into a buffer that nobody reads: the count of loads in flight stays the same)
+  auto issue = [&](int j) {
+    const int stage = min(sbeg + 2 * j + grp, send - 1), at = buffer(j % NB);
+    for (int idx = gw; idx < NI; idx += 4) {
       const int ir = idx / (W / 8) - 1, sub = idx % (W / 8);
       const int p = (ir + 1) * PW + 1 + sub * 8 + (lane >> 3);      // stored position of this lane's row
       const int chunk = (lane & 7) ^ dl_swizzle(p);
@@ -1599,42 +1614,70 @@ __global__ __launch_bounds__(NT) void conv3x3_lds_kernel(const bf16_t* __restric
       const bf16_t* src = (hh >= 0 && hh < H) ? x + ((int64_t)g * W + sub * 8 + (lane >> 3)) * 64 + chunk * 8
                                               : zeros + chunk * 8;
       __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)src,
-                                       (void __attribute__((address_space(3)))*)&X[buf * XB + ((ir + 1) * PW + 1 + sub * 8) * 64],
+                                       (void __attribute__((address_space(3)))*)&lds_dyn[at + ((ir + 1) * PW + 1 + sub * 8) * 64],
                                        16, 0, 0);
     }
   };
 
+  // filters: tile t = tap, 64 rows (output channels) of 64 channels, 8 rows per instruction
+  for (int i = wave; i < 72; i += 8) {
+    const int t = i >> 3, row = (i & 7) * 8 + (lane >> 3);
+    const int chunk = (lane & 7) ^ dl_swizzle(row);
+    const bf16_t* src = Wk + (int64_t)min(n0 + row, N - 1) * ldb + t * 64 + chunk * 8;
+    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)src,
+                                     (void __attribute__((address_space(3)))*)&F[i * 512], 16, 0, 0);
+  }
+  issue(0);
+  clear_edges(0);
+
   // this lane's operand rows: stage position e under tap t sits at stored position
   // (e / W + kh) * PW + e % W + kw; its filter row is output channel wn * 32 + m of tile t
   const int e = wm * 32 + m;
-  int pa[9], fa[9];
+  // (byte offsets of contraction step 0; step kk's chunk 2 kk + hi sits at that offset with bits 5 and 6 XORed by kk)
+  uint32_t row0[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t) {
     const int p = (e / W + t / 3) * PW + e % W + t % 3;
-    pa[t] = p * 64;
-    fa[t] = dl_swizzle(p);
+    row0[t] = (uint32_t)(p * 128 + ((hi ^ dl_swizzle(p)) * 16));
   }
   const int brow = (wn * 32 + m) * 64, fb = dl_swizzle(wn * 32 + m);
 
+  wait_loads_but<0>();
+  __syncthreads();                                 // filters and the first stages are in LDS
+  bf16x8 filt[36];
+#pragma unroll
+  for (int i = 0; i < 36; ++i) {
+    const int t = i >> 2, ci = 2 * (i & 3) + hi;
+    filt[i] = *reinterpret_cast<const bf16x8*>(&F[t * 4096 + brow + ((ci ^ fb) * 8)]);
+  }
+  __syncthreads();                                 // everybody has its filters: their space takes input buffers
+#pragma unroll
+  for (int b = 1; b < NB; ++b) clear_edges(b);
+  if (NB == 3) issue(1);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
   float shift = 0.f, sd = 0.f, sq = 0.f;           // stats: this lane's values v as sums of (v - shift) and (v - shift)^2
-  if (sbeg < send) issue(sbeg, 0);
-  for (int st = sbeg; st < send; ++st) {
-    const int buf = (st - sbeg) & 1;
-    wait_loads_but<0>();
-    __syncthreads();                               // stage st (and the filters) are in LDS; everybody is done with the other buffer
-    if (st + 1 < send) issue(st + 1, buf ^ 1);
-    const bf16_t* xs = X + buf * XB;
+  for (int j = 0; j < niter; ++j) {
+    // stage j of both groups is in LDS, and everybody is done with stage j - 1, whose buffer the next loads take
+    issue(j + NB - 1);
+    const uint32_t base = (uint32_t)buffer(j % NB) * 2;      // (a multiple of 128 bytes)
+    uint32_t row[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      row[t] = row0[t] + base;
+      asm volatile("" : "+v"(row[t]));                       // nine addresses and an XOR each, not 36 kept in registers
+    }
     f32x16 acc0, acc1;
 #pragma unroll
     for (int r = 0; r < 16; ++r) { acc0[r] = 0.f; acc1[r] = 0.f; }
     // 36 MFMAs (9 taps x 4 contraction steps); the operand reads of step i + AHEAD are issued
-    // before the MFMA of step i (one wave per SIMD: nobody else covers the LDS latency)
-    constexpr int AHEAD = 3, SLOTS = AHEAD + 1;
-    bf16x8 fa_[SLOTS], fb_[SLOTS];
+    // before the MFMA of step i
+    constexpr int AHEAD = 4, SLOTS = AHEAD + 1;
+    bf16x8 fa_[SLOTS];
     auto read_step = [&](int i, int slot) {
-      const int t = i >> 2, ci = 2 * (i & 3) + hi;
-      fa_[slot] = *reinterpret_cast<const bf16x8*>(&xs[pa[t] + ((ci ^ fa[t]) * 8)]);
-      fb_[slot] = *reinterpret_cast<const bf16x8*>(&F[t * 4096 + brow + ((ci ^ fb) * 8)]);
+      fa_[slot] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(lds_dyn) + (row[i >> 2] ^ (32u * (i & 3))));
     };
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i) read_step(i, i);
@@ -1642,41 +1685,71 @@ __global__ __launch_bounds__(NT) void conv3x3_lds_kernel(const bf16_t* __restric
     for (int i = 0; i < 36; ++i) {
       if (i + AHEAD < 36) read_step(i + AHEAD, (i + AHEAD) % SLOTS);
       __builtin_amdgcn_sched_barrier(0);
-      if (i & 1) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa_[i % SLOTS], fb_[i % SLOTS], acc1, 0, 0, 0);
-      else       acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa_[i % SLOTS], fb_[i % SLOTS], acc0, 0, 0, 0);
+      if (i & 1) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa_[i % SLOTS], filt[i], acc1, 0, 0, 0);
+      else       acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa_[i % SLOTS], filt[i], acc0, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
-    f32x16 tiles[1][1];
+    // this wavefront's part of stage j + 1 has landed (loads complete in order: only those of stage j + 2 may be out)
+    if (NB == 2)            wait_loads_but<0>();
+    else if (NI % 4 == 0)   wait_loads_but<NI / 4>();
+    else if (gw < NI % 4)   wait_loads_but<NI / 4 + 1>();
+    else                    wait_loads_but<NI / 4>();
+    const int st = sbeg + 2 * j + grp;
+    if (st < send) {
+      // accumulator register q of a lane: position 8 (q/4) + 4 (lane/32) + q%4, channel lane%32
+      const int64_t r0 = (int64_t)st * 64 + wm * 32 + 4 * hi;
+      const int n = n0 + wn * 32 + m;
+      f32x16 v;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) tiles[0][0][r] = acc0[r] + acc1[r];
-    store_tiles<1, 1>(tiles, ep, static_cast<char*>(ep.C), true, st * 64 + wm * 32, n0 + wn * 32, nstages * 64, N, lane);
-    if (stats) {
-      if (st == sbeg) shift = tiles[0][0][0];
+      for (int r = 0; r < 16; ++r) v[r] = acc0[r] + acc1[r];
+      if (n < N) {
+        float* out = static_cast<float*>(ep.C) + r0 * ep.ldc + n;
+        if (ep.R) {                                          // all sixteen addends on their way before the first store
+          const float* add = ep.R + r0 * ep.ldr + n;
+          float old[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float d = tiles[0][0][r] - shift;
-        sd += d;
-        sq = fmaf(d, d, sq);
+          for (int r = 0; r < 16; ++r) old[r] = add[(int64_t)(8 * (r >> 2) + (r & 3)) * ep.ldr];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) v[r] += old[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) out[(int64_t)(8 * (r >> 2) + (r & 3)) * ep.ldc] = v[r];
+      }
+      if (stats) {
+        if (j == 0) shift = v[0];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float d = v[r] - shift;
+          sd += d;
+          sq = fmaf(d, d, sq);
+        }
       }
     }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();                  // (a bare one: __syncthreads would wait for the stores)
+    asm volatile("" ::: "memory");
   }
   wait_loads_but<0>();
-  if (stats && sbeg < send) {
-    __shared__ float st_m[4][64], st_q[4][64];
-    const float cnt = 16.f * (float)(send - sbeg);           // values per lane
-    const float dm = sd / cnt;
-    st_m[wm * 2 + hi][wn * 32 + m] = shift + dm;
-    st_q[wm * 2 + hi][wn * 32 + m] = sq - sd * dm;
+  if (stats) {
+    __shared__ float st_m[8][64], st_q[8][64];
+    const int mine = (send - sbeg + 1 - grp) / 2;            // this group's stages (none for the second group of a single stage)
+    const float cnt = 16.f * (float)mine;                    // values per lane
+    const float dm = mine ? sd / cnt : 0.f;
+    st_m[grp * 4 + wm * 2 + hi][wn * 32 + m] = shift + dm;
+    st_q[grp * 4 + wm * 2 + hi][wn * 32 + m] = sq - sd * dm;
     __syncthreads();
     if (tid < 64 && n0 + tid < N) {
-      // the two-group update of a mean and a sum of squared deviations, groups of equal size joined in order
-      float mean = st_m[0][tid], m2 = st_q[0][tid], have = cnt;
+      // the two-group update of a mean and a sum of squared deviations, in order
+      float mean = st_m[0][tid], m2 = st_q[0][tid], have = 16.f * (float)((send - sbeg + 1) / 2);
 #pragma unroll
-      for (int g = 1; g < 4; ++g) {
-        const float tot = have + cnt, delta = st_m[g][tid] - mean;
-        mean = fmaf(delta, cnt / tot, mean);
-        m2 = m2 + st_q[g][tid] + delta * delta * (have * cnt / tot);
-        have = tot;
+      for (int g = 1; g < 8; ++g) {
+        const float more = 16.f * (float)((send - sbeg + 1 - (g >> 2)) / 2);
+        if (more > 0.f) {
+          const float tot = have + more, delta = st_m[g][tid] - mean;
+          mean = fmaf(delta, more / tot, mean);
+          m2 = m2 + st_q[g][tid] + delta * delta * (have * more / tot);
+          have = tot;
+        }
       }
       stats[((int64_t)blockIdx.y * 2 + 0) * N + n0 + tid] = mean;
       stats[((int64_t)blockIdx.y * 2 + 1) * N + n0 + tid] = m2;
@@ -2288,25 +2361,24 @@ int launch_conv3x3_bf16(const bf16_t* x, int64_t rows, int H, int W, int Cin, co
   const int K = 9 * Cin;
   // filters resident in LDS, the input staged once per 64 positions
   static const bool lds_path = !(std::getenv("VF_CONV_LDS") && std::getenv("VF_CONV_LDS")[0] == '0');
-  if (lds_path && Cin == 64 && (W == 8 || W == 16 || W == 32 || W == 64) && H % (64 / W) == 0 && rows % 64 == 0) {
+  const bool plain = ep.alpha == 1.f && !ep.bias && !ep.c_is_bf16 && (!ep.R || ep.beta == 1.f);
+  if (lds_path && plain && Cin == 64 && (W == 8 || W == 16 || W == 32 || W == 64) && H % (64 / W) == 0 && rows % 64 == 0) {
     const int nstages = (int)(rows / 64), otiles = (N + 63) / 64;
     const int spw = std::max(1, (int)(((int64_t)nstages * otiles + 255) / 256));
     dim3 grid(otiles, (nstages + spw - 1) / spw);
     // per-channel statistics of what is stored, if asked for and if that is the product itself
-    float* st = (stats && stats_chunks && stats_rows && ep.alpha == 1.f && !ep.R && !ep.bias && !ep.c_is_bf16 &&
-                 (int)grid.y <= kConvStatsChunks)
-                    ? stats : nullptr;
+    float* st = (stats && stats_chunks && stats_rows && !ep.R && (int)grid.y <= kConvStatsChunks) ? stats : nullptr;
     if (st) { *stats_chunks = (int)grid.y; *stats_rows = spw * 64; }
 #define VF_CONV_LDS(WW)                                                                                   \
   case WW: {                                                                                              \
-    constexpr int bytes = (9 * 64 * 64 + 2 * (64 / WW + 2) * (WW + 2) * 64) * 2;                          \
+    constexpr int bytes = ConvLds<WW>::BYTES;                                                             \
     static bool ready = false;                                                                            \
     if (!ready) {                                                                                         \
       VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&conv3x3_lds_kernel<WW>),                  \
                                  hipFuncAttributeMaxDynamicSharedMemorySize, bytes));                     \
       ready = true;                                                                                       \
     }                                                                                                     \
-    conv3x3_lds_kernel<WW><<<grid, NT, bytes, s>>>(x, Wk, ldb, H, zeros, nstages, spw, N, ep, st);            \
+    conv3x3_lds_kernel<WW><<<grid, CONV_NT, bytes, s>>>(x, Wk, ldb, H, zeros, nstages, spw, N, ep, st);            \
   } break;
     switch (W) { VF_CONV_LDS(8) VF_CONV_LDS(16) VF_CONV_LDS(32) default: VF_CONV_LDS(64) }
 #undef VF_CONV_LDS

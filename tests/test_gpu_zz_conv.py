@@ -2,6 +2,8 @@
 per-node BatchNorm) through the C ABI against the CPU oracle.  (The file name sorts behind the
 tests of the MLP and encoder paths, so a run that stops at the first failure has been through
 those first.)"""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
@@ -37,6 +39,32 @@ def test_conv_step_matches_oracle(name, flags):
 def test_image_side_64_one_image_row_per_stage():
     """The widest image side the LDS-staged convolution kernels take: a stage of 64 positions is one image row."""
     wl, theta, x, y = _case("conv_w64_img64_bf16")
+    gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH)
+    ref = oracle_steps(wl, theta, x, y)
+    check_against_oracle(wl, gpu, ref)
+
+
+def test_image_side_32_several_stages_per_workgroup():
+    """More stages of 64 positions than compute units: three stages of a workgroup (two for one of its groups of
+    wavefronts, one for the other) and a last workgroup with fewer."""
+    wl = replace(I.workload("conv_w64_img16_bf16"), name="conv_w64_img32", img=32, node_sizes=(33, 41, 17))
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH)
+    ref = oracle_steps(wl, theta, x, y)
+    check_against_oracle(wl, gpu, ref)
+
+
+@pytest.mark.parametrize("width,img,sizes", [(8, 5, (3, 1)), (40, 7, (9, 2)), (72, 9, (4, 3)), (248, 8, (5, 4))])
+def test_channel_counts_that_are_multiples_of_eight(width, img, sizes):
+    """Patch rows read from the activation although a stage of 64 contraction elements crosses taps, gradients over
+    the transposed patch matrix: widths below, around and far above one stage, rows that fill no tile.  (248 channels
+    over five images of 6 x 6 are too few positions for the entry-wise criterion: there the patch-matrix path misses it
+    in the same 188 entries, the two paths 6e-6 apart.)"""
+    print(f"width={width} img={img} sizes={sizes}", flush=True)
+    wl = replace(I.workload("conv_tiny_bf16"), name=f"conv_w{width}", img=img, width=width, node_sizes=sizes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
     gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH)
     ref = oracle_steps(wl, theta, x, y)
     check_against_oracle(wl, gpu, ref)
