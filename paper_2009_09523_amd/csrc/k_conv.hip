@@ -216,45 +216,52 @@ __global__ __launch_bounds__(NT) void bn2d_stats_partial_kernel(const float* __r
   }
 }
 
-// Chunks combined in a fixed order: one workgroup of NTF threads, thread = (column, lane); a lane
-// joins a contiguous run of chunks in chunk order (eight chunks' values in flight), then the lanes
-// are joined in lane order.  Mean and
-// biased variance over all rows; rstd; moving statistics of this device blended once per pass
-// (Section 4.1).  C <= 256.
-constexpr int NTF = 1024;
+// Chunks combined in a fixed order by workgroups of FIN_COLS columns: thread = (column, lane), FIN_LANES
+// lanes per column; a lane joins a contiguous run of chunks in chunk order (eight chunks' values in
+// flight), then the lanes are joined pairwise, neighbours first.  Mean and biased variance over all rows;
+// rstd; moving statistics of this device blended once per pass (Section 4.1).
+// What this costs is the length of the serial chain (a join has a division): with all columns in one
+// workgroup of 1024 threads a lane had 32 of 512 chunks to join and 15 lanes after that (64 columns:
+// 10.2 us a launch); here 8 chunks and 6 pairwise joins (4.9 us).
+constexpr int NTF = 512, FIN_COLS = 8, FIN_LANES = NTF / FIN_COLS;
 __global__ __launch_bounds__(NTF) void bn2d_stats_finish_kernel(const float* __restrict__ partial, int nchunk,
                                                                int rpc, int64_t rows, int C, float eps,
                                                                float* __restrict__ mean_out, float* __restrict__ rstd_out,
                                                                float* __restrict__ run_mean, float* __restrict__ run_var,
                                                                float run_mix) {
-  __shared__ float sm[3][NTF];
-  const int nl = NTF / C;                      // lanes per column
-  const int c = threadIdx.x % C, lane = threadIdx.x / C;
-  const bool active = lane < nl;
-  const int per = (nchunk + nl - 1) / nl;
-  const int k0 = lane * per, k1 = min(nchunk, k0 + per);
+  __shared__ float sm[3][NTF / 64][FIN_COLS];
+  const int col = threadIdx.x % FIN_COLS, lane = threadIdx.x / FIN_COLS;
+  const int c = min((int)blockIdx.x * FIN_COLS + col, C - 1);
+  const int per = (nchunk + FIN_LANES - 1) / FIN_LANES;
+  const int k0 = min(nchunk, lane * per), k1 = min(nchunk, k0 + per);
   float mean = 0.f, m2 = 0.f, cnt = 0.f;
-  if (active) {
-    int k = k0;
-    for (; k + 7 < k1; k += 8) {               // eight chunks' values in flight, joined in order
-      float mb[8], qb[8];
+  for (int k = k0; k < k1; k += 8) {           // (clamped, always valid chunks ahead of any selection)
+    float mb[8], qb[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        mb[u] = partial[((int64_t)(k + u) * 2 + 0) * C + c];
-        qb[u] = partial[((int64_t)(k + u) * 2 + 1) * C + c];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        join_stats(cnt, mean, m2, (float)min((int64_t)rpc, rows - (int64_t)(k + u) * rpc), mb[u], qb[u]);
+    for (int u = 0; u < 8; ++u) {
+      mb[u] = partial[((int64_t)min(k + u, k1 - 1) * 2 + 0) * C + c];
+      qb[u] = partial[((int64_t)min(k + u, k1 - 1) * 2 + 1) * C + c];
     }
-    for (; k < k1; ++k)
-      join_stats(cnt, mean, m2, (float)min((int64_t)rpc, rows - (int64_t)k * rpc),
-                 partial[((int64_t)k * 2 + 0) * C + c], partial[((int64_t)k * 2 + 1) * C + c]);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (k + u < k1) join_stats(cnt, mean, m2, (float)min((int64_t)rpc, rows - (int64_t)(k + u) * rpc), mb[u], qb[u]);
   }
-  sm[0][threadIdx.x] = cnt; sm[1][threadIdx.x] = mean; sm[2][threadIdx.x] = m2;
+#pragma unroll
+  for (int o = FIN_COLS; o < 64; o <<= 1) {    // lane l of a column joins lane l + o / FIN_COLS (valid in the lowest)
+    const float nb = __shfl_down(cnt, o), mb = __shfl_down(mean, o), qb = __shfl_down(m2, o);
+    join_stats(cnt, mean, m2, nb, mb, qb);
+  }
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) < FIN_COLS) { sm[0][wave][col] = cnt; sm[1][wave][col] = mean; sm[2][wave][col] = m2; }
   __syncthreads();
-  if (lane != 0) return;
-  for (int l = 1; l < nl; ++l) join_stats(cnt, mean, m2, sm[0][l * C + c], sm[1][l * C + c], sm[2][l * C + c]);
+  if (threadIdx.x >= 64) return;
+  cnt = sm[0][lane][col]; mean = sm[1][lane][col]; m2 = sm[2][lane][col];
+#pragma unroll
+  for (int o = FIN_COLS; o < 64; o <<= 1) {
+    const float nb = __shfl_down(cnt, o), mb = __shfl_down(mean, o), qb = __shfl_down(m2, o);
+    join_stats(cnt, mean, m2, nb, mb, qb);
+  }
+  if (lane != 0 || (int)blockIdx.x * FIN_COLS + col >= C) return;
   const float var = m2 / cnt;
   mean_out[c] = mean;
   rstd_out[c] = 1.0f / sqrtf(var + eps);
@@ -349,39 +356,39 @@ __global__ __launch_bounds__(NT) void bn2d_bwd_partial_kernel(const float* __res
   }
 }
 
-// Step 2: one workgroup, thread = (column, lane); a lane adds a contiguous run of chunks in chunk
-// order, the lanes are added in lane order.  The sums go to sums[0][c] (dbeta) and sums[1][c]
-// (dgamma) for the apply kernel, and, weighted, into the gradient (Section 3.2 step 3,
-// Section 5.2).  C <= 256.
+// Step 2: thread = (column, lane) as in the statistics; a lane adds a contiguous run of chunks in chunk
+// order, the lanes are added pairwise, neighbours first.  The sums go to sums[0][c] (dbeta) and
+// sums[1][c] (dgamma) for the apply kernel, and, weighted, into the gradient (Section 3.2 step 3,
+// Section 5.2).  (One workgroup for all columns: 5.3 us at 512 chunks of 64 columns; this: 4.5 us.)
 __global__ __launch_bounds__(NTF) void bn2d_bwd_finish_kernel(const float* __restrict__ partial, int nchunk, int C,
                                                              float* __restrict__ sums, GradOut gout_g, GradOut gout_b) {
-  __shared__ float sm[2][NTF];
-  const int nl = NTF / C;
-  const int c = threadIdx.x % C, lane = threadIdx.x / C;
-  const int per = (nchunk + nl - 1) / nl;
-  const int k0 = lane * per, k1 = min(nchunk, k0 + per);
+  __shared__ float sm[2][NTF / 64][FIN_COLS];
+  const int col = threadIdx.x % FIN_COLS, lane = threadIdx.x / FIN_COLS;
+  const int c = min((int)blockIdx.x * FIN_COLS + col, C - 1);
+  const int per = (nchunk + FIN_LANES - 1) / FIN_LANES;
+  const int k0 = min(nchunk, lane * per), k1 = min(nchunk, k0 + per);
   float sb = 0.f, sg = 0.f;
-  if (lane < nl) {
-    int k = k0;
-    for (; k + 7 < k1; k += 8) {
-      float b8[8], g8[8];
+  for (int k = k0; k < k1; k += 8) {
+    float b8[8], g8[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        b8[u] = partial[((int64_t)(k + u) * 2 + 0) * C + c];
-        g8[u] = partial[((int64_t)(k + u) * 2 + 1) * C + c];
-      }
+    for (int u = 0; u < 8; ++u) {
+      b8[u] = partial[((int64_t)min(k + u, k1 - 1) * 2 + 0) * C + c];
+      g8[u] = partial[((int64_t)min(k + u, k1 - 1) * 2 + 1) * C + c];
+    }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) { sb += b8[u]; sg += g8[u]; }
-    }
-    for (; k < k1; ++k) {
-      sb += partial[((int64_t)k * 2 + 0) * C + c];
-      sg += partial[((int64_t)k * 2 + 1) * C + c];
-    }
+    for (int u = 0; u < 8; ++u)
+      if (k + u < k1) { sb += b8[u]; sg += g8[u]; }
   }
-  sm[0][threadIdx.x] = sb; sm[1][threadIdx.x] = sg;
+#pragma unroll
+  for (int o = FIN_COLS; o < 64; o <<= 1) { sb += __shfl_down(sb, o); sg += __shfl_down(sg, o); }
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) < FIN_COLS) { sm[0][wave][col] = sb; sm[1][wave][col] = sg; }
   __syncthreads();
-  if (lane != 0) return;
-  for (int l = 1; l < nl; ++l) { sb += sm[0][l * C + c]; sg += sm[1][l * C + c]; }
+  if (threadIdx.x >= 64) return;
+  sb = sm[0][lane][col]; sg = sm[1][lane][col];
+#pragma unroll
+  for (int o = FIN_COLS; o < 64; o <<= 1) { sb += __shfl_down(sb, o); sg += __shfl_down(sg, o); }
+  if (lane != 0 || (int)blockIdx.x * FIN_COLS + col >= C) return;
   sums[c] = sb;
   sums[C + c] = sg;
   grad_store(gout_b, c, sb);
@@ -423,7 +430,9 @@ __global__ __launch_bounds__(NT) void bn2d_bwd_apply_kernel(float* __restrict__ 
 
 // ---- mean over the positions of an image -------------------------------------------------------
 // pooled[n, c] = (1/HW) sum_p a[n, p, c], stored bf16 (operand of the classifier's product).
-// One workgroup per image: threads = C/4 column groups x row lanes, lanes combined in order.
+// One workgroup per image: threads = C/4 column groups x row lanes, lanes combined in order.  Sixteen
+// loads of a thread in flight (one: 20.4 us for 128 images of 32 x 32 x 64; sixteen: 8.5 us).
+constexpr int PP = 16;
 __global__ __launch_bounds__(NT) void avgpool_fwd_kernel(const bf16_t* __restrict__ a, int HW, int C,
                                                          bf16_t* __restrict__ pooled, int64_t ldp) {
   extern __shared__ float4 red[];
@@ -433,9 +442,17 @@ __global__ __launch_bounds__(NT) void avgpool_fwd_kernel(const bf16_t* __restric
   const int64_t base = (int64_t)blockIdx.x * HW * C;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (active)
-    for (int p = lane; p < HW; p += t.rl) {
-      const float4 v = unpack4(*reinterpret_cast<const uint2*>(&a[base + (int64_t)p * C + 4 * g]));
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    for (int p0 = lane; p0 < HW; p0 += PP * t.rl) {
+      uint2 v2[PP];
+#pragma unroll
+      for (int u = 0; u < PP; ++u)
+        v2[u] = *reinterpret_cast<const uint2*>(&a[base + (int64_t)min(p0 + u * t.rl, HW - 1) * C + 4 * g]);
+#pragma unroll
+      for (int u = 0; u < PP; ++u)
+        if (p0 + u * t.rl < HW) {
+          const float4 v = unpack4(v2[u]);
+          s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
     }
   const float4 tot = lanes_sum(s, red, g, lane, t);
   if (lane == 0) {
@@ -711,7 +728,7 @@ int launch_bn2d_stats(const float* y, int64_t rows, int C, float eps, float* par
   const int nchunk = conv_chunks(rows);
   bn2d_stats_partial_kernel<<<nchunk, NT, tall_lds(C), s>>>(y, rows, C, partial);
   VF_LAUNCH_CHECK();
-  bn2d_stats_finish_kernel<<<1, NTF, 0, s>>>(partial, nchunk, CHUNK, rows, C, eps, mean, rstd, run_mean, run_var, run_mix);
+  bn2d_stats_finish_kernel<<<(C + FIN_COLS - 1) / FIN_COLS, NTF, 0, s>>>(partial, nchunk, CHUNK, rows, C, eps, mean, rstd, run_mean, run_var, run_mix);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }
@@ -721,7 +738,7 @@ int launch_bn2d_stats_finish(const float* partial, int nchunk, int rows_per_chun
   if (rows <= 0 || !tall_ok(C) || !partial || nchunk < 1 || rows_per_chunk < 1) return VF_EINVAL;
   if ((int64_t)nchunk * rows_per_chunk < rows || (int64_t)(nchunk - 1) * rows_per_chunk >= rows) return VF_EINVAL;
   if ((run_mean == nullptr) != (run_var == nullptr)) return VF_EINVAL;
-  bn2d_stats_finish_kernel<<<1, NTF, 0, s>>>(partial, nchunk, rows_per_chunk, rows, C, eps, mean, rstd, run_mean, run_var,
+  bn2d_stats_finish_kernel<<<(C + FIN_COLS - 1) / FIN_COLS, NTF, 0, s>>>(partial, nchunk, rows_per_chunk, rows, C, eps, mean, rstd, run_mean, run_var,
                                              run_mix);
   VF_LAUNCH_CHECK();
   return VF_OK;
@@ -743,7 +760,7 @@ int launch_bn2d_bwd(float* da, const bf16_t* a, const float* y, int64_t rows, in
   const int nchunk = conv_chunks(rows);
   bn2d_bwd_partial_kernel<<<nchunk, NT, tall_lds(C), s>>>(da, a, y, rows, C, mean, rstd, partial);
   VF_LAUNCH_CHECK();
-  bn2d_bwd_finish_kernel<<<1, NTF, 0, s>>>(partial, nchunk, C, sums, gout_g, gout_b);
+  bn2d_bwd_finish_kernel<<<(C + FIN_COLS - 1) / FIN_COLS, NTF, 0, s>>>(partial, nchunk, C, sums, gout_g, gout_b);
   VF_LAUNCH_CHECK();
   const int64_t n4 = rows * C / 4;
   bn2d_bwd_apply_kernel<<<(unsigned)blocks(n4), NT, 0, s>>>(da, a, y, n4, C, 1.0f / (float)rows, gamma, round_params,
@@ -821,7 +838,8 @@ int launch_conv_wgrad_direct(const bf16_t* dy, int Cout, const bf16_t* x, int Ci
 
 int launch_fold_slabs(const float* slabs, int nsplit, int64_t stride, int64_t n, GradOut out, hipStream_t s) {
   if (n <= 0 || nsplit < 1 || !slabs || !out.dst) return VF_EINVAL;
-  if (nsplit >= 64 && (n & 3) == 0 && (stride & 3) == 0 && (reinterpret_cast<uintptr_t>(slabs) & 15) == 0)
+  // (32 slabs of 14400: one thread per element 9.1 us, eight lanes per four elements 4.8 us)
+  if (nsplit >= 16 && (n & 3) == 0 && (stride & 3) == 0 && (reinterpret_cast<uintptr_t>(slabs) & 15) == 0)
     fold_slabs_wide_kernel<<<(unsigned)((n / 4 + 31) / 32), NT, 0, s>>>(slabs, nsplit, stride, n / 4, out);
   else
     fold_slabs_kernel<<<(unsigned)blocks(n), NT, 0, s>>>(slabs, nsplit, stride, n, out);

@@ -93,11 +93,13 @@ class Conv final : public Model {
     a.request(&gB_, rows * C_);
     a.request(&partial_, (size_t)std::max(conv_chunks(rows_max_), kConvStatsChunks) * 2 * C_);
     a.request(&sums_, (size_t)2 * C_);
-    // contraction slabs of a weight gradient: up to kMaxSplit from the product over the transposed
+    // contraction slabs of a weight gradient: up to wgrad_split from the product over the transposed
     // patch matrix, up to kDirectSplit per 64 x 64 channel block from the direct kernel
-    const size_t per_slab = (size_t)C_ * (kp_max > 9 * C_ ? kp_max : 9 * C_);
     const int blocks64 = std::max(1, (C_ / 64) * (C_ / 64));
-    a.request(&slabs_, per_slab * (size_t)std::max(kMaxSplit, (kDirectSplit + blocks64 - 1) / blocks64));
+    size_t slab_floats = (size_t)C_ * 9 * C_ * ((kDirectSplit + blocks64 - 1) / blocks64);
+    for (const ConvLayer& L : layers_)
+      slab_floats = std::max(slab_floats, (size_t)L.C * L.Kc * wgrad_split(L, rows_max_));
+    a.request(&slabs_, slab_floats);
     a.request(&fc_wnat_, (size_t)C_ * ldz_);
     a.request(&fc_wtr_, (size_t)cfg_.classes * ldc_);
     a.request(&pooled_, (size_t)cfg_.max_node_size * ldc_);
@@ -138,8 +140,17 @@ class Conv final : public Model {
   }
 
  private:
-  static constexpr int kMaxSplit = 32;
+  static constexpr int kMaxSplit = 256;
   static constexpr int kDirectSplit = 256;
+
+  // Slabs of a weight gradient taken from the transposed patch matrix, at most.  A few tiles of output
+  // contracted over 10^4 to 10^5 positions: two workgroups per compute unit, slices of at least 256 positions.
+  // (The first layer's 64 x 27 gradient over 131072 positions took 36.9 us on the 32 workgroups that the
+  // general rule gives it, 9.0 us on 256.)
+  static int wgrad_split(const ConvLayer& L, int64_t rows) {
+    const int tiles = L.Kc <= 32 ? (L.C + 127) / 128 : ((L.C + 63) / 64) * ((L.Kc + 63) / 64);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(kMaxSplit, (512 + tiles - 1) / tiles), rows / 256));
+  }
 
   // y = patches(in) x filters^T; statistics over the node's rows; a = relu(BatchNorm(y) (+ skip))
   int conv_bn_relu(Ctx& c, ConvLayer& L, const bf16_t* in, const bf16_t* skip, int rows, const float* P,
@@ -216,7 +227,9 @@ class Conv final : public Model {
     VF_KS(c, st, "transpose", launch_transpose_bf16(L.in, L.Cin, inT_, ldr_, rows, L.Cin, st));
     VF_KS(c, st, "im2col", launch_im2col3x3_transposed(inT_, ldr_, rows, H_, H_, L.Cin, colsT_, ldr_, st));
     VF_KS(c, st, "transpose", launch_transpose_bf16(dy_, L.C, dyT_, ldr_, rows, L.C, st));
-    int split = std::min(kMaxSplit, gemm_bf16_pick_split(L.C, L.Kc, rows));
+    int split = wgrad_split(L, rows);
+    const int slice = ((rows + split - 1) / split + 63) / 64 * 64;
+    split = (rows + slice - 1) / slice;                       // no empty slice
     Epilogue ep;
     ep.C = slabs_; ep.ldc = L.Kc;
     VF_KS(c, st, "gemm_wgrad", launch_gemm_bf16(dyT_, ldr_, colsT_, ldr_, L.C, L.Kc, rows, split, slab, ep, st));
