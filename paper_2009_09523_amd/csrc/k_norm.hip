@@ -928,11 +928,26 @@ int launch_bn_relu_fwd(const float* zp, int nsplit, int64_t slab, int64_t ldzp, 
   const bool pair = group >= 2 && nsplit == 1 && zp == z && a_is_bf16 && pair_width(C) && !(ldz & 1) && !(lda & 1) &&
                     aligned_to(z, 8) && aligned_to(a, 4) && aligned_to(gamma, 8) && aligned_to(beta, 8) &&
                     aligned_to(mean, 8) && aligned_to(rstd, 8);
+  if (group > 1 && !a_is_bf16) {
+    // fp32: one launch per node, in node order.  Without BatchNorm nothing in a unit belongs to a node, and a
+    // launch takes as many rows as its workgroups hold in registers.
+    int total = 0;
+    for (int n = 0; n < group; ++n) total += node_rows ? node_rows[n] : R;
+    int64_t row = 0;
+    for (int n = 0; row < total; ++n) {
+      const int rows = !gamma ? std::min<int>(RCH, total - (int)row) : node_rows ? node_rows[n] : R;
+      const int64_t at = gamma ? (int64_t)n * C : 0;
+      VF_TRY(launch_bn_relu_fwd(zp + row * ldzp, nsplit, slab, ldzp, rows, C, gamma, beta, round_params, eps, z + row * ldz,
+                                ldz, static_cast<float*>(a) + row * lda, lda, 0, aT, ldt, mean + at, rstd + at, run_mean,
+                                run_var, run_mix, s, 1, nullptr));
+      row += rows;
+    }
+    return VF_OK;
+  }
   const int per = pair ? kBnGroupPair : kBnGroup;
   if (group > per) {
     // a unit of more nodes than a launch takes: one launch per `per` nodes, in node order (the moving
     // statistics are blended node after node by launches that follow each other on the stream)
-    if (!a_is_bf16) return VF_EINVAL;
     int64_t row = 0;
     for (int n0 = 0; n0 < group; n0 += per) {
       const int cnt = std::min(per, group - n0);
@@ -953,7 +968,6 @@ int launch_bn_relu_fwd(const float* zp, int nsplit, int64_t slab, int64_t ldzp, 
   const bool small = R <= RCH;
   GroupRows gr{};
   if (group != 1) {
-    if (!a_is_bf16) return VF_EINVAL;
     VF_TRY(group_rows(group, R, node_rows, aT != nullptr, &gr));
   }
   if (pair) {
@@ -1006,10 +1020,25 @@ int launch_bn_relu_bwd(float* dap, int nsplit, int64_t slab, int64_t ldda, const
   const bool pair = group >= 2 && nsplit == 1 && dz_is_bf16 && pair_width(C) && !(ldz & 1) && !(ldda & 1) && !(lddz & 1) &&
                     aligned_to(z, 8) && aligned_to(dap, 8) && aligned_to(dz, 4) && aligned_to(gamma, 8) &&
                     aligned_to(beta, 8) && aligned_to(mean, 8) && aligned_to(rstd, 8);
+  if (group > 1 && !dz_is_bf16) {      // fp32: as in the forward pass
+    int total = 0;
+    for (int n = 0; n < group; ++n) total += node_rows ? node_rows[n] : R;
+    int64_t row = 0;
+    for (int n = 0; row < total; ++n) {
+      const int rows = !gamma ? std::min<int>(RCH, total - (int)row) : node_rows ? node_rows[n] : R;
+      const int64_t at = gamma ? (int64_t)n * C : 0;
+      GradOut gg = gout_g, gb = gout_b;
+      if (n) { gg.accumulate = 1; gb.accumulate = 1; }
+      VF_TRY(launch_bn_relu_bwd(dap + row * ldda, nsplit, slab, ldda, z + row * ldz, ldz, rows, C, gamma, beta, round_params,
+                                mean + at, rstd + at, static_cast<float*>(dz) + row * lddz, lddz, 0, dzT, ldt, gg, gb, s,
+                                tscale, 1, nullptr));
+      row += rows;
+    }
+    return VF_OK;
+  }
   if (group > kBnGroup) {
     // a unit of more than kBnGroup nodes: one launch per kBnGroup nodes; the small-vector gradients
     // of the later launches are added to what the first one left
-    if (!dz_is_bf16) return VF_EINVAL;
     int64_t row = 0;
     for (int n0 = 0; n0 < group; n0 += kBnGroup) {
       const int cnt = std::min(kBnGroup, group - n0);
@@ -1031,7 +1060,6 @@ int launch_bn_relu_bwd(float* dap, int nsplit, int64_t slab, int64_t ldda, const
   const bool small = R <= RCH;
   GroupRows gr{};
   if (group != 1) {
-    if (!dz_is_bf16) return VF_EINVAL;
     VF_TRY(group_rows(group, R, node_rows, dzT != nullptr, &gr));
   }
   if (pair) {

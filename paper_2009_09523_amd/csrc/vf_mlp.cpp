@@ -43,7 +43,9 @@ class Mlp final : public Model {
     bf16_ = cfg.dtype == VF_BF16;
     // a unit of the passes is one node of any size, or up to node_group nodes of at most 128 rows each
     // (max_group), and never has more rows than a batch: every per-unit buffer is sized for that
-    group_ = bf16_ ? std::max(1, cfg.node_group) : 1;
+    // (fp32 takes units as well: a node of 16 rows is eleven launches of 3 us, four nodes in one unit cost
+    // no more; not with the node-by-node chain of the ordered fold)
+    group_ = bf16_ || !(cfg.flags & VF_FLAG_ORDERED_FOLD) ? std::max(1, cfg.node_group) : 1;
     const int64_t grouped = std::min<int64_t>((int64_t)std::min(cfg.max_node_size, 128) * group_,
                                               std::max(cfg.max_batch, cfg.max_node_size));
     max_rows_ = (int)std::max<int64_t>(cfg.max_node_size, group_ > 1 ? grouped : 0);
@@ -112,8 +114,8 @@ class Mlp final : public Model {
   int64_t num_params() const override { return P_; }
   bool supports_overlap() const override { return bf16_; }
   // groups of nodes: the BatchNorm kernels keep a node of up to 128 rows in registers, and the
-  // transposed copies want node boundaries on 16-byte boundaries
-  int max_group(int rows) const override { return (bf16_ && rows <= 128 && (rows & 7) == 0) ? 32 : 1; }
+  // transposed copies (bf16) want node boundaries on 16-byte boundaries
+  int max_group(int rows) const override { return rows <= 128 && (!bf16_ || (rows & 7) == 0) ? group_ : 1; }
   bool groups_unequal() const override { return true; }
   int max_window() const override { return bf16_ ? kFoldMax : 1; }
 

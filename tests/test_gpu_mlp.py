@@ -446,6 +446,24 @@ def test_node_groups_match_the_oracle(name, sizes, group):
     assert np.linalg.norm(gpu["G"] - plain["G"]) <= 2e-2 * np.linalg.norm(plain["G"])
 
 
+@pytest.mark.parametrize("group", [2, 4, 32])
+@pytest.mark.parametrize("name", ["mlp_small_f32", "mlp_small_bn_f32"])
+def test_node_groups_in_fp32_match_the_oracle(name, group):
+    """Units of fp32 nodes of any sizes (a node of more than 128 rows goes alone), more rows than the row-resident
+    kernels take at once; replayed and launched one by one give the same bits."""
+    print(f"case {name} group={group}", flush=True)
+    sizes = (37, 2, 101, 16, 128, 3, 130, 9)
+    wl = I.workload(name).with_nodes(sizes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    ref = oracle_steps(wl, theta, x, y)
+    base = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH, node_group=group)
+    check_against_oracle(wl, base, ref)
+    again = run_gpu(wl, theta, x, y, flags=FUSED, node_group=group)
+    assert base["G"].tobytes() == again["G"].tobytes()
+    check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=0, node_group=group), ref)
+
+
 @pytest.mark.parametrize("group", [16, 32])
 @pytest.mark.parametrize("name,sizes", [("mlp_mid_bn_bf16", [8] * 30), ("mlp_mid_bf16", [8] * 30),
                                         ("mlp_mid_bn_bf16", [16, 8, 8] * 7 + [16]), ("mlp_mid_bn_bf16", [24] * 9)])
