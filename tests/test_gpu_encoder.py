@@ -50,6 +50,18 @@ def test_encoder_sequence_lengths(T):
     assert base["G"].tobytes() == two["G"].tobytes()
 
 
+@pytest.mark.parametrize("name,T,sizes", [("enc_small_f32", 5, (3, 1)), ("enc_small_f32", 70, (2, 1)),
+                                          ("enc_small_f32", 130, (24,)), ("enc_small_bf16", 131, (22, 2))])
+def test_generic_attention_products(name, T, sizes):
+    """The batched products on the fp32 matrix instruction: contractions and tiles that are not filled, rows that
+    allow no vector reads, one 16 x 16 tile per wavefront and (1024 and more of them) 32 x 32."""
+    print(f"case {name} T={T} sizes={sizes}", flush=True)
+    wl = replace(I.workload(name), name=f"{name}_T{T}", seq_len=T, n_masked=max(1, int(0.15 * T)), node_sizes=sizes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH), oracle_steps(wl, theta, x, y))
+
+
 def test_encoder_fused_and_staged_agree_bitwise():
     wl, theta, x, y = _case("enc_small_bf16")
     a = run_gpu(wl, theta, x, y, flags=0)
