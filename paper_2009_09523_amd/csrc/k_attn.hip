@@ -39,6 +39,13 @@ __device__ __forceinline__ float half_sum(float v) {
   return v;
 }
 
+// FULL: the sequence fills its tiles (T = TS), nothing is clamped or masked (T = 128, 3 heads: forward
+// 13.6 -> 13.0 us, backward 16.1 -> 14.1 us).
+template <bool FULL>
+__device__ __forceinline__ int row_of(int t, int T) { return FULL ? t : min(t, T - 1); }
+template <bool FULL>
+__device__ __forceinline__ bool is_row(int t, int T) { return FULL || t < T; }
+
 __device__ __forceinline__ u32x4 row_or_zero(u32x4 v, bool inside) {
 #pragma unroll
   for (int u = 0; u < 4; ++u) v[u] = inside ? v[u] : 0u;
@@ -46,12 +53,12 @@ __device__ __forceinline__ u32x4 row_or_zero(u32x4 v, bool inside) {
 }
 
 // Stage a [T][64] bf16 window (row stride `rs` elements) into LDS as [t][e] (ld LDE), TS rows.
-template <int TS>
+template <int TS, bool FULL>
 __device__ __forceinline__ void stage_rows(const bf16_t* __restrict__ g, int64_t rs, int T, bf16_t* lds) {
   for (int v = threadIdx.x; v < TS * (DH / 8); v += blockDim.x) {
     const int t = v >> 3, e8 = (v & 7) * 8;
     *reinterpret_cast<u32x4*>(&lds[t * LDE + e8]) =
-        row_or_zero(*reinterpret_cast<const u32x4*>(&g[(int64_t)min(t, T - 1) * rs + e8]), t < T);
+        row_or_zero(*reinterpret_cast<const u32x4*>(&g[(int64_t)row_of<FULL>(t, T) * rs + e8]), is_row<FULL>(t, T));
   }
 }
 // Stage the same window transposed: lds[e][t] (ld TS+8).  A thread takes two neighbouring rows
@@ -59,20 +66,20 @@ __device__ __forceinline__ void stage_rows(const bf16_t* __restrict__ g, int64_t
 // threads of a wavefront run along t, so the words of one store instruction are neighbours in
 // LDS (one bank each) -- single 16-bit stores 272 bytes apart had put sixteen lanes on two banks.
 __device__ __forceinline__ uint32_t pick16(const u32x4& x, int u) { return (x[u >> 1] >> ((u & 1) * 16)) & 0xffffu; }
-template <int TS>
+template <int TS, bool FULL>
 __device__ __forceinline__ void stage_cols(const bf16_t* __restrict__ g, int64_t rs, int T, bf16_t* lds) {
   constexpr int LDT = TS + 8;
   for (int v = threadIdx.x; v < (TS / 2) * (DH / 8); v += blockDim.x) {
     const int t = 2 * (v % (TS / 2)), e8 = (v / (TS / 2)) * 8;
-    const u32x4 x0 = row_or_zero(*reinterpret_cast<const u32x4*>(&g[(int64_t)min(t, T - 1) * rs + e8]), t < T);
-    const u32x4 x1 = row_or_zero(*reinterpret_cast<const u32x4*>(&g[(int64_t)min(t + 1, T - 1) * rs + e8]), t + 1 < T);
+    const u32x4 x0 = row_or_zero(*reinterpret_cast<const u32x4*>(&g[(int64_t)row_of<FULL>(t, T) * rs + e8]), is_row<FULL>(t, T));
+    const u32x4 x1 = row_or_zero(*reinterpret_cast<const u32x4*>(&g[(int64_t)row_of<FULL>(t + 1, T) * rs + e8]), is_row<FULL>(t + 1, T));
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       *reinterpret_cast<uint32_t*>(&lds[(e8 + u) * LDT + t]) = pick16(x0, u) | (pick16(x1, u) << 16);
   }
 }
 
-template <int TS>
+template <int TS, bool FULL>
 __global__ __launch_bounds__(2 * TS) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, int T, int d, int n_heads,
                                                           bf16_t* __restrict__ prob, bf16_t* __restrict__ om,
                                                           float scale) {
@@ -88,10 +95,10 @@ __global__ __launch_bounds__(2 * TS) void attn_fwd_kernel(const bf16_t* __restri
   const int bh = blockIdx.x, seq = bh / n_heads, head = bh % n_heads;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t rs = 3 * (int64_t)d;
-  const bf16_t* qg = qkv + (int64_t)seq * T * rs + head * DH;
-  stage_rows<TS>(qg, rs, T, Qs);
-  stage_rows<TS>(qg + d, rs, T, Ks);
-  stage_cols<TS>(qg + 2 * d, rs, T, Vt);
+  const bf16_t* qg = qkv + (int64_t)seq * (FULL ? TS : T) * rs + head * DH;
+  stage_rows<TS, FULL>(qg, rs, T, Qs);
+  stage_rows<TS, FULL>(qg + d, rs, T, Ks);
+  stage_cols<TS, FULL>(qg + 2 * d, rs, T, Vt);
   __syncthreads();
 
   // scores of this wave's 32 query rows against all keys
@@ -113,7 +120,7 @@ __global__ __launch_bounds__(2 * TS) void attn_fwd_kernel(const bf16_t* __restri
     float m = -INFINITY;
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) {
-      if (32 * jt + (lane & 31) >= T) s[jt][r] = -INFINITY;    // no such key
+      if (!is_row<FULL>(32 * jt + (lane & 31), T)) s[jt][r] = -INFINITY;    // no such key
       m = fmaxf(m, s[jt][r] * scale);
     }
     m = half_max(m);
@@ -155,12 +162,12 @@ __global__ __launch_bounds__(2 * TS) void attn_fwd_kernel(const bf16_t* __restri
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = 32 * w + acc_row(r, lane);
-      if (row < T) om[((int64_t)seq * T + row) * d + head * DH + 32 * et + (lane & 31)] = f32_to_bf16(o[r]);
+      if (is_row<FULL>(row, T)) om[((int64_t)seq * T + row) * d + head * DH + 32 * et + (lane & 31)] = f32_to_bf16(o[r]);
     }
   }
 }
 
-template <int TS>
+template <int TS, bool FULL>
 __global__ __launch_bounds__(2 * TS) void attn_bwd_kernel(const float* __restrict__ dO,
                                                           const bf16_t* __restrict__ qkv,
                                                           const bf16_t* __restrict__ prob, int T, int d,
@@ -180,16 +187,16 @@ __global__ __launch_bounds__(2 * TS) void attn_bwd_kernel(const float* __restric
   const int bh = blockIdx.x, seq = bh / n_heads, head = bh % n_heads;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t rs = 3 * (int64_t)d;
-  const bf16_t* qg = qkv + (int64_t)seq * T * rs + head * DH;
-  stage_cols<TS>(qg, rs, T, Qt);
-  stage_cols<TS>(qg + d, rs, T, Kt);
-  stage_rows<TS>(qg + 2 * d, rs, T, Vs);
+  const bf16_t* qg = qkv + (int64_t)seq * (FULL ? TS : T) * rs + head * DH;
+  stage_cols<TS, FULL>(qg, rs, T, Qt);
+  stage_cols<TS, FULL>(qg + d, rs, T, Kt);
+  stage_rows<TS, FULL>(qg + 2 * d, rs, T, Vs);
   // dO: fp32 [t][e] -> bf16, both orientations: rows as they are (16-byte stores), and transposed
   // with the pair-of-rows mapping of stage_cols
-  const float* dog = dO + (int64_t)seq * T * d + head * DH;
+  const float* dog = dO + (int64_t)seq * (FULL ? TS : T) * d + head * DH;
   for (int v = threadIdx.x; v < TS * (DH / 8); v += blockDim.x) {
     const int t = v >> 3, e8 = (v & 7) * 8;
-    const float* src = &dog[(int64_t)min(t, T - 1) * d + e8];
+    const float* src = &dog[(int64_t)row_of<FULL>(t, T) * d + e8];
     const float4 a = *reinterpret_cast<const float4*>(src);
     const float4 b = *reinterpret_cast<const float4*>(src + 4);
     u32x4 h;
@@ -197,13 +204,13 @@ __global__ __launch_bounds__(2 * TS) void attn_bwd_kernel(const float* __restric
     h[1] = (uint32_t)f32_to_bf16(a.z) | ((uint32_t)f32_to_bf16(a.w) << 16);
     h[2] = (uint32_t)f32_to_bf16(b.x) | ((uint32_t)f32_to_bf16(b.y) << 16);
     h[3] = (uint32_t)f32_to_bf16(b.z) | ((uint32_t)f32_to_bf16(b.w) << 16);
-    *reinterpret_cast<u32x4*>(&dOs[t * LDE + e8]) = row_or_zero(h, t < T);
+    *reinterpret_cast<u32x4*>(&dOs[t * LDE + e8]) = row_or_zero(h, is_row<FULL>(t, T));
   }
   for (int v = threadIdx.x; v < (TS / 2) * (DH / 8); v += blockDim.x) {
     const int t = 2 * (v % (TS / 2)), e8 = (v / (TS / 2)) * 8;
-    const float* src0 = &dog[(int64_t)min(t, T - 1) * d + e8];
-    const float* src1 = &dog[(int64_t)min(t + 1, T - 1) * d + e8];
-    const uint32_t in0 = t < T ? 0xffffu : 0u, in1 = t + 1 < T ? 0xffff0000u : 0u;
+    const float* src0 = &dog[(int64_t)row_of<FULL>(t, T) * d + e8];
+    const float* src1 = &dog[(int64_t)row_of<FULL>(t + 1, T) * d + e8];
+    const uint32_t in0 = is_row<FULL>(t, T) ? 0xffffu : 0u, in1 = is_row<FULL>(t + 1, T) ? 0xffff0000u : 0u;
     const float4 a0 = *reinterpret_cast<const float4*>(src0);
     const float4 b0 = *reinterpret_cast<const float4*>(src0 + 4);
     const float4 a1 = *reinterpret_cast<const float4*>(src1);
@@ -227,7 +234,7 @@ __global__ __launch_bounds__(2 * TS) void attn_bwd_kernel(const float* __restric
   }
   __syncthreads();
 
-  const int64_t orow = (int64_t)seq * T;
+  const int64_t orow = (int64_t)seq * (FULL ? TS : T);
   // dV[j, e] = sum_q P[q, j] dO[q, e]: this wave's 32 key rows
 #pragma unroll
   for (int et = 0; et < DH / 32; ++et) {
@@ -243,7 +250,7 @@ __global__ __launch_bounds__(2 * TS) void attn_bwd_kernel(const float* __restric
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = 32 * w + acc_row(r, lane);
-      if (row < T) dqkv[(orow + row) * rs + 2 * d + head * DH + 32 * et + (lane & 31)] = f32_to_bf16(a[r]);
+      if (is_row<FULL>(row, T)) dqkv[(orow + row) * rs + 2 * d + head * DH + 32 * et + (lane & 31)] = f32_to_bf16(a[r]);
     }
   }
   // dP[q, j] = sum_e dO[q, e] v[j, e]: this wave's 32 query rows
@@ -303,7 +310,7 @@ __global__ __launch_bounds__(2 * TS) void attn_bwd_kernel(const float* __restric
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int t = 32 * w + acc_row(r, lane);
-      if (t >= T) continue;
+      if (!is_row<FULL>(t, T)) continue;
       const int64_t row = (orow + t) * rs + head * DH + 32 * et + (lane & 31);
       dqkv[row] = f32_to_bf16(aq[r] * scale);
       dqkv[row + d] = f32_to_bf16(ak[r] * scale);
@@ -322,10 +329,12 @@ template <int TS>
 int set_lds_limits() {
   static bool done = false;      // per process; the attribute is per function
   if (done) return VF_OK;
-  VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd_kernel<TS>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_lds<TS>()));
-  VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_kernel<TS>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bwd_lds<TS>()));
+  const void* fwd[] = {reinterpret_cast<const void*>(&attn_fwd_kernel<TS, false>),
+                       reinterpret_cast<const void*>(&attn_fwd_kernel<TS, true>)};
+  const void* bwd[] = {reinterpret_cast<const void*>(&attn_bwd_kernel<TS, false>),
+                       reinterpret_cast<const void*>(&attn_bwd_kernel<TS, true>)};
+  for (const void* f : fwd) VF_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_lds<TS>()));
+  for (const void* f : bwd) VF_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bwd_lds<TS>()));
   done = true;
   return VF_OK;
 }
@@ -345,7 +354,8 @@ int launch_attn_fwd(const bf16_t* qkv, int n_seq, int seq_len, int d, int n_head
 #define VF_AF(TS)                                                                                  \
   case TS:                                                                                         \
     VF_TRY(set_lds_limits<TS>());                                                                  \
-    attn_fwd_kernel<TS><<<grid, 2 * TS, fwd_lds<TS>(), s>>>(qkv, seq_len, d, n_heads, prob, om, scale);      \
+    if (seq_len == TS) attn_fwd_kernel<TS, true><<<grid, 2 * TS, fwd_lds<TS>(), s>>>(qkv, TS, d, n_heads, prob, om, scale); \
+    else attn_fwd_kernel<TS, false><<<grid, 2 * TS, fwd_lds<TS>(), s>>>(qkv, seq_len, d, n_heads, prob, om, scale); \
     break;
   switch (attn_mfma_pitch(seq_len)) { VF_AF(32) VF_AF(64) VF_AF(96) VF_AF(128) default: return VF_EINVAL; }
 #undef VF_AF
@@ -360,7 +370,8 @@ int launch_attn_bwd(const float* dO, const bf16_t* qkv, const bf16_t* prob, int 
 #define VF_AB(TS)                                                                                  \
   case TS:                                                                                         \
     VF_TRY(set_lds_limits<TS>());                                                                  \
-    attn_bwd_kernel<TS><<<grid, 2 * TS, bwd_lds<TS>(), s>>>(dO, qkv, prob, seq_len, d, n_heads, dqkv, scale); \
+    if (seq_len == TS) attn_bwd_kernel<TS, true><<<grid, 2 * TS, bwd_lds<TS>(), s>>>(dO, qkv, prob, TS, d, n_heads, dqkv, scale); \
+    else attn_bwd_kernel<TS, false><<<grid, 2 * TS, bwd_lds<TS>(), s>>>(dO, qkv, prob, seq_len, d, n_heads, dqkv, scale); \
     break;
   switch (attn_mfma_pitch(seq_len)) { VF_AB(32) VF_AB(64) VF_AB(96) VF_AB(128) default: return VF_EINVAL; }
 #undef VF_AB
