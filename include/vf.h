@@ -171,8 +171,9 @@ typedef struct vf_config {
                                     step computes what it computes node by node, up to the order of
                                     additions and (nodes of different sizes) one bf16 rounding of
                                     the output gradients, which carry 1/rows of the unit instead of
-                                    1/b_i.  MLP: nodes of at most 128 rows (bf16: a multiple of 8), of any
-                                    mix of sizes; other nodes go alone (units of 16 or 32 nodes, and fp32: the
+                                    1/b_i.  MLP: nodes of at most 128 rows (with
+                                    VF_FLAG_ORDERED_FOLD a multiple of 8), of any mix of sizes; other
+                                    nodes go alone (units of 16 or 32 nodes, and fp32: the
                                     staged fold then differs from the fused one by fp32 rounding in the
                                     BatchNorm scale / shift gradients, and a fold window holds at most
                                     as many units as a batch has).  Encoder: up to four

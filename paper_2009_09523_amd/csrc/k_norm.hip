@@ -48,16 +48,35 @@ __device__ __forceinline__ float sum_slabs(const float* __restrict__ p, int64_t 
   return t;
 }
 
+// Eight rows of a transposed copy, or the `n` < 8 that a node still has there.  In a unit of nodes the copy of a
+// node may start at any column, so the 16 bytes lie on any 2-byte boundary, and what follows a node's last row
+// belongs to the next node.
+__device__ __forceinline__ void store_rows8(bf16_t* dst, const bf16_t* src, int n) {
+  if (n >= 8) {
+    const uint4 v = *reinterpret_cast<const uint4*>(src);      // (LDS rows are 16-byte aligned)
+    __builtin_memcpy(dst, &v, 16);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+      if (i < n) dst[i] = src[i];
+  }
+}
+
 // Writes the bf16 tile held in LDS ([CB][RCH+8]: column c, rows r0..r0+RCH) to
-// outT[c*ldt + r] with 16-byte stores; rows beyond R are padding inside the buffer's row.
+// outT[c*ldt + r] with 16-byte stores; rows beyond R are padding inside the buffer's row (if it
+// starts on a 16-byte boundary; the last node of a unit may not).
 __device__ __forceinline__ void store_transposed(const bf16_t (*tile)[RCH + 8], bf16_t* __restrict__ outT,
                                                  int64_t ldt, int c0, int C, int r0, int R) {
   const int col = threadIdx.x >> 4, seg = threadIdx.x & 15;    // 16 columns x 16 segments of 8 rows
   const int c = c0 + col;
   const int rl = seg * 8;
-  if (c < C && r0 + rl < R)   // the vector holds at least one live row; ldt is a multiple of 8
-    *reinterpret_cast<uint4*>(&outT[(int64_t)c * ldt + r0 + rl]) =
-        *reinterpret_cast<const uint4*>(&tile[col][rl]);
+  if (c < C && r0 + rl < R) {   // the vector holds at least one live row; ldt is a multiple of 8
+    bf16_t* dst = &outT[(int64_t)c * ldt + r0 + rl];
+    if ((reinterpret_cast<uintptr_t>(outT) & 15) == 0)
+      *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(&tile[col][rl]);
+    else
+      store_rows8(dst, &tile[col][rl], R - r0 - rl);
+  }
 }
 
 // Which block of CB columns workgroup b takes.  A block of 16 columns is half a 128-byte line of
@@ -324,7 +343,7 @@ __global__ __launch_bounds__(256) void bn_relu_bwd_kernel(float* __restrict__ da
 // through LDS and is finished by one thread per column.  mean_out / rstd_out hold G vectors of C,
 // the transposed copy node n's rows at columns n*R .. n*R + R-1.
 // Row ranges of the nodes of a unit: node n has rows[n] <= 128 rows starting at row base[n] of the
-// unit (a multiple of 8 when transposed copies are written); entries beyond the unit's nodes are 0.
+// unit; entries beyond the unit's nodes are 0.
 constexpr int kBnGroup = 8;   // nodes per launch of the group kernels
 constexpr int kBnGroupPair = 16;   // nodes per launch of the forward two-column kernel
 struct GroupRows { int base[16]; int rows[16]; };
@@ -340,8 +359,7 @@ __device__ __forceinline__ void store_transposed_sub(const bf16_t (*tile)[RCH + 
   const int col = t >> 4, seg = t & 15;          // 16 columns x 16 segments of 8 rows
   const int c = c0 + col;
   const int rl = seg * 8;
-  if (c < C && rl < R)
-    *reinterpret_cast<uint4*>(&outT[(int64_t)c * ldt + rl]) = *reinterpret_cast<const uint4*>(&tile[col][rl]);
+  if (c < C && rl < R) store_rows8(&outT[(int64_t)c * ldt + rl], &tile[col][rl], R - rl);
 }
 
 template <int NS, int G, int SGP>
@@ -564,8 +582,13 @@ __device__ __forceinline__ void store_transposed_pair(const bf16_t (*tile)[RCH +
   for (int h = 0; h < 2; ++h) {
     const int col = (t >> 4) + 16 * h;          // 2 x 16 columns x 16 segments of 8 rows
     const int c = c0 + col;
-    if (c < C && rl < R)
-      store16_stream(&outT[(int64_t)c * ldt + rl], *reinterpret_cast<const uint4*>(&tile[col][rl]));
+    if (c < C && rl < R) {
+      bf16_t* dst = &outT[(int64_t)c * ldt + rl];
+      if (((reinterpret_cast<uintptr_t>(dst) & 15) | (R & 7)) == 0)
+        store16_stream(dst, *reinterpret_cast<const uint4*>(&tile[col][rl]));
+      else
+        store_rows8(dst, &tile[col][rl], R - rl);
+    }
   }
 }
 
@@ -906,12 +929,12 @@ int group_subgroups(int grid) {
 // The row ranges of a unit's nodes for the group kernels: `group` nodes of R rows each, or of
 // node_rows[n] rows when given.  Every node at most 128 rows; ranges start on multiples of 8 when
 // transposed copies are written.
-int group_rows(int group, int R, const int* node_rows, bool transposed, GroupRows* gr) {
+int group_rows(int group, int R, const int* node_rows, GroupRows* gr) {
   if (group < 2 || group > kBnGroupPair) return VF_EINVAL;
   int at = 0;
   for (int n = 0; n < kBnGroupPair; ++n) {
     const int rows = n < group ? (node_rows ? node_rows[n] : R) : 0;
-    if (n < group && (rows < 1 || rows > RCH || (transposed && (rows & 7)))) return VF_EINVAL;
+    if (n < group && (rows < 1 || rows > RCH)) return VF_EINVAL;
     gr->base[n] = n < group ? at : 0;
     gr->rows[n] = rows;
     at += rows;
@@ -968,7 +991,7 @@ int launch_bn_relu_fwd(const float* zp, int nsplit, int64_t slab, int64_t ldzp, 
   const bool small = R <= RCH;
   GroupRows gr{};
   if (group != 1) {
-    VF_TRY(group_rows(group, R, node_rows, aT != nullptr, &gr));
+    VF_TRY(group_rows(group, R, node_rows, &gr));
   }
   if (pair) {
     const int pgrid = (C + CB2 - 1) / CB2;
@@ -1060,7 +1083,7 @@ int launch_bn_relu_bwd(float* dap, int nsplit, int64_t slab, int64_t ldda, const
   const bool small = R <= RCH;
   GroupRows gr{};
   if (group != 1) {
-    VF_TRY(group_rows(group, R, node_rows, dzT != nullptr, &gr));
+    VF_TRY(group_rows(group, R, node_rows, &gr));
   }
   if (pair) {
     const int pgrid = (C + CB2 - 1) / CB2;

@@ -113,9 +113,9 @@ class Mlp final : public Model {
 
   int64_t num_params() const override { return P_; }
   bool supports_overlap() const override { return bf16_; }
-  // groups of nodes: the BatchNorm kernels keep a node of up to 128 rows in registers, and the
-  // transposed copies (bf16) want node boundaries on 16-byte boundaries
-  int max_group(int rows) const override { return rows <= 128 && (!bf16_ || (rows & 7) == 0) ? group_ : 1; }
+  // groups of nodes: the BatchNorm kernels keep a node of up to 128 rows in registers.  (The ordered fold of bf16
+  // nodes that are no multiple of 8 is bitwise the node-by-node one: those go alone.)
+  int max_group(int rows) const override { return rows <= 128 && (!ordered_ || (rows & 7) == 0) ? group_ : 1; }
   bool groups_unequal() const override { return true; }
   int max_window() const override { return bf16_ ? kFoldMax : 1; }
 

@@ -422,7 +422,7 @@ def test_changing_the_split_between_steps_replays_the_right_graph():
                                         ("mlp_mid_bn_bf16", [112, 112, 16]), ("mlp_mid_bn_bf16", [24] * 10)])
 def test_node_groups_match_the_oracle(name, sizes, group):
     """Up to 2, 4 or 8 consecutive nodes, of one size or of several, taken through their passes as one
-    unit (ten nodes go as 8 + 2; sizes that are no multiple of 8 would go alone), in every fold mode, on one and two streams, replayed and
+    unit (ten nodes go as 8 + 2), in every fold mode, on one and two streams, replayed and
     launched one by one: BatchNorm statistics, node losses and the weights b_i/B stay per node, so
     the oracle's node-by-node result must come out; the modes agree bitwise with one another."""
     wl, theta, x, y = _case(name)
@@ -444,6 +444,31 @@ def test_node_groups_match_the_oracle(name, sizes, group):
     gpu = run_gpu(wl, theta, x, y, node_sizes=sizes, flags=FUSED | NO_GRAPH | OVERLAP, fold_window=4, node_group=group)
     check_against_oracle(wl, gpu, ref)
     assert np.linalg.norm(gpu["G"] - plain["G"]) <= 2e-2 * np.linalg.norm(plain["G"])
+
+
+@pytest.mark.parametrize("group", [2, 4, 8, 32])
+@pytest.mark.parametrize("name,sizes", [("mlp_mid_bn_bf16", [37] * 6), ("mlp_mid_bf16", [33, 2, 40, 7, 16, 101, 5]),
+                                        ("mlp_mid_bn_bf16", [33, 2, 40, 7, 16, 101, 5, 9, 3, 12, 4])])
+def test_node_groups_of_odd_sizes_match_the_oracle(name, sizes, group):
+    """Units whose nodes end anywhere: their transposed copies lie side by side at any column.  Fused and staged, one
+    and two streams, replayed and one by one, single units and windows of them; the last node of a unit alone in its
+    launch (nine and eleven nodes)."""
+    print(f"case {name} sizes={sizes} group={group}", flush=True)
+    wl, theta, x, y = _case(name)
+    B = sum(sizes)
+    x, y = x[:B], y[:B]
+    assert len(x) == B
+    ref = oracle_steps(wl, theta, x, y, node_sizes=sizes)
+    base = None
+    for flags in (FUSED, FUSED | NO_GRAPH, FUSED | NO_GRAPH | OVERLAP, FUSED | OVERLAP):
+        gpu = run_gpu(wl, theta, x, y, node_sizes=sizes, flags=flags, node_group=group)
+        if base is None:
+            base = gpu
+            check_against_oracle(wl, gpu, ref)
+        assert gpu["G"].tobytes() == base["G"].tobytes(), flags
+    check_against_oracle(wl, run_gpu(wl, theta, x, y, node_sizes=sizes, flags=0, node_group=group), ref)
+    check_against_oracle(wl, run_gpu(wl, theta, x, y, node_sizes=sizes, flags=FUSED | NO_GRAPH | OVERLAP, fold_window=4,
+                                     node_group=group), ref)
 
 
 @pytest.mark.parametrize("group", [2, 4, 32])
