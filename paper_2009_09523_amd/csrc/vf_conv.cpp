@@ -4,8 +4,8 @@
 //
 // A convolution is a product over patch rows (per output position the 3x3 neighbourhood of the
 // bf16, channels-last input: 9*Cin values) with the filters.  When the input channels are a
-// multiple of 64 the kernels read the patches straight from the activation (no patch matrix) --
-// with 64 channels and an image side of 8 to 64, a kernel that keeps the filters in LDS and
+// multiple of 8 the kernels read the patches straight from the activation (no patch matrix) --
+// with 64 channels and an image side of 8 to 64, a kernel that keeps the filters in registers and
 // stages the input once per 64 positions; otherwise (the first layer) im2col writes them.  The
 // input gradient is the same convolution of the output gradient with the filters turned by 180
 // degrees and the channel roles exchanged (a second bf16 copy of the filters, made once per
@@ -159,7 +159,7 @@ class Conv final : public Model {
     Epilogue ep;
     ep.C = L.y; ep.ldc = L.C;
     int chunks = 0, chunk_rows = 0;     // statistics partials that the convolution kernel leaves, if it does
-    if (L.Cin % 64 == 0 && !explicit_) {
+    if (!explicit_ && (L.Cin % 64 == 0 || (L.Cin % 8 == 0 && L.Cin <= 256 && (reinterpret_cast<uintptr_t>(in) & 15) == 0))) {
       VF_KS(c, st, "gemm_fwd", launch_conv3x3_bf16(in, rows, H_, H_, L.Cin, L.wnat, L.Kp, L.C, ep, zeros_, st, partial_,
                                                    &chunks, &chunk_rows));
     } else {
@@ -242,7 +242,7 @@ class Conv final : public Model {
     Epilogue ep;
     ep.C = out; ep.ldc = L.Cin;
     if (addend) { ep.R = addend; ep.ldr = L.Cin; ep.beta = 1.f; }
-    if (L.C % 64 == 0 && !explicit_) {
+    if (!explicit_) {                                        // (C is a multiple of 8)
       VF_KS(c, st, "gemm_dgrad", launch_conv3x3_bf16(dy_, rows, H_, H_, L.C, L.wflip, L.Kpf, L.Cin, ep, zeros_, st));
     } else {
       VF_KS(c, st, "im2col", launch_im2col3x3(dy_, rows, H_, H_, L.C, cols_, L.Kpf, st));
