@@ -2115,10 +2115,10 @@ static bool wide_fits(int M, int N) { return wide_mode() && M > 128 && N >= 128;
 static float tile64_cost(int M, int N, int K, int nsplit) {
   const float tiles = (float)((M + 63) / 64) * (float)((N + 63) / 64) * nsplit;
   const float stages = (float)(((K + nsplit - 1) / nsplit + BK - 1) / BK);
-  // two workgroups per compute unit, all of them fed: 0.38 us per stage, more in further rounds and with
-  // operands that pass through the L2s
+  // one workgroup per compute unit 0.27 us per stage; two 0.38 us, as soon as one unit has two (640 x 1904 x 8192
+  // unsplit, 300 tiles: 50.6 us); more in further rounds and with operands that pass through the L2s
   const bool far = ((float)M + N) * K * 2 > 48e6f;
-  const float stage = (far ? 0.55f : tiles > 512 ? 0.5f : 0.38f) / 512 * tiles;
+  const float stage = (far ? 0.55f : tiles > 512 ? 0.5f : 0.38f) / 512 * (tiles > 256 ? std::max(512.f, tiles) : tiles);
   return 3.4f + stages * std::max(0.27f, stage) + (float)M * N * nsplit * 1e-6f;
 }
 static float wide_cost(int M, int N, int K, int nsplit) {
@@ -2135,7 +2135,9 @@ static bool takes_wide(int M, int N, int K, int nsplit) {
 // that many slices plus what the consumer needs to read the slabs (the BatchNorm kernels read them at
 // 1.5 TB/s or so).  256 x 4096 x 4096 (a unit of small nodes): two slabs off the 64 x 64 kernel,
 // 17.7 us, where eight off the 256-row kernel took 17.8 us and the kernels behind them 25 and 39 us.
-int gemm_bf16_pick_split(int M, int N, int K) {
+// A fold of gradient slabs reads them faster (four slabs of 640 x 1904: 6.1 us, 1.3 us per million elements):
+// `slab_us` is the consumer's cost of a million elements of one slab.
+int gemm_bf16_pick_split(int M, int N, int K, float slab_us) {
   if (M > 32 && N > 32) {
     const bool wide = wide_fits(M, N);
     const int bn = wide ? wide_tile_n(M, N) : 64, bm = wide ? 256 : 64;
@@ -2151,7 +2153,7 @@ int gemm_bf16_pick_split(int M, int N, int K) {
       if (!few64 && !few_wide) continue;
       const float c64 = few64 ? tile64_cost(M, N, K, split) : 1e30f;
       const float cw = few_wide ? wide_cost(M, N, K, split) : 1e30f;
-      const float c = std::min(c64, cw) + (float)M * N * split * 2.7e-6f;
+      const float c = std::min(c64, cw) + (float)M * N * split * slab_us * 1e-6f;
       if (split == 1 || c < cost) { best = split; cost = c; }
     }
     return best;

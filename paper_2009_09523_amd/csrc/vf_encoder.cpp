@@ -158,7 +158,7 @@ class Encoder final : public Model {
       wslab_elems_ = 0;
       for (const Lin* L : lins_)
         if (L != &out_)
-          wslab_elems_ = std::max(wslab_elems_, (size_t)gemm_bf16_pick_split(L->K, L->N, (int)maxR_) * L->K * L->N);
+          wslab_elems_ = std::max(wslab_elems_, (size_t)gemm_bf16_pick_split(L->K, L->N, (int)maxR_, kSlabFoldUs) * L->K * L->N);
       if (wslab_elems_) {
         a.request(&wslab_[0], wslab_elems_);
         if (sets_ == 2) a.request(&wslab_[1], wslab_elems_);
@@ -438,7 +438,7 @@ class Encoder final : public Model {
       const bf16_t* Bt = dy_transposed && dyT ? dyT : sB_;
       float* slabs = wslab_[sA_ == tA2_ && tA2_ ? 1 : 0];
       const int64_t each = (int64_t)L.K * L.N;
-      int ns = (slabs && &L != &out_) ? gemm_bf16_pick_split(L.K, L.N, R) : 1;
+      int ns = (slabs && &L != &out_) ? gemm_bf16_pick_split(L.K, L.N, R, kSlabFoldUs) : 1;
       while (ns > 1 && (size_t)ns * each > wslab_elems_) ns /= 2;
       if (ns > 1) {
         // slices of the contraction into slabs, added in slab order into the gradient

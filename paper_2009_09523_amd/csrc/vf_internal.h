@@ -152,7 +152,8 @@ int launch_bn_stats_finish(const float* mean, const float* var, int nodes, int C
 // Scale / shift (or bias) gradients from the per-node column sums, added up in node order.
 int launch_bn_sums_finish(const float* sums, int nodes, int C, GradOut gout_g, GradOut gout_b, hipStream_t s);
 // Number of slices that fills the chip for this shape (1 when the tile grid already does).
-int gemm_bf16_pick_split(int M, int N, int K);
+constexpr float kSlabFoldUs = 1.3f;    // a million elements of a slab that launch_fold_slabs reads
+int gemm_bf16_pick_split(int M, int N, int K, float slab_us = 2.7f);
 
 // Weight gradients of `count` consecutive nodes folded into C in one pass over it:
 //   C <- fma(w[count-1], A[count-1] B[count-1]^T, ... fma(w[0], A[0] B[0]^T, overwrite ? 0 : C))
