@@ -2136,7 +2136,9 @@ static bool takes_wide(int M, int N, int K, int nsplit) {
 // 1.5 TB/s or so).  256 x 4096 x 4096 (a unit of small nodes): two slabs off the 64 x 64 kernel,
 // 17.7 us, where eight off the 256-row kernel took 17.8 us and the kernels behind them 25 and 39 us.
 // A fold of gradient slabs reads them faster (four slabs of 640 x 1904: 6.1 us, 1.3 us per million elements):
-// `slab_us` is the consumer's cost of a million elements of one slab.
+// `slab_us` is the consumer's cost of a million elements of one slab; a fold also takes any number of them (the
+// BatchNorm kernels powers of two): 768 x 3072 x 8192 has 72 tiles for the 256-row kernel, 144 workgroups in two
+// slices, 216 in three.
 int gemm_bf16_pick_split(int M, int N, int K, float slab_us) {
   if (M > 32 && N > 32) {
     const bool wide = wide_fits(M, N);
@@ -2145,11 +2147,13 @@ int gemm_bf16_pick_split(int M, int N, int K, float slab_us) {
     const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
     int best = 1;
     float cost = 0.f;
-    for (int split = 1; split <= 32; split *= 2) {
+    const bool any = slab_us == kSlabFoldUs;
+    for (int split = 1; split <= 32; split = any && split < 16 ? split + 1 : split * 2) {
+      if ((int64_t)(split - 1) * (((K + split - 1) / split + BK - 1) / BK * BK) >= K) continue;   // an empty slice
       // slices of three stages at least (eight for the 256-row kernel) until every compute unit has a
       // workgroup (two for the 64 x 64 kernel)
       const bool few64 = split == 1 || (tiles * split <= 512 && K / split >= 3 * BK);
-      const bool few_wide = wide && (split == 1 || (wtiles * split <= 256 && K / split >= 8 * BK && (K / BK) % split == 0));
+      const bool few_wide = wide && (split == 1 || (wtiles * split <= 256 && K / split >= 8 * BK && ((any && bn == 128) || (K / BK) % split == 0)));
       if (!few64 && !few_wide) continue;
       const float c64 = few64 ? tile64_cost(M, N, K, split) : 1e30f;
       const float cw = few_wide ? wide_cost(M, N, K, split) : 1e30f;
