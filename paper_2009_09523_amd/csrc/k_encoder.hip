@@ -459,21 +459,37 @@ __global__ __launch_bounds__(NT) void layernorm_bwd4_kernel(const float* __restr
     pg[j] = make_float4(0.f, 0.f, 0.f, 0.f); pb[j] = pg[j];
     const int c = min(4 * lane + 256 * j, d - 4);
     gv[j] = *reinterpret_cast<const float4*>(&gamma[c]);
-    if (round_params) { gv[j].x = round_bf16(gv[j].x); gv[j].y = round_bf16(gv[j].y); gv[j].z = round_bf16(gv[j].z); gv[j].w = round_bf16(gv[j].w); }
   }
-  for (int r = rbeg + wave; r < rend; r += WAVES) {
-    const int64_t orow = row_map ? row_map[r] : r;
-    const float* xr = x + orow * ldx;
-    const float mean = mean_in[r], rstd = rstd_in[r];
-    float4 dyv[JQ], xhv[JQ], resv[JQ];
-    // all loads first, at clamped (always valid) columns, so that they are in flight together
+  if (round_params) {
+#pragma unroll
+    for (int j = 0; j < JQ; ++j) {
+      gv[j].x = round_bf16(gv[j].x); gv[j].y = round_bf16(gv[j].y); gv[j].z = round_bf16(gv[j].z); gv[j].w = round_bf16(gv[j].w);
+    }
+  }
+  // A wavefront has eight rows or so and its SIMD to itself: the next row's loads go out before this row is
+  // worked on, at clamped (always valid) rows and columns.
+  struct Row { float4 dy[JQ], x[JQ], res[JQ]; float mean, rstd; int64_t orow; };
+  auto load = [&](int r, Row& q) {
+    r = min(r, rend - 1);
+    q.orow = row_map ? row_map[r] : r;
+    q.mean = mean_in[r]; q.rstd = rstd_in[r];
 #pragma unroll
     for (int j = 0; j < JQ; ++j) {
       const int c = min(4 * lane + 256 * j, d - 4);
-      resv[j] = dres ? *reinterpret_cast<const float4*>(&dres[orow * lddx + c]) : make_float4(0.f, 0.f, 0.f, 0.f);
-      dyv[j] = *reinterpret_cast<const float4*>(&dyp[(int64_t)r * lddy + c]);
-      xhv[j] = *reinterpret_cast<const float4*>(&xr[c]);
+      q.res[j] = dres ? *reinterpret_cast<const float4*>(&dres[q.orow * lddx + c]) : make_float4(0.f, 0.f, 0.f, 0.f);
+      q.dy[j] = *reinterpret_cast<const float4*>(&dyp[(int64_t)r * lddy + c]);
+      q.x[j] = *reinterpret_cast<const float4*>(&x[q.orow * ldx + c]);
     }
+  };
+  Row next;
+  load(rbeg + wave, next);
+  for (int r = rbeg + wave; r < rend; r += WAVES) {
+    float4 dyv[JQ], xhv[JQ], resv[JQ];
+    const float mean = next.mean, rstd = next.rstd;
+    const int64_t orow = next.orow;
+#pragma unroll
+    for (int j = 0; j < JQ; ++j) { dyv[j] = next.dy[j]; xhv[j] = next.x[j]; resv[j] = next.res[j]; }
+    load(r + WAVES, next);
     for (int s = 1; s < nsplit; ++s) {            // the slabs in order
 #pragma unroll
       for (int j = 0; j < JQ; ++j) {
