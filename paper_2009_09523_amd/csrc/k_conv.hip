@@ -169,22 +169,25 @@ __global__ __launch_bounds__(NT) void conv_weight_copies_kernel(const float* __r
 }
 
 // ---- tall column reductions --------------------------------------------------------------------
-// A workgroup owns CHUNK consecutive rows; a thread owns 4 consecutive columns (float4) of every
+// A workgroup owns `chunk` consecutive rows (chunk_rows); a thread owns 4 consecutive columns (float4) of every
 // RL-th row: NT threads = C/4 column groups x RL row lanes (C in {8, 16, 32, 64, 128, 256} uses
 // all 256 threads; other C leave the last few idle).  C % 4 == 0, C <= 256.
-constexpr int CHUNK = 256;       // rows per workgroup
+// Rows per workgroup: 256 where that gives every compute unit a workgroup, else 128 (37632 rows of 40 columns:
+// partials 7.1 -> 6.6 us and 6.7 -> 6.0 us; 131072 rows of 64: 15.4 -> 14.9 us, but the finish kernel behind
+// them 4.5 -> 5.0 us).
+inline int chunk_rows(int64_t rows) { return rows >= 65536 ? 256 : 128; }
 
 struct Tall {
   int cg;        // column groups of 4 (C / 4)
   int rl;        // row lanes = NT / cg (at least 1)
-  int passes;    // ceil(CHUNK / rl)
+  int passes;    // ceil(chunk / rl)
 };
-__device__ __forceinline__ Tall tall_shape(int C) {
+__device__ __forceinline__ Tall tall_shape(int C, int chunk) {
   Tall t;
   t.cg = C >> 2;
   t.rl = NT / t.cg;
   if (t.rl < 1) t.rl = 1;
-  t.passes = (CHUNK + t.rl - 1) / t.rl;
+  t.passes = (chunk + t.rl - 1) / t.rl;
   return t;
 }
 
@@ -221,14 +224,14 @@ __device__ __forceinline__ void join_stats(float& cnt, float& mean, float& m2, f
 // Per chunk and column: the mean of the chunk's rows and the sum of squared deviations from it.
 // partial[(chunk*2 + 0)*C + c] = mean, partial[(chunk*2 + 1)*C + c] = M2.
 __global__ __launch_bounds__(NT) void bn2d_stats_partial_kernel(const float* __restrict__ y, int64_t rows, int C,
-                                                                float* __restrict__ partial) {
+                                                                int chunk, float* __restrict__ partial) {
   extern __shared__ float4 red[];
   __shared__ float4 mean_s[64];
-  const Tall t = tall_shape(C);
+  const Tall t = tall_shape(C, chunk);
   const int g = threadIdx.x % t.cg, lane = threadIdx.x / t.cg;
   const bool active = lane < t.rl;
-  const int64_t r0 = (int64_t)blockIdx.x * CHUNK;
-  const int n = (int)min((int64_t)CHUNK, rows - r0);
+  const int64_t r0 = (int64_t)blockIdx.x * chunk;
+  const int n = (int)min((int64_t)chunk, rows - r0);
   const float* yb = y + r0 * C + 4 * g;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int p0 = 0; p0 < t.passes; p0 += PB) {
@@ -368,14 +371,14 @@ __global__ __launch_bounds__(NT) void bn2d_apply_fwd_kernel(const float* __restr
 // xhat = (y - mean) * rstd.  partial[(chunk*2 + 0)*C + c] = sum dpre, [.. + 1 ..] = sum dpre*xhat.
 __global__ __launch_bounds__(NT) void bn2d_bwd_partial_kernel(const float* __restrict__ da, const bf16_t* __restrict__ a,
                                                               const float* __restrict__ y, int64_t rows, int C,
-                                                              const float* __restrict__ mean, const float* __restrict__ rstd,
-                                                              float* __restrict__ partial) {
+                                                              int chunk, const float* __restrict__ mean,
+                                                              const float* __restrict__ rstd, float* __restrict__ partial) {
   extern __shared__ float4 red[];
-  const Tall t = tall_shape(C);
+  const Tall t = tall_shape(C, chunk);
   const int g = threadIdx.x % t.cg, lane = threadIdx.x / t.cg;
   const bool active = lane < t.rl;
-  const int64_t r0 = (int64_t)blockIdx.x * CHUNK;
-  const int n = (int)min((int64_t)CHUNK, rows - r0);
+  const int64_t r0 = (int64_t)blockIdx.x * chunk;
+  const int n = (int)min((int64_t)chunk, rows - r0);
   const int64_t base = r0 * C + 4 * g;
   const float4 m = *reinterpret_cast<const float4*>(&mean[4 * g]);
   const float4 rs = *reinterpret_cast<const float4*>(&rstd[4 * g]);
@@ -489,7 +492,7 @@ constexpr int PP = 16;
 __global__ __launch_bounds__(NT) void avgpool_fwd_kernel(const bf16_t* __restrict__ a, int HW, int C,
                                                          bf16_t* __restrict__ pooled, int64_t ldp) {
   extern __shared__ float4 red[];
-  Tall t = tall_shape(C);
+  const Tall t = tall_shape(C, 0);
   const int g = threadIdx.x % t.cg, lane = threadIdx.x / t.cg;
   const bool active = lane < t.rl;
   const int64_t base = (int64_t)blockIdx.x * HW * C;
@@ -765,7 +768,8 @@ __global__ __launch_bounds__(WG_NT) void conv_wgrad_kernel(const bf16_t* __restr
 
 }  // namespace
 
-int conv_chunks(int64_t rows) { return (int)((rows + CHUNK - 1) / CHUNK); }
+int conv_chunks(int64_t rows) { return (int)((rows + chunk_rows(rows) - 1) / chunk_rows(rows)); }
+int conv_chunks_max(int64_t rows) { return std::max(conv_chunks(rows), conv_chunks(std::min<int64_t>(rows, 65535))); }
 
 int launch_im2col3x3(const bf16_t* x, int64_t rows, int H, int W, int C, bf16_t* cols, int64_t Kp, hipStream_t s) {
   if (rows <= 0 || H <= 0 || W <= 0 || C <= 0 || Kp < 9 * C || (Kp & 7) || rows % ((int64_t)H * W)) return VF_EINVAL;
@@ -806,9 +810,9 @@ int launch_bn2d_stats(const float* y, int64_t rows, int C, float eps, float* par
   if (rows <= 0 || !tall_ok(C) || !partial) return VF_EINVAL;
   if ((run_mean == nullptr) != (run_var == nullptr)) return VF_EINVAL;
   const int nchunk = conv_chunks(rows);
-  bn2d_stats_partial_kernel<<<nchunk, NT, tall_lds(C), s>>>(y, rows, C, partial);
+  bn2d_stats_partial_kernel<<<nchunk, NT, tall_lds(C), s>>>(y, rows, C, chunk_rows(rows), partial);
   VF_LAUNCH_CHECK();
-  bn2d_stats_finish_kernel<<<(C + FIN_COLS - 1) / FIN_COLS, NTF, 0, s>>>(partial, nchunk, CHUNK, rows, C, eps, mean, rstd, run_mean, run_var, run_mix);
+  bn2d_stats_finish_kernel<<<(C + FIN_COLS - 1) / FIN_COLS, NTF, 0, s>>>(partial, nchunk, chunk_rows(rows), rows, C, eps, mean, rstd, run_mean, run_var, run_mix);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }
@@ -838,7 +842,7 @@ int launch_bn2d_bwd(float* da, const bf16_t* a, const float* y, int64_t rows, in
                     int keep_dpre, bf16_t* dy, GradOut gout_g, GradOut gout_b, hipStream_t s) {
   if (rows <= 0 || !tall_ok(C) || !partial || !sums) return VF_EINVAL;
   const int nchunk = conv_chunks(rows);
-  bn2d_bwd_partial_kernel<<<nchunk, NT, tall_lds(C), s>>>(da, a, y, rows, C, mean, rstd, partial);
+  bn2d_bwd_partial_kernel<<<nchunk, NT, tall_lds(C), s>>>(da, a, y, rows, C, chunk_rows(rows), mean, rstd, partial);
   VF_LAUNCH_CHECK();
   bn2d_bwd_finish_kernel<<<(C + FIN_COLS - 1) / FIN_COLS, NTF, 0, s>>>(partial, nchunk, C, sums, gout_g, gout_b);
   VF_LAUNCH_CHECK();
@@ -916,10 +920,11 @@ int launch_conv_wgrad_direct(const bf16_t* dy, int Cout, const bf16_t* x, int Ci
   return rc;
 }
 
-int launch_fold_slabs(const float* slabs, int nsplit, int64_t stride, int64_t n, GradOut out, hipStream_t s) {
+int launch_fold_slabs(const float* slabs, int nsplit, int64_t stride, int64_t n, GradOut out, hipStream_t s, bool in_order) {
   if (n <= 0 || nsplit < 1 || !slabs || !out.dst) return VF_EINVAL;
-  // (32 slabs of 14400: one thread per element 9.1 us, eight lanes per four elements 4.8 us)
-  if (nsplit >= 16 && (n & 3) == 0 && (stride & 3) == 0 && (reinterpret_cast<uintptr_t>(slabs) & 15) == 0)
+  // (32 slabs of 14400: one thread per element 9.1 us, eight lanes per four elements 4.8 us; from 64 slabs on it is
+  // taken everywhere)
+  if (nsplit >= (in_order ? 64 : 16) && (n & 3) == 0 && (stride & 3) == 0 && (reinterpret_cast<uintptr_t>(slabs) & 15) == 0)
     fold_slabs_wide_kernel<<<(unsigned)((n / 4 + 31) / 32), NT, 0, s>>>(slabs, nsplit, stride, n / 4, out);
   else if (n >= (1 << 16) && (n & 3) == 0 && (stride & 3) == 0 &&
            ((reinterpret_cast<uintptr_t>(slabs) | reinterpret_cast<uintptr_t>(out.dst)) & 15) == 0)

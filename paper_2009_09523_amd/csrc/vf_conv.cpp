@@ -91,7 +91,7 @@ class Conv final : public Model {
     a.request(&dy_, rows * C_);
     a.request(&gA_, rows * C_);
     a.request(&gB_, rows * C_);
-    a.request(&partial_, (size_t)std::max(conv_chunks(rows_max_), kConvStatsChunks) * 2 * C_);
+    a.request(&partial_, (size_t)std::max(conv_chunks_max(rows_max_), kConvStatsChunks) * 2 * C_);
     a.request(&sums_, (size_t)2 * C_);
     // contraction slabs of a weight gradient: up to wgrad_split from the product over the transposed
     // patch matrix, up to kDirectSplit per 64 x 64 channel block from the direct kernel
@@ -233,7 +233,7 @@ class Conv final : public Model {
     Epilogue ep;
     ep.C = slabs_; ep.ldc = L.Kc;
     VF_KS(c, st, "gemm_wgrad", launch_gemm_bf16(dyT_, ldr_, colsT_, ldr_, L.C, L.Kc, rows, split, slab, ep, st));
-    VF_KS(c, st, "fold_slabs", launch_fold_slabs(slabs_, split, slab, slab, c.gout(L.w_off, w, node), st));
+    VF_KS(c, st, "fold_slabs", launch_fold_slabs(slabs_, split, slab, slab, c.gout(L.w_off, w, node), st, false));
     return VF_OK;
   }
 

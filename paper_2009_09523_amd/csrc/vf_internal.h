@@ -256,7 +256,8 @@ int launch_colsum(const void* x, int64_t ld, int x_is_bf16, int R, int C, GradOu
 
 // k_conv.hip -- the convolutional family: 3x3 convolutions (stride 1, zero padding 1, NHWC) as
 // products over patch rows, BatchNorm over a node's n*H*W positions in chunks of rows.
-int conv_chunks(int64_t rows);     // row chunks of the tall reductions: sizes their partial buffers (2*C floats each)
+int conv_chunks(int64_t rows);     // row chunks of the tall reductions (2*C floats of partials each)
+int conv_chunks_max(int64_t rows); // the most that any number of rows up to `rows` has: sizes their partial buffers
 // cols[r, (kh*3+kw)*C + c] = x[n, h+kh-1, w+kw-1, c] or 0; row pitch Kp >= 9C, a multiple of 8
 int launch_im2col3x3(const bf16_t* x, int64_t rows, int H, int W, int C, bf16_t* cols, int64_t Kp, hipStream_t s);
 // the same patches transposed, [9C, ldo] (positions along the row), from the transposed input
@@ -294,8 +295,10 @@ bool conv_wgrad_direct_fits(int Cout, int Cin, int H, int W, int64_t rows);
 int launch_conv_wgrad_direct(const bf16_t* dy, int Cout, const bf16_t* x, int Cin, int64_t rows, int H, int W,
                              const bf16_t* zeros, float* slabs, int64_t slab_stride, int max_split, int* nsplit_out,
                              hipStream_t s);
-// out (+)= alpha * (slab 0 + slab 1 + ...), slabs in order
-int launch_fold_slabs(const float* slabs, int nsplit, int64_t stride, int64_t n, GradOut out, hipStream_t s);
+// out (+)= alpha * (slab 0 + slab 1 + ...), slabs in order; with in_order = false (and for 64 slabs and more)
+// possibly as eight runs of slabs, each in order, added up in order
+int launch_fold_slabs(const float* slabs, int nsplit, int64_t stride, int64_t n, GradOut out, hipStream_t s,
+                      bool in_order = true);
 
 // k_loss.hip
 // Softmax cross-entropy over R rows of fp32 logits with C classes.  zp: nsplit partial slabs
