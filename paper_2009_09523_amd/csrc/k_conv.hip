@@ -542,6 +542,7 @@ __global__ __launch_bounds__(NT) void fold_slabs_kernel(const float* __restrict_
 }
 
 // The same, four elements per thread and four slabs on their way (16-byte aligned, n and stride multiples of 4).
+// Bound by memory: two slabs of 2.36 M elements into a gradient 9.9 us one element a thread, 8.4 us this way.
 __global__ __launch_bounds__(NT) void fold_slabs4_kernel(const float* __restrict__ slabs, int nsplit, int64_t stride,
                                                          int64_t n4, GradOut out) {
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
