@@ -11,12 +11,15 @@
 // chunks of 16 contraction elements in flight: a contraction of 64 is one trip.  No LDS, no barrier;
 // neighbouring wavefronts share their operands through the caches.  (64 x 64 tiles of one workgroup,
 // staged 16 elements at a time through LDS, on the vector ALUs: 14.8 us for 8 to 16 heads of 64 x 64 x 64; this: 4.3 to 4.8 us.)
+#include <algorithm>
+
 #include "vf_device.h"
 
 namespace vf {
 namespace {
 
 constexpr int NT = 256, WAVES = NT / 64;
+constexpr int kGridRows = 65535;             // batches of one launch
 constexpr int CHUNK_K = 16, DEPTH = 4;       // contraction elements of a chunk, chunks in flight
 
 // Four consecutive contraction elements of one operand row: fp32 or bf16, as one vector or one by one.
@@ -145,7 +148,18 @@ int kind_of(const BMat& x, int K) {
 int launch_bgemm(const BMat& A, const BMat& B, const BMat& C, int M, int N, int K, int batch, int inner,
                  float alpha, hipStream_t s) {
   if (M <= 0 || N <= 0 || K <= 0 || batch <= 0 || inner <= 0 || !A.p || !B.p || !C.p) return VF_EINVAL;
-  if (batch > 65535) return VF_EINVAL;
+  if (batch > kGridRows) {      // (rows of a grid: a unit of several nodes may hold more heads than that)
+    const int run = kGridRows / inner;          // whole steps of `outer`
+    if (run < 1) return VF_EINVAL;
+    auto from = [](BMat x, int64_t step) {
+      x.p = static_cast<const char*>(x.p) + step * x.outer * (x.is_bf16 ? 2 : 4);
+      return x;
+    };
+    for (int64_t o = 0; o * inner < batch; o += run)
+      VF_TRY(launch_bgemm(from(A, o), from(B, o), from(C, o), M, N, K, (int)std::min<int64_t>((int64_t)run * inner, batch - o * inner),
+                          inner, alpha, s));
+    return VF_OK;
+  }
   // 32 x 32 outputs per wavefront (half the operand reads per output) as soon as that leaves four wavefronts for
   // each of the 256 compute units
   const int64_t big = (int64_t)batch * ((M + 31) / 32) * ((N + 31) / 32);

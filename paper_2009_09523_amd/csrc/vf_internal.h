@@ -333,7 +333,7 @@ struct BMat {
   int64_t outer, inner, rs, cs;
   int round_bf16 = 0;   // fp32 storage, but values enter the product rounded to bf16
 };
-// C[b][m,n] = alpha * sum_k A[b][m,k] * B[b][n,k], b < batch (<= 65535)
+// C[b][m,n] = alpha * sum_k A[b][m,k] * B[b][n,k], b < batch (inner <= 65535 where batch is more)
 int launch_bgemm(const BMat& A, const BMat& B, const BMat& C, int M, int N, int K, int batch, int inner,
                  float alpha, hipStream_t s);
 

@@ -62,6 +62,19 @@ def test_generic_attention_products(name, T, sizes):
     check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH), oracle_steps(wl, theta, x, y))
 
 
+@pytest.mark.parametrize("sizes", [(4099, 4100, 4101, 4098), (3, 4100, 4101, 4098, 4100, 2)])
+def test_units_of_more_heads_than_a_grid_has_rows(sizes):
+    """Four nodes of different sizes go as one unit, whose attention products are then more than 65535 (16398
+    sequences of four heads): each node alone has few enough."""
+    print(f"sizes={sizes}", flush=True)
+    wl = replace(I.workload("enc_small_f32"), name="enc_many", n_layers=1, d_model=16, n_heads=4, d_ffn=32, seq_len=2,
+                 vocab=53, n_masked=1, node_sizes=sizes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH, node_group=4)
+    check_against_oracle(wl, gpu, oracle_steps(wl, theta, x, y))
+
+
 def test_encoder_fused_and_staged_agree_bitwise():
     wl, theta, x, y = _case("enc_small_bf16")
     a = run_gpu(wl, theta, x, y, flags=0)
