@@ -198,20 +198,87 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
   }
 }
 
-// Operands that a workgroup cannot reach with 32-bit offsets (row pitches of 32 MB and more): one element of C
-// per thread.
-__global__ __launch_bounds__(256) void gemm_f32_far_kernel(const float* __restrict__ A, int64_t sam, int64_t sak,
-                                                           const float* __restrict__ B, int64_t sbn, int64_t sbk,
-                                                           int M, int N, int K, int kslab, int64_t slab_stride, Epilogue ep) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (int64_t)M * N) return;
-  const int m = (int)(e / N), n = (int)(e % N);
-  float acc = 0.f;
-  for (int k = blockIdx.z * kslab, end = min(K, (int)(blockIdx.z + 1) * kslab); k < end; ++k)
-    acc = fmaf(A[m * sam + k * sak], B[n * sbn + k * sbk], acc);
-  float add = (ep.bias && blockIdx.z == 0) ? ep.bias[n] : 0.f;
-  if (ep.R) add = fmaf(ep.beta, ep.R[(int64_t)m * ep.ldr + n], add);
-  static_cast<float*>(ep.C)[(int64_t)blockIdx.z * slab_stride + (int64_t)m * ep.ldc + n] = fmaf(ep.alpha, acc, add);
+// The general form: any strides, 64-bit addresses.  64 x 64 tiles of 256 threads, 16 contraction elements at a time
+// through LDS, products on the vector ALUs.
+constexpr int TT = 64, TK = 16, TILED_NT = 256;
+
+// Loads a [64 x TK] tile (row r, element k) into dst[k][r].  When the k stride is 1 consecutive threads walk k,
+// otherwise they walk rows, so that the unit-stride index is the fastest across a wavefront.
+__device__ __forceinline__ void load_tile(const float* __restrict__ base, int64_t srow, int64_t sk, int row0, int nrows,
+                                          int k0, int K, float (*dst)[TT + 4], int tid) {
+  if (sk == 1) {
+#pragma unroll
+    for (int i = 0; i < TT * TK / TILED_NT; ++i) {
+      const int e = tid + i * TILED_NT;
+      const int k = e % TK, r = e / TK;
+      const int gr = row0 + r, gk = k0 + k;
+      dst[k][r] = gr < nrows && gk < K ? base[(int64_t)gr * srow + gk] : 0.f;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TT * TK / TILED_NT; ++i) {
+      const int e = tid + i * TILED_NT;
+      const int r = e % TT, k = e / TT;
+      const int gr = row0 + r, gk = k0 + k;
+      dst[k][r] = gr < nrows && gk < K ? base[(int64_t)gr * srow + (int64_t)gk * sk] : 0.f;
+    }
+  }
+}
+
+__global__ __launch_bounds__(TILED_NT) void gemm_f32_tiled_kernel(const float* __restrict__ A, int64_t sam, int64_t sak,
+                                                                  const float* __restrict__ B, int64_t sbn, int64_t sbk,
+                                                                  int M, int N, int K, int kslab, int64_t slab_stride,
+                                                                  Epilogue ep) {
+  __shared__ float As[TK][TT + 4];
+  __shared__ float Bs[TK][TT + 4];
+  const int tid = threadIdx.x;
+  const int tx = tid % 16, ty = tid / 16;
+  const int m0 = blockIdx.y * TT, n0 = blockIdx.x * TT;
+  float acc[4][4] = {};
+  const int kbeg = blockIdx.z * kslab;
+  const int kend = min(K, kbeg + kslab);
+  for (int k0 = kbeg; k0 < kend; k0 += TK) {
+    load_tile(A, sam, sak, m0, M, k0, kend, As, tid);
+    load_tile(B, sbn, sbk, n0, N, k0, kend, Bs, tid);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < TK; ++k) {
+      float a[4], b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    }
+    __syncthreads();
+  }
+  float* C = static_cast<float*>(ep.C) + (int64_t)blockIdx.z * slab_stride;
+  const bool first_slice = blockIdx.z == 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = m0 + ty * 4 + i;
+    if (m >= M) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = n0 + tx * 4 + j;
+      if (n >= N) continue;
+      float add = (ep.bias && first_slice) ? ep.bias[n] : 0.f;
+      if (ep.R) add = fmaf(ep.beta, ep.R[(int64_t)m * ep.ldr + n], add);
+      C[(int64_t)m * ep.ldc + n] = fmaf(ep.alpha, acc[i][j], add);
+    }
+  }
+}
+
+int launch_tiled(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbn, int64_t sbk, int M, int N, int K,
+                 int nsplit, int64_t slab_stride, const Epilogue& ep, hipStream_t s) {
+  const int kslab = ((K + nsplit - 1) / nsplit + TK - 1) / TK * TK;
+  dim3 grid((N + TT - 1) / TT, (M + TT - 1) / TT, nsplit);
+  gemm_f32_tiled_kernel<<<grid, TILED_NT, 0, s>>>(A, sam, sak, B, sbn, sbk, M, N, K, kslab, slab_stride, ep);
+  VF_LAUNCH_CHECK();
+  return VF_OK;
 }
 
 struct F32Shape {
@@ -267,14 +334,13 @@ int launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, in
   const bool akc = sak == 1, bkc = sbk == 1;
   if ((!akc && sam != 1) || (!bkc && sbn != 1)) return VF_EINVAL;
   F32Shape g{A, akc ? sam : sak, B, bkc ? sbn : sbk, M, N, K, nsplit, slab_stride};
-  // what a workgroup's loads reach (64 rows, or the whole contraction of an operand contiguous along its rows)
+  // What a workgroup's loads reach: 64 rows of an operand contiguous along k (pitches of 32 MB and more are out of
+  // reach), or the whole contraction of one contiguous along its rows (any weight of 2 GiB and more).  Out of
+  // 32-bit reach the tiled kernel takes them (64 x 32768 x 16384, a weight of 2 GiB: 3.9 ms; one thread per output
+  // 27 ms).
   auto near = [&](bool kc, int64_t ld, int rows) { return (kc ? 64 * ld + K : (int64_t)K * ld + rows) * 4 < ((int64_t)1 << 31); };
   if (!near(akc, g.lda, M) || !near(bkc, g.ldb, N)) {
-    const int kslab = (K + nsplit - 1) / nsplit;
-    dim3 grid((unsigned)(((int64_t)M * N + 255) / 256), 1, nsplit);
-    gemm_f32_far_kernel<<<grid, 256, 0, s>>>(A, sam, sak, B, sbn, sbk, M, N, K, kslab, slab_stride, ep);
-    VF_LAUNCH_CHECK();
-    return VF_OK;
+    return launch_tiled(A, sam, sak, B, sbn, sbk, M, N, K, nsplit, slab_stride, ep, s);
   }
   auto al = [](const float* p, int64_t ld) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && (ld & 3) == 0; };
   const bool vec = (K & 3) == 0 && (!akc || al(A, g.lda)) && (!bkc || al(B, g.ldb));

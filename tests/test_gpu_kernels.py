@@ -258,3 +258,42 @@ def test_gemm_f32_tiles(M, N, K, pad):
     bound = K * 2.0 ** -24 * 0.5 * (np.abs(a) @ np.abs(b).T) + 2.0 ** -23 * (1 + np.abs(C0[:, :N]))
     assert np.all(np.abs(got[:, :N] - (0.5 * (a @ b.T) + C0[:, :N])) <= bound + 2.0 ** -23 * np.abs(a @ b.T))
     np.testing.assert_array_equal(got[:, N:], C0[:, N:])
+
+
+def _time_us(f, repeats=5):
+    """The fastest of a few runs of f, in microseconds."""
+    import torch
+    f()
+    best = float("inf")
+    for _ in range(repeats):
+        a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+        a.record(), f(), b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("M,N,K,limit_us", [(5, 13, 4099, None), (65, 130, 33, None), (64, 8192, 1024, 700)])
+def test_gemm_f32_of_operands_out_of_32_bit_reach(M, N, K, limit_us):
+    """Rows 32 MB and more apart: a workgroup of the kernel with 32-bit offsets cannot reach them.  Right, and as fast as
+    the tiled kernel is (64 x 8192 x 1024: 197 us; one thread per output took 1695 us, and the forward product of a
+    weight of 2 GiB, 64 x 32768 x 16384, 27 ms instead of 4)."""
+    import torch
+    import paper_2009_09523_amd as vf
+    print(f"gemm f32 far M={M} N={N} K={K}", flush=True)
+    pitch = (1 << 23) + 3
+    gen = torch.Generator().manual_seed(5)
+    A = torch.empty(M * pitch, device="cuda").as_strided((M, K), (pitch, 1))
+    a, B = torch.randn((M, K), generator=gen), torch.randn((N, K), generator=gen)
+    A.copy_(a)
+    C0 = torch.randn((M, N), generator=gen)
+    Bd, C = B.cuda(), C0.cuda()
+    vf.vf_gemm(A, Bd, C, M, N, K, alpha=0.5, accumulate=True)
+    torch.cuda.synchronize()
+    exact = a.double() @ B.double().T
+    # fp32 sums of K products: at most K roundings of partial sums no larger than sum |a||b|
+    bound = K * 2.0 ** -24 * 0.5 * (a.abs().double() @ B.abs().double().T) + 2.0 ** -23 * (1 + C0.abs() + exact.abs())
+    assert torch.all((C.cpu().double() - (0.5 * exact + C0.double())).abs() <= bound)
+    if limit_us:
+        us = _time_us(lambda: vf.vf_gemm(A, Bd, C, M, N, K))
+        assert us < limit_us, us
