@@ -10,7 +10,9 @@
 // tile, operands straight from memory into the MFMA registers (nothing is shared between wavefronts, so LDS
 // would only add a round trip), two groups of 32 or 64 contraction elements in flight; the partial tiles are
 // then added through LDS in wavefront order, so results do not depend on scheduling.  The same products now
-// take 4.9 and 15 us; 2048 x 1024 x 1024 runs at 81 TFLOP/s.
+// take 4.9 us and, with the operands in cache, 15 us (24 us inside a step); 2048 x 1024 x 1024 runs at 81 TFLOP/s.
+// Where there are tiles enough for every wavefront to have one of its own, and for operands out of 32-bit reach,
+// see launch_operands and launch_gemm_f32.
 #include "vf_device.h"
 
 namespace vf {
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
   constexpr int R = MF::R;
   constexpr int E = TM * TN * MS * MS;                   // elements of the tile
   constexpr int GK = GU * 4 * (64 / MS);                 // contraction elements of a group
-  __shared__ float part[NW * E];
+  __shared__ float part[NW > 1 ? NW * E : 1];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.y * (MS * TM), n0 = blockIdx.x * (MS * TN);
@@ -163,13 +165,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
   }
 
   // Partial tiles through LDS as the registers hold them, added in wavefront order.
+  if (NW > 1) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < R; ++r) part[wave * E + ((i * TN + j) * R + r) * 64 + lane] = acc[i][j][r];
-  __syncthreads();
+        for (int r = 0; r < R; ++r) part[wave * E + ((i * TN + j) * R + r) * 64 + lane] = acc[i][j][r];
+    __syncthreads();
+  }
   float* C = static_cast<float*>(ep.C) + (int64_t)blockIdx.z * slab_stride;
   const bool first_slice = blockIdx.z == 0;
   constexpr int NT = NW * 64;
@@ -191,9 +195,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
   for (int p = 0; p < PER; ++p) {
     const int e = p * NT + tid;
     if (mm[p] >= M || nn[p] >= N) continue;
-    float sum = part[e];
+    float sum;
+    if (NW > 1) {
+      sum = part[e];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) sum += part[w * E + e];
+      for (int w = 1; w < NW; ++w) sum += part[w * E + e];
+    } else {
+      sum = acc[p / R / TN][p / R % TN][p % R];            // (element e of the tile is this lane's p-th)
+    }
     C[(int64_t)mm[p] * ep.ldc + nn[p]] = fmaf(ep.alpha, sum, add[p]);
   }
 }
@@ -304,11 +313,40 @@ int launch_tile(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
 //   more tiles      256 x 1024 x 256: 32/16 4.2, 32/4 5.2, 16/4 5.0;  256 x 4099 x 36: 32/4 6.1, 32/8 7.9, 16/4 8.0
 //                   512 x 1024 x 1024: 32/8 17.1, 32/16 22.6, 64/4 26.9;  2048 x 1152 x 384: 32/4 29.8, 32/8 37.0
 //   64 x 64         300 x 30522 x 384: 64/4 111, 32/16 147, 32/4 156;  2048 x 1024 x 1024: 53, 88, 56
+// More than 512 tiles of 64 x 64 (two workgroups per compute unit, one round): the chip is full whatever the tile,
+// and wavefronts that share a tile wait for one another -- with a contraction of a group or two most of them have
+// nothing to multiply at all.  So up to 32 elements (80, 128 with many more tiles), where writing the result is all
+// there is, the tiled kernel's sixteen elements per trip waste the least, and then one wavefront owns a tile of its
+// own (no LDS, no barrier) until the contraction is long enough for 64/4.  The tiled kernel also takes operands that
+// are contiguous along k but allow no vector reads: four scalar loads per lane over 32 rows each are bound by the
+// cache lines they touch.  us, tiled | 64/4 | taken; rows: a weight gradient (both operands contiguous along their
+// rows, result accumulated), k: both contiguous along k, fwd: one and one:
+//   rows  4096 x 4096 x 16: 37 | 86 | tiled       x 128: 83 | 105 | 32/4 75       x 256: 140 | 166 | 32/1 126
+//         1001 x 2051 x 24: 14.2 | 21.7 | tiled   x 80: 20.6 | 24.2 | 32/4 16.0   2048 x 2048 x 200: 40 | 39 | 32/1 35
+//   k     4096 x 4096 x 16: 30 | 52 | tiled       2048 x 2048 x 128: 26 | 25 | 32/1 23      x 256: 47 | 47 | 32x64/1 33
+//         8192 x 8192 x 128: 233 | 348 | tiled    x 256: 434 | 657 | 32x64/1 420            x 255: 426 | 1113 | tiled
+//         2051 x 3001 x 201: 55 | 99 | tiled      1001 x 2051 x 99: 21.6 | 19.8 | 32/4 18.9  x 513: 117 | 82 | 64/4
+//   fwd   4096 x 4096 x 255: 128 | 203 | tiled    2051 x 3001 x 255: 65 | 84 | 32x64/1 61   x 99: 35 | 34 | 32/4 32
 template <bool AKC, bool BKC, bool VEC>
 int launch_operands(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
   auto tiles = [&](int t) { return (int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.nsplit; };
   const int K = g.K / g.nsplit;
-  if (tiles(64) >= 512) return launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
+  const int64_t t64 = tiles(64);
+  if (t64 > 512) {
+    constexpr bool along_k = AKC && BKC, scalar_k = !VEC && (AKC || BKC);
+    const bool scalar_tiled = along_k ? (t64 >= 1536 || (K > (t64 < 1024 ? 112 : 80) && K <= (t64 < 1024 ? 256 : 640)))
+                                      : t64 >= 4096 && (K <= 640 || t64 >= 8192);
+    if (K <= (t64 < 1024 ? 32 : t64 <= 4096 ? 80 : 128) || (scalar_k && scalar_tiled))
+      return launch_tiled(g.A, AKC ? g.lda : 1, AKC ? 1 : g.lda, g.B, BKC ? g.ldb : 1, BKC ? 1 : g.ldb, g.M, g.N, g.K, g.nsplit,
+                          g.slab, ep, s);
+    if (K <= (scalar_k ? 112 : 128))
+      return along_k && !scalar_k ? launch_tile<32, 1, 1, 1, AKC, BKC, VEC>(g, ep, s) : launch_tile<32, 1, 1, 4, AKC, BKC, VEC>(g, ep, s);
+    if ((along_k && !scalar_k && t64 >= 1024) || (scalar_k && !along_k && K <= 640))
+      return launch_tile<32, 1, 2, 1, AKC, BKC, VEC>(g, ep, s);
+    if (!along_k && !scalar_k && K <= (t64 < 1024 ? 256 : 512)) return launch_tile<32, 1, 1, 1, AKC, BKC, VEC>(g, ep, s);
+    return launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
+  }
+  if (t64 == 512) return launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
   if (tiles(16) <= (K <= 128 ? 1024 : 512))
     return K >= 512 ? launch_tile<16, 1, 1, 16, AKC, BKC, VEC>(g, ep, s) : launch_tile<16, 1, 1, 4, AKC, BKC, VEC>(g, ep, s);
   if (K <= 128 || tiles(32) > 1024) return launch_tile<32, 1, 1, 4, AKC, BKC, VEC>(g, ep, s);

@@ -297,3 +297,19 @@ def test_gemm_f32_of_operands_out_of_32_bit_reach(M, N, K, limit_us):
     if limit_us:
         us = _time_us(lambda: vf.vf_gemm(A, Bd, C, M, N, K))
         assert us < limit_us, us
+
+
+@pytest.mark.parametrize("M,N,K,ratio", [(8192, 8192, 16, 3.2), (4096, 4096, 64, 4.3), (8192, 8192, 255, 12.5)])
+def test_gemm_f32_of_a_short_contraction_keeps_up_with_memory(M, N, K, ratio):
+    """A large result over few elements is bound by reading and writing the result: its time as a multiple of what an
+    element-wise pass over as much memory takes on the same card: 2.1, 3.1 and 8.5 (as on the tiled kernel alone); 4.9, 5.7
+    and 18 when four wavefronts shared a 64 x 64 tile whose contraction only one of them had anything of.  The limits
+    lie halfway (on the logarithm).  255: no vector reads."""
+    import torch
+    import paper_2009_09523_amd as vf
+    print(f"gemm f32 short M={M} N={N} K={K}", flush=True)
+    A, B, C = torch.randn((M, K), device="cuda"), torch.randn((N, K), device="cuda"), torch.zeros((M, N), device="cuda")
+    product = _time_us(lambda: [vf.vf_gemm(A, B, C, M, N, K, accumulate=True) for _ in range(4)])
+    add = _time_us(lambda: [C.add_(1.0) for _ in range(4)])
+    print(f"{product / 4:.1f} us, {product / add:.2f} of the pass", flush=True)
+    assert product < ratio * add

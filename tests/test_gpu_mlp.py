@@ -46,6 +46,29 @@ def test_f32_step_on_wide_layers(dims, nodes):
     check_against_oracle(wl, gpu, ref)
 
 
+@pytest.mark.parametrize("dims,rows", [((31, 2051, 33), 1100), ((99, 2051, 100), 1100), ((130, 2051, 131), 1100), ((260, 2051, 204), 1100),
+                                       ((700, 2051, 321), 1100), ((131, 2051, 260), 2100), ((81, 2100, 97), 2100),
+                                       ((100, 4100, 129), 4200), ((129, 4100, 256), 4200), ((2051, 1101, 10), 24),
+                                       ((2051, 1101, 10), 72), ((2051, 1101, 10), 200)])
+def test_f32_step_on_products_of_many_tiles(dims, rows):
+    """More than 512 tiles of 64 x 64: every contraction length at which the tile changes, in the forward product (one
+    operand along k), the input gradient (both) and the weight gradient (both along rows), aligned and not.
+    One of these millions of ReLU units lies within fp32 rounding of zero, and one flipped unit is 5e-4 of the first
+    layer's gradient.  So the biases are +-12, eight standard deviations of what is added to them: no unit is
+    closer to zero than 1, and the products alone are compared."""
+    from dataclasses import replace
+    print(f"f32 dims={dims} rows={rows}", flush=True)
+    wl = replace(I.workload("mlp_small_f32"), dims=dims, node_sizes=(rows,))
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    K, N = dims[:2]
+    bias = theta[K * N:K * N + N]
+    bias[:] = np.where(np.arange(N) % 3 == 0, -12.0, 12.0)
+    assert np.abs(x.astype(np.float64) @ theta[:K * N].reshape(K, N) + bias).min() > 1.0
+    gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH)
+    check_against_oracle(wl, gpu, oracle_steps(wl, theta, x, y))
+
+
 def test_c1_exact_configuration():
     """MLP 784-256-10, fp32, B=64 in 4 nodes of 16, He init, one SGD step lr 0.1 mu 0.9."""
     wl, theta, x, y = _case("C1", jitter=0.0)
