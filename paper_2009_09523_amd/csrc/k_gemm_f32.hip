@@ -346,7 +346,14 @@ int launch_operands(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
     if (!along_k && !scalar_k && K <= (t64 < 1024 ? 256 : 512)) return launch_tile<32, 1, 1, 1, AKC, BKC, VEC>(g, ep, s);
     return launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
   }
-  if (t64 == 512) return launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
+  if (t64 == 512)
+    return K <= 32 ? launch_tile<32, 1, 1, 1, AKC, BKC, VEC>(g, ep, s) : launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
+  if (tiles(32) > 1024) {      // (up to 512 tiles of 64 x 64: the same two reasons, tiled | 32/4 | taken)
+    // rows  1210 x 1300 x 8: 10.6 | 12.1 | tiled      k  1210 x 1300 x 255: 43 | 58 | 32x64/1 37   x 1025: 220 | 149 | 111
+    if (!AKC && !BKC && K <= 16)
+      return launch_tiled(g.A, 1, g.lda, g.B, 1, g.ldb, g.M, g.N, g.K, g.nsplit, g.slab, ep, s);
+    if (AKC && BKC && !VEC && K > 128) return launch_tile<32, 1, 2, 1, AKC, BKC, VEC>(g, ep, s);
+  }
   if (tiles(16) <= (K <= 128 ? 1024 : 512))
     return K >= 512 ? launch_tile<16, 1, 1, 16, AKC, BKC, VEC>(g, ep, s) : launch_tile<16, 1, 1, 4, AKC, BKC, VEC>(g, ep, s);
   if (K <= 128 || tiles(32) > 1024) return launch_tile<32, 1, 1, 4, AKC, BKC, VEC>(g, ep, s);

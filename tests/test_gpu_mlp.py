@@ -49,9 +49,10 @@ def test_f32_step_on_wide_layers(dims, nodes):
 @pytest.mark.parametrize("dims,rows", [((31, 2051, 33), 1100), ((99, 2051, 100), 1100), ((130, 2051, 131), 1100), ((260, 2051, 204), 1100),
                                        ((700, 2051, 321), 1100), ((131, 2051, 260), 2100), ((81, 2100, 97), 2100),
                                        ((100, 4100, 129), 4200), ((129, 4100, 256), 4200), ((2051, 1101, 10), 24),
-                                       ((2051, 1101, 10), 72), ((2051, 1101, 10), 200)])
+                                       ((2051, 1101, 10), 72), ((2051, 1101, 10), 200), ((255, 1300, 201), 1210),
+                                       ((1210, 1300, 10), 8), ((24, 4096, 10), 512)])
 def test_f32_step_on_products_of_many_tiles(dims, rows):
-    """More than 512 tiles of 64 x 64: every contraction length at which the tile changes, in the forward product (one
+    """About and more than 512 tiles of 64 x 64: every contraction length at which the tile changes, in the forward product (one
     operand along k), the input gradient (both) and the weight gradient (both along rows), aligned and not.
     One of these millions of ReLU units lies within fp32 rounding of zero, and one flipped unit is 5e-4 of the first
     layer's gradient.  So the biases are +-12, eight standard deviations of what is added to them: no unit is
