@@ -223,6 +223,10 @@ template <int N>
 __device__ __forceinline__ void wait_loads_but() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+template <int N>
+__device__ __forceinline__ void wait_loads_but_and_reads() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
 // The same wait for loads whose destinations are registers (load_vec_async).  The compiler takes
 // the output of the load statement as defined at once, and a statement that only clobbers
 // memory orders memory accesses, not register arithmetic: a v_and of the edge masking below was
@@ -422,7 +426,7 @@ __device__ __forceinline__ int dl_swizzle(int r) { return (r & 7) ^ ((r >> 3) & 
 // positions, 40 to 40 channels, writing and reading the patch matrix took 10.2 + 13.3 us; this takes 14.9.
 struct ConvOperand { int H, W, Cin; const bf16_t* zeros; int inv; };
 
-template <int NS, int CONV = 0>
+template <int NS, int CONV = 0, bool TAIL = false>
 __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                           const bf16_t* __restrict__ B, int64_t ldb,
                                                           int M, int N, int K, int kchunk,
@@ -435,7 +439,8 @@ __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restri
   __shared__ __attribute__((aligned(1024))) bf16_t lds[NS * STAGE];
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  // (scalar: the LDS address of a load goes through a scalar register)
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
   const int kbeg = blockIdx.z * kchunk;
@@ -523,7 +528,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restri
   };
 
   const int ktail = kbeg + nstage * BK;
-  if (!CONV && ktail < kend) {
+  if (TAIL && ktail < kend) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const int row = (wave * 2 + q) * 8 + (lane >> 3);
@@ -542,8 +547,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restri
     for (int s = 0; s < NS - 1; ++s) issue(min(s, nstage - 1), s);
     for (int it = 0; it < nstage; ++it) {
       // loads complete in order: stage `it` has landed when at most NS-2 stages are outstanding
-      wait_loads_but<(NS - 2) * LPS>();
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (this wave's reads of stage it-1 have returned)
+      wait_loads_but_and_reads<(NS - 2) * LPS>();
       // every wave's part of stage `it` is in LDS, and every wave is done reading stage it-1,
       // whose slot the next loads overwrite.  (A bare barrier: the loop issues no LDS stores, and
       // __syncthreads would wait for ALL outstanding loads.)
@@ -2358,11 +2362,15 @@ static int launch_gemm_bf16_ep(const Shape& g, const Epilogue& ep, hipStream_t s
   const int depth = dl_depth();
   if (depth) {
     dim3 grid((N + 63) / 64, (M + 63) / 64, nsplit);
+#define VF_DL(D)                                                                                                             \
+  if (K % BK) gemm_bf16_dl_kernel<D, 0, true><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, kchunk, slab_stride, ep); \
+  else gemm_bf16_dl_kernel<D><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, kchunk, slab_stride, ep)
     switch (depth) {
-      case 3: gemm_bf16_dl_kernel<3><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, kchunk, slab_stride, ep); break;
-      case 5: gemm_bf16_dl_kernel<5><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, kchunk, slab_stride, ep); break;
-      default: gemm_bf16_dl_kernel<4><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, kchunk, slab_stride, ep); break;
+      case 3: VF_DL(3); break;
+      case 5: VF_DL(5); break;
+      default: VF_DL(4); break;
     }
+#undef VF_DL
     VF_LAUNCH_CHECK();
     return VF_OK;
   }
