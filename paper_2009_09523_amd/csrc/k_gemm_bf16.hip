@@ -2341,40 +2341,55 @@ static int launch_gemm_bf16_ep(const Shape& g, const Epilogue& ep, hipStream_t s
     case 6: return launch_cfg<128, 32, 4, 1>(g, ep, s);
     default: break;
   }
-  // short contraction into an fp32 matrix (weight gradients): single-trip kernel
+  // what the single-trip kernel's 16-byte epilogue accepts
   const bool vec_ok = !ep.c_is_bf16 && (N & 3) == 0 && (ep.ldc & 3) == 0 &&
                       (reinterpret_cast<uintptr_t>(ep.C) & 15) == 0 &&
                       (!ep.R || ((ep.ldr & 3) == 0 && (reinterpret_cast<uintptr_t>(ep.R) & 15) == 0)) &&
                       (!ep.bias || (reinterpret_cast<uintptr_t>(ep.bias) & 15) == 0);
-  if (K <= 2 * BK && nsplit == 1 && vec_ok && M > 32 && N > 32 && shortk_enabled()) {
-    dim3 grid((N + 63) / 64, (M + 63) / 64);
-    gemm_bf16_shortk_kernel<64, 64><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, ep);
-    VF_LAUNCH_CHECK();
-    return VF_OK;
-  }
   // (the 256-row kernels address their operands with 32-bit byte offsets)
   const bool spans32 = (int64_t)M * lda * 2 < ((int64_t)1 << 31) && (int64_t)N * ldb * 2 < ((int64_t)1 << 31);
-  if (spans32 && takes_wide(M, N, K, nsplit)) return launch_wide(g, ep, s);
-  if (M <= 32) return launch_cfg<32, 128, 1, 4>(g, ep, s);
-  if (N <= 32) return launch_cfg<128, 32, 4, 1>(g, ep, s);
-  // operand tiles straight into LDS
   const int kchunk = ((K + nsplit - 1) / nsplit + BK - 1) / BK * BK;
-  const int depth = dl_depth();
-  if (depth) {
-    dim3 grid((N + 63) / 64, (M + 63) / 64, nsplit);
+  const dim3 grid((N + 63) / 64, (M + 63) / 64, nsplit);
+  switch (gemm_bf16_route(M, N, K, nsplit, spans32, vec_ok)) {
+    case GemmRoute::kShortK: gemm_bf16_shortk_kernel<64, 64><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, ep); break;
+    case GemmRoute::kWide: return launch_wide(g, ep, s);
+    case GemmRoute::kStaged32x128: return launch_cfg<32, 128, 1, 4>(g, ep, s);
+    case GemmRoute::kStaged128x32: return launch_cfg<128, 32, 4, 1>(g, ep, s);
+    case GemmRoute::kStaged64: return launch_cfg<64, 64, 2, 2>(g, ep, s);
+    case GemmRoute::kDirect64:
 #define VF_DL(D)                                                                                                             \
   if (K % BK) gemm_bf16_dl_kernel<D, 0, true><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, kchunk, slab_stride, ep); \
   else gemm_bf16_dl_kernel<D><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, kchunk, slab_stride, ep)
-    switch (depth) {
-      case 3: VF_DL(3); break;
-      case 5: VF_DL(5); break;
-      default: VF_DL(4); break;
-    }
+      switch (dl_depth()) {
+        case 3: VF_DL(3); break;
+        case 5: VF_DL(5); break;
+        default: VF_DL(4); break;
+      }
 #undef VF_DL
-    VF_LAUNCH_CHECK();
-    return VF_OK;
+      break;
   }
-  return launch_cfg<64, 64, 2, 2>(g, ep, s);
+  VF_LAUNCH_CHECK();
+  return VF_OK;
+}
+
+// Which kernel a product goes to.  `spans32`: both operands span less than 2 GiB; `vec_ok`: the result allows 16-byte
+// accesses.
+GemmRoute gemm_bf16_route(int M, int N, int K, int nsplit, bool spans32, bool vec_ok) {
+  // short contraction into an fp32 matrix (weight gradients): single-trip kernel
+  if (K <= 2 * BK && nsplit == 1 && vec_ok && M > 32 && N > 32 && shortk_enabled()) return GemmRoute::kShortK;
+  // Short ragged contractions of more 64 x 64 tiles than two per compute unit: the masked tail costs the LDS-direct
+  // kernels a stage without overlap, and the register-staged one has four workgroups on a unit (64 x 64 LDS-direct or
+  // 256-row | register-staged): 2544 x 880 x 200 9.3 | 8.4, x 456 12.2 | 11.8, x 712 15.6 | 15.7; 4000 x 1000 x 264
+  // 13.7 | 11.9; 3000 x 3000 x 328 26.4 | 23.6; 8192 x 512 x 200 12.6 | 11.0; but x 264 and x 328 (whole 256-row tiles)
+  // 12.2 | 12.8 and 12.8 | 14.4, and 1000 x 500 x 200 (128 tiles) 4.6 | 5.3.
+  if (K % BK && K < 6 * BK && nsplit == 1 && M > 32 && N > 32 && (int64_t)((M + 63) / 64) * ((N + 63) / 64) > 512 &&
+      (K < 4 * BK || M % 256 || N % 128))
+    return GemmRoute::kStaged64;
+  if (spans32 && takes_wide(M, N, K, nsplit)) return GemmRoute::kWide;
+  if (M <= 32) return GemmRoute::kStaged32x128;
+  if (N <= 32) return GemmRoute::kStaged128x32;
+  // operand tiles straight into LDS
+  return dl_depth() ? GemmRoute::kDirect64 : GemmRoute::kStaged64;
 }
 
 // C[r, n] = sum over the 3x3 neighbourhood and the channels of x (rows = images * H * W

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "vf.h"
+#include "vf_internal.h"
 
 static int failures = 0;
 #define CHECK(cond)                                                         \
@@ -109,6 +110,26 @@ static void null_handle_checks() {
   CHECK(vf_gemm_noalloc(nullptr, 8, &f, 8, &f, 1, 1, 8, 1.f, 0, 1, nullptr) == VF_EINVAL);
 }
 
+// which kernel a bf16 product goes to, at the lines of the rule
+static void route_checks() {
+  using vf::GemmRoute;
+  auto route = [](int M, int N, int K, int nsplit = 1, bool spans32 = true) { return vf::gemm_bf16_route(M, N, K, nsplit, spans32, true); };
+  CHECK(route(4096, 4096, 128) == GemmRoute::kShortK);
+  CHECK(route(16, 4096, 4096) == GemmRoute::kStaged32x128);
+  CHECK(route(4096, 16, 4096) == GemmRoute::kStaged128x32);
+  CHECK(route(128, 4096, 4096, 2) == GemmRoute::kDirect64);
+  CHECK(route(8192, 8192, 8192) == GemmRoute::kWide);
+  // short ragged contractions of many tiles
+  CHECK(route(2544, 880, 200) == GemmRoute::kStaged64);
+  CHECK(route(2544, 880, 192) != GemmRoute::kStaged64);
+  CHECK(route(2544, 880, 456) != GemmRoute::kStaged64);
+  CHECK(route(1000, 500, 200) == GemmRoute::kDirect64);
+  CHECK(route(3000, 3000, 328) == GemmRoute::kStaged64);
+  CHECK(route(8192, 512, 200) == GemmRoute::kStaged64);
+  CHECK(route(8192, 512, 328) == GemmRoute::kWide);
+  CHECK(route(2544, 880, 200, 2) == GemmRoute::kDirect64);
+}
+
 // exhaustive search over every per-device batch 0..B, the definition of Section 5.1.2
 static double brute(const std::vector<vf_device_profile>& t, int32_t B, double comm) {
   double best = std::numeric_limits<double>::infinity();
@@ -182,6 +203,7 @@ int main() {
   partition_checks();
   config_checks();
   null_handle_checks();
+  route_checks();
   solver_checks();
   if (failures) { std::printf("%d checks failed\n", failures); return 1; }
   std::printf("host checks ok\n");

@@ -209,10 +209,10 @@ def test_gemm_ragged_contraction_with_cold_operands(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K,nsplit", [(70, 131, 193, 1), (64, 66, 63, 1), (200, 130, 1000, 3), (65, 64, 130, 4),
-                                         (300, 1003, 71, 1), (700, 3000, 321, 1), (1030, 4100, 1001, 2),
-                                         (4096, 4100, 211, 1), (515, 2050, 2049, 8)])
+                                         (300, 1003, 71, 1), (700, 2000, 321, 1), (700, 3000, 321, 1), (768, 6144, 321, 1),
+                                         (3000, 700, 131, 1), (1030, 4100, 1001, 2), (4096, 4100, 211, 1), (515, 2050, 2049, 8)])
 def test_gemm_bf16_contraction_tails(M, N, K, nsplit):
-    """Contraction slices that are no whole number of 64-element stages, on the 64 x 64 and on the 256-row kernel
+    """Contraction slices that are no whole number of 64-element stages, on the 64 x 64 kernels and on the 256-row one
     (and slices with no element at all): what lies in the rows' padding (here NaN) must not be read into the product."""
     import torch
     import paper_2009_09523_amd as vf
