@@ -2356,6 +2356,7 @@ static int launch_gemm_bf16_ep(const Shape& g, const Epilogue& ep, hipStream_t s
     case GemmRoute::kStaged32x128: return launch_cfg<32, 128, 1, 4>(g, ep, s);
     case GemmRoute::kStaged128x32: return launch_cfg<128, 32, 4, 1>(g, ep, s);
     case GemmRoute::kStaged64: return launch_cfg<64, 64, 2, 2>(g, ep, s);
+    case GemmRoute::kStaged128: return launch_cfg<128, 128, 2, 2>(g, ep, s);
     case GemmRoute::kDirect64:
 #define VF_DL(D)                                                                                                             \
   if (K % BK) gemm_bf16_dl_kernel<D, 0, true><<<grid, NT, 0, s>>>(A, lda, B, ldb, M, N, K, kchunk, slab_stride, ep); \
@@ -2386,6 +2387,9 @@ GemmRoute gemm_bf16_route(int M, int N, int K, int nsplit, bool spans32, bool ve
       (K < 4 * BK || M % 256 || N % 128))
     return GemmRoute::kStaged64;
   if (spans32 && takes_wide(M, N, K, nsplit)) return GemmRoute::kWide;
+  // Operands of 2 GiB and more (64-bit addresses): 128 x 128 tiles read half as much per flop as 64 x 64 ones
+  // (131072 x 1024 x 8192 3.8 | 4.7 ms, 1048576 x 1024 x 1024 5.6 | 6.3).
+  if (!spans32 && M >= 1024 && N >= 1024 && K >= 512) return GemmRoute::kStaged128;
   if (M <= 32) return GemmRoute::kStaged32x128;
   if (N <= 32) return GemmRoute::kStaged128x32;
   // operand tiles straight into LDS

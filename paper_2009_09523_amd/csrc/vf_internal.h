@@ -152,7 +152,7 @@ int launch_bn_stats_finish(const float* mean, const float* var, int nodes, int C
 // Scale / shift (or bias) gradients from the per-node column sums, added up in node order.
 int launch_bn_sums_finish(const float* sums, int nodes, int C, GradOut gout_g, GradOut gout_b, hipStream_t s);
 // The kernels of the general bf16 product (k_gemm_bf16.hip) and which of them a product goes to.
-enum class GemmRoute { kShortK, kWide, kStaged32x128, kStaged128x32, kStaged64, kDirect64 };
+enum class GemmRoute { kShortK, kWide, kStaged32x128, kStaged128x32, kStaged64, kStaged128, kDirect64 };
 GemmRoute gemm_bf16_route(int M, int N, int K, int nsplit, bool spans32, bool vec_ok);
 // Number of slices that fills the chip for this shape (1 when the tile grid already does).
 constexpr float kSlabFoldUs = 1.3f;    // a million elements of a slab that launch_fold_slabs reads

@@ -128,6 +128,11 @@ static void route_checks() {
   CHECK(route(8192, 512, 200) == GemmRoute::kStaged64);
   CHECK(route(8192, 512, 328) == GemmRoute::kWide);
   CHECK(route(2544, 880, 200, 2) == GemmRoute::kDirect64);
+  // operands of 2 GiB and more
+  CHECK(route(131072, 1024, 8192, 1, false) == GemmRoute::kStaged128);
+  CHECK(route(131072, 1024, 8191, 1, false) == GemmRoute::kStaged128);
+  CHECK(route(131072, 1000, 8192, 1, false) == GemmRoute::kDirect64);
+  CHECK(route(1 << 23, 1024, 136, 1, false) == GemmRoute::kStaged64);
 }
 
 // exhaustive search over every per-device batch 0..B, the definition of Section 5.1.2

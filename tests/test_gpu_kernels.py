@@ -313,3 +313,22 @@ def test_gemm_f32_of_a_short_contraction_keeps_up_with_memory(M, N, K, ratio):
     add = _time_us(lambda: [C.add_(1.0) for _ in range(4)])
     print(f"{product / 4:.1f} us, {product / add:.2f} of the pass", flush=True)
     assert product < ratio * add
+
+
+def test_gemm_bf16_of_operands_of_2_gib():
+    """Rows of an operand further than 2 GiB apart, on the 128 x 128 tiles: the first and the last rows' products (the
+    operand's last element is 2.1 GiB behind its first)."""
+    import torch
+    import paper_2009_09523_amd as vf
+    M, N, K, pitch = 1100, 1030, 520, 1024000
+    print(f"gemm bf16 far M={M} N={N} K={K} pitch={pitch}", flush=True)
+    gen = torch.Generator().manual_seed(3)
+    a, b = (torch.randn((r, K), generator=gen).to(torch.bfloat16) for r in (M, N))
+    A = torch.empty(M * pitch, device="cuda", dtype=torch.bfloat16).as_strided((M, K), (pitch, 1))
+    A.copy_(a)
+    C = torch.zeros((M, N), device="cuda")
+    vf.vf_gemm(A, b.cuda(), C, M, N, K)
+    torch.cuda.synchronize()
+    a, b = a.double(), b.double()
+    # exact products, fp32 sums: at most K roundings of partial sums no larger than sum |a||b|
+    assert torch.all((C.double().cpu() - a @ b.T).abs() <= K * 2.0 ** -24 * (a.abs() @ b.abs().T))
