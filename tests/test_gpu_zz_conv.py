@@ -55,6 +55,20 @@ def test_image_side_32_several_stages_per_workgroup():
     check_against_oracle(wl, gpu, ref)
 
 
+@pytest.mark.parametrize("img,sizes", [(8, (525, 3)), (8, (1601, 260)), (16, (131, 66)), (64, (9, 5))])
+def test_every_image_side_with_several_stages_per_workgroup(img, sizes):
+    """The loop of the LDS-staged convolution at its other image sides: three stages of a workgroup (two for one of its
+    groups of wavefronts), at side 8 also seven (the ring of three input buffers wraps, and the wavefronts of a
+    group have unlike numbers of loads in flight), at side 64 the ring of two whose second buffer lies in the
+    filters' space; both groups' statistics joined at each of them."""
+    print(f"img={img} sizes={sizes}", flush=True)
+    wl = replace(I.workload("conv_w64_img16_bf16"), name=f"conv_w64_side{img}", img=img, node_sizes=sizes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH)
+    check_against_oracle(wl, gpu, oracle_steps(wl, theta, x, y))
+
+
 @pytest.mark.parametrize("width,img,sizes", [(8, 5, (3, 1)), (40, 7, (9, 2)), (72, 9, (4, 3)), (248, 8, (5, 4))])
 def test_channel_counts_that_are_multiples_of_eight(width, img, sizes):
     """Patch rows read from the activation although a stage of 64 contraction elements crosses taps, gradients over
