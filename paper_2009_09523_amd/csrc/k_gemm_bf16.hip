@@ -424,14 +424,14 @@ __device__ __forceinline__ int dl_swizzle(int r) { return (r & 7) ^ ((r >> 3) & 
 // tap of its own 16 bytes (chunk / (Cin / 8), by a multiplication: `inv` = ceil(65536 / (Cin / 8)) is exact
 // for the 288 chunks there are at most); chunks beyond 9 Cin are zeros in both operands.  At 37632
 // positions, 40 to 40 channels, writing and reading the patch matrix took 10.2 + 13.3 us; this takes 14.9.
-struct ConvOperand { int H, W, Cin; const bf16_t* zeros; int inv; };
+struct ConvOperand { int H, W, Cin; const bf16_t* zeros; int inv; int rows_on_x; };
 
 template <int NS, int CONV = 0, bool TAIL = false>
 __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                           const bf16_t* __restrict__ B, int64_t ldb,
                                                           int M, int N, int K, int kchunk,
                                                           int64_t slab_stride, Epilogue ep,
-                                                          ConvOperand cv = ConvOperand{0, 0, 0, nullptr, 0}) {
+                                                          ConvOperand cv = ConvOperand{0, 0, 0, nullptr, 0, 0}) {
   constexpr int TILE = 64 * BK;                 // elements of one operand tile (8 KB)
   constexpr int STAGE = 2 * TILE;
   constexpr int LPS = 4;                        // loads per lane and stage (2 for A, 2 for B)
@@ -442,7 +442,8 @@ __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restri
   // (scalar: the LDS address of a load goes through a scalar register)
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  const bool swapped = CONV && cv.rows_on_x;
+  const int m0 = (swapped ? blockIdx.x : blockIdx.y) * 64, n0 = (swapped ? blockIdx.y : blockIdx.x) * 64;
   const int kbeg = blockIdx.z * kchunk;
   const int kend = min(K, kbeg + kchunk);
   const int nstage = CONV == 8 ? (K + BK - 1) / BK : kend > kbeg ? (kend - kbeg) / BK : 0;
@@ -2436,8 +2437,11 @@ int launch_conv3x3_bf16(const bf16_t* x, int64_t rows, int H, int W, int Cin, co
     VF_LAUNCH_CHECK();
     return VF_OK;
   }
-  dim3 grid((N + 63) / 64, (unsigned)((rows + 63) / 64), 1);
-  ConvOperand cv{H, W, Cin, zeros, 0};
+  // Column tiles of the same positions run side by side (they share the patches); a grid's second dimension ends at
+  // 65535 row tiles (4.2 million positions), its first does not.
+  const int64_t mtiles = (rows + 63) / 64;
+  ConvOperand cv{H, W, Cin, zeros, 0, mtiles > 65535};
+  const dim3 grid = cv.rows_on_x ? dim3((unsigned)mtiles, (N + 63) / 64) : dim3((N + 63) / 64, (unsigned)mtiles);
   if (Cin % BK) {
     cv.inv = (65536 + Cin / 8 - 1) / (Cin / 8);
     gemm_bf16_dl_kernel<4, 8><<<grid, NT, 0, s>>>(x, Cin, Wk, ldb, (int)rows, N, K, K, 0, ep, cv);

@@ -84,6 +84,17 @@ def test_channel_counts_that_are_multiples_of_eight(width, img, sizes):
     check_against_oracle(wl, gpu, ref)
 
 
+def test_more_row_tiles_than_a_grids_second_dimension():
+    """A node of 4.3 million positions (66560 tiles of 64).  Its 1040 images are 8 images 130 times over, so statistics,
+    loss and gradient (means over the node) are those of the 8 images."""
+    few = replace(I.workload("conv_tiny_bf16"), name="conv_w16_img64", img=64, width=16, node_sizes=(8,))
+    many = replace(few, name="conv_w16_img64_many", node_sizes=(1040,))
+    theta = I.make_params(few, jitter=0.1)
+    x, y = I.make_batch(few)
+    gpu = run_gpu(many, theta, np.tile(x, (130, 1, 1, 1)), np.tile(y, 130), flags=FUSED | NO_GRAPH)
+    check_against_oracle(few, gpu, oracle_steps(few, theta, x, y))
+
+
 def test_two_steps_carry_momentum():
     wl, theta, x, y = _case("conv_tiny_bf16")
     gpu = run_gpu(wl, theta, x, y, flags=FUSED, steps=2)
