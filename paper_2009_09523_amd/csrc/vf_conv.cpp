@@ -4,9 +4,9 @@
 //
 // A convolution is a product over patch rows (per output position the 3x3 neighbourhood of the
 // bf16, channels-last input: 9*Cin values) with the filters.  When the input channels are a
-// multiple of 8 the kernels read the patches straight from the activation (no patch matrix) --
+// multiple of 8 from 16 on the kernels read the patches straight from the activation (no patch matrix) --
 // with 64 channels and an image side of 8 to 64, a kernel that keeps the filters in registers and
-// stages the input once per 64 positions; otherwise (the first layer) im2col writes them.  The
+// stages the input once per 64 positions; otherwise (the first layer, 8 channels) im2col writes them.  The
 // input gradient is the same convolution of the output gradient with the filters turned by 180
 // degrees and the channel roles exchanged (a second bf16 copy of the filters, made once per
 // step).  The weight gradient contracts over all positions of the node, cut into slabs that are
@@ -152,6 +152,12 @@ class Conv final : public Model {
     return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(kMaxSplit, (512 + tiles - 1) / tiles), rows / 256));
   }
 
+  // Whether a convolution over `cin` channels reads its patches from the activation instead of writing them as a matrix
+  // first.  A step of one block, 131072 positions (65536 from 72 channels on), us with the matrix | without: 8 channels
+  // 315 | 323, 16: 357 | 349, 24: 406 | 382, 32: 480 | 418, 72: 648 | 552, 104: 864 | 694, 168: 1377 | 1167, 248: 2195 |
+  // 1990.  (At 8 channels a 64-wide tile is seven eighths padding; the product over the matrix has one of 32.)
+  bool patch_free(int cin) const { return !explicit_ && (cin % 64 == 0 || (cin % 8 == 0 && cin >= 16 && cin <= 256)); }
+
   // y = patches(in) x filters^T; statistics over the node's rows; a = relu(BatchNorm(y) (+ skip))
   int conv_bn_relu(Ctx& c, ConvLayer& L, const bf16_t* in, const bf16_t* skip, int rows, const float* P,
                    hipStream_t st) {
@@ -159,7 +165,7 @@ class Conv final : public Model {
     Epilogue ep;
     ep.C = L.y; ep.ldc = L.C;
     int chunks = 0, chunk_rows = 0;     // statistics partials that the convolution kernel leaves, if it does
-    if (!explicit_ && (L.Cin % 64 == 0 || (L.Cin % 8 == 0 && L.Cin <= 256 && (reinterpret_cast<uintptr_t>(in) & 15) == 0))) {
+    if (patch_free(L.Cin) && (L.Cin % 64 == 0 || (reinterpret_cast<uintptr_t>(in) & 15) == 0)) {
       VF_KS(c, st, "gemm_fwd", launch_conv3x3_bf16(in, rows, H_, H_, L.Cin, L.wnat, L.Kp, L.C, ep, zeros_, st, partial_,
                                                    &chunks, &chunk_rows));
     } else {
@@ -242,7 +248,7 @@ class Conv final : public Model {
     Epilogue ep;
     ep.C = out; ep.ldc = L.Cin;
     if (addend) { ep.R = addend; ep.ldr = L.Cin; ep.beta = 1.f; }
-    if (!explicit_) {                                        // (C is a multiple of 8)
+    if (patch_free(L.C)) {
       VF_KS(c, st, "gemm_dgrad", launch_conv3x3_bf16(dy_, rows, H_, H_, L.C, L.wflip, L.Kpf, L.Cin, ep, zeros_, st));
     } else {
       VF_KS(c, st, "im2col", launch_im2col3x3(dy_, rows, H_, H_, L.C, cols_, L.Kpf, st));

@@ -69,7 +69,7 @@ def test_every_image_side_with_several_stages_per_workgroup(img, sizes):
     check_against_oracle(wl, gpu, oracle_steps(wl, theta, x, y))
 
 
-@pytest.mark.parametrize("width,img,sizes", [(8, 5, (3, 1)), (40, 7, (9, 2)), (72, 9, (4, 3)), (248, 8, (5, 4))])
+@pytest.mark.parametrize("width,img,sizes", [(8, 5, (3, 1)), (16, 5, (3, 2)), (40, 7, (9, 2)), (72, 9, (4, 3)), (248, 8, (5, 4))])
 def test_channel_counts_that_are_multiples_of_eight(width, img, sizes):
     """Patch rows read from the activation although a stage of 64 contraction elements crosses taps, gradients over
     the transposed patch matrix: widths below, around and far above one stage, rows that fill no tile.  (248 channels
