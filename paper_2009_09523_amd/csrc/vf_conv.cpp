@@ -73,7 +73,9 @@ class Conv final : public Model {
 
   void request_buffers(Arena& a) override {
     const size_t rows = (size_t)rows_max_;
-    int kp_max = 0;
+    // row pitch of the patch matrix (of the layers that write one: the first, whose input may also lie unaligned, and
+    // the convolutions that are not patch-free) and rows of the transposed one
+    int kp_cols = 0, kp_max = 0;
     for (ConvLayer& L : layers_) {
       a.request(&L.wnat, (size_t)L.C * L.Kp);
       if (L.Kpf) a.request(&L.wflip, (size_t)L.Cin * L.Kpf);
@@ -82,8 +84,10 @@ class Conv final : public Model {
       a.request(&L.rstd, (size_t)L.C);
       a.request(&L.a, rows * L.C);
       kp_max = std::max(kp_max, std::max(L.Kp, L.Kpf));
+      if (&L == &layers_[0] ? explicit_ || L.Cin % 64 : !patch_free(L.Cin)) kp_cols = std::max(kp_cols, L.Kp);
+      if (L.Kpf && !patch_free(L.C)) kp_cols = std::max(kp_cols, L.Kpf);
     }
-    a.request(&cols_, rows * (size_t)kp_max);
+    a.request(&cols_, rows * (size_t)kp_cols);
     a.request(&zeros_, (size_t)64);
     a.request(&colsT_, (size_t)kp_max * ldr_);
     a.request(&dyT_, (size_t)C_ * ldr_);
@@ -311,7 +315,7 @@ class Conv final : public Model {
   int64_t ldb_ = 0, ldc_ = 0, ldz_ = 0;   // pitches: node rows, channels, classes (rounded to 8)
   int64_t fc_w_off_ = 0, fc_b_off_ = 0;
   std::vector<ConvLayer> layers_;
-  bf16_t* cols_ = nullptr;         // [rows, Kp] patch matrix (of a layer's input, or of an output gradient)
+  bf16_t* cols_ = nullptr;         // [rows, Kp] patch matrix (of a layer's input, or of an output gradient), where one is written
   bf16_t* zeros_ = nullptr;        // 128 bytes of 0: what the product kernel reads outside the image
   bf16_t* colsT_ = nullptr;        // [Kp, ldr]  patches transposed
   bf16_t* dyT_ = nullptr;          // [C, ldr]   output gradient transposed

@@ -95,6 +95,18 @@ def test_more_row_tiles_than_a_grids_second_dimension():
     check_against_oracle(few, gpu, oracle_steps(few, theta, x, y))
 
 
+@pytest.mark.parametrize("width,pitch", [(64, 32), (24, 32), (8, 72)])
+def test_workspace_holds_the_patch_matrix_of_the_layers_that_write_one(width, pitch):
+    """From 16 channels on only the first layer (9 x 3 columns) writes its patches.  Bytes a position takes: per layer the
+    product (fp32) and the activation, the gradients (two fp32, one bf16), patches and transposed operands."""
+    wl = replace(I.workload("conv_tiny_bf16"), name="conv_ws", img=32, width=width, node_sizes=(64,))
+    x, y = I.make_batch(wl)
+    gpu = run_gpu(wl, I.make_params(wl, jitter=0.1), x, y, flags=FUSED | NO_GRAPH)
+    per_position = 3 * 6 * width + 10 * width + 2 * pitch + 2 * 9 * width + 2 * 2 * width
+    slabs = 4 * 256 * 9 * width * max(width, 3)
+    assert gpu["workspace_bytes"] < 64 * 32 * 32 * per_position + slabs + (4 << 20)
+
+
 def test_two_steps_carry_momentum():
     wl, theta, x, y = _case("conv_tiny_bf16")
     gpu = run_gpu(wl, theta, x, y, flags=FUSED, steps=2)
