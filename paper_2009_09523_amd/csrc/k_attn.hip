@@ -5,7 +5,7 @@
 // Head size 64, sequences of T <= 128 tokens in tiles of TS = T rounded up to 32 (TS/32 wavefronts,
 // each owning 32 query rows); other shapes use the generic batched kernel.  Rows of q, k, v and dO
 // beyond T are staged as zeros and their keys take no part in the softmax, so they add nothing to any
-// product; the stored probabilities are [TS][TS] per head, 0 beyond the last key.  Every operand that
+// product; the stored probabilities are [T][T rounded up to 8] per head, 0 beyond the last key.  Every operand that
 // the MFMA reads along a non-contiguous axis is transposed while it is staged into LDS.
 // T = 100, 8 heads, 40 sequences (TS = 128): forward 18 us, backward 35 us; the generic kernels took
 // 123 us for the six batched products of 16 such sequences, with two passes over fp32 scores besides.
@@ -45,6 +45,9 @@ template <bool FULL>
 __device__ __forceinline__ int row_of(int t, int T) { return FULL ? t : min(t, T - 1); }
 template <bool FULL>
 __device__ __forceinline__ bool is_row(int t, int T) { return FULL || t < T; }
+
+// Row pitch of the stored probabilities.
+__host__ __device__ __forceinline__ int prob_pitch(int T) { return (T + 7) & ~7; }
 
 __device__ __forceinline__ u32x4 row_or_zero(u32x4 v, bool inside) {
 #pragma unroll
@@ -135,7 +138,8 @@ __global__ __launch_bounds__(2 * TS) void attn_fwd_kernel(const bf16_t* __restri
     for (int jt = 0; jt < JT; ++jt) s[jt][r] *= inv;
   }
   __syncthreads();                                  // every wave is done with Qs / Ks
-  bf16_t* pg = prob + (int64_t)bh * TS * TS;
+  const int pT = FULL ? TS : prob_pitch(T);
+  bf16_t* pg = prob + (int64_t)bh * (FULL ? TS : T) * pT;
 #pragma unroll
   for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
@@ -143,7 +147,7 @@ __global__ __launch_bounds__(2 * TS) void attn_fwd_kernel(const bf16_t* __restri
       const int row = 32 * w + acc_row(r, lane), col = 32 * jt + (lane & 31);
       const bf16_t p = f32_to_bf16(s[jt][r]);
       Ps[row * LDT + col] = p;
-      pg[row * TS + col] = p;
+      if (FULL || (row < T && col < pT)) pg[row * pT + col] = p;
     }
   __syncthreads();
 
@@ -223,11 +227,13 @@ __global__ __launch_bounds__(2 * TS) void attn_bwd_kernel(const float* __restric
           ((uint32_t)f32_to_bf16(f0[u]) & in0) | (((uint32_t)f32_to_bf16(f1[u]) << 16) & in1);
   }
   // P: [q][j] in memory -> Pt[j][q], two query rows per thread, words along q
-  const bf16_t* pg = prob + (int64_t)bh * TS * TS;
+  const int pT = FULL ? TS : prob_pitch(T);
+  const bf16_t* pg = prob + (int64_t)bh * (FULL ? TS : T) * pT;
   for (int v = threadIdx.x; v < (TS / 2) * (TS / 8); v += blockDim.x) {
     const int q = 2 * (v % (TS / 2)), j8 = (v / (TS / 2)) * 8;
-    const u32x4 x0 = *reinterpret_cast<const u32x4*>(&pg[q * TS + j8]);
-    const u32x4 x1 = *reinterpret_cast<const u32x4*>(&pg[(q + 1) * TS + j8]);
+    const int at = FULL ? j8 : min(j8, pT - 8);
+    const u32x4 x0 = row_or_zero(*reinterpret_cast<const u32x4*>(&pg[row_of<FULL>(q, T) * pT + at]), FULL || (q < T && j8 < pT));
+    const u32x4 x1 = row_or_zero(*reinterpret_cast<const u32x4*>(&pg[row_of<FULL>(q + 1, T) * pT + at]), FULL || (q + 1 < T && j8 < pT));
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       *reinterpret_cast<uint32_t*>(&Pt[(j8 + u) * LDT + q]) = pick16(x0, u) | (pick16(x1, u) << 16);
@@ -345,7 +351,7 @@ bool attn_mfma_supported(int seq_len, int d_head) {
   return d_head == DH && seq_len >= 1 && seq_len <= 128;
 }
 
-int attn_mfma_pitch(int seq_len) { return (seq_len + 31) / 32 * 32; }
+int64_t attn_prob_elems(int seq_len) { return (int64_t)seq_len * prob_pitch(seq_len); }
 
 int launch_attn_fwd(const bf16_t* qkv, int n_seq, int seq_len, int d, int n_heads, bf16_t* prob, bf16_t* om,
                     float scale, hipStream_t s) {
@@ -357,7 +363,7 @@ int launch_attn_fwd(const bf16_t* qkv, int n_seq, int seq_len, int d, int n_head
     if (seq_len == TS) attn_fwd_kernel<TS, true><<<grid, 2 * TS, fwd_lds<TS>(), s>>>(qkv, TS, d, n_heads, prob, om, scale); \
     else attn_fwd_kernel<TS, false><<<grid, 2 * TS, fwd_lds<TS>(), s>>>(qkv, seq_len, d, n_heads, prob, om, scale); \
     break;
-  switch (attn_mfma_pitch(seq_len)) { VF_AF(32) VF_AF(64) VF_AF(96) VF_AF(128) default: return VF_EINVAL; }
+  switch ((seq_len + 31) / 32 * 32) { VF_AF(32) VF_AF(64) VF_AF(96) VF_AF(128) default: return VF_EINVAL; }
 #undef VF_AF
   VF_LAUNCH_CHECK();
   return VF_OK;
@@ -373,7 +379,7 @@ int launch_attn_bwd(const float* dO, const bf16_t* qkv, const bf16_t* prob, int 
     if (seq_len == TS) attn_bwd_kernel<TS, true><<<grid, 2 * TS, bwd_lds<TS>(), s>>>(dO, qkv, prob, TS, d, n_heads, dqkv, scale); \
     else attn_bwd_kernel<TS, false><<<grid, 2 * TS, bwd_lds<TS>(), s>>>(dO, qkv, prob, seq_len, d, n_heads, dqkv, scale); \
     break;
-  switch (attn_mfma_pitch(seq_len)) { VF_AB(32) VF_AB(64) VF_AB(96) VF_AB(128) default: return VF_EINVAL; }
+  switch ((seq_len + 31) / 32 * 32) { VF_AB(32) VF_AB(64) VF_AB(96) VF_AB(128) default: return VF_EINVAL; }
 #undef VF_AB
   VF_LAUNCH_CHECK();
   return VF_OK;

@@ -27,7 +27,7 @@ struct BlockActs {
   float *mean1 = nullptr, *rstd1 = nullptr, *mean2 = nullptr, *rstd2 = nullptr;
   void* a = nullptr;                    // T [R, d]   LN1 output
   void* qkv_act = nullptr;              // T [R, 3d]
-  void* prob = nullptr;                 // T [b*heads, T, T] attention probabilities (T: attn_mfma_pitch on the fused path)
+  void* prob = nullptr;                 // T [b*heads, T, T] attention probabilities (attn_prob_elems each on the fused path)
   void* om = nullptr;                   // T [R, d]   attention output, heads merged
   float* hmid = nullptr;                // fp32 [R, d] after the attention residual
   void* f = nullptr;                    // T [R, d]   LN2 output
@@ -108,14 +108,14 @@ class Encoder final : public Model {
     const size_t esz = bf16_ ? 2 : 4;
     const size_t R = (size_t)maxR_, Rm = (size_t)maxRm_;
     const size_t heads = (size_t)max_seqs_ * nh_;
-    const size_t pT = (size_t)(mfma_attn_ ? attn_mfma_pitch(T_) : T_);    // row pitch of the stored probabilities
+    const size_t per_head = mfma_attn_ ? (size_t)attn_prob_elems(T_) : (size_t)T_ * T_;    // stored probabilities
     auto act = [&](void** p, size_t n) { a.request(reinterpret_cast<char**>(p), n * esz); };
     for (int q = 0; q < sets_; ++q) {
       for (Block& B : blocks_) {
         BlockActs& X = B.x[q];
         a.request(&X.hin, R * d_);
         a.request(&X.mean1, R); a.request(&X.rstd1, R); a.request(&X.mean2, R); a.request(&X.rstd2, R);
-        act(&X.a, R * d_); act(&X.qkv_act, R * 3 * d_); act(&X.prob, heads * pT * pT); act(&X.om, R * d_);
+        act(&X.a, R * d_); act(&X.qkv_act, R * 3 * d_); act(&X.prob, heads * per_head); act(&X.om, R * d_);
         a.request(&X.hmid, R * d_);
         act(&X.f, R * d_); a.request(&X.u, R * f_); act(&X.g, R * f_);
         if (sets_ == 2) {

@@ -341,10 +341,10 @@ int launch_bgemm(const BMat& A, const BMat& B, const BMat& C, int M, int N, int 
                  float alpha, hipStream_t s);
 
 // k_attn.hip -- fused self-attention on the matrix cores (bf16, head size 64, up to 128 tokens).
-// qkv: [n_seq*T, 3d] (q | k | v, heads side by side); prob: [n_seq*heads, p, p] softmax probabilities,
-// p = attn_mfma_pitch(T) (written by the forward pass, read by the backward pass); om: [n_seq*T, d].
+// qkv: [n_seq*T, 3d] (q | k | v, heads side by side); prob: softmax probabilities, attn_prob_elems(T) per
+// sequence and head (written by the forward pass, read by the backward pass); om: [n_seq*T, d].
 bool attn_mfma_supported(int seq_len, int d_head);
-int attn_mfma_pitch(int seq_len);
+int64_t attn_prob_elems(int seq_len);
 int launch_attn_fwd(const bf16_t* qkv, int n_seq, int seq_len, int d, int n_heads, bf16_t* prob, bf16_t* om,
                     float scale, hipStream_t s);
 // dO: fp32 [n_seq*T, d] gradient w.r.t. om (rounded to bf16 as it is staged); dqkv: [n_seq*T, 3d]

@@ -50,6 +50,26 @@ def test_encoder_sequence_lengths(T):
     assert base["G"].tobytes() == two["G"].tobytes()
 
 
+@pytest.mark.parametrize("T", [1, 17, 33, 100])
+def test_workspace_of_sequences_that_fill_no_tile(T):
+    """Stored probabilities take T rows of T rounded up to 8 per head, not whole tiles of 32 x 32.  The rest of the
+    workspace grows with the tokens: a line through 32 and 64, where the tiles are full."""
+    import paper_2009_09523_amd as vf
+    from paper_2009_09523_amd.binding import config_from_workload
+    layers, heads, sequences = 3, 2, 512
+
+    def workspace(t, p):
+        wl = replace(I.workload("enc_small_bf16"), name=f"enc_ws_T{t}", n_layers=layers, d_model=128, n_heads=heads, d_ffn=128,
+                     seq_len=t, n_masked=1, node_sizes=(sequences,))
+        eng = vf.VirtualNodeStep(config_from_workload(wl, flags=FUSED | NO_GRAPH))
+        size = eng.workspace_bytes - layers * sequences * heads * 2 * t * p
+        eng.close()
+        return size
+    a, b = workspace(32, 32), workspace(64, 64)
+    pitch = (T + 7) // 8 * 8
+    assert workspace(T, pitch) <= a + (T - 32) * (b - a) / 32 + (2 << 20)
+
+
 @pytest.mark.parametrize("name,T,sizes", [("enc_small_f32", 5, (3, 1)), ("enc_small_f32", 70, (2, 1)),
                                           ("enc_small_f32", 130, (24,)), ("enc_small_bf16", 131, (22, 2))])
 def test_generic_attention_products(name, T, sizes):
