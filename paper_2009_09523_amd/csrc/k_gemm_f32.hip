@@ -325,6 +325,7 @@ int launch_tile(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
 //         1001 x 2051 x 24: 14.2 | 21.7 | tiled   x 80: 20.6 | 24.2 | 32/4 16.0   2048 x 2048 x 200: 40 | 39 | 32/1 35
 //   k     4096 x 4096 x 16: 30 | 52 | tiled       2048 x 2048 x 128: 26 | 25 | 32/1 23      x 256: 47 | 47 | 32x64/1 33
 //         8192 x 8192 x 128: 233 | 348 | tiled    x 256: 434 | 657 | 32x64/1 420            x 255: 426 | 1113 | tiled
+//         2048 x 2048 x 1024: 177 | 101 | 32x64/1 98   x 4096: 630 | 297 | 64/4 (32x64/1: 350)
 //         2051 x 3001 x 201: 55 | 99 | tiled      1001 x 2051 x 99: 21.6 | 19.8 | 32/4 18.9  x 513: 117 | 82 | 64/4
 //   fwd   4096 x 4096 x 255: 128 | 203 | tiled    2051 x 3001 x 255: 65 | 84 | 32x64/1 61   x 99: 35 | 34 | 32/4 32
 template <bool AKC, bool BKC, bool VEC>
@@ -341,7 +342,7 @@ int launch_operands(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
                           g.slab, ep, s);
     if (K <= (scalar_k ? 112 : 128))
       return along_k && !scalar_k ? launch_tile<32, 1, 1, 1, AKC, BKC, VEC>(g, ep, s) : launch_tile<32, 1, 1, 4, AKC, BKC, VEC>(g, ep, s);
-    if ((along_k && !scalar_k && t64 >= 1024) || (scalar_k && !along_k && K <= 640))
+    if ((along_k && !scalar_k && t64 >= 1024 && K <= 1024) || (scalar_k && !along_k && K <= 640))
       return launch_tile<32, 1, 2, 1, AKC, BKC, VEC>(g, ep, s);
     if (!along_k && !scalar_k && K <= (t64 < 1024 ? 256 : 512)) return launch_tile<32, 1, 1, 1, AKC, BKC, VEC>(g, ep, s);
     return launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);

@@ -50,7 +50,7 @@ def test_f32_step_on_wide_layers(dims, nodes):
                                        ((700, 2051, 321), 1100), ((131, 2051, 260), 2100), ((81, 2100, 97), 2100),
                                        ((100, 4100, 129), 4200), ((129, 4100, 256), 4200), ((2051, 1101, 10), 24),
                                        ((2051, 1101, 10), 72), ((2051, 1101, 10), 200), ((255, 1300, 201), 1210),
-                                       ((1210, 1300, 10), 8), ((24, 4096, 10), 512)])
+                                       ((1210, 1300, 10), 8), ((24, 4096, 10), 512), ((64, 2048, 1028), 2048)])
 def test_f32_step_on_products_of_many_tiles(dims, rows):
     """About and more than 512 tiles of 64 x 64: every contraction length at which the tile changes, in the forward product (one
     operand along k), the input gradient (both) and the weight gradient (both along rows), aligned and not.
