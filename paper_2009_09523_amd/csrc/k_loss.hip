@@ -235,24 +235,8 @@ __global__ __launch_bounds__(ROW_NT) void softmax_xent_row_kernel(const float* _
   if (threadIdx.x == 0) rowloss[r] = logf(sum) + mx - zlabel;   // zlabel: visible after the reductions' barriers
 }
 
-__global__ __launch_bounds__(256) void loss_reduce_kernel(const float* __restrict__ rowloss, int R,
-                                                          float w, int node,
-                                                          float* __restrict__ node_loss,
-                                                          float* __restrict__ total) {
-  __shared__ float red[4];
-  float s = 0.f;
-  for (int r = threadIdx.x; r < R; r += 256) s += rowloss[r];
-  s = block_reduce(s, false, red);
-  if (threadIdx.x == 0) {
-    float L = s / (float)R;
-    node_loss[node] = L;
-    float old = node == 0 ? 0.f : *total;
-    *total = fmaf(w, L, old);
-  }
-}
-
-// The same bookkeeping for a run of nodes in one launch: node j's rows start at off[j] of
-// `rowloss`; sums and the chain over the nodes are those of one launch per node, node by node.
+// Loss bookkeeping of a run of nodes (Section 5.2): node j's rows start at off[j] of `rowloss`; its loss is their mean, and
+// the total is the chain over the nodes in node order.
 __global__ __launch_bounds__(256) void loss_reduce_nodes_kernel(const float* __restrict__ rowloss, LossNodes ln,
                                                                 float* __restrict__ node_loss,
                                                                 float* __restrict__ total) {
@@ -285,11 +269,9 @@ int launch_loss_reduce_nodes(const float* rowloss, const LossNodes& ln, float* n
 
 int launch_softmax_xent(const float* zp, int nsplit, int64_t slab, int64_t ldzp, float* z, int64_t ldz,
                         const int32_t* labels, int R, int C, float* rowloss, void* dz, int64_t lddz,
-                        int dz_is_bf16, bf16_t* dzT, int64_t ldt, float w, int node, float* node_loss,
-                        float* total, hipStream_t s, float tscale) {
+                        int dz_is_bf16, bf16_t* dzT, int64_t ldt, hipStream_t s, float tscale) {
   if (R <= 0 || C <= 0 || nsplit < 1) return VF_EINVAL;
   if (dzT && !dz_is_bf16) return VF_EINVAL;
-  if (node_loss && !total) return VF_EINVAL;
   const bool small = C <= 256 * CPT;
   // rows of up to 32768 classes that one workgroup can keep in registers
   const bool even = !(ldzp & 1) && !(ldz & 1) && !(lddz & 1) && !(reinterpret_cast<uintptr_t>(zp) & 7) &&
@@ -315,7 +297,6 @@ int launch_softmax_xent(const float* zp, int nsplit, int64_t slab, int64_t ldzp,
 #undef VF_SXR2
 #undef VF_SXR
     VF_LAUNCH_CHECK();
-    if (node_loss) return launch_loss_reduce(rowloss, R, w, node, node_loss, total, s);
     return VF_OK;
   }
 #define VF_SX3(TT, SM, NS)                                                                         \
@@ -334,16 +315,6 @@ int launch_softmax_xent(const float* zp, int nsplit, int64_t slab, int64_t ldzp,
   else            { if (small) { VF_SX2(float, true) }  else { VF_SX2(float, false) } }
 #undef VF_SX2
 #undef VF_SX3
-  VF_LAUNCH_CHECK();
-  // the node's loss bookkeeping: a second, tiny launch (folding it into the last workgroup to
-  // finish costs a device-scope fence per workgroup, which is slower than the launch)
-  if (node_loss) return launch_loss_reduce(rowloss, R, w, node, node_loss, total, s);
-  return VF_OK;
-}
-
-int launch_loss_reduce(const float* rowloss, int R, float w, int node, float* node_loss,
-                       float* total, hipStream_t s) {
-  loss_reduce_kernel<<<1, 256, 0, s>>>(rowloss, R, w, node, node_loss, total);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }

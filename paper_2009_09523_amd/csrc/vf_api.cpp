@@ -543,21 +543,12 @@ int vf_step(vf_ctx* h, void* params, const void* batch_x, const int32_t* batch_y
   a.node_off.resize(V + 1);
   a.node_w.resize(V);
   vf_partition(node_sizes, V, B, a.node_off.data(), a.node_w.data());
-  // the units of the passes: the nodes, or runs of up to `group` consecutive nodes -- of any sizes the
-  // model takes together, or (models that want equal sizes) 2, 4 or 8 nodes of one size
+  // the units of the passes: the nodes, or runs of up to `group` consecutive nodes of any sizes the model takes
+  // together
   for (int32_t i = 0; i < V;) {
     int take = 1;
     const int most = std::min(c.group, c.model->max_group(node_sizes[i]));
-    if (most > 1) {
-      int run = 1;
-      if (c.model->groups_unequal()) {
-        while (i + run < V && run < most && c.model->max_group(node_sizes[i + run]) > 1) ++run;
-        take = run;
-      } else {
-        while (i + run < V && run < most && node_sizes[i + run] == node_sizes[i]) ++run;
-        take = run >= 8 ? 8 : (run >= 4 ? 4 : (run >= 2 ? 2 : 1));
-      }
-    }
+    while (i + take < V && take < most && c.model->max_group(node_sizes[i + take]) > 1) ++take;
     int32_t rows = 0;
     for (int j = 0; j < take; ++j) rows += node_sizes[i + j];
     a.sizes.push_back(rows);

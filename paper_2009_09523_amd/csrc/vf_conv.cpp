@@ -206,8 +206,7 @@ class Conv final : public Model {
     ep.bias = P + fc_b_off_; ep.bias_round_bf16 = 1;
     VF_KS(c, st, "gemm_fc", launch_gemm_bf16(pooled_, ldc_, fc_wtr_, ldc_, b, cfg_.classes, C_, 1, 0, ep, st));
     VF_KS(c, st, "softmax_xent", launch_softmax_xent(zslab_, 1, 0, ldz_, z_, ldz_, s.y + row0, b, cfg_.classes,
-                                                     c.rowloss + row0, dz_, ldz_, 1, dzT_, ldb_, s.w[i], i, nullptr,
-                                                     nullptr, st));
+                                                     c.rowloss + row0, dz_, ldz_, 1, dzT_, ldb_, st));
     if (i == s.V - 1) {   // loss bookkeeping of the whole step, in node order (Section 5.2)
       for (int first = 0; first < s.V; first += kLossNodes) {
         LossNodes ln{};

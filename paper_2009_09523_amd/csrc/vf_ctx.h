@@ -116,10 +116,9 @@ class Model {
   virtual void update_ranges(std::vector<UpdateRange>* out) const { out->clear(); }
   // Largest fold window the side part can take (it must keep that many nodes' operands).
   virtual int max_window() const { return 1; }
-  // How many nodes of `rows` rows the passes take as one unit at most (1: none) ...
+  // How many consecutive nodes the passes take as one unit at most, given that one of them has `rows` rows (1: such a
+  // node goes alone).  The nodes of a unit may differ in size.
   virtual int max_group(int rows) const { (void)rows; return 1; }
-  // ... and whether the nodes of a unit may differ in size.
-  virtual bool groups_unequal() const { return false; }
   // State that the passes themselves carry from step to step on this device (BatchNorm moving
   // mean and variance, Section 4.1): `state_floats` fp32 values at `state_ptr`, laid out as all
   // layers' means then all layers' variances; init_state sets the starting values.

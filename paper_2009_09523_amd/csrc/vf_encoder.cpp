@@ -96,11 +96,10 @@ class Encoder final : public Model {
   }
 
   int64_t num_params() const override { return P_; }
-  // (the row-chunked reductions of the backward pass take units of up to 8192 tokens)
+  // (the row-chunked reductions of the backward pass take units of up to 8192 tokens; the sequences of a unit are
+  // independent, and every masked row carries 1/rows of the unit times the unit's weight: 1/B of the loss, whatever
+  // the sizes of its nodes)
   int max_group(int) const override { return 4; }
-  // the sequences of a unit are independent, and every masked row carries 1/rows of the unit times the
-  // unit's weight: 1/B of the loss, whatever the sizes of its nodes
-  bool groups_unequal() const override { return true; }
   // the forward part of the fp32 / non-MFMA attention path shares its score scratch with the backward part
   bool supports_overlap() const override { return bf16_ && mfma_attn_; }
 
@@ -208,7 +207,6 @@ class Encoder final : public Model {
     HeadActs& H = head_[q];
     const int b = s.sizes[i];
     const int64_t row0 = s.off[i];
-    const float w = s.w[i];
     const float* P = s.params;
     const int R = b * T_, Rm = b * m_;
     const int nl = (int)blocks_.size();
@@ -249,7 +247,7 @@ class Encoder final : public Model {
                                                   cfg_.ln_eps, H.rows, d_, bf16_, H.meanf, H.rstdf, st));
     VF_TRY(lin_fwd(c, "gemm_head", out_, P, H.rows, d_, Rm, logits_, ldV_, false, nullptr));
     VF_KS(c, st, "softmax_xent", launch_softmax_xent(logits_, 1, 0, ldV_, logits_, ldV_, H.labels, Rm, V_, c.rowloss,
-                                                H.dlogits, ldV_, bf16_, nullptr, 0, w, i, nullptr, nullptr, st));
+                                                H.dlogits, ldV_, bf16_, nullptr, 0, st));
     // loss bookkeeping per virtual node (Section 5.2), in node order
     LossNodes ln{};
     ln.first = s.first[i];

@@ -309,13 +309,11 @@ int launch_fold_slabs(const float* slabs, int nsplit, int64_t stride, int64_t n,
 //   rowloss[r] = logsumexp(z_r) - z_r[label_r];  dz[r,c] = (softmax(z_r)[c] - [c==label_r]) / R
 // dzT (optional, bf16 only): tscale times the same gradient (rounded once, from the fp32 value),
 // transposed, [C, ldt].
-// With node_loss != null the node's loss bookkeeping (launch_loss_reduce) follows.
 int launch_softmax_xent(const float* zp, int nsplit, int64_t slab, int64_t ldzp, float* z, int64_t ldz,
                         const int32_t* labels, int R, int C, float* rowloss, void* dz, int64_t lddz,
-                        int dz_is_bf16, bf16_t* dzT, int64_t ldt, float w, int node, float* node_loss,
-                        float* total, hipStream_t s, float tscale = 1.f);
-// node_loss[i] = (1/R) sum_r rowloss[r];  total = (i == 0 ? 0 : total) + w * node_loss[i]
-// The same for nodes first .. first+count-1 in one launch (rows of node j at rowloss + off[j]).
+                        int dz_is_bf16, bf16_t* dzT, int64_t ldt, hipStream_t s, float tscale = 1.f);
+// Loss bookkeeping of nodes first .. first+count-1 (the R_j rows of node j at rowloss + off[j]):
+// node_loss[i] = (1/R_i) sum_r rowloss[r];  total = (i == 0 ? 0 : total) + w_i * node_loss[i]
 constexpr int kLossNodes = 32;
 struct LossNodes {
   int32_t off[kLossNodes];
@@ -325,8 +323,6 @@ struct LossNodes {
 };
 int launch_loss_reduce_nodes(const float* rowloss, const LossNodes& ln, float* node_loss, float* total,
                              hipStream_t s);
-int launch_loss_reduce(const float* rowloss, int R, float w, int node, float* node_loss,
-                       float* total, hipStream_t s);
 
 // k_bgemm.hip -- batched strided GEMM for the attention contractions.
 // Element [b][i,k] of an operand lives at p + (b / inner)*outer + (b % inner)*inner + i*rs + k*cs.

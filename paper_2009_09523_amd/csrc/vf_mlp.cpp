@@ -116,7 +116,6 @@ class Mlp final : public Model {
   // groups of nodes: the BatchNorm kernels keep a node of up to 128 rows in registers.  (The ordered fold of bf16
   // nodes that are no multiple of 8 is bitwise the node-by-node one: those go alone.)
   int max_group(int rows) const override { return rows <= 128 && (!ordered_ || (rows & 7) == 0) ? group_ : 1; }
-  bool groups_unequal() const override { return true; }
   int max_window() const override { return bf16_ ? kFoldMax : 1; }
 
   // The side part finishes the layers from the last to the first; a layer's stretch of the
@@ -214,7 +213,6 @@ class Mlp final : public Model {
     float* slab_buf = slab_[0];
     const int b = s.sizes[i];
     const int64_t row0 = s.off[i];
-    const float w = s.w[i];
     const float* P = s.params;
     const int nl = (int)layers_.size();
     const int D = cfg_.dims[0];
@@ -272,8 +270,8 @@ class Mlp final : public Model {
                                        s.group(i), s.rows_of(i)));
       else
         VF_KS(c, st, "softmax_xent", launch_softmax_xent(slab_buf, split, slab, L.ld, L.z[q], L.ld, y, b, L.N,
-                                                         c.rowloss + row0, L.dz[q], L.ld, bf16_, bf16_ ? L.dzT + pc : nullptr, ldw_, w, i,
-                                                         nullptr, nullptr, st, tscale(c, s, i)));
+                                                         c.rowloss + row0, L.dz[q], L.ld, bf16_, bf16_ ? L.dzT + pc : nullptr, ldw_, st,
+                                                         tscale(c, s, i)));
     }
     wait_casts_ = false;
     // loss bookkeeping of the whole step after the last node's rows are in: node losses and
