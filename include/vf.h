@@ -51,7 +51,6 @@
  *     VF_GEMM_SHORTK=0     weight gradients go to the general kernel, not the short-contraction one
  *     VF_GEMM_DL=0|3|4|5   LDS-direct product kernel off, or its ring depth (default 4)
  *     VF_GEMM_PIPE=0..4    ring depth of the register-staged product kernel (default 3, 0 = off)
- *     VF_GEMM_SPLIT_TARGET=<n>   workgroups a small product is sliced up to (default 256)
  *     VF_GEMM_WIDE=0|1|128|256   256-row product kernel off / on (default) / with 128 or 256 columns
  *     VF_GEMM_WIDE_V=1|2   256 x 256 tiles on the ring of three 32-element stages (1) or on the whole-line kernel
  *                          with the 32x32x16 instruction (2) instead of the whole-line kernel with 16x16x32
@@ -177,7 +176,7 @@ typedef struct vf_config {
                                     staged fold then differs from the fused one by fp32 rounding in the
                                     BatchNorm scale / shift gradients, and a fold window holds at most
                                     as many units as a batch has).  Encoder: up to four
-                                    nodes of any sizes.   The per-node workspace grows by this factor
+                                    nodes of any sizes.  The per-node workspace grows by this factor
                                     (not with V). */
   uint32_t flags;                /* VF_FLAG_* */
   void*   stream;                /* hipStream_t; NULL = the default stream */

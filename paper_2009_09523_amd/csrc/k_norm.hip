@@ -927,8 +927,8 @@ int group_subgroups(int grid) {
 }
 
 // The row ranges of a unit's nodes for the group kernels: `group` nodes of R rows each, or of
-// node_rows[n] rows when given.  Every node at most 128 rows; ranges start on multiples of 8 when
-// transposed copies are written.
+// node_rows[n] rows when given.  Every node at most 128 rows; a range may start at any row (store_rows8 writes the
+// transposed copies of such nodes).
 int group_rows(int group, int R, const int* node_rows, GroupRows* gr) {
   if (group < 2 || group > kBnGroupPair) return VF_EINVAL;
   int at = 0;

@@ -164,7 +164,7 @@ def test_c4_full_size():
 @pytest.mark.parametrize("name,sizes", [("enc_small_bf16", [2, 2, 2, 1, 1, 1]), ("enc_small_f32", [1] * 9),
                                         ("enc_mid_bf16", [1, 1, 1, 1, 1])])
 def test_encoder_node_groups_match_the_oracle(name, sizes, group):
-    """Groups of equal-sized nodes as one unit of the passes (the sequences of an encoder node are
+    """Groups of up to four consecutive nodes, of one size or of several, as one unit of the passes (the sequences of an encoder node are
     independent: only the loss bookkeeping tells the nodes apart): per-node losses and the combined
     gradient against the oracle, one and two streams bitwise equal."""
     wl, theta, x, y = _case(name)
