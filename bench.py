@@ -95,21 +95,18 @@ def algorithmic_work(wl, P, fused=False, window=1, group=1):
 
 def pass_units(wl, group):
     """Units that go through the passes of a step: the nodes, or (the library's rule) runs of up to
-    `group` consecutive nodes where the model takes groups -- bf16 MLP: nodes of at most 128 rows, a
-    multiple of 8, of any mix of sizes; encoder: 2 or 4 nodes of one size."""
+    `group` consecutive nodes of any sizes where the model takes groups -- MLP: nodes of at most 128
+    rows; encoder: up to four nodes."""
     sizes, units, i = list(wl.node_sizes), 0, 0
-    mlp = wl.kind == "mlp" and wl.dtype == "bf16"
-    enc = wl.kind == "encoder"
+    most = min(group, 4) if wl.kind == "encoder" else group if wl.kind == "mlp" else 1
+
+    def joins(rows):
+        return wl.kind == "encoder" or rows <= 128
+
     while i < len(sizes):
         take = 1
-        if group > 1 and mlp and sizes[i] <= 128 and sizes[i] % 8 == 0:
-            while i + take < len(sizes) and take < group and sizes[i + take] <= 128 and sizes[i + take] % 8 == 0:
-                take += 1
-        elif group > 1 and enc:
-            run, most = 1, min(group, 4)
-            while i + run < len(sizes) and run < most and sizes[i + run] == sizes[i]:
-                run += 1
-            take = 4 if run >= 4 else (2 if run >= 2 else 1)
+        while joins(sizes[i]) and i + take < len(sizes) and take < most and joins(sizes[i + take]):
+            take += 1
         units += 1
         i += take
     return units

@@ -147,3 +147,14 @@ def test_config_struct_matches_the_header_field_for_field():
         for n in parts[1].split(","):
             names.append(re.sub(r"\[.*\]", "", n.strip().lstrip("*")))
     assert names == [f[0] for f in binding.VfConfig._fields_]
+
+
+@pytest.mark.parametrize("name,sizes,group,units", [("C1", None, 32, 1), ("C2", None, 32, 1), ("C4", None, 32, 4), ("C5", None, 32, 2),
+                                                   ("C6", None, 32, 8), ("mlp_mid_bn_bf16", (37, 130, 3, 2), 32, 3),
+                                                   ("enc_small_bf16", (3, 2, 4, 1, 2), 4, 2), ("C3", None, 1, 8)])
+def test_bench_counts_the_units_the_library_forms(name, sizes, group, units):
+    """The work bench.py prices a launch with: units of fp32 nodes, of odd sizes, and of unequal encoder nodes."""
+    import bench
+    import vf_inputs as I
+    wl = I.workload(name)
+    assert bench.pass_units(wl.with_nodes(sizes) if sizes else wl, group) == units
