@@ -333,15 +333,15 @@ __global__ __launch_bounds__(256) void bn_relu_bwd_kernel(float* __restrict__ da
 }
 
 // ---- groups of nodes ------------------------------------------------------------------------------
-// The rows are G virtual nodes of R <= 128 rows each, one after the other (a group of equal-sized
-// nodes whose products were taken as one).  Statistics, normalisation, the blend of the moving
+// The rows are up to G virtual nodes of at most 128 rows each, of any sizes (GroupRows), one after
+// the other (a unit of nodes whose products were taken as one).  Statistics, normalisation, the blend of the moving
 // statistics and the small-vector gradients are per node, in node order, exactly as G launches of
 // the kernels above would do them (same sums, same order).  A workgroup owns CB columns as
 // above but has up to four sub-groups of 256 threads, each working on a node of its own at the
 // same time (G = 8: two rounds); what couples the nodes -- the moving statistics, blended node
 // after node, and the gamma / beta gradients, added up in node order and folded in once -- goes
 // through LDS and is finished by one thread per column.  mean_out / rstd_out hold G vectors of C,
-// the transposed copy node n's rows at columns n*R .. n*R + R-1.
+// the transposed copy node n's rows at the columns that GroupRows gives.
 // Row ranges of the nodes of a unit: node n has rows[n] <= 128 rows starting at row base[n] of the
 // unit; entries beyond the unit's nodes are 0.
 constexpr int kBnGroup = 8;   // nodes per launch of the group kernels

@@ -178,7 +178,7 @@ struct Ctx {
   hipEvent_t side_done[2] = {nullptr, nullptr};  // side part of window w (parity) is complete
   hipEvent_t prep_done = nullptr;                // weight preparation
 
-  int group = 1;                          // consecutive equal-sized nodes taken through their passes together
+  int group = 1;                          // most consecutive nodes taken through their passes together
   int window = 1;                         // nodes whose weight gradients are folded in one pass
   // copies of the side part's operands: one window's worth, and two with overlap at window 1
   int copies() const { return overlap ? std::max(2, window) : window; }

@@ -31,7 +31,7 @@ struct Layer {
   // the columns of copy Ctx::slot(i) (Mlp::cols), its rows contiguous along the matrix row.  So
   // the operands of a whole fold window are still there when its weight gradients are taken in
   // one pass, or (two streams) the second stream can read node i's operands while the first
-  // produces those of node i+1; and the nodes of a window of equal sizes lie side by side, one
+  // produces those of node i+1; and the nodes of a window (join_kind) lie side by side, one
   // long contraction.
   bf16_t* aT = nullptr;      // a transposed
   bf16_t* dzT = nullptr;     // dz transposed
