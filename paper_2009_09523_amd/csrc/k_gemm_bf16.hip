@@ -1557,6 +1557,352 @@ __global__ __launch_bounds__(512) void gemm_bf16_wide_line16_kernel(const bf16_t
   store_row(std::integral_constant<int, 3>{});
 }
 
+// ---- 128 x 128 tiles, four wavefronts: one node of 128 rows per tile --------------------------------
+// For the products of a unit of whole 128-row nodes whose BatchNorm pass the 256 x 256 kernel cannot take (fewer than
+// one 256 x 256 tile per compute unit): a tile's rows are one node, so its epilogue has everything the node's
+// statistics need, and neither slabs of partial products nor a kernel that reads them are left.  1024 x 4096 x 4096 gives
+// every compute unit one tile; a wavefront owns 64 x 64 as 4 x 4 tiles of 16 x 16, one wavefront on a SIMD, stages and
+// fragment reads as in the 256-row kernels (a ring of three stages of 64 elements, one instruction behind every MFMA).
+// What bounds its main loop is LDS (32 KB in, 64 KB of fragments out per stage): 0.47 us a stage with four or eight
+// wavefronts, a ring of three to five stages, or lines touched ahead by a wavefront of their own.
+struct MidLds { static constexpr int NS = 3, STAGE = 2 * 128 * 64, BYTES = NS * STAGE * 2; };
+
+// Sums over the node's 128 rows of four columns per group j and lane: 16 lanes by exchange, the two wavefronts with the
+// node's lower and upper rows through LDS (lower rows first).  part: [wave][64].
+__device__ __forceinline__ void mid_node_sums(f32x4 (&v)[4], float* part, int wave, int lr, int lq) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[j][e] = row16_sum(v[j][e]);
+  if (lr == 0)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *reinterpret_cast<f32x4*>(&part[wave * 64 + 16 * j + 4 * lq]) = v[j];
+}
+__device__ __forceinline__ void mid_node_join(f32x4 (&v)[4], const float* part, int wave, int lq) {
+  const int w0 = wave & 1, w1 = w0 + 2;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const f32x4 lo = *reinterpret_cast<const f32x4*>(&part[w0 * 64 + 16 * j + 4 * lq]);
+    const f32x4 hi = *reinterpret_cast<const f32x4*>(&part[w1 * 64 + 16 * j + 4 * lq]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[j][e] = lo[e] + hi[e];
+  }
+}
+// A wavefront's 64 x 64 bf16 values: rows in 8-byte stores (a row's 128 bytes from four stores one behind the other),
+// the transposed copy through LDS in 16-byte stores of eight rows.
+__device__ __forceinline__ void mid_store_rows(const uint2 (&v)[4][4], bf16_t* out, int64_t ld, int row0, int colw, int lr, int lq) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<uint2*>(&out[(int64_t)(row0 + 16 * i + lr) * ld + colw + 16 * j + 4 * lq]) = v[i][j];
+}
+__device__ __forceinline__ void mid_put_transposed(uint2 v, bf16_t* tT, int i, int j, int lr, int lq) {
+  bf16_t* tp = &tT[(16 * j + 4 * lq) * kFuseTPitch + 16 * i + lr];
+  tp[0] = (bf16_t)v.x; tp[kFuseTPitch] = (bf16_t)(v.x >> 16);
+  tp[2 * kFuseTPitch] = (bf16_t)v.y; tp[3 * kFuseTPitch] = (bf16_t)(v.y >> 16);
+}
+__device__ __forceinline__ void mid_store_transposed(const bf16_t* tT, bf16_t* out, int64_t ld, int row0, int colw, int lane) {
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    const int col = it * 8 + (lane >> 3), seg = lane & 7;
+    *reinterpret_cast<u32x4*>(&out[(int64_t)(colw + col) * ld + row0 + seg * 8]) =
+        *reinterpret_cast<const u32x4*>(&tT[col * kFuseTPitch + seg * 8]);
+  }
+}
+
+// The arithmetic of bn_bwd_tile / bn_fwd_tile, all four column groups of a wavefront at once (two exchanges a tile
+// instead of one or two per group).  z: the layer's pre-activations, requested before the product's main loop.
+__device__ __forceinline__ void mid_bn_bwd(f32x4 (&acc)[4][4], f32x4 (&z)[4][4], const BnBwdArgs& fa, bf16_t* lds, int m0,
+                                           int n0, int N, int wave, int lane) {
+  const int wm = wave >> 1, wn = wave & 1, lq = lane >> 4, lr = lane & 15;
+  const int node = m0 >> 7, colw = n0 + wn * 64, row0 = m0 + wm * 64;
+  const bool bn = fa.gamma != nullptr, same = fa.tscale == 1.f;
+  const float invR = 1.0f / 128.0f;
+  float* part = reinterpret_cast<float*>(lds);            // [2][wave][64]
+  bf16_t* tT = lds + 4096 + wave * (64 * kFuseTPitch);
+  f32x4 rstd[4], g[4], sg[4], sb[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int c = colw + 16 * j + 4 * lq;
+    f32x4 mean = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+    rstd[j] = g[j] = f32x4{1.f, 1.f, 1.f, 1.f};
+    if (bn) {
+      mean = *reinterpret_cast<const f32x4*>(&fa.mean[(int64_t)node * N + c]);
+      rstd[j] = *reinterpret_cast<const f32x4*>(&fa.rstd[(int64_t)node * N + c]);
+      g[j] = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
+      b = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
+      if (fa.round_params)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[e] = round_bf16(b[e]); }
+    }
+    sg[j] = sb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float xhat = (z[i][j][e] - mean[e]) * rstd[j][e];
+        const float pre = bn ? fmaf(g[j][e], xhat, b[e]) : z[i][j][e];
+        const float dr = pre > 0.f ? acc[i][j][e] : 0.f;
+        acc[i][j][e] = dr;
+        z[i][j][e] = xhat;
+        sg[j][e] = fmaf(dr, xhat, sg[j][e]);
+        sb[j][e] += dr;
+      }
+  }
+  // (every wavefront is done with the operand stages before the sums overwrite them)
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  mid_node_sums(sg, part, wave, lr, lq);
+  mid_node_sums(sb, part + 256, wave, lr, lq);
+  __syncthreads();
+  mid_node_join(sg, part, wave, lq);
+  mid_node_join(sb, part + 256, wave, lq);
+  if (wm == 0 && lr == 0)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int c = colw + 16 * j + 4 * lq;
+      *reinterpret_cast<f32x4*>(&fa.sums[((int64_t)node * 2 + 0) * N + c]) = sg[j];
+      *reinterpret_cast<f32x4*>(&fa.sums[((int64_t)node * 2 + 1) * N + c]) = sb[j];
+    }
+  uint2 out[4][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float dr = acc[i][j][e], kk = g[j][e] * rstd[j][e];
+        v[e] = bn ? kk * (dr - sb[j][e] * invR - z[i][j][e] * sg[j][e] * invR) : dr;
+      }
+      uint2 pk, pt;
+      pk.x = f32x2_to_bf16x2(v[0], v[1]); pk.y = f32x2_to_bf16x2(v[2], v[3]);
+      pt = pk;
+      if (!same) { pt.x = f32x2_to_bf16x2(v[0] * fa.tscale, v[1] * fa.tscale); pt.y = f32x2_to_bf16x2(v[2] * fa.tscale, v[3] * fa.tscale); }
+      out[i][j] = pk;
+      mid_put_transposed(pt, tT, i, j, lr, lq);
+    }
+  mid_store_rows(out, fa.dz, fa.lddz, row0, colw, lr, lq);
+  mid_store_transposed(tT, fa.dzT, fa.ldt, row0, colw, lane);   // (a wavefront's own tile: no barrier)
+}
+
+__device__ __forceinline__ void mid_bn_fwd(f32x4 (&acc)[4][4], const BnFwdArgs& fa, bf16_t* lds, int m0, int n0, int N,
+                                           int wave, int lane) {
+  const int wm = wave >> 1, wn = wave & 1, lq = lane >> 4, lr = lane & 15;
+  const int node = m0 >> 7, colw = n0 + wn * 64, row0 = m0 + wm * 64;
+  const bool bn = fa.gamma != nullptr;
+  const float invR = 1.0f / 128.0f;
+  float* part = reinterpret_cast<float*>(lds);            // [2][wave][64]
+  bf16_t* tT = lds + 4096 + wave * (64 * kFuseTPitch);
+  f32x4 g[4], b[4], mean[4], rstd[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int c = colw + 16 * j + 4 * lq;
+    g[j] = rstd[j] = f32x4{1.f, 1.f, 1.f, 1.f};
+    b[j] = mean[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (bn) {
+      g[j] = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
+      b[j] = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
+      if (fa.round_params)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[j][e] = round_bf16(b[j][e]); }
+    } else if (fa.bias) {
+      const f32x4 bias = *reinterpret_cast<const f32x4*>(&fa.bias[c]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float bb = fa.round_params ? round_bf16(bias[e]) : bias[e];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][j][e] = fmaf(1.f, acc[i][j][e], bb);   // (the product epilogue's own form)
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<f32x4*>(&fa.z[(int64_t)(row0 + 16 * i + lr) * fa.ldz + colw + 16 * j + 4 * lq]) = acc[i][j];
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  if (bn) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mean[j][e] = acc[0][j][e] + acc[1][j][e] + acc[2][j][e] + acc[3][j][e];
+    mid_node_sums(mean, part, wave, lr, lq);
+    __syncthreads();
+    mid_node_join(mean, part, wave, lq);
+    f32x4 var[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        mean[j][e] *= invR;
+        float q = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float d = acc[i][j][e] - mean[j][e];
+          q = fmaf(d, d, q);
+        }
+        var[j][e] = q;
+      }
+    mid_node_sums(var, part + 256, wave, lr, lq);
+    __syncthreads();
+    mid_node_join(var, part + 256, wave, lq);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { var[j][e] *= invR; rstd[j][e] = 1.0f / sqrtf(var[j][e] + fa.eps); }
+    if (wm == 0 && lr == 0)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int64_t at = (int64_t)node * N + colw + 16 * j + 4 * lq;
+        *reinterpret_cast<f32x4*>(&fa.mean[at]) = mean[j];
+        *reinterpret_cast<f32x4*>(&fa.rstd[at]) = rstd[j];
+        *reinterpret_cast<f32x4*>(&fa.var[at]) = var[j];
+      }
+  }
+  uint2 out[4][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float zz = acc[i][j][e];
+        v[e] = bn ? fmaxf(fmaf(g[j][e], (zz - mean[j][e]) * rstd[j][e], b[j][e]), 0.f) : fmaxf(zz, 0.f);
+      }
+      out[i][j].x = f32x2_to_bf16x2(v[0], v[1]); out[i][j].y = f32x2_to_bf16x2(v[2], v[3]);
+      mid_put_transposed(out[i][j], tT, i, j, lr, lq);
+    }
+  mid_store_rows(out, fa.a, fa.lda, row0, colw, lr, lq);
+  mid_store_transposed(tT, fa.aT, fa.ldt, row0, colw, lane);
+}
+
+// BWD: mid_bn_bwd ends the tile, else mid_bn_fwd.  M, N multiples of 128, K of 64.
+template <bool BWD>
+__global__ __launch_bounds__(NT) void gemm_bf16_mid_bn_kernel(const bf16_t* __restrict__ A, int64_t lda,
+                                                              const bf16_t* __restrict__ B, int64_t ldb, int N, int K,
+                                                              int tiles_m, int tiles_n, BnBwdArgs fa, BnFwdArgs ff) {
+  constexpr int KS = 64, NS = MidLds::NS, STAGE = MidLds::STAGE, ATILE = STAGE / 2;
+  constexpr int LPS = 8, H0 = 4;                          // load instructions per lane and stage; of them behind the barrier
+  extern __shared__ __attribute__((aligned(1024))) bf16_t lds_wide[];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (in a scalar register)
+  const int wm = wave >> 1, wn = wave & 1;
+  const int ntile = tiles_m * tiles_n;
+  const int per = (ntile + 7) >> 3;
+  const int local = blockIdx.x >> 3;
+  if (local >= per) return;
+  const int t = (blockIdx.x & 7) * per + local;
+  if (t >= ntile) return;
+  const int panel = t / (8 * tiles_n);
+  const int in_panel = t - panel * 8 * tiles_n;
+  const int prow = min(8, tiles_m - panel * 8);
+  const int m0 = (panel * 8 + in_panel % prow) * 128, n0 = (in_panel / prow) * 128;
+  const int nstage = K / KS;
+
+  uint32_t oa[4], ob[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row = (wave + 4 * q) * 8 + (lane >> 3);
+    const int chunk = ((lane & 7) ^ line16_swizzle(row)) * 8;
+    oa[q] = (uint32_t)(((int64_t)(m0 + row) * lda + chunk) * 2);
+    ob[q] = (uint32_t)(((int64_t)(n0 + row) * ldb + chunk) * 2);
+  }
+  const char* Ab = reinterpret_cast<const char*>(A);
+  const char* Bb = reinterpret_cast<const char*>(B);
+  auto issue_one = [&](int j, int stage, int slot) {      // load j of a stage: A and B rows in turn
+    const size_t k = (size_t)stage * (KS * 2);
+    bf16_t* base = &lds_wide[slot * STAGE];
+    const int q = j >> 1;
+    if (!(j & 1)) lds_load16(Ab + k, oa[q], base + (wave + 4 * q) * 512);
+    else lds_load16(Bb + k, ob[q], base + ATILE + (wave + 4 * q) * 512);
+  };
+
+  f32x4 acc[4][4], z[4][4];
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s)
+#pragma unroll
+    for (int j = 0; j < LPS; ++j) issue_one(j, min(s, nstage - 1), s);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (BWD) z[i][j] = *reinterpret_cast<const f32x4*>(&fa.z[(int64_t)(m0 + wm * 64 + 16 * i + (lane & 15)) * fa.ldz + n0 +
+                                                                  wn * 64 + 16 * j + 4 * (lane >> 4)]);
+    }
+  // (in registers before the loop: what follows counts its own outstanding loads)
+  if (BWD)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(z[i][j]));
+  wait_loads_but<(NS - 2) * LPS>();
+
+  const int ar = wm * 64 + (lane & 15), br = wn * 64 + (lane & 15);
+  const int asw = line16_swizzle(ar), bsw = line16_swizzle(br);
+  bf16x8 a[2][4], b[2][4];
+  // fragment r of step ks, in the order a step uses them: A tile 0, the B tiles, the other A tiles
+  auto read_one = [&](int slot, int ks, int r) {
+    const bf16_t* as = &lds_wide[slot * STAGE];
+    if (r == 0 || r > 4) {
+      const int i = r == 0 ? 0 : r - 4;
+      a[ks][i] = *reinterpret_cast<const bf16x8*>(&as[(ar + 16 * i) * KS + (((4 * ks + (lane >> 4)) ^ asw) * 8)]);
+    } else {
+      const int j = r - 1;
+      b[ks][j] = *reinterpret_cast<const bf16x8*>(&as[ATILE + (br + 16 * j) * KS + (((4 * ks + (lane >> 4)) ^ bsw) * 8)]);
+    }
+  };
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int r = 0; r < 8; ++r) read_one(0, 0, r);
+#pragma unroll
+  for (int j = 0; j < H0; ++j) issue_one(j, min(NS - 1, nstage - 1), NS - 1);
+  int slot = 0, nslot = 1, pslot = NS - 1;                // it % NS, (it + 1) % NS, (it + NS - 1) % NS
+  for (int it = 0; it < nstage; ++it) {
+    const int cur_ld = min(it + NS - 1, nstage - 1), nxt_ld = min(it + NS, nstage - 1);
+    const bool more = it + 1 < nstage;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (ks == 1 && more) {
+        // this wavefront's reads of stage `it` have returned and its loads of stage it + 1 have landed; behind the
+        // barrier both hold for all four
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        wait_loads_but<(NS - 2) * LPS>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+#pragma unroll
+      for (int m = 0; m < 16; ++m) {
+        const int i = m >> 2, j = m & 3;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[ks][j], a[ks][i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (ks == 0) {
+          if (m < 8) read_one(slot, 1, m);
+          else if (m < 8 + LPS - H0) issue_one(H0 + m - 8, cur_ld, pslot);
+        } else if (more) {
+          if (m < 8) read_one(nslot, 0, m);
+          else if (m < 8 + H0) issue_one(m - 8, nxt_ld, slot);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    pslot = slot;
+    slot = nslot;
+    nslot = nslot + 1 == NS ? 0 : nslot + 1;
+  }
+  wait_loads_but<0>();
+  if constexpr (BWD) mid_bn_bwd(acc, z, fa, lds_wide, m0, n0, N, wave, lane);
+  else mid_bn_fwd(acc, ff, lds_wide, m0, n0, N, wave, lane);
+}
+
 // ---- 3x3 convolution with the filters resident in LDS -------------------------------------------
 // 64 input channels (one 128-byte row per position), 64 output channels per workgroup, image width
 // W a power of two from 8 to 64.  The workgroup keeps its 64 x 576 filters in LDS (nine 64 x 64 tiles,
@@ -2144,7 +2490,8 @@ static bool takes_wide(int M, int N, int K, int nsplit) {
 // `slab_us` is the consumer's cost of a million elements of one slab; a fold also takes any number of them (the
 // BatchNorm kernels powers of two): 768 x 3072 x 8192 has 72 tiles for the 256-row kernel, 144 workgroups in two
 // slices, 216 in three.
-int gemm_bf16_pick_split(int M, int N, int K, float slab_us) {
+int gemm_bf16_pick_split(int M, int N, int K, float slab_us, float* us) {
+  if (us) *us = 0.f;
   if (M > 32 && N > 32) {
     const bool wide = wide_fits(M, N);
     const int bn = wide ? wide_tile_n(M, N) : 64, bm = wide ? 256 : 64;
@@ -2163,7 +2510,7 @@ int gemm_bf16_pick_split(int M, int N, int K, float slab_us) {
       const float c64 = few64 ? tile64_cost(M, N, K, split) : 1e30f;
       const float cw = few_wide ? wide_cost(M, N, K, split) : 1e30f;
       const float c = std::min(c64, cw) + (float)M * N * split * slab_us * 1e-6f;
-      if (split == 1 || c < cost) { best = split; cost = c; }
+      if (split == 1 || c < cost) { best = split; cost = c; if (us) *us = std::min(c64, cw); }
     }
     return best;
   }
@@ -2194,16 +2541,27 @@ int launch_wide_cfg(const Shape& g, const Epilogue& ep, hipStream_t s) {
   VF_LAUNCH_CHECK();
   return VF_OK;
 }
+template <bool BWD>
+int launch_mid_bn(const Shape& g, const BnBwdArgs& fa, const BnFwdArgs& ff, hipStream_t s) {
+  static bool ready = false;
+  if (!ready) {
+    VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_mid_bn_kernel<BWD>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, MidLds::BYTES));
+    ready = true;
+  }
+  const int tiles_m = g.M / 128, tiles_n = g.N / 128;
+  gemm_bf16_mid_bn_kernel<BWD><<<(tiles_m * tiles_n + 7) / 8 * 8, NT, MidLds::BYTES, s>>>(g.A, g.lda, g.B, g.ldb, g.N, g.K,
+                                                                                          tiles_m, tiles_n, fa, ff);
+  VF_LAUNCH_CHECK();
+  return VF_OK;
+}
 int wide_variant();
-int launch_wide_line(const Shape& g, const Epilogue& ep, hipStream_t s) {
+template <int FUSE>
+int launch_wide_line16(const Shape& g, const Epilogue& ep, const BnBwdArgs& fa, const BnFwdArgs& ff, hipStream_t s) {
   constexpr int bytes = 160 * 1024;
   static bool ready = false;
   if (!ready) {
-    VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_wide_line_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-    VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_wide_line16_kernel<0>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-    VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_wide_line16_kernel<1>),
+    VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_wide_line16_kernel<FUSE>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     ready = true;
   }
@@ -2215,12 +2573,28 @@ int launch_wide_line(const Shape& g, const Epilogue& ep, hipStream_t s) {
   // which is worth 9 % there (8192^3: 690 -> 630 us on operands of zeros); one round gains nothing.
   Epilogue epx = ep;
   if (ntile >= 512 && !ep.c_is_bf16 && !ep.R) epx.stream_c = 1;
-  if (wide_variant() == 2)
-    gemm_bf16_wide_line_kernel<<<grid, 512, bytes, s>>>(g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K, kchunk, g.slab, epx, tiles_m,
-                                                        tiles_n);
-  else
-    gemm_bf16_wide_line16_kernel<0><<<grid, 512, bytes, s>>>(g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K, kchunk, g.slab, epx,
-                                                                 tiles_m, tiles_n, BnBwdArgs{}, BnFwdArgs{});
+  gemm_bf16_wide_line16_kernel<FUSE><<<grid, 512, bytes, s>>>(g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K, kchunk, g.slab, epx,
+                                                              tiles_m, tiles_n, fa, ff);
+  VF_LAUNCH_CHECK();
+  return VF_OK;
+}
+int launch_wide_line(const Shape& g, const Epilogue& ep, hipStream_t s) {
+  if (wide_variant() != 2) return launch_wide_line16<0>(g, ep, BnBwdArgs{}, BnFwdArgs{}, s);
+  constexpr int bytes = 160 * 1024;
+  static bool ready = false;
+  if (!ready) {
+    VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_wide_line_kernel),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    ready = true;
+  }
+  const int kchunk = ((g.K + g.nsplit - 1) / g.nsplit + BK - 1) / BK * BK;
+  const int tiles_m = (g.M + 255) / 256, tiles_n = (g.N + 255) / 256;
+  const int ntile = tiles_m * tiles_n;
+  dim3 grid(((ntile + 7) / 8) * 8, 1, g.nsplit);
+  Epilogue epx = ep;
+  if (ntile >= 512 && !ep.c_is_bf16 && !ep.R) epx.stream_c = 1;
+  gemm_bf16_wide_line_kernel<<<grid, 512, bytes, s>>>(g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K, kchunk, g.slab, epx, tiles_m,
+                                                      tiles_n);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }
@@ -2240,71 +2614,64 @@ int launch_wide(const Shape& g, const Epilogue& ep, hipStream_t s) {
 }
 }  // namespace
 
-// The product with the BatchNorm backward pass in its epilogue (see bn_bwd_tile): shapes that the
-// 256 x 256 kernel on the 16x16x32 MFMA takes in whole tiles.  VF_BN_FUSE = 0 switches it off.
+// The product with a BatchNorm pass in its epilogue (see bn_bwd_tile, bn_fwd_tile): which tile takes it, 256, 128 or none (0).
+static int bn_tile(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int M, int N, int K, bool backward) {
+  if (M <= 0 || N <= 0 || K <= 0 || !A || !B || (lda & 7) || (ldb & 7) || wide_variant() != 0 || !wide_mode()) return 0;
+  if ((reinterpret_cast<uintptr_t>(A) & 15) || (reinterpret_cast<uintptr_t>(B) & 15)) return 0;
+  const bool spans32 = (int64_t)M * lda * 2 < ((int64_t)1 << 31) && (int64_t)N * ldb * 2 < ((int64_t)1 << 31);
+  if (!spans32 || M <= 128 || (M % 128) || (N % 128) || (K % 64)) return 0;
+  if ((M % 256) == 0 && (N % 256) == 0 && wide_tile_n(M, N) == 256) return 256;
+  // One launch on 128 x 128 tiles against the product, its slabs and a BatchNorm launch per eight nodes (microseconds;
+  // a million elements of the epilogue's stores: 2 backward, 4.5 forward, which stores the pre-activations as well).
+  // Whole steps of K-N-K-64 networks, apart | one launch backward, and forward: 32 x 128, N = 1024, K = 256 both ways
+  // 0.78 and 0.85 of the time; 8 x 128, 4096 x 4096 backward 95 -> 76 us for two layers, forward 131 -> 147 (apart); 2 x 128
+  // and long contractions onto few tiles (2 x 128, 4096 onto 256: 43 -> 98) apart.
+  float us = 0.f;
+  const int split = gemm_bf16_pick_split(M, N, K, 2.7f, &us);
+  const float e = (float)M * N * 1e-6f;
+  const float apart = us + std::max(8.f * ((M / 128 + 7) / 8), 2.7f * e * split);
+  const float one = 14.f + (float)(((int64_t)(M / 128) * (N / 128) + 255) / 256) * (K / 64) * 0.47f + (backward ? 2.f : 4.5f) * e;
+  return one < apart ? 128 : 0;
+}
+
+// VF_BN_FUSE_FWD = 0, VF_BN_FUSE = 0 switch the fused forms off.
 bool gemm_bf16_bn_fwd_takes(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int M, int N, int K,
                             const BnFwdArgs& fa) {
   static const bool enabled = !(std::getenv("VF_BN_FUSE_FWD") && std::atoi(std::getenv("VF_BN_FUSE_FWD")) == 0);
-  if (!enabled || M <= 0 || N <= 0 || K <= 0 || !A || !B || !fa.z || !fa.a || !fa.aT) return false;
+  if (!enabled || !fa.z || !fa.a || !fa.aT) return false;
   if ((fa.gamma == nullptr) != (fa.beta == nullptr) || (fa.gamma && (!fa.mean || !fa.rstd || !fa.var || fa.bias))) return false;
   auto al = [](const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; };
-  const bool spans32 = (int64_t)M * lda * 2 < ((int64_t)1 << 31) && (int64_t)N * ldb * 2 < ((int64_t)1 << 31);
-  return (M % 256) == 0 && (N % 256) == 0 && (K % 64) == 0 && spans32 && wide_fits(M, N) &&
-         wide_tile_n(M, N) == 256 && wide_variant() == 0 && !(lda & 7) && !(ldb & 7) && al(A, 16) && al(B, 16) &&
-         !(fa.ldz & 3) && !(fa.lda & 3) && !(fa.ldt & 7) && al(fa.z, 16) && al(fa.a, 8) && al(fa.aT, 16) &&
-         al(fa.mean, 16) && al(fa.rstd, 16) && al(fa.var, 16) && al(fa.gamma, 16) && al(fa.beta, 16) && al(fa.bias, 16);
+  return !(fa.ldz & 3) && !(fa.lda & 3) && !(fa.ldt & 7) && al(fa.z, 16) && al(fa.a, 8) && al(fa.aT, 16) &&
+         al(fa.mean, 16) && al(fa.rstd, 16) && al(fa.var, 16) && al(fa.gamma, 16) && al(fa.beta, 16) && al(fa.bias, 16) &&
+         bn_tile(A, lda, B, ldb, M, N, K, false) != 0;
 }
 
 int launch_gemm_bf16_bn_fwd(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int M, int N, int K,
                             const BnFwdArgs& fa, hipStream_t s) {
   if (!gemm_bf16_bn_fwd_takes(A, lda, B, ldb, M, N, K, fa)) return VF_EINVAL;
-  constexpr int bytes = 160 * 1024;
-  static bool ready = false;
-  if (!ready) {
-    VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_wide_line16_kernel<2>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-    ready = true;
-  }
-  const int tiles_m = M / 256, tiles_n = N / 256;
-  const int ntile = tiles_m * tiles_n;
-  dim3 grid(((ntile + 7) / 8) * 8, 1, 1);
-  gemm_bf16_wide_line16_kernel<2><<<grid, 512, bytes, s>>>(A, lda, B, ldb, M, N, K, K, 0, Epilogue{}, tiles_m, tiles_n,
-                                                           BnBwdArgs{}, fa);
-  VF_LAUNCH_CHECK();
-  return VF_OK;
+  const Shape g{A, lda, B, ldb, M, N, K, 1, 0};
+  if (bn_tile(A, lda, B, ldb, M, N, K, false) == 128) return launch_mid_bn<false>(g, BnBwdArgs{}, fa, s);
+  return launch_wide_line16<2>(g, Epilogue{}, BnBwdArgs{}, fa, s);
 }
 
 bool gemm_bf16_bn_bwd_takes(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int M, int N, int K,
                             const BnBwdArgs& fa) {
   static const bool enabled = !(std::getenv("VF_BN_FUSE") && std::atoi(std::getenv("VF_BN_FUSE")) == 0);
-  if (!enabled || M <= 0 || N <= 0 || K <= 0 || !A || !B || !fa.z || !fa.dz || !fa.dzT || !fa.sums) return false;
+  if (!enabled || !fa.z || !fa.dz || !fa.dzT || !fa.sums) return false;
   if ((fa.gamma == nullptr) != (fa.beta == nullptr) || (fa.gamma && (!fa.mean || !fa.rstd))) return false;
   auto al = [](const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; };
-  const bool spans32 = (int64_t)M * lda * 2 < ((int64_t)1 << 31) && (int64_t)N * ldb * 2 < ((int64_t)1 << 31);
-  return (M % 256) == 0 && (N % 256) == 0 && (K % 64) == 0 && spans32 && wide_fits(M, N) &&
-         wide_tile_n(M, N) == 256 && wide_variant() == 0 && !(lda & 7) && !(ldb & 7) && al(A, 16) && al(B, 16) &&
-         !(fa.ldz & 3) && !(fa.lddz & 3) && !(fa.ldt & 7) && al(fa.z, 16) && al(fa.dz, 8) && al(fa.dzT, 16) &&
-         al(fa.sums, 16) && al(fa.mean, 16) && al(fa.rstd, 16) && al(fa.gamma, 16) && al(fa.beta, 16);
+  return !(fa.ldz & 3) && !(fa.lddz & 3) && !(fa.ldt & 7) && al(fa.z, 16) && al(fa.dz, 8) && al(fa.dzT, 16) &&
+         al(fa.sums, 16) && al(fa.mean, 16) && al(fa.rstd, 16) && al(fa.gamma, 16) && al(fa.beta, 16) &&
+         bn_tile(A, lda, B, ldb, M, N, K, true) != 0;
 }
 
 int launch_gemm_bf16_bn_bwd(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int M, int N, int K,
                             const BnBwdArgs& fa, hipStream_t s) {
   if (!gemm_bf16_bn_bwd_takes(A, lda, B, ldb, M, N, K, fa)) return VF_EINVAL;
-  constexpr int bytes = 160 * 1024;
-  static bool ready = false;
-  if (!ready) {
-    VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_wide_line16_kernel<1>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-    ready = true;
-  }
-  const int tiles_m = M / 256, tiles_n = N / 256;
-  const int ntile = tiles_m * tiles_n;
-  dim3 grid(((ntile + 7) / 8) * 8, 1, 1);
-  gemm_bf16_wide_line16_kernel<1><<<grid, 512, bytes, s>>>(A, lda, B, ldb, M, N, K, K, 0, Epilogue{}, tiles_m, tiles_n, fa, BnFwdArgs{});
-  VF_LAUNCH_CHECK();
-  return VF_OK;
+  const Shape g{A, lda, B, ldb, M, N, K, 1, 0};
+  if (bn_tile(A, lda, B, ldb, M, N, K, true) == 128) return launch_mid_bn<true>(g, fa, BnFwdArgs{}, s);
+  return launch_wide_line16<1>(g, Epilogue{}, fa, BnFwdArgs{}, s);
 }
-
 
 int launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int M, int N,
                      int K, int nsplit, int64_t slab_stride, const Epilogue& ep, hipStream_t s) {

@@ -804,21 +804,22 @@ __global__ __launch_bounds__((GroupShape<G, SGP>::THREADS)) void bn_relu_bwd_pai
   }
 }
 
-// Scale / shift (or bias) gradients from per-node column sums [nodes][2][C] (left by a product whose
-// epilogue took the BatchNorm backward pass): added up in node order and folded in once, as the
-// group kernels do.
-__global__ __launch_bounds__(256) void bn_sums_finish_kernel(const float* __restrict__ sums, int nodes, int C,
-                                                             GradOut gout_g, GradOut gout_b) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
+// What the products whose epilogues took a BatchNorm pass leave to do, for all layers of a unit in one launch (a layer's own
+// launch of 6 to 9 us stood between two products).  Sixteen nodes' loads in flight together.
+// Scale / shift (or bias) gradients from per-node column sums [nodes][2][C]: added up in node order and folded in once,
+// as the group kernels do.
+__global__ __launch_bounds__(256) void bn_sums_finish_kernel(BnFinishJobs jobs, int nodes) {
+  const BnFinishJob& job = jobs.job[blockIdx.y];
+  const int C = job.C, c = blockIdx.x * 256 + threadIdx.x;
   if (c >= C) return;
   float tg = 0.f, tb = 0.f;
-  for (int n0 = 0; n0 < nodes; n0 += 16) {         // sixteen nodes' loads in flight together
+  for (int n0 = 0; n0 < nodes; n0 += 16) {
     float sg[16], sb[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       const int n = min(n0 + k, nodes - 1);
-      sg[k] = sums[((int64_t)n * 2 + 0) * C + c];
-      sb[k] = sums[((int64_t)n * 2 + 1) * C + c];
+      sg[k] = job.src0[((int64_t)n * 2 + 0) * C + c];
+      sb[k] = job.src0[((int64_t)n * 2 + 1) * C + c];
     }
 #pragma unroll
     for (int k = 0; k < 16; ++k)
@@ -827,25 +828,24 @@ __global__ __launch_bounds__(256) void bn_sums_finish_kernel(const float* __rest
         tb = (n0 + k) ? tb + sb[k] : sb[k];
       }
   }
-  if (gout_g.dst) grad_store(gout_g, c, tg);
-  if (gout_b.dst) grad_store(gout_b, c, tb);
+  if (job.gout_g.dst) grad_store(job.gout_g, c, tg);
+  if (job.gout_b.dst) grad_store(job.gout_b, c, tb);
 }
 
-// Moving statistics from per-node batch statistics [nodes][C] (left by a product whose epilogue took
-// the BatchNorm forward pass): one blend per node, node after node (Section 4.1), as the kernels above.
-__global__ __launch_bounds__(256) void bn_stats_finish_kernel(const float* __restrict__ mean, const float* __restrict__ var,
-                                                              int nodes, int C, float* __restrict__ run_mean,
-                                                              float* __restrict__ run_var, float run_mix) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
+// Moving statistics from per-node batch statistics [nodes][C]: one blend per node, node after node (Section 4.1), as the
+// kernels above.
+__global__ __launch_bounds__(256) void bn_stats_finish_kernel(BnFinishJobs jobs, int nodes, float run_mix) {
+  const BnFinishJob& job = jobs.job[blockIdx.y];
+  const int C = job.C, c = blockIdx.x * 256 + threadIdx.x;
   if (c >= C) return;
-  float rm = run_mean[c], rv = run_var[c];
+  float rm = job.run_mean[c], rv = job.run_var[c];
   for (int n0 = 0; n0 < nodes; n0 += 16) {
     float m[16], v[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       const int n = min(n0 + k, nodes - 1);
-      m[k] = mean[(int64_t)n * C + c];
-      v[k] = var[(int64_t)n * C + c];
+      m[k] = job.src0[(int64_t)n * C + c];
+      v[k] = job.src1[(int64_t)n * C + c];
     }
 #pragma unroll
     for (int k = 0; k < 16; ++k)
@@ -854,7 +854,7 @@ __global__ __launch_bounds__(256) void bn_stats_finish_kernel(const float* __res
         rv = fmaf(run_mix, v[k] - rv, rv);
       }
   }
-  run_mean[c] = rm; run_var[c] = rv;
+  job.run_mean[c] = rm; job.run_var[c] = rv;
 }
 
 constexpr int SCB = 32, SRL = 8;
@@ -1125,17 +1125,30 @@ int launch_bn_relu_bwd(float* dap, int nsplit, int64_t slab, int64_t ldda, const
   return VF_OK;
 }
 
-int launch_bn_stats_finish(const float* mean, const float* var, int nodes, int C, float* run_mean, float* run_var,
-                           float run_mix, hipStream_t s) {
-  if (!mean || !var || !run_mean || !run_var || nodes < 1 || C <= 0) return VF_EINVAL;
-  bn_stats_finish_kernel<<<(C + 255) / 256, 256, 0, s>>>(mean, var, nodes, C, run_mean, run_var, run_mix);
+static int finish_width(const BnFinishJobs& jobs, int nodes) {
+  if (nodes < 1 || jobs.count < 1 || jobs.count > VF_MAX_DIMS) return 0;
+  int width = 0;
+  for (int j = 0; j < jobs.count; ++j) {
+    if (!jobs.job[j].src0 || jobs.job[j].C <= 0) return 0;
+    width = std::max(width, jobs.job[j].C);
+  }
+  return width;
+}
+
+int launch_bn_stats_finish(const BnFinishJobs& jobs, int nodes, float run_mix, hipStream_t s) {
+  const int width = finish_width(jobs, nodes);
+  if (!width) return VF_EINVAL;
+  for (int j = 0; j < jobs.count; ++j)
+    if (!jobs.job[j].src1 || !jobs.job[j].run_mean || !jobs.job[j].run_var) return VF_EINVAL;
+  bn_stats_finish_kernel<<<dim3((width + 255) / 256, jobs.count), 256, 0, s>>>(jobs, nodes, run_mix);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }
 
-int launch_bn_sums_finish(const float* sums, int nodes, int C, GradOut gout_g, GradOut gout_b, hipStream_t s) {
-  if (!sums || nodes < 1 || C <= 0) return VF_EINVAL;
-  bn_sums_finish_kernel<<<(C + 255) / 256, 256, 0, s>>>(sums, nodes, C, gout_g, gout_b);
+int launch_bn_sums_finish(const BnFinishJobs& jobs, int nodes, hipStream_t s) {
+  const int width = finish_width(jobs, nodes);
+  if (!width) return VF_EINVAL;
+  bn_sums_finish_kernel<<<dim3((width + 255) / 256, jobs.count), 256, 0, s>>>(jobs, nodes);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }

@@ -104,7 +104,7 @@ struct BnFwdArgs {
   int64_t ldt = 0;
   float* mean = nullptr;         // [nodes, N] (BatchNorm only)
   float* rstd = nullptr;
-  float* var = nullptr;          // [nodes, N] scratch (BatchNorm only)
+  float* var = nullptr;          // [nodes, N] (BatchNorm only)
 };
 
 // ---------------------------------------------------------------------------------------
@@ -146,17 +146,26 @@ bool gemm_bf16_bn_fwd_takes(const bf16_t* A, int64_t lda, const bf16_t* B, int64
                             const BnFwdArgs& fa);
 int launch_gemm_bf16_bn_fwd(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int M, int N, int K,
                             const BnFwdArgs& fa, hipStream_t s);
+// What such products leave to do, for several layers of a unit in one launch (k_norm.hip).
+struct BnFinishJob {
+  const float* src0;             // sums [nodes][2][C], or the per-node means [nodes][C] ...
+  const float* src1;             // ... with their variances [nodes][C]
+  float* run_mean;
+  float* run_var;
+  GradOut gout_g, gout_b;
+  int C;
+};
+struct BnFinishJobs { BnFinishJob job[VF_MAX_DIMS]; int count; };
 // Moving statistics blended with the per-node batch statistics, node after node (Section 4.1).
-int launch_bn_stats_finish(const float* mean, const float* var, int nodes, int C, float* run_mean, float* run_var,
-                           float run_mix, hipStream_t s);
+int launch_bn_stats_finish(const BnFinishJobs& jobs, int nodes, float run_mix, hipStream_t s);
 // Scale / shift (or bias) gradients from the per-node column sums, added up in node order.
-int launch_bn_sums_finish(const float* sums, int nodes, int C, GradOut gout_g, GradOut gout_b, hipStream_t s);
+int launch_bn_sums_finish(const BnFinishJobs& jobs, int nodes, hipStream_t s);
 // The kernels of the general bf16 product (k_gemm_bf16.hip) and which of them a product goes to.
 enum class GemmRoute { kShortK, kWide, kStaged32x128, kStaged128x32, kStaged64, kStaged128, kDirect64 };
 GemmRoute gemm_bf16_route(int M, int N, int K, int nsplit, bool spans32, bool vec_ok);
 // Number of slices that fills the chip for this shape (1 when the tile grid already does).
 constexpr float kSlabFoldUs = 1.3f;    // a million elements of a slab that launch_fold_slabs reads
-int gemm_bf16_pick_split(int M, int N, int K, float slab_us = 2.7f);
+int gemm_bf16_pick_split(int M, int N, int K, float slab_us = 2.7f, float* us = nullptr);   // *us: the product's own share
 
 // Weight gradients of `count` consecutive nodes folded into C in one pass over it:
 //   C <- fma(w[count-1], A[count-1] B[count-1]^T, ... fma(w[0], A[0] B[0]^T, overwrite ? 0 : C))

@@ -22,6 +22,8 @@ struct Layer {
   float* z[2] = {nullptr, nullptr};     // fp32 [max_b, ld]: Linear output (logits for the last layer)
   float* mean[2] = {nullptr, nullptr};  // [N]
   float* rstd[2] = {nullptr, nullptr};  // [N]
+  float* var = nullptr;            // [nodes, N], [nodes][2][N]: what a product with the BatchNorm pass in its epilogue leaves
+  float* sums = nullptr;           // of its nodes for the launch that finishes all layers (units of several nodes only)
   int64_t s_off = 0;               // offset of this layer's moving statistics within a state half
   void* a[2] = {nullptr, nullptr};      // T [max_b, ld]: activation after BatchNorm/ReLU
   // T [max_b, ld]: gradient w.r.t. z.  Two sets only for the last layer (the softmax of the
@@ -154,6 +156,10 @@ class Mlp final : public Model {
         a.request(&L.wnat, (size_t)L.K * L.ldn);
         a.request(&L.wtr, (size_t)L.N * L.ldt);
         a.request(&L.dzT, (size_t)L.N * ldw_);
+        if (L.hidden && group_ > 1) {
+          if (L.has_bn) a.request(&L.var, (size_t)L.N * group_);
+          a.request(&L.sums, (size_t)2 * L.N * group_);
+        }
         if (L.hidden) a.request(&L.aT, (size_t)L.N * ldw_);
       }
     }
@@ -219,6 +225,7 @@ class Mlp final : public Model {
     const void* x = bf16_ ? (const void*)(static_cast<const bf16_t*>(s.x) + row0 * D)
                           : (const void*)(static_cast<const float*>(s.x) + row0 * D);
     const int32_t* y = s.y + row0;
+    BnFinishJobs stats{};
 
     for (int l = 0; l < nl; ++l) {
       Layer& L = layers_[l];
@@ -231,9 +238,9 @@ class Mlp final : public Model {
       // normalisation kernel then has nothing to copy
       float* zsrc = (split == 1 && L.hidden) ? L.z[q] : slab_buf;
       // A unit of whole nodes of 128 rows on a wide layer: the product's epilogue takes BatchNorm and
-      // ReLU itself (the pre-activations are stored and not read again in this pass); the scratch
-      // holds the per-node variances for the small launch that blends the moving statistics.
-      bool whole = bf16_ && L.hidden && split == 1 && s.group(i) >= 2 && b == 128 * s.group(i);
+      // ReLU itself (the pre-activations are stored and not read again in this pass); the small launch
+      // behind the layers blends the moving statistics with what the nodes leave.
+      bool whole = bf16_ && L.hidden && s.group(i) >= 2 && b == 128 * s.group(i);
       for (int n = 0; n < s.group(i) && whole; ++n) whole = s.rows_of(i)[n] == 128;
       if (whole) {
         BnFwdArgs ff;
@@ -244,12 +251,11 @@ class Mlp final : public Model {
         ff.eps = cfg_.bn_eps;
         ff.a = static_cast<bf16_t*>(L.a[q]); ff.lda = L.ld;
         ff.aT = L.aT + pc; ff.ldt = ldw_;
-        ff.mean = L.mean[q]; ff.rstd = L.rstd[q]; ff.var = slab_buf;
+        ff.mean = L.mean[q]; ff.rstd = L.rstd[q]; ff.var = L.var;
         if (gemm_bf16_bn_fwd_takes(static_cast<const bf16_t*>(in), ldin, L.wtr, L.ldt, b, L.N, L.K, ff)) {
           VF_KS(c, st, "gemm_fwd_bn", launch_gemm_bf16_bn_fwd(static_cast<const bf16_t*>(in), ldin, L.wtr, L.ldt, b, L.N, L.K, ff, st));
           if (L.has_bn)
-            VF_KS(c, st, "bn_stats_finish", launch_bn_stats_finish(L.mean[q], slab_buf, s.group(i), L.N, state_ + L.s_off,
-                                                                   state_ + bn_width_ + L.s_off, cfg_.bn_momentum, st));
+            stats.job[stats.count++] = {L.mean[q], L.var, state_ + L.s_off, state_ + bn_width_ + L.s_off, {}, {}, L.N};
           continue;
         }
       }
@@ -274,6 +280,7 @@ class Mlp final : public Model {
                                                          tscale(c, s, i)));
     }
     wait_casts_ = false;
+    if (stats.count) VF_KS(c, st, "bn_stats_finish", launch_bn_stats_finish(stats, s.group(i), cfg_.bn_momentum, st));
     // loss bookkeeping of the whole step after the last node's rows are in: node losses and
     // their weighted sum (Section 5.2), in node order
     if (i == s.V - 1) {
@@ -300,6 +307,7 @@ class Mlp final : public Model {
     const float w = s.w[i];
     const float* P = s.params;
     const int nl = (int)layers_.size();
+    BnFinishJobs sums{};
     for (int l = nl - 1; l >= 1; --l) {
       Layer& L = layers_[l];
       // input gradient da[l-1][b,K] = dz W^T, then through ReLU / BatchNorm of layer l-1
@@ -312,9 +320,9 @@ class Mlp final : public Model {
       GradOut gg = Pv.has_bn ? c.gout(Pv.g_off, w, i) : GradOut{nullptr, 0.f, 0};
       GradOut gb = c.gout(Pv.has_bn ? Pv.be_off : Pv.b_off, w, i);
       // A unit of whole nodes of 128 rows on a wide layer: the product's epilogue takes the BatchNorm /
-      // ReLU backward pass itself (the incoming gradient is never stored); the scratch holds the
-      // per-node column sums for the small launch that makes the scale / shift gradients of them.
-      bool whole = bf16_ && split == 1 && s.group(i) >= 2 && b == 128 * s.group(i);
+      // ReLU backward pass itself (the incoming gradient is never stored) and leaves per-node column
+      // sums, of which the small launch behind the layers makes the scale / shift gradients.
+      bool whole = bf16_ && s.group(i) >= 2 && b == 128 * s.group(i);
       for (int n = 0; n < s.group(i) && whole; ++n) whole = s.rows_of(i)[n] == 128;
       if (whole) {
         BnBwdArgs fa;
@@ -325,11 +333,11 @@ class Mlp final : public Model {
         fa.dz = static_cast<bf16_t*>(Pv.dz[0]); fa.lddz = Pv.ld;
         fa.dzT = Pv.dzT + pc; fa.ldt = ldw_;
         fa.tscale = tscale(c, s, i);
-        fa.sums = slab_buf;
+        fa.sums = Pv.sums;
         if (gemm_bf16_bn_bwd_takes(static_cast<const bf16_t*>(dz_in), L.ld, L.wnat, L.ldn, b, L.K, kdim(L), fa)) {
           VF_KS(c, st, "gemm_dgrad_bn", launch_gemm_bf16_bn_bwd(static_cast<const bf16_t*>(dz_in), L.ld, L.wnat, L.ldn, b, L.K,
                                                              kdim(L), fa, st));
-          VF_KS(c, st, "bn_sums_finish", launch_bn_sums_finish(slab_buf, s.group(i), Pv.N, gg, gb, st));
+          sums.job[sums.count++] = {Pv.sums, nullptr, nullptr, nullptr, gg, gb, Pv.N};
           continue;
         }
       }
@@ -343,6 +351,7 @@ class Mlp final : public Model {
                                      bf16_, Pv.mean[q], Pv.rstd[q], Pv.dz[0], Pv.ld, bf16_, bf16_ ? Pv.dzT + pc : nullptr, ldw_,
                                      gg, gb, st, tscale(c, s, i), s.group(i), s.rows_of(i)));
     }
+    if (sums.count) VF_KS(c, st, "bn_sums_finish", launch_bn_sums_finish(sums, s.group(i), st));
     return VF_OK;
   }
 

@@ -1,4 +1,6 @@
 """GPU parity: the HIP path through the C ABI against the CPU oracle, MLP workloads."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -579,6 +581,33 @@ def test_wide_units_of_whole_nodes_match_the_oracle(name):
         ref = oracle_steps(wl2, theta, x2, y2)
         gpu = run_gpu(wl2, theta, x2, y2, flags=BENCH, fold_window=8, node_group=16)
         check_against_oracle(wl2, gpu, ref)
+
+
+@pytest.mark.parametrize("name", ["mlp_mid_bn_bf16", "mlp_mid_bf16"])
+@pytest.mark.parametrize("dims,nodes,group", [((64, 128, 384, 256, 16), 17, 32), ((320, 640, 128, 64), 32, 32),
+                                              ((192, 256, 512, 24), 20, 16), ((64, 1024, 1024, 10), 9, 16)])
+def test_units_of_whole_nodes_on_narrow_layers_match_the_oracle(name, dims, nodes, group):
+    """Many nodes of 128 rows on layers too narrow for the 256-wide tiles: the products run on 128 x 128 tiles, one node
+    a tile row, with the BatchNorm / ReLU passes in their epilogues (one stage of the contraction up to many; one tile
+    column up to eight; a last unit of one or few nodes goes the ordinary way).  The oracle's result and the same bits in
+    every launch mode, and with the nodes' weights inside the transposed operand."""
+    wl = dataclasses.replace(I.workload(name), dims=list(dims)).with_nodes([128] * nodes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    ref = oracle_steps(wl, theta, x, y)
+    base = None
+    for flags in (BENCH, FUSED, 0):
+        gpu = run_gpu(wl, theta, x, y, flags=flags, node_group=group)
+        check_against_oracle(wl, gpu, ref)
+        np.testing.assert_allclose(gpu["node_losses"], ref["node_losses"], rtol=1e-3)
+        if base is None:
+            base = gpu
+        if flags & FUSED:
+            assert gpu["G"].tobytes() == base["G"].tobytes(), flags
+            assert gpu["theta"].tobytes() == base["theta"].tobytes(), flags
+    wl = wl.with_nodes([128] * 16 + [64] * 16)
+    x, y = I.make_batch(wl)
+    check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=BENCH, fold_window=8, node_group=16), oracle_steps(wl, theta, x, y))
 
 
 def test_node_groups_keep_the_workspace_independent_of_the_node_count():
