@@ -13,6 +13,8 @@
 // take 4.9 us and, with the operands in cache, 15 us (24 us inside a step); 2048 x 1024 x 1024 runs at 81 TFLOP/s.
 // Where there are tiles enough for every wavefront to have one of its own, and for operands out of 32-bit reach,
 // see launch_operands and launch_gemm_f32.
+#include <algorithm>
+
 #include "vf_device.h"
 
 namespace vf {
@@ -27,12 +29,12 @@ constexpr uint32_t kOutside = 0x80000000u;   // an offset beyond every buffer: t
 // One lane's part of an operand: T row tiles of MS rows, this lane's row of each.  A chunk is 4 * 64 / MS
 // contraction elements: the q-th copy of the rows among the lanes (q = lane / MS) holds elements 4 q .. 4 q + 3
 // of it, and MFMA step s contracts element s of every copy (any assignment of k to steps will do as long as
-// both operands use the same one).  A group is GU chunks.  KC: the operand is contiguous along k; VEC: in
+// both operands use the same one).  A group is G chunks.  KC: the operand is contiguous along k; VEC: in
 // 16-byte vectors (rows 16-byte aligned, K % 4 == 0).  Loads go through a buffer descriptor over the operand
 // from the workgroup's first row on: what lies outside the matrix (rows, or k at and beyond K) is asked for
 // beyond the buffer's end and comes back as 0, so there are neither branches nor selections around the loads
 // and the compiler keeps a whole group's in flight.
-template <int MS, int T, bool KC, bool VEC>
+template <int MS, int T, bool KC, bool VEC, int G>
 struct Operand {
   static constexpr int CK = 4 * (64 / MS);
   __amdgpu_buffer_rsrc_t buf;
@@ -54,12 +56,12 @@ struct Operand {
     }
   }
   // The group of contraction elements k0 .. k0 + GU * CK - 1 (k0 the same for the whole wavefront).
-  __device__ __forceinline__ void load(float (&v)[GU][T][4], int k0) const {
+  __device__ __forceinline__ void load(float (&v)[G][T][4], int k0) const {
     const int left = K - k0 - kl;                        // elements of this lane from its first one on
     // (a chunk that starts past the end: nothing is fetched, and its scalar offset stays inside the buffer, so that
     // the bounds check -- lane offset against the buffer's size, with or without the scalar offset -- is the same)
 #pragma unroll
-    for (int u = 0; u < GU; ++u)
+    for (int u = 0; u < G; ++u)
 #pragma unroll
       for (int t = 0; t < T; ++t) {
         if (KC && VEC) {
@@ -94,6 +96,54 @@ template <> struct Mfma<16> {
   static __device__ __forceinline__ int row(int r, int lane) { return 4 * (lane >> 4) + r; }
 };
 
+// A wavefront's share of a tile's product: the contraction elements [kbeg, kend), added to acc.
+template <int MS, int TM, int TN, bool AKC, bool BKC, bool VEC, int G>
+__device__ __forceinline__ void slice_product(typename Mfma<MS>::acc_t (&acc)[TM][TN], const float* __restrict__ A, int64_t lda,
+                                              const float* __restrict__ B, int64_t ldb, int M, int N, int K, int m0, int n0,
+                                              int kbeg, int kend, int lane) {
+  constexpr int GK = G * 4 * (64 / MS);                  // contraction elements of a group
+  const int groups = kend > kbeg ? (kend - kbeg + GK - 1) / GK : 0;
+  if (groups <= 0) return;
+  Operand<MS, TM, AKC, VEC, G> oa;
+  Operand<MS, TN, BKC, VEC, G> ob;
+  oa.init(A, lda, m0, M, K, lane);
+  ob.init(B, ldb, n0, N, K, lane);
+  float a0[G][TM][4], b0[G][TN][4], a1[G][TM][4], b1[G][TN][4];
+  auto multiply = [&](const float (&a)[G][TM][4], const float (&b)[G][TN][4]) {
+#pragma unroll
+    for (int u = 0; u < G; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<MS>::mul(a[u][i][s], b[u][j][s], acc[i][j]);
+  };
+  // two groups in flight: the loads of group g + 2 are issued as soon as group g has been multiplied (past the
+  // operand's end they fetch nothing and return 0; past the slice's end they are not used)
+  oa.load(a0, kbeg);
+  ob.load(b0, kbeg);
+  if (groups > 1) {
+    oa.load(a1, kbeg + GK);
+    ob.load(b1, kbeg + GK);
+    int k = kbeg;
+    for (int g = 0; g + 2 <= groups; g += 2, k += 2 * GK) {
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(a0, b0);
+      __builtin_amdgcn_sched_barrier(0);
+      oa.load(a0, min(k + 2 * GK, K));
+      ob.load(b0, min(k + 2 * GK, K));
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(a1, b1);
+      __builtin_amdgcn_sched_barrier(0);
+      oa.load(a1, min(k + 3 * GK, K));
+      ob.load(b1, min(k + 3 * GK, K));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (groups & 1) multiply(a0, b0);
+}
+
 // blockIdx.z selects the contraction slice [z * kslab, (z + 1) * kslab); slice z writes its partial product
 // to slab z of C (the consumer adds the slabs in order), the bias goes to slab 0.  Wavefront w of a
 // workgroup takes the elements [w * kwave, (w + 1) * kwave) of the slice (kwave and kslab multiples of a group).
@@ -105,7 +155,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
   typedef Mfma<MS> MF;
   constexpr int R = MF::R;
   constexpr int E = TM * TN * MS * MS;                   // elements of the tile
-  constexpr int GK = GU * 4 * (64 / MS);                 // contraction elements of a group
   __shared__ float part[NW > 1 ? NW * E : 1];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -122,47 +171,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
 #pragma unroll
       for (int r = 0; r < R; ++r) acc[i][j][r] = 0.f;
 
-  const int groups = kend > kbeg ? (kend - kbeg + GK - 1) / GK : 0;
-  if (groups > 0) {
-    Operand<MS, TM, AKC, VEC> oa;
-    Operand<MS, TN, BKC, VEC> ob;
-    oa.init(A, lda, m0, M, K, lane);
-    ob.init(B, ldb, n0, N, K, lane);
-    float a0[GU][TM][4], b0[GU][TN][4], a1[GU][TM][4], b1[GU][TN][4];
-    auto multiply = [&](const float (&a)[GU][TM][4], const float (&b)[GU][TN][4]) {
-#pragma unroll
-      for (int u = 0; u < GU; ++u)
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = MF::mul(a[u][i][s], b[u][j][s], acc[i][j]);
-    };
-    // two groups in flight: the loads of group g + 2 are issued as soon as group g has been multiplied (past the
-    // operand's end they fetch nothing and return 0; past the slice's end they are not used)
-    oa.load(a0, kbeg);
-    ob.load(b0, kbeg);
-    if (groups > 1) {
-      oa.load(a1, kbeg + GK);
-      ob.load(b1, kbeg + GK);
-      int k = kbeg;
-      for (int g = 0; g + 2 <= groups; g += 2, k += 2 * GK) {
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(a0, b0);
-        __builtin_amdgcn_sched_barrier(0);
-        oa.load(a0, min(k + 2 * GK, K));
-        ob.load(b0, min(k + 2 * GK, K));
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(a1, b1);
-        __builtin_amdgcn_sched_barrier(0);
-        oa.load(a1, min(k + 3 * GK, K));
-        ob.load(b1, min(k + 3 * GK, K));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (groups & 1) multiply(a0, b0);
-  }
+  slice_product<MS, TM, TN, AKC, BKC, VEC, GU>(acc, A, lda, B, ldb, M, N, K, m0, n0, kbeg, kend, lane);
 
   // Partial tiles through LDS as the registers hold them, added in wavefront order.
   if (NW > 1) {
@@ -178,7 +187,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
   const bool first_slice = blockIdx.z == 0;
   constexpr int NT = NW * 64;
   constexpr int PER = (E + NT - 1) / NT;
-  float add[PER];
+  float add[PER], gate[PER];
   int mm[PER], nn[PER];
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
@@ -190,6 +199,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
     const int m = min(mm[p], M - 1), n = min(nn[p], N - 1);
     add[p] = (ep.bias && first_slice) ? ep.bias[n] : 0.f;
     if (ep.R) add[p] = fmaf(ep.beta, ep.R[(int64_t)m * ep.ldr + n], add[p]);
+    gate[p] = ep.gate ? ep.gate[(int64_t)m * ep.ldg + n] : 1.f;
   }
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
@@ -203,7 +213,269 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
     } else {
       sum = acc[p / R / TN][p / R % TN][p % R];            // (element e of the tile is this lane's p-th)
     }
-    C[(int64_t)mm[p] * ep.ldc + nn[p]] = fmaf(ep.alpha, sum, add[p]);
+    const float v = fmaf(ep.alpha, sum, add[p]);
+    C[(int64_t)mm[p] * ep.ldc + nn[p]] = gate[p] > 0.f ? v : 0.f;
+    if (ep.relu) ep.relu[(int64_t)mm[p] * ep.ldrelu + nn[p]] = fmaxf(v, 0.f);
+  }
+}
+
+// ---- one node's product with its BatchNorm pass ---------------------------------------------------
+// A node of up to 128 rows: a workgroup takes ALL its rows of 16 columns (TM tiles of 16 rows), so the columns' sums over
+// the node stay inside it and the BatchNorm + ReLU pass needs no launch of its own (4 us behind a product of 5 to 10).
+// Eight wavefronts cut the contraction among themselves as above; bound by the trips to memory and, with only N / 16
+// workgroups, by the fp32 matrix rate of their compute units, hence the limit on rows times contraction (f32_bn_takes).
+// The arithmetic is that of bn_relu_fwd_kernel / bn_relu_bwd_kernel.
+constexpr int BN_NW = 8;
+
+template <int TM, bool BKC, bool VEC, bool BWD>
+__global__ __launch_bounds__(BN_NW * 64) void gemm_f32_bn_kernel(const float* __restrict__ A, int64_t lda,
+                                                                 const float* __restrict__ B, int64_t ldb, int R, int N,
+                                                                 int K, int kwave, F32BnArgs f) {
+  constexpr int E = TM * 256, NT = BN_NW * 64, PER = E / NT;
+  __shared__ float part[BN_NW * E];
+  __shared__ float red[2][BN_NW][16];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n0 = blockIdx.x * 16, n = n0 + (lane & 15), nc = min(n, N - 1);
+  // element p of this thread: element p * NT + tid of the tile in register order (tile row f / 4, register f % 4)
+  int mm[PER];
+  float zz[PER];
+  const float g = f.gamma[nc], b = f.beta[nc];
+  float mean = 0.f, rstd = 1.f, rm = 0.f, rv = 0.f;
+  if (BWD) { mean = f.mean[nc]; rstd = f.rstd[nc]; }
+  else if (f.run_mean) { rm = f.run_mean[nc]; rv = f.run_var[nc]; }
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    const int e = p * BN_NW + wave;
+    mm[p] = 16 * (e >> 2) + 4 * (lane >> 4) + (e & 3);
+    zz[p] = BWD ? f.z[(int64_t)min(mm[p], R - 1) * f.ldz + nc] : 0.f;
+  }
+  f32x4v acc[TM][1];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[i][0][r] = 0.f;
+  slice_product<16, TM, 1, true, BKC, VEC, 2>(acc, A, lda, B, ldb, R, N, K, 0, n0, wave * kwave, min(K, (wave + 1) * kwave), lane);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wave * E + (i * 4 + r) * 64 + lane] = acc[i][0][r];
+  __syncthreads();
+  float v[PER];
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    v[p] = part[p * NT + tid];
+#pragma unroll
+    for (int w = 1; w < BN_NW; ++w) v[p] += part[w * E + p * NT + tid];
+  }
+  // sum over the node's rows of this thread's column, to every thread of the column
+  auto column_sum = [&](float s, int k) {
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    if (lane < 16) red[k][wave][lane] = s;
+    __syncthreads();
+    float t = red[k][0][lane & 15];
+#pragma unroll
+    for (int w = 1; w < BN_NW; ++w) t += red[k][w][lane & 15];
+    return t;
+  };
+  const bool mine = n < N;
+  if (!BWD) {
+    float s = 0.f;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) s += mm[p] < R ? v[p] : 0.f;
+    mean = column_sum(s, 0) / (float)R;
+    float q = 0.f;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const float d = mm[p] < R ? v[p] - mean : 0.f;
+      q = fmaf(d, d, q);
+    }
+    const float var = column_sum(q, 1) / (float)R;
+    rstd = 1.0f / sqrtf(var + f.eps);
+    if (mine && tid < 16) {
+      f.mean[n] = mean; f.rstd[n] = rstd;
+      if (f.run_mean) {
+        f.run_mean[n] = fmaf(f.run_mix, mean - rm, rm);
+        f.run_var[n] = fmaf(f.run_mix, var - rv, rv);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < PER; ++p)
+      if (mine && mm[p] < R) {
+        f.z[(int64_t)mm[p] * f.ldz + n] = v[p];
+        f.out[(int64_t)mm[p] * f.ldo + n] = fmaxf(fmaf(g, (v[p] - mean) * rstd, b), 0.f);
+      }
+    return;
+  }
+  float sg = 0.f, sb = 0.f;
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    const float xhat = (zz[p] - mean) * rstd;
+    const bool on = mm[p] < R && fmaf(g, xhat, b) > 0.f;
+    zz[p] = mm[p] < R ? xhat : 0.f;
+    v[p] = on ? v[p] : 0.f;
+    sg = fmaf(v[p], zz[p], sg);
+    sb += v[p];
+  }
+  sg = column_sum(sg, 0);
+  sb = column_sum(sb, 1);
+  if (mine && tid < 16) {
+    grad_store(f.gout_g, n, sg);
+    grad_store(f.gout_b, n, sb);
+  }
+  const float invR = 1.0f / (float)R, kk = g * rstd;
+#pragma unroll
+  for (int p = 0; p < PER; ++p)
+    if (mine && mm[p] < R) f.out[(int64_t)mm[p] * f.ldo + n] = kk * (v[p] - sb * invR - zz[p] * sg * invR);
+}
+
+// ---- the last layer's product with the loss -------------------------------------------------------------
+// Few classes (TN tiles of 16): a workgroup takes all logits of 16 rows, so the softmax cross-entropy needs no launch of its
+// own.  The logits pass through LDS; 32 lanes take a row.  What is computed is what softmax_xent_kernel computes.
+template <int TN, bool VEC>
+__global__ __launch_bounds__(512) void gemm_f32_xent_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ B,
+                                                            int64_t ldb, int R, int N, int K, int kwave,
+                                                            const float* __restrict__ bias, const int32_t* __restrict__ labels,
+                                                            float* __restrict__ z, int64_t ldz, float* __restrict__ dz,
+                                                            int64_t lddz, float* __restrict__ rowloss) {
+  constexpr int NW = 8, E = TN * 256, NT = NW * 64, PER = (E + NT - 1) / NT, CPL = (16 * TN + 31) / 32;
+  __shared__ float part[NW * E];
+  __shared__ float logit[16][16 * TN + 1];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = blockIdx.x * 16;
+  const int row = tid >> 5, l = tid & 31, m = m0 + row, mc = min(m, R - 1);
+  const int label = min(max(labels[mc], 0), N - 1);
+  float bb[PER];
+#pragma unroll
+  for (int p = 0; p < PER; ++p) bb[p] = bias[min(16 * (((p * NT + tid) >> 6) >> 2) + (lane & 15), N - 1)];
+  f32x4v acc[1][TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[0][j][r] = 0.f;
+  slice_product<16, 1, TN, true, false, VEC, TN <= 2 ? 4 : 2>(acc, A, lda, B, ldb, R, N, K, m0, 0, wave * kwave,
+                                                              min(K, (wave + 1) * kwave), lane);
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wave * E + (j * 4 + r) * 64 + lane] = acc[0][j][r];
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    const int e = p * NT + tid;
+    if (E % NT && e >= E) break;
+    float v = part[e];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += part[w * E + e];
+    const int f = e >> 6;
+    logit[4 * (lane >> 4) + (f & 3)][16 * (f >> 2) + (lane & 15)] = v + bb[p];
+  }
+  __syncthreads();
+  float v[CPL], mx = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < CPL; ++k) {
+    const int c = l + 32 * k;
+    v[k] = c < N ? logit[row][c] : -INFINITY;
+    if (c < N && m < R) z[(int64_t)m * ldz + c] = v[k];
+    mx = fmaxf(mx, v[k]);
+  }
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  float sum = 0.f;
+#pragma unroll
+  for (int k = 0; k < CPL; ++k) {
+    v[k] = expf(v[k] - mx);                              // exp(-inf) = 0 for the padding
+    sum += v[k];
+  }
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  const float inv = 1.0f / sum, invR = 1.0f / (float)R;
+  if (m >= R) return;
+#pragma unroll
+  for (int k = 0; k < CPL; ++k) {
+    const int c = l + 32 * k;
+    if (c < N) dz[(int64_t)m * lddz + c] = (v[k] * inv - (c == label ? 1.f : 0.f)) * invR;
+  }
+  if (l == 0) rowloss[m] = logf(sum) + mx - logit[row][label];
+}
+
+// ---- the weight and bias gradients of a unit in one launch ------------------------------------------
+// They depend on nothing but the unit's activations and output gradients and none of them fills the chip (784 x 256 x 64 is
+// 3.6 us, most of it launch): one grid holds the tiles of all layers, a workgroup finding its job from the running totals.
+// A job without A is a bias gradient: the sums over the unit's rows of 32 columns of B.  The last workgroup does the loss
+// bookkeeping of the step if there is any to do (as loss_reduce_nodes_kernel).
+template <int MS>
+__global__ __launch_bounds__(256) void gemm_f32_jobs_kernel(F32Jobs jobs, const float* __restrict__ rowloss, LossNodes ln,
+                                                            float* __restrict__ node_loss, float* __restrict__ total) {
+  typedef Mfma<MS> MF;
+  constexpr int R = MF::R, E = MS * MS, NW = 4, PER = E / 256 ? E / 256 : 1;
+  __shared__ float part[NW * E];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int j = 0;                                              // (no chain of loads: the totals come with one or two)
+#pragma unroll
+  for (int i = 0; i < kF32Jobs; ++i) j += (int)blockIdx.x >= jobs.end[i] ? 1 : 0;
+  if (j == jobs.count) {
+    float acc = ln.first == 0 ? 0.f : *total;
+    for (int i = 0; i < ln.count; ++i) {
+      float s = 0.f;
+      for (int r = tid; r < ln.rows[i]; r += 256) s += rowloss[ln.off[i] + r];
+      s = wave_sum(s);
+      __syncthreads();
+      if (lane == 0) part[wave] = s;
+      __syncthreads();
+      const float L = (part[0] + part[1] + part[2] + part[3]) / (float)ln.rows[i];
+      if (tid == 0) node_loss[ln.first + i] = L;
+      acc = fmaf(ln.w[i], L, acc);
+    }
+    if (tid == 0) *total = acc;
+    return;
+  }
+  const F32Job& job = jobs.job[j];
+  const int t = (int)blockIdx.x - (j ? jobs.end[j - 1] : 0);
+  const int N = job.N, K = jobs.rows;
+  if (!job.A) {
+    const int n = t * 32 + (tid & 31), r0 = tid >> 5, nc = min(n, N - 1);
+    float s = 0.f;
+    int r = r0;
+    for (; r + 24 < K; r += 32) {                        // four rows' loads in flight together
+      float x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = job.B[(int64_t)(r + 8 * q) * job.ldb + nc];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s += x[q];
+    }
+    for (; r < K; r += 8) s += job.B[(int64_t)r * job.ldb + nc];
+    part[r0 * 32 + (tid & 31)] = s;
+    __syncthreads();
+    if (tid < 32 && n < N) {
+      s = part[tid];
+#pragma unroll
+      for (int q = 1; q < 8; ++q) s += part[q * 32 + tid];
+      grad_store(job.out, n, s);
+    }
+    return;
+  }
+  const int tiles_n = (N + MS - 1) / MS;
+  const int m0 = t / tiles_n * MS, n0 = t % tiles_n * MS;
+  typename MF::acc_t acc[1][1];
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[0][0][r] = 0.f;
+  slice_product<MS, 1, 1, false, false, false, GU>(acc, job.A, job.lda, job.B, job.ldb, job.M, N, K, m0, n0, wave * jobs.kwave,
+                                                   min(K, (wave + 1) * jobs.kwave), lane);
+#pragma unroll
+  for (int r = 0; r < R; ++r) part[wave * E + r * 64 + lane] = acc[0][0][r];
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    const int e = p * 256 + tid, m = m0 + MF::row(e / 64, lane), n = n0 + lane % MS;
+    if (m >= job.M || n >= N) continue;
+    float sum = part[e];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) sum += part[w * E + e];
+    grad_store(job.out, (int64_t)m * N + n, sum);
   }
 }
 
@@ -276,7 +548,9 @@ __global__ __launch_bounds__(TILED_NT) void gemm_f32_tiled_kernel(const float* _
       if (n >= N) continue;
       float add = (ep.bias && first_slice) ? ep.bias[n] : 0.f;
       if (ep.R) add = fmaf(ep.beta, ep.R[(int64_t)m * ep.ldr + n], add);
-      C[(int64_t)m * ep.ldc + n] = fmaf(ep.alpha, acc[i][j], add);
+      const float v = fmaf(ep.alpha, acc[i][j], add);
+      C[(int64_t)m * ep.ldc + n] = !ep.gate || ep.gate[(int64_t)m * ep.ldg + n] > 0.f ? v : 0.f;
+      if (ep.relu) ep.relu[(int64_t)m * ep.ldrelu + n] = fmaxf(v, 0.f);
     }
   }
 }
@@ -394,6 +668,108 @@ int launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, in
   if (akc) return vec ? launch_operands<true, false, true>(g, ep, s) : launch_operands<true, false, false>(g, ep, s);
   if (!bkc) return launch_operands<false, false, false>(g, ep, s);
   return launch_operands<false, true, false>(g, ep, s);
+}
+
+// What a workgroup's loads reach in 32-bit byte offsets: 64 (128) rows of an operand contiguous along k, or the whole
+// contraction of one contiguous along its rows.
+static bool near32(bool kc, int64_t ld, int rows, int K) {
+  return (kc ? 128 * ld + K : (int64_t)K * ld + rows) * 4 < ((int64_t)1 << 31);
+}
+
+// Rows (rounded up to 32) times contraction that a workgroup of the fused kernel takes: a node's product is cut by columns
+// only, so with long contractions of many rows its few workgroups cost more than the BatchNorm launch they save.  Steps of
+// K-N-N-10 networks of three nodes, launches apart | fused (us): 16 rows, N = 64, K = 1000 115 | 86; 32 rows, N = 1000,
+// K = 1000 193 | 180; 64 rows, N = 256, K = 256 124 | 104, K = 512 111 | 118; 100 rows, N = 500, K = 64 131 | 129, K = 256 136 | 171.
+bool f32_bn_takes(int R, int N, int K, int64_t lda, int64_t ldb, bool backward) {
+  if (R < 1 || R > 128 || N < 1 || K < 1) return false;
+  return (int64_t)((R + 31) / 32 * 32) * K <= (R <= 32 ? 32768 : 16384) && near32(true, lda, R, K) && near32(backward, ldb, N, K);
+}
+
+int launch_gemm_f32_bn(const float* A, int64_t lda, const float* B, int64_t ldb, int R, int N, int K, bool backward,
+                       const F32BnArgs& f, hipStream_t s) {
+  if (!A || !B || !f.gamma || !f.beta || !f.mean || !f.rstd || !f.z || !f.out || (f.run_mean == nullptr) != (f.run_var == nullptr) ||
+      (backward && (!f.gout_g.dst || !f.gout_b.dst)) || !f32_bn_takes(R, N, K, lda, ldb, backward))
+    return VF_EINVAL;
+  auto al = [](const float* p, int64_t ld) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && (ld & 3) == 0; };
+  const bool vec = (K & 3) == 0 && al(A, lda) && (!backward || al(B, ldb));
+  const int kwave = ((K + BN_NW - 1) / BN_NW + 31) / 32 * 32;
+  const int grid = (N + 15) / 16;
+#define VF_F32BN2(TM, VEC)                                                                                              \
+  if (backward) gemm_f32_bn_kernel<TM, true, VEC, true><<<grid, BN_NW * 64, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, f); \
+  else gemm_f32_bn_kernel<TM, false, VEC, false><<<grid, BN_NW * 64, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, f)
+#define VF_F32BN(TM) if (vec) { VF_F32BN2(TM, true); } else { VF_F32BN2(TM, false); }
+  switch ((R + 31) / 32) {
+    case 1: VF_F32BN(2) break;
+    case 2: VF_F32BN(4) break;
+    case 3: VF_F32BN(6) break;
+    default: VF_F32BN(8) break;
+  }
+#undef VF_F32BN
+#undef VF_F32BN2
+  VF_LAUNCH_CHECK();
+  return VF_OK;
+}
+
+// Classes (rounded up to 16) times contraction that a workgroup of the kernel with the loss takes: it is cut by rows only.
+bool f32_xent_takes(int R, int N, int K, int64_t lda, int64_t ldb) {
+  return R >= 1 && N >= 1 && K >= 1 && N <= 128 && (int64_t)((N + 15) / 16 * 16) * K <= 32768 && near32(true, lda, R, K) &&
+         near32(false, ldb, N, K);
+}
+
+int launch_gemm_f32_xent(const float* A, int64_t lda, const float* B, int64_t ldb, int R, int N, int K, const float* bias,
+                         const int32_t* labels, float* z, int64_t ldz, float* dz, int64_t lddz, float* rowloss, hipStream_t s) {
+  if (!A || !B || !bias || !labels || !z || !dz || !rowloss || !f32_xent_takes(R, N, K, lda, ldb)) return VF_EINVAL;
+  const bool vec = (K & 3) == 0 && (lda & 3) == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0;
+  const int tn = (N + 15) / 16, gk = (tn <= 2 ? 4 : 2) * 16;
+  const int kwave = ((K + 7) / 8 + gk - 1) / gk * gk;
+  const int grid = (R + 15) / 16;
+#define VF_XENT(TN)                                                                                                        \
+  if (vec) gemm_f32_xent_kernel<TN, true><<<grid, 512, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, bias, labels, z, ldz, dz, lddz, rowloss); \
+  else gemm_f32_xent_kernel<TN, false><<<grid, 512, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, bias, labels, z, ldz, dz, lddz, rowloss)
+  if (tn <= 1) { VF_XENT(1); }
+  else if (tn <= 2) { VF_XENT(2); }
+  else if (tn <= 4) { VF_XENT(4); }
+  else { VF_XENT(8); }
+#undef VF_XENT
+  VF_LAUNCH_CHECK();
+  return VF_OK;
+}
+
+// Up to 512 contraction elements and as many tiles as a launch of one layer takes without sharing wavefronts out
+// differently (launch_operands); 16 x 16 tiles while they are few.
+bool f32_jobs_take(const F32Jobs& jobs) {
+  if (jobs.count < 1 || jobs.count > kF32Jobs || jobs.rows < 1 || jobs.rows > 512) return false;
+  int64_t t64 = 0;
+  for (int j = 0; j < jobs.count; ++j) {
+    const F32Job& g = jobs.job[j];
+    if (!g.B || !g.out.dst || g.N < 1 || !near32(false, g.ldb, g.N, jobs.rows)) return false;
+    if (g.A && (g.M < 1 || !near32(false, g.lda, g.M, jobs.rows))) return false;
+    if (g.A) t64 += (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  }
+  return t64 <= 512;
+}
+
+int launch_gemm_f32_jobs(F32Jobs jobs, const float* rowloss, const LossNodes& ln, float* node_loss, float* total, hipStream_t s) {
+  if (!f32_jobs_take(jobs) || ln.count < 0 || ln.count > kLossNodes || (ln.count && (!rowloss || !node_loss || !total)))
+    return VF_EINVAL;
+  int64_t t16 = 0;
+  for (int j = 0; j < jobs.count; ++j)
+    if (jobs.job[j].A) t16 += (int64_t)((jobs.job[j].M + 15) / 16) * ((jobs.job[j].N + 15) / 16);
+  const int ms = t16 <= (jobs.rows <= 128 ? 1024 : 512) ? 16 : 32;
+  int end = 0;
+  for (int j = 0; j < jobs.count; ++j) {
+    const F32Job& g = jobs.job[j];
+    end += g.A ? ((g.M + ms - 1) / ms) * ((g.N + ms - 1) / ms) : (g.N + 31) / 32;
+    jobs.end[j] = end;
+  }
+  for (int j = jobs.count; j < kF32Jobs; ++j) jobs.end[j] = 0x7fffffff;
+  const int gk = GU * 4 * (64 / ms);
+  jobs.kwave = ((jobs.rows + 3) / 4 + gk - 1) / gk * gk;
+  const int grid = end + (ln.count ? 1 : 0);
+  if (ms == 16) gemm_f32_jobs_kernel<16><<<grid, 256, 0, s>>>(jobs, rowloss, ln, node_loss, total);
+  else gemm_f32_jobs_kernel<32><<<grid, 256, 0, s>>>(jobs, rowloss, ln, node_loss, total);
+  VF_LAUNCH_CHECK();
+  return VF_OK;
 }
 
 }  // namespace vf

@@ -63,6 +63,11 @@ struct Epilogue {
   int64_t ldc = 0;
   int c_is_bf16 = 0;             // store C as bf16 (RNE) instead of fp32
   int stream_c = 0;              // store C with the non-temporal hint (it is not kept in the L2s)
+  // fp32 products only: C is 0 where gate[m, n] <= 0 (ReLU backward); relu[m, n] = max(C, 0) beside C (ReLU forward)
+  const float* gate = nullptr;
+  int64_t ldg = 0;
+  float* relu = nullptr;
+  int64_t ldrelu = 0;
 };
 
 // BatchNorm + ReLU backward of whole nodes of 128 rows, taken inside the epilogue of the product that
@@ -125,6 +130,62 @@ int launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, in
                     int64_t sbk, int M, int N, int K, int nsplit, int64_t slab_stride,
                     const Epilogue& ep, hipStream_t s);
 int gemm_f32_pick_split(int M, int N, int K);
+
+// Loss bookkeeping of nodes first .. first+count-1 (the R_j rows of node j at rowloss + off[j]):
+// node_loss[i] = (1/R_i) sum_r rowloss[r];  total = (i == 0 ? 0 : total) + w_i * node_loss[i]
+constexpr int kLossNodes = 32;
+struct LossNodes {
+  int32_t off[kLossNodes];
+  int32_t rows[kLossNodes];
+  float w[kLossNodes];
+  int32_t first, count;
+};
+
+// One node's fp32 product A [R, K] (contiguous along k) B with the BatchNorm + ReLU pass of its R <= 128 rows in the same
+// launch.  Forward: B [K, N], the product is the pre-activation: z, out = the activation, mean, rstd written, the moving
+// statistics blended.  Backward: B [N, K], the product is the incoming gradient: out = the gradient at z, the scale and
+// shift gradients.  f32_bn_takes: whether the kernel takes the shape (the launch returns VF_EINVAL otherwise).
+struct F32BnArgs {
+  const float* gamma;
+  const float* beta;
+  float eps;
+  float* z;
+  int64_t ldz;
+  float* out;
+  int64_t ldo;
+  float* mean;                   // [N]
+  float* rstd;
+  float* run_mean;               // or null
+  float* run_var;
+  float run_mix;
+  GradOut gout_g, gout_b;
+};
+bool f32_bn_takes(int R, int N, int K, int64_t lda, int64_t ldb, bool backward);
+int launch_gemm_f32_bn(const float* A, int64_t lda, const float* B, int64_t ldb, int R, int N, int K, bool backward,
+                       const F32BnArgs& f, hipStream_t s);
+// The last layer of an fp32 MLP: logits z = A [R, K] B [K, N] + bias, and of each row (all R rows one mean) the loss and the
+// gradient dz = (softmax - onehot) / R, in one launch.
+bool f32_xent_takes(int R, int N, int K, int64_t lda, int64_t ldb);
+int launch_gemm_f32_xent(const float* A, int64_t lda, const float* B, int64_t ldb, int R, int N, int K, const float* bias,
+                         const int32_t* labels, float* z, int64_t ldz, float* dz, int64_t lddz, float* rowloss, hipStream_t s);
+// The weight gradients A^T B (A [rows, M], B [rows, N] -> out [M, N]) and bias gradients (A null: column sums of B) of a
+// unit's layers in one launch, and with ln.count > 0 the loss bookkeeping of up to kLossNodes nodes.
+constexpr int kF32Jobs = 2 * VF_MAX_DIMS;
+struct F32Job {
+  const float* A;
+  int64_t lda;
+  const float* B;
+  int64_t ldb;
+  GradOut out;
+  int M, N;
+};
+struct F32Jobs {
+  int count, rows, kwave;
+  int end[kF32Jobs];             // workgroups of a job and those before it (set by the launch)
+  F32Job job[kF32Jobs];
+};
+bool f32_jobs_take(const F32Jobs& jobs);
+int launch_gemm_f32_jobs(F32Jobs jobs, const float* rowloss, const LossNodes& ln, float* node_loss, float* total, hipStream_t s);
 
 // k_gemm_bf16.hip: acc[m,n] = sum_k A[m*lda + k] * B[n*ldb + k]  (bf16 operands, fp32 MFMA
 // accumulation).  lda, ldb multiples of 8, A and B 16-byte aligned.  The contraction is cut
@@ -321,15 +382,7 @@ int launch_fold_slabs(const float* slabs, int nsplit, int64_t stride, int64_t n,
 int launch_softmax_xent(const float* zp, int nsplit, int64_t slab, int64_t ldzp, float* z, int64_t ldz,
                         const int32_t* labels, int R, int C, float* rowloss, void* dz, int64_t lddz,
                         int dz_is_bf16, bf16_t* dzT, int64_t ldt, hipStream_t s, float tscale = 1.f);
-// Loss bookkeeping of nodes first .. first+count-1 (the R_j rows of node j at rowloss + off[j]):
-// node_loss[i] = (1/R_i) sum_r rowloss[r];  total = (i == 0 ? 0 : total) + w_i * node_loss[i]
-constexpr int kLossNodes = 32;
-struct LossNodes {
-  int32_t off[kLossNodes];
-  int32_t rows[kLossNodes];
-  float w[kLossNodes];
-  int32_t first, count;
-};
+// Loss bookkeeping of a run of nodes (LossNodes, above).
 int launch_loss_reduce_nodes(const float* rowloss, const LossNodes& ln, float* node_loss, float* total,
                              hipStream_t s);
 

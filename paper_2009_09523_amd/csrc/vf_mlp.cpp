@@ -259,14 +259,29 @@ class Mlp final : public Model {
           continue;
         }
       }
+      if (!bf16_ && L.has_bn && s.group(i) == 1 && split == 1 && f32_bn_takes(b, L.N, L.K, ldin, L.N, false)) {
+        F32BnArgs f{P + L.g_off, P + L.be_off, cfg_.bn_eps, L.z[q], L.ld, static_cast<float*>(L.a[q]), L.ld, L.mean[q], L.rstd[q],
+                    state_ + L.s_off, state_ + bn_width_ + L.s_off, cfg_.bn_momentum, {}, {}};
+        VF_KS(c, st, "gemm_fwd_bn", launch_gemm_f32_bn(static_cast<const float*>(in), ldin, P + L.w_off, L.N, b, L.N, L.K, false, f, st));
+        continue;
+      }
+      if (!bf16_ && !L.hidden && split == 1 && f32_xent_takes(b, L.N, L.K, ldin, L.N)) {
+        VF_KS(c, st, "gemm_fwd_xent", launch_gemm_f32_xent(static_cast<const float*>(in), ldin, P + L.w_off, L.N, b, L.N, L.K,
+                                                           P + L.b_off, y, L.z[q], L.ld, static_cast<float*>(L.dz[q]), L.ld,
+                                                           c.rowloss + row0, st));
+        continue;
+      }
       Epilogue ep;
       ep.C = zsrc; ep.ldc = L.ld;
+      const bool relu = relu_in_product(L, split);
+      if (relu) { ep.relu = static_cast<float*>(L.a[q]); ep.ldrelu = L.ld; }
       if (L.has_bias) { ep.bias = P + L.b_off; ep.bias_round_bf16 = bf16_; }
       if (bf16_)
         VF_KS(c, st, "gemm_fwd", launch_gemm_bf16(static_cast<const bf16_t*>(in), ldin, L.wtr, L.ldt, b, L.N, L.K,
                                                   split, slab, ep, st));
       else
         VF_KS(c, st, "gemm_fwd", launch_gemm_f32(static_cast<const float*>(in), ldin, 1, P + L.w_off, 1, L.N, b, L.N, L.K, split, slab, ep, st));
+      if (relu) continue;
       if (L.hidden)
         VF_KS(c, st, "bn_relu_fwd", launch_bn_relu_fwd(zsrc, split, slab, L.ld, s.seg[i], L.N,
                                        L.has_bn ? P + L.g_off : nullptr, L.has_bn ? P + L.be_off : nullptr,
@@ -282,20 +297,28 @@ class Mlp final : public Model {
     wait_casts_ = false;
     if (stats.count) VF_KS(c, st, "bn_stats_finish", launch_bn_stats_finish(stats, s.group(i), cfg_.bn_momentum, st));
     // loss bookkeeping of the whole step after the last node's rows are in: node losses and
-    // their weighted sum (Section 5.2), in node order
-    if (i == s.V - 1) {
-      for (int first = 0; first < s.nodes; first += kLossNodes) {
-        LossNodes ln{};
-        ln.first = first;
-        ln.count = std::min(kLossNodes, s.nodes - first);
-        for (int j = 0; j < ln.count; ++j) {
-          ln.off[j] = s.node_off[first + j]; ln.rows[j] = s.node_sizes[first + j]; ln.w[j] = s.node_w[first + j];
-        }
-        VF_KS(c, st, "loss_reduce", launch_loss_reduce_nodes(c.rowloss, ln, c.node_loss, c.loss_total, st));
-      }
-    }
+    // their weighted sum (Section 5.2), in node order (fp32: with the weight gradients)
+    if (i == s.V - 1 && bf16_) return reduce_losses(c, s, st);
     return VF_OK;
   }
+
+  static LossNodes loss_nodes(const StepArgs& s, int first) {
+    LossNodes ln{};
+    ln.first = first;
+    ln.count = std::min(kLossNodes, s.nodes - first);
+    for (int j = 0; j < ln.count; ++j) {
+      ln.off[j] = s.node_off[first + j]; ln.rows[j] = s.node_sizes[first + j]; ln.w[j] = s.node_w[first + j];
+    }
+    return ln;
+  }
+  int reduce_losses(Ctx& c, const StepArgs& s, hipStream_t st) {
+    for (int first = 0; first < s.nodes; first += kLossNodes)
+      VF_KS(c, st, "loss_reduce", launch_loss_reduce_nodes(c.rowloss, loss_nodes(s, first), c.node_loss, c.loss_total, st));
+    return VF_OK;
+  }
+  // fp32 without BatchNorm: the product's epilogue takes the ReLU of the layer it arrives at, forward and backward (the
+  // layer's bias gradient then goes with the weight gradients).
+  bool relu_in_product(const Layer& L, int split) const { return !bf16_ && L.hidden && !L.has_bn && split == 1; }
 
   // The input-gradient chain of node i (with the small-vector gradients the BatchNorm/ReLU
   // backward kernels fold into the gradient buffer on the way).
@@ -341,11 +364,20 @@ class Mlp final : public Model {
           continue;
         }
       }
+      if (!bf16_ && Pv.has_bn && s.group(i) == 1 && split == 1 && f32_bn_takes(b, L.K, L.N, L.ld, L.N, true)) {
+        F32BnArgs f{P + Pv.g_off, P + Pv.be_off, cfg_.bn_eps, Pv.z[q], Pv.ld, static_cast<float*>(Pv.dz[0]), Pv.ld, Pv.mean[q],
+                    Pv.rstd[q], nullptr, nullptr, 0.f, gg, gb};
+        VF_KS(c, st, "gemm_dgrad_bn", launch_gemm_f32_bn(static_cast<const float*>(dz_in), L.ld, P + L.w_off, L.N, b, L.K, L.N, true, f, st));
+        continue;
+      }
+      const bool relu = relu_in_product(Pv, split);
+      if (relu) { ed.C = Pv.dz[0]; ed.gate = Pv.z[q]; ed.ldg = Pv.ld; }
       if (bf16_)
         VF_KS(c, st, "gemm_dgrad", launch_gemm_bf16(static_cast<const bf16_t*>(dz_in), L.ld, L.wnat, L.ldn, b, L.K, kdim(L),
                                                     split, slab, ed, st));
       else
         VF_KS(c, st, "gemm_dgrad", launch_gemm_f32(static_cast<const float*>(dz_in), L.ld, 1, P + L.w_off, L.N, 1, b, L.K, L.N, split, slab, ed, st));
+      if (relu) continue;
       VF_KS(c, st, "bn_relu_bwd", launch_bn_relu_bwd(slab_buf, split, slab, Pv.ld, Pv.z[q], Pv.ld, s.seg[i], Pv.N,
                                      Pv.has_bn ? P + Pv.g_off : nullptr, Pv.has_bn ? P + Pv.be_off : nullptr,
                                      bf16_, Pv.mean[q], Pv.rstd[q], Pv.dz[0], Pv.ld, bf16_, bf16_ ? Pv.dzT + pc : nullptr, ldw_,
@@ -416,34 +448,23 @@ class Mlp final : public Model {
       }
       return VF_OK;
     }
+    if (!bf16_) return run_side_f32(c, s, i0, st);      // (window 1)
     for (int i = i0; i < i0 + count && !fold; ++i) {
       const int64_t pc = cols(c, s, i);
       const int b = s.sizes[i];
       const int64_t row0 = s.off[i];
       const float w = s.w[i];
-      const void* x = bf16_ ? (const void*)(static_cast<const bf16_t*>(s.x) + row0 * D)
-                            : (const void*)(static_cast<const float*>(s.x) + row0 * D);
-      if (bf16_)
-        VF_KS(c, st, "transpose", launch_transpose_bf16(static_cast<const bf16_t*>(x), D, xT_ + pc, ldw_, b, D, st));
+      VF_KS(c, st, "transpose", launch_transpose_bf16(static_cast<const bf16_t*>(s.x) + row0 * D, D, xT_ + pc, ldw_, b, D, st));
       for (int l = nl - 1; l >= 0; --l) {
         Layer& L = layers_[l];
-        const void* in = l == 0 ? x : layers_[l - 1].a[0];   // fp32 path: one tensor set
-        const int64_t ldin = l == 0 ? D : layers_[l - 1].ld;
-        if (!L.hidden) {   // last layer: bias gradient = sums over the node of dlogits
-          if (bf16_) VF_KS(c, st, "bias_grad", launch_rowsum_bf16(L.dzT + pc, ldw_, L.N, b, c.gout(L.b_off, w, i), st));
-          else       VF_KS(c, st, "bias_grad", launch_colsum(L.dz[0], L.ld, 0, b, L.N, c.gout(L.b_off, w, i), st));
-        }
+        if (!L.hidden)     // last layer: bias gradient = sums over the node of dlogits
+          VF_KS(c, st, "bias_grad", launch_rowsum_bf16(L.dzT + pc, ldw_, L.N, b, c.gout(L.b_off, w, i), st));
         GradOut go = c.gout(L.w_off, w, i);
         Epilogue ep;
         ep.C = go.dst; ep.ldc = L.N; ep.alpha = go.alpha;
         if (go.accumulate) { ep.R = go.dst; ep.ldr = L.N; ep.beta = 1.f; }
-        if (bf16_) {
-          const bf16_t* inT = (l == 0 ? xT_ : layers_[l - 1].aT) + pc;
-          VF_KS(c, st, "gemm_wgrad", launch_gemm_bf16(inT, ldw_, L.dzT + pc, ldw_, L.K, L.N, b, 1, 0, ep, st));
-        } else {
-          VF_KS(c, st, "gemm_wgrad", launch_gemm_f32(static_cast<const float*>(in), 1, ldin,
-                                                     static_cast<const float*>(L.dz[0]), 1, L.ld, L.K, L.N, b, 1, 0, ep, st));
-        }
+        const bf16_t* inT = (l == 0 ? xT_ : layers_[l - 1].aT) + pc;
+        VF_KS(c, st, "gemm_wgrad", launch_gemm_bf16(inT, ldw_, L.dzT + pc, ldw_, L.K, L.N, b, 1, 0, ep, st));
         if (c.fused && i == i0 + count - 1) VF_TRY(layer_done(l));
       }
       VF_TRY(c.fold(i, w, st));
@@ -468,6 +489,44 @@ class Mlp final : public Model {
       }
     }
     return VF_OK;
+  }
+
+  // The same for an fp32 unit: weight gradients, bias gradients and the step's loss bookkeeping in one launch where that
+  // kernel takes the shapes, else a launch each.
+  int run_side_f32(Ctx& c, const StepArgs& s, int i, hipStream_t st) {
+    const int nl = (int)layers_.size(), D = cfg_.dims[0], b = s.sizes[i];
+    const float w = s.w[i];
+    F32Jobs jobs{};
+    jobs.rows = b;
+    for (int l = nl - 1; l >= 0; --l) {
+      const Layer& L = layers_[l];
+      const float* in = l == 0 ? static_cast<const float*>(s.x) + (int64_t)s.off[i] * D : static_cast<const float*>(layers_[l - 1].a[0]);
+      const float* dz = static_cast<const float*>(L.dz[0]);
+      jobs.job[jobs.count++] = {in, l == 0 ? D : layers_[l - 1].ld, dz, L.ld, c.gout(L.w_off, w, i), L.K, L.N};
+      // (a hidden layer's bias gradient comes from the BatchNorm / ReLU backward kernel unless the product took the ReLU)
+      if (!L.hidden || relu_in_product(L, split_for(b, layers_[l + 1].K, kdim(layers_[l + 1]), L.ld)))
+        jobs.job[jobs.count++] = {nullptr, 0, dz, L.ld, c.gout(L.b_off, w, i), 0, L.N};
+    }
+    const bool last = i == s.V - 1;
+    if (f32_jobs_take(jobs)) {
+      const bool losses = last && s.nodes <= kLossNodes;
+      VF_KS(c, st, "gemm_wgrad", launch_gemm_f32_jobs(jobs, c.rowloss, losses ? loss_nodes(s, 0) : LossNodes{}, c.node_loss, c.loss_total, st));
+      if (last && !losses) VF_TRY(reduce_losses(c, s, st));
+      return c.fold(i, w, st);
+    }
+    for (int j = 0; j < jobs.count; ++j) {
+      const F32Job& g = jobs.job[j];
+      if (!g.A) {
+        VF_KS(c, st, "bias_grad", launch_colsum(g.B, g.ldb, 0, b, g.N, g.out, st));
+        continue;
+      }
+      Epilogue ep;
+      ep.C = g.out.dst; ep.ldc = g.N; ep.alpha = g.out.alpha;
+      if (g.out.accumulate) { ep.R = g.out.dst; ep.ldr = g.N; ep.beta = 1.f; }
+      VF_KS(c, st, "gemm_wgrad", launch_gemm_f32(g.A, 1, g.lda, g.B, 1, g.ldb, g.M, g.N, b, 1, 0, ep, st));
+    }
+    if (last) VF_TRY(reduce_losses(c, s, st));
+    return c.fold(i, w, st);
   }
 
  private:

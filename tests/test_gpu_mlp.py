@@ -48,6 +48,26 @@ def test_f32_step_on_wide_layers(dims, nodes):
     check_against_oracle(wl, gpu, ref)
 
 
+@pytest.mark.parametrize("name", ["mlp_small_bn_f32", "mlp_small_f32"])
+@pytest.mark.parametrize("dims,nodes", [((128, 40, 17, 16), (128, 97, 1, 65)), ((256, 33, 129), (64, 33, 2)),
+                                        ((1023, 66, 64, 33), (32, 31, 17)), ((1025, 24, 65), (32, 96)), ((16, 7, 1), (5, 128)),
+                                        ((129, 256, 128, 128), (128, 100)), ((20, 255, 512, 64), (16, 130))])
+def test_f32_fused_launches_at_their_edges(name, dims, nodes):
+    """The fp32 launches that take BatchNorm / ReLU, the loss, or all weight gradients along with their products: rows and
+    classes at and beside their tiles, contractions at and beside their limits, a node too long for them; node after node,
+    in both folds, and as units."""
+    wl = dataclasses.replace(I.workload(name), dims=dims, node_sizes=nodes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    ref = oracle_steps(wl, theta, x, y)
+    base = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH)
+    check_against_oracle(wl, base, ref)
+    np.testing.assert_allclose(base["node_losses"], ref["node_losses"], rtol=1e-5, atol=1e-6)
+    staged = run_gpu(wl, theta, x, y, flags=0)
+    assert staged["G"].tobytes() == base["G"].tobytes()
+    check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=FUSED, node_group=4), ref)
+
+
 @pytest.mark.parametrize("dims,rows", [((31, 2051, 33), 1100), ((99, 2051, 100), 1100), ((130, 2051, 131), 1100), ((260, 2051, 204), 1100),
                                        ((700, 2051, 321), 1100), ((131, 2051, 260), 2100), ((81, 2100, 97), 2100),
                                        ((100, 4100, 129), 4200), ((129, 4100, 256), 4200), ((2051, 1101, 10), 24),
