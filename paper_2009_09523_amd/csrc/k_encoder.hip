@@ -745,16 +745,10 @@ __global__ __launch_bounds__(NT) void dy_bf16_prepare_kernel(const bf16_t* __res
         (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
 }
 
-// ---- GELU (exact) ---------------------------------------------------------------------------
+// ---- GELU (exact; gelu_f, gelu_df: vf_device.h) ------------------------------------------------
 // The pre-activation u is what a Linear layer put out: fp32 in every workload (only operands of
 // contractions are bf16).  T is the type of the GELU output (the next Linear layer's operand) and
 // of the gradient du handed to the backward products.
-__device__ __forceinline__ float gelu_f(float v) { return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_df(float v) {
-  const float cdf = 0.5f * (1.0f + erff(v * 0.70710678118654752f));
-  const float pdf = 0.3989422804014327f * expf(-0.5f * v * v);
-  return cdf + v * pdf;
-}
 template <typename T>
 __global__ __launch_bounds__(NT) void gelu_fwd_kernel(const float* __restrict__ u, T* __restrict__ g, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;

@@ -24,17 +24,20 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 typedef float f32x16v __attribute__((ext_vector_type(16)));
 
 constexpr int GU = 4;        // chunks of the contraction per group
+// Contractions from which rows that allow no aligned vectors are read with unaligned ones (36 x 256 x 4099 in four slices:
+// scalar loads 24.4 us, unaligned vectors 9.5; 100 x 500 x 10: 6.0, 9.3).
+constexpr int kUnalignedK = 64;
 constexpr uint32_t kOutside = 0x80000000u;   // an offset beyond every buffer: the load returns 0
 
 // One lane's part of an operand: T row tiles of MS rows, this lane's row of each.  A chunk is 4 * 64 / MS
 // contraction elements: the q-th copy of the rows among the lanes (q = lane / MS) holds elements 4 q .. 4 q + 3
 // of it, and MFMA step s contracts element s of every copy (any assignment of k to steps will do as long as
 // both operands use the same one).  A group is G chunks.  KC: the operand is contiguous along k; VEC: in
-// 16-byte vectors (rows 16-byte aligned, K % 4 == 0).  Loads go through a buffer descriptor over the operand
+// 16-byte vectors, 1 (rows 16-byte aligned, K % 4 == 0) or 2 (any rows of at least four elements).  Loads go through a buffer descriptor over the operand
 // from the workgroup's first row on: what lies outside the matrix (rows, or k at and beyond K) is asked for
 // beyond the buffer's end and comes back as 0, so there are neither branches nor selections around the loads
 // and the compiler keeps a whole group's in flight.
-template <int MS, int T, bool KC, bool VEC, int G>
+template <int MS, int T, bool KC, int VEC, int G>
 struct Operand {
   static constexpr int CK = 4 * (64 / MS);
   __amdgpu_buffer_rsrc_t buf;
@@ -64,12 +67,24 @@ struct Operand {
     for (int u = 0; u < G; ++u)
 #pragma unroll
       for (int t = 0; t < T; ++t) {
-        if (KC && VEC) {
+        if (KC && VEC == 1) {
           typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
           const u32x4v q = __builtin_amdgcn_raw_buffer_load_b128(buf, CK * u < left ? off[t] : kOutside,
                                                               min(k0 + CK * u, K - 1) * 4, 0);
 #pragma unroll
           for (int s = 0; s < 4; ++s) v[u][t][s] = __uint_as_float(q[s]);
+        } else if (KC && VEC == 2) {
+          typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+          const int rest = left - CK * u;                // elements from this vector's first one to the end of the row
+          // (a vector that reaches past the row's end is read so that it ends there, and moved into place: rows need no
+          // alignment beyond their elements' own, and the contraction no multiple of 4)
+          const uint32_t back = rest < 4 ? 16u - 4u * (uint32_t)max(rest, 0) : 0u;
+          const uint32_t o = rest > 0 && off[t] != kOutside ? off[t] + 4u * (uint32_t)min(k0 + CK * u, K - 1) - back : kOutside;
+          const u32x4v q = __builtin_amdgcn_raw_buffer_load_b128(buf, o, 0, 0);
+          v[u][t][0] = __uint_as_float(rest >= 4 ? q[0] : rest == 3 ? q[1] : rest == 2 ? q[2] : q[3]);
+          v[u][t][1] = __uint_as_float(rest >= 4 ? q[1] : rest == 3 ? q[2] : rest == 2 ? q[3] : 0u);
+          v[u][t][2] = __uint_as_float(rest >= 4 ? q[2] : rest == 3 ? q[3] : 0u);
+          v[u][t][3] = __uint_as_float(rest >= 4 ? q[3] : 0u);
         } else {
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
@@ -97,7 +112,7 @@ template <> struct Mfma<16> {
 };
 
 // A wavefront's share of a tile's product: the contraction elements [kbeg, kend), added to acc.
-template <int MS, int TM, int TN, bool AKC, bool BKC, bool VEC, int G>
+template <int MS, int TM, int TN, bool AKC, bool BKC, int VEC, int G>
 __device__ __forceinline__ void slice_product(typename Mfma<MS>::acc_t (&acc)[TM][TN], const float* __restrict__ A, int64_t lda,
                                               const float* __restrict__ B, int64_t ldb, int M, int N, int K, int m0, int n0,
                                               int kbeg, int kend, int lane) {
@@ -147,7 +162,9 @@ __device__ __forceinline__ void slice_product(typename Mfma<MS>::acc_t (&acc)[TM
 // blockIdx.z selects the contraction slice [z * kslab, (z + 1) * kslab); slice z writes its partial product
 // to slab z of C (the consumer adds the slabs in order), the bias goes to slab 0.  Wavefront w of a
 // workgroup takes the elements [w * kwave, (w + 1) * kwave) of the slice (kwave and kslab multiples of a group).
-template <int MS, int TM, int TN, int NW, bool AKC, bool BKC, bool VEC>
+// GELU: the epilogue's activation is GELU instead of ReLU (in a kernel of its own: its registers would cost the others a
+// workgroup per compute unit, 100 x 1000 x 784 in a step 8.8 -> 11 us).
+template <int MS, int TM, int TN, int NW, bool AKC, bool BKC, int VEC, bool GELU>
 __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __restrict__ A, int64_t lda,
                                                                 const float* __restrict__ B, int64_t ldb,
                                                                 int M, int N, int K, int kslab, int kwave,
@@ -199,7 +216,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
     const int m = min(mm[p], M - 1), n = min(nn[p], N - 1);
     add[p] = (ep.bias && first_slice) ? ep.bias[n] : 0.f;
     if (ep.R) add[p] = fmaf(ep.beta, ep.R[(int64_t)m * ep.ldr + n], add[p]);
-    gate[p] = ep.gate ? ep.gate[(int64_t)m * ep.ldg + n] : 1.f;
+    gate[p] = ep.gate ? ep.gate[(int64_t)m * ep.ldg + n] : 0.f;
   }
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
@@ -214,8 +231,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
       sum = acc[p / R / TN][p / R % TN][p % R];            // (element e of the tile is this lane's p-th)
     }
     const float v = fmaf(ep.alpha, sum, add[p]);
-    C[(int64_t)mm[p] * ep.ldc + nn[p]] = gate[p] > 0.f ? v : 0.f;
-    if (ep.relu) ep.relu[(int64_t)mm[p] * ep.ldrelu + nn[p]] = fmaxf(v, 0.f);
+    C[(int64_t)mm[p] * ep.ldc + nn[p]] = !ep.gate ? v : GELU ? v * gelu_df(gate[p]) : gate[p] > 0.f ? v : 0.f;
+    if (ep.act) ep.act[(int64_t)mm[p] * ep.ldact + nn[p]] = GELU ? gelu_f(v) : fmaxf(v, 0.f);
   }
 }
 
@@ -227,7 +244,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_mfma_kernel(const float* __r
 // The arithmetic is that of bn_relu_fwd_kernel / bn_relu_bwd_kernel.
 constexpr int BN_NW = 8;
 
-template <int TM, bool BKC, bool VEC, bool BWD>
+template <int TM, bool BKC, int VEC, bool BWD>
 __global__ __launch_bounds__(BN_NW * 64) void gemm_f32_bn_kernel(const float* __restrict__ A, int64_t lda,
                                                                  const float* __restrict__ B, int64_t ldb, int R, int N,
                                                                  int K, int kwave, F32BnArgs f) {
@@ -333,7 +350,7 @@ __global__ __launch_bounds__(BN_NW * 64) void gemm_f32_bn_kernel(const float* __
 // ---- the last layer's product with the loss -------------------------------------------------------------
 // Few classes (TN tiles of 16): a workgroup takes all logits of 16 rows, so the softmax cross-entropy needs no launch of its
 // own.  The logits pass through LDS; 32 lanes take a row.  What is computed is what softmax_xent_kernel computes.
-template <int TN, bool VEC>
+template <int TN, int VEC>
 __global__ __launch_bounds__(512) void gemm_f32_xent_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ B,
                                                             int64_t ldb, int R, int N, int K, int kwave,
                                                             const float* __restrict__ bias, const int32_t* __restrict__ labels,
@@ -463,7 +480,7 @@ __global__ __launch_bounds__(256) void gemm_f32_jobs_kernel(F32Jobs jobs, const 
   typename MF::acc_t acc[1][1];
 #pragma unroll
   for (int r = 0; r < R; ++r) acc[0][0][r] = 0.f;
-  slice_product<MS, 1, 1, false, false, false, GU>(acc, job.A, job.lda, job.B, job.ldb, job.M, N, K, m0, n0, wave * jobs.kwave,
+  slice_product<MS, 1, 1, false, false, 0, GU>(acc, job.A, job.lda, job.B, job.ldb, job.M, N, K, m0, n0, wave * jobs.kwave,
                                                    min(K, (wave + 1) * jobs.kwave), lane);
 #pragma unroll
   for (int r = 0; r < R; ++r) part[wave * E + r * 64 + lane] = acc[0][0][r];
@@ -549,8 +566,9 @@ __global__ __launch_bounds__(TILED_NT) void gemm_f32_tiled_kernel(const float* _
       float add = (ep.bias && first_slice) ? ep.bias[n] : 0.f;
       if (ep.R) add = fmaf(ep.beta, ep.R[(int64_t)m * ep.ldr + n], add);
       const float v = fmaf(ep.alpha, acc[i][j], add);
-      C[(int64_t)m * ep.ldc + n] = !ep.gate || ep.gate[(int64_t)m * ep.ldg + n] > 0.f ? v : 0.f;
-      if (ep.relu) ep.relu[(int64_t)m * ep.ldrelu + n] = fmaxf(v, 0.f);
+      const float gate = ep.gate ? ep.gate[(int64_t)m * ep.ldg + n] : 0.f;
+      C[(int64_t)m * ep.ldc + n] = !ep.gate ? v : ep.gelu ? v * gelu_df(gate) : gate > 0.f ? v : 0.f;
+      if (ep.act) ep.act[(int64_t)m * ep.ldact + n] = ep.gelu ? gelu_f(v) : fmaxf(v, 0.f);
     }
   }
 }
@@ -568,14 +586,22 @@ struct F32Shape {
   const float* A; int64_t lda; const float* B; int64_t ldb; int M, N, K, nsplit; int64_t slab;
 };
 
-template <int MS, int TM, int TN, int NW, bool AKC, bool BKC, bool VEC>
+template <int MS, int TM, int TN, int NW, bool AKC, bool BKC, int VEC>
 int launch_tile(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
   constexpr int GK = GU * 4 * (64 / MS);
   const int kslab = ((g.K + g.nsplit - 1) / g.nsplit + GK - 1) / GK * GK;
   const int kwave = ((kslab + NW - 1) / NW + GK - 1) / GK * GK;
   dim3 grid((g.N + MS * TN - 1) / (MS * TN), (g.M + MS * TM - 1) / (MS * TM), g.nsplit);
-  gemm_f32_mfma_kernel<MS, TM, TN, NW, AKC, BKC, VEC><<<grid, NW * 64, 0, s>>>(g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K,
-                                                                                   kslab, kwave, g.slab, ep);
+  if constexpr (AKC)                                     // (no weight gradient has an activation)
+    if (ep.gelu) {
+      gemm_f32_mfma_kernel<MS, TM, TN, NW, AKC, BKC, VEC, true><<<grid, NW * 64, 0, s>>>(g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K,
+                                                                                         kslab, kwave, g.slab, ep);
+      VF_LAUNCH_CHECK();
+      return VF_OK;
+    }
+  if (ep.gelu) return VF_EINVAL;
+  gemm_f32_mfma_kernel<MS, TM, TN, NW, AKC, BKC, VEC, false><<<grid, NW * 64, 0, s>>>(g.A, g.lda, g.B, g.ldb, g.M, g.N, g.K,
+                                                                                      kslab, kwave, g.slab, ep);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }
@@ -602,11 +628,13 @@ int launch_tile(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
 //         2048 x 2048 x 1024: 177 | 101 | 32x64/1 98   x 4096: 630 | 297 | 64/4 (32x64/1: 350)
 //         2051 x 3001 x 201: 55 | 99 | tiled      1001 x 2051 x 99: 21.6 | 19.8 | 32/4 18.9  x 513: 117 | 82 | 64/4
 //   fwd   4096 x 4096 x 255: 128 | 203 | tiled    2051 x 3001 x 255: 65 | 84 | 32x64/1 61   x 99: 35 | 34 | 32/4 32
-template <bool AKC, bool BKC, bool VEC>
+template <bool AKC, bool BKC, int VEC>
 int launch_operands(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
   auto tiles = [&](int t) { return (int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.nsplit; };
   const int K = g.K / g.nsplit;
   const int64_t t64 = tiles(64);
+  if constexpr (VEC == 2)
+    if (t64 >= 512 || tiles(32) > 1024) return launch_operands<AKC, BKC, 0>(g, ep, s);   // (what was measured above)
   if (t64 > 512) {
     constexpr bool along_k = AKC && BKC, scalar_k = !VEC && (AKC || BKC);
     const bool scalar_tiled = along_k ? (t64 >= 1536 || (K > (t64 < 1024 ? 112 : 80) && K <= (t64 < 1024 ? 256 : 640)))
@@ -663,11 +691,14 @@ int launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, in
     return launch_tiled(A, sam, sak, B, sbn, sbk, M, N, K, nsplit, slab_stride, ep, s);
   }
   auto al = [](const float* p, int64_t ld) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && (ld & 3) == 0; };
-  const bool vec = (K & 3) == 0 && (!akc || al(A, g.lda)) && (!bkc || al(B, g.ldb));
-  if (akc && bkc) return vec ? launch_operands<true, true, true>(g, ep, s) : launch_operands<true, true, false>(g, ep, s);
-  if (akc) return vec ? launch_operands<true, false, true>(g, ep, s) : launch_operands<true, false, false>(g, ep, s);
-  if (!bkc) return launch_operands<false, false, false>(g, ep, s);
-  return launch_operands<false, true, false>(g, ep, s);
+  const int vec = (K & 3) == 0 && (!akc || al(A, g.lda)) && (!bkc || al(B, g.ldb)) ? 1 : K >= kUnalignedK ? 2 : 0;
+#define VF_F32_OPS(A_, B_) \
+  return vec == 1 ? launch_operands<A_, B_, 1>(g, ep, s) : vec == 2 ? launch_operands<A_, B_, 2>(g, ep, s) : launch_operands<A_, B_, 0>(g, ep, s)
+  if (akc && bkc) VF_F32_OPS(true, true);
+  if (akc) VF_F32_OPS(true, false);
+#undef VF_F32_OPS
+  if (!bkc) return launch_operands<false, false, 0>(g, ep, s);
+  return launch_operands<false, true, 0>(g, ep, s);
 }
 
 // What a workgroup's loads reach in 32-bit byte offsets: 64 (128) rows of an operand contiguous along k, or the whole
@@ -691,13 +722,13 @@ int launch_gemm_f32_bn(const float* A, int64_t lda, const float* B, int64_t ldb,
       (backward && (!f.gout_g.dst || !f.gout_b.dst)) || !f32_bn_takes(R, N, K, lda, ldb, backward))
     return VF_EINVAL;
   auto al = [](const float* p, int64_t ld) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && (ld & 3) == 0; };
-  const bool vec = (K & 3) == 0 && al(A, lda) && (!backward || al(B, ldb));
+  const int vec = (K & 3) == 0 && al(A, lda) && (!backward || al(B, ldb)) ? 1 : K >= kUnalignedK ? 2 : 0;
   const int kwave = ((K + BN_NW - 1) / BN_NW + 31) / 32 * 32;
   const int grid = (N + 15) / 16;
 #define VF_F32BN2(TM, VEC)                                                                                              \
   if (backward) gemm_f32_bn_kernel<TM, true, VEC, true><<<grid, BN_NW * 64, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, f); \
   else gemm_f32_bn_kernel<TM, false, VEC, false><<<grid, BN_NW * 64, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, f)
-#define VF_F32BN(TM) if (vec) { VF_F32BN2(TM, true); } else { VF_F32BN2(TM, false); }
+#define VF_F32BN(TM) if (vec == 1) { VF_F32BN2(TM, 1); } else if (vec) { VF_F32BN2(TM, 2); } else { VF_F32BN2(TM, 0); }
   switch ((R + 31) / 32) {
     case 1: VF_F32BN(2) break;
     case 2: VF_F32BN(4) break;
@@ -719,13 +750,14 @@ bool f32_xent_takes(int R, int N, int K, int64_t lda, int64_t ldb) {
 int launch_gemm_f32_xent(const float* A, int64_t lda, const float* B, int64_t ldb, int R, int N, int K, const float* bias,
                          const int32_t* labels, float* z, int64_t ldz, float* dz, int64_t lddz, float* rowloss, hipStream_t s) {
   if (!A || !B || !bias || !labels || !z || !dz || !rowloss || !f32_xent_takes(R, N, K, lda, ldb)) return VF_EINVAL;
-  const bool vec = (K & 3) == 0 && (lda & 3) == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0;
+  const int vec = (K & 3) == 0 && (lda & 3) == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0 ? 1 : K >= kUnalignedK ? 2 : 0;
   const int tn = (N + 15) / 16, gk = (tn <= 2 ? 4 : 2) * 16;
   const int kwave = ((K + 7) / 8 + gk - 1) / gk * gk;
   const int grid = (R + 15) / 16;
 #define VF_XENT(TN)                                                                                                        \
-  if (vec) gemm_f32_xent_kernel<TN, true><<<grid, 512, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, bias, labels, z, ldz, dz, lddz, rowloss); \
-  else gemm_f32_xent_kernel<TN, false><<<grid, 512, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, bias, labels, z, ldz, dz, lddz, rowloss)
+  if (vec == 1) gemm_f32_xent_kernel<TN, 1><<<grid, 512, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, bias, labels, z, ldz, dz, lddz, rowloss); \
+  else if (vec) gemm_f32_xent_kernel<TN, 2><<<grid, 512, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, bias, labels, z, ldz, dz, lddz, rowloss); \
+  else gemm_f32_xent_kernel<TN, 0><<<grid, 512, 0, s>>>(A, lda, B, ldb, R, N, K, kwave, bias, labels, z, ldz, dz, lddz, rowloss)
   if (tn <= 1) { VF_XENT(1); }
   else if (tn <= 2) { VF_XENT(2); }
   else if (tn <= 4) { VF_XENT(4); }

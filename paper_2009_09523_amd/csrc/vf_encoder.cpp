@@ -239,8 +239,8 @@ class Encoder final : public Model {
       VF_TRY(lin_fwd(c, "gemm_fwd", B.o, P, X.om, d_, R, X.hmid, d_, false, X.hin));
       VF_KS(c, st, "layernorm_fwd", launch_layernorm_fwd(X.hmid, d_, nullptr, R, d_, P + B.ln2_g, P + B.ln2_b, bf16_,
                                                     cfg_.ln_eps, X.f, d_, bf16_, X.mean2, X.rstd2, st));
-      VF_TRY(lin_fwd(c, "gemm_fwd", B.w1, P, X.f, d_, R, X.u, f_, false, nullptr));
-      VF_KS(c, st, "gelu_fwd", launch_gelu_fwd(X.u, X.g, bf16_, (int64_t)R * f_, st));
+      VF_TRY(lin_fwd(c, "gemm_fwd", B.w1, P, X.f, d_, R, X.u, f_, false, nullptr, bf16_ ? nullptr : static_cast<float*>(X.g)));
+      if (bf16_) VF_KS(c, st, "gelu_fwd", launch_gelu_fwd(X.u, X.g, bf16_, (int64_t)R * f_, st));   // (fp32: in the product's epilogue)
       VF_TRY(lin_fwd(c, "gemm_fwd", B.w2, P, X.g, f_, R, hnext, d_, false, X.hmid));
     }
     VF_KS(c, st, "layernorm_fwd", launch_layernorm_fwd(H.hlast, d_, H.rowidx, Rm, d_, P + lnf_g_, P + lnf_b_, bf16_,
@@ -278,10 +278,15 @@ class Encoder final : public Model {
 
     fin_.count = 0; fin_.used = 0;   // nothing is left over from a pass that ended in an error
     // ---- backward: output head -----------------------------------------------------------
-    VF_KS(c, st, "colsum", launch_colsum_rows(H.dlogits, ldV_, bf16_, Rm, V_, red_, c.gout(out_.b_off, w, i), st, &fin_));
+    F32Jobs head{};
+    head.rows = Rm;
+    if (!bf16_) add_jobs(c, &head, out_, H.rows, H.dlogits, w, i, ldV_);
+    const bool head_jobs = !bf16_ && f32_jobs_take(head);
+    if (head_jobs) VF_KS(c, st, "gemm_head_wgrad", launch_gemm_f32_jobs(head, nullptr, LossNodes{}, nullptr, nullptr, st));
+    else VF_KS(c, st, "colsum", launch_colsum_rows(H.dlogits, ldV_, bf16_, Rm, V_, red_, c.gout(out_.b_off, w, i), st, &fin_));
     const bool defer = side_beside_forward(c);
     sA_ = tA_; sB_ = tB_;
-    VF_TRY(lin_bwd_w(c, "gemm_head_wgrad", out_, H.rows, d_, H.dlogits, ldV_, Rm, c.gout(out_.w_off, w, i)));
+    if (!head_jobs) VF_TRY(lin_bwd_w(c, "gemm_head_wgrad", out_, H.rows, d_, H.dlogits, ldV_, Rm, c.gout(out_.w_off, w, i)));
     int osplit = 1;
     VF_TRY(lin_bwd_x(c, "gemm_head_dgrad", out_, P, H.dlogits, ldV_, Rm, drows_, d_, &osplit));
     const int64_t oslab = (int64_t)Rm * d_;
@@ -297,21 +302,29 @@ class Encoder final : public Model {
       // FFN
       const void* dh_op = dh_buf_;
       bool dyT = false;
-      VF_TRY(prepare_dy(c, dh_buf_, true, d_, R, d_, c.gout(B.w2.b_off, w, i), defer ? X.dyT[0] : nullptr, &dh_op, &dyT));
-      if (!(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.w2, X.g, f_, dh_op, d_, R, c.gout(B.w2.w_off, w, i), dyT));
-      VF_TRY(lin_bwd_x(c, "gemm_dgrad", B.w2, P, dh_op, d_, R, tmp32_, f_, nullptr));
-      VF_KS(c, st, "gelu_bwd", launch_gelu_bwd(tmp32_, X.u, du_, bf16_, (int64_t)R * f_, st));
+      // fp32: a block's weight and bias gradients go out together, while all four output gradients are there
+      F32Jobs jobs{};
+      jobs.rows = R;
+      if (!bf16_) {
+        add_jobs(c, &jobs, B.w2, X.g, dh_buf_, w, i); add_jobs(c, &jobs, B.w1, X.f, du_, w, i);
+        add_jobs(c, &jobs, B.o, X.om, dmid_, w, i); add_jobs(c, &jobs, B.qkv, X.a, dqkv_, w, i);
+      }
+      const bool together = !bf16_ && f32_jobs_take(jobs);
+      if (!together) VF_TRY(prepare_dy(c, dh_buf_, true, d_, R, d_, c.gout(B.w2.b_off, w, i), defer ? X.dyT[0] : nullptr, &dh_op, &dyT));
+      if (!together && !(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.w2, X.g, f_, dh_op, d_, R, c.gout(B.w2.w_off, w, i), dyT));
+      VF_TRY(lin_bwd_x(c, "gemm_dgrad", B.w2, P, dh_op, d_, R, bf16_ ? tmp32_ : static_cast<float*>(du_), f_, nullptr, bf16_ ? nullptr : X.u));
+      if (bf16_) VF_KS(c, st, "gelu_bwd", launch_gelu_bwd(tmp32_, X.u, du_, bf16_, (int64_t)R * f_, st));
       const void* du_op = du_;
-      VF_TRY(prepare_dy(c, du_, !bf16_, f_, R, f_, c.gout(B.w1.b_off, w, i), defer ? X.dyT[1] : nullptr, &du_op, &dyT));
-      if (!(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.w1, X.f, d_, du_, f_, R, c.gout(B.w1.w_off, w, i), dyT));
+      if (!together) VF_TRY(prepare_dy(c, du_, !bf16_, f_, R, f_, c.gout(B.w1.b_off, w, i), defer ? X.dyT[1] : nullptr, &du_op, &dyT));
+      if (!together && !(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.w1, X.f, d_, du_, f_, R, c.gout(B.w1.w_off, w, i), dyT));
       VF_TRY(lin_bwd_x(c, "gemm_dgrad", B.w1, P, du_, f_, R, tmp32_, d_, nullptr));
       VF_KS(c, st, "layernorm_bwd", launch_layernorm_bwd(tmp32_, 1, 0, d_, X.hmid, d_, nullptr, R, d_, P + B.ln2_g,
                                                     bf16_, X.mean2, X.rstd2, dh_buf_, dmid_, d_, red_,
                                                     c.gout(B.ln2_g, w, i), c.gout(B.ln2_b, w, i), st, &fin_));
       // attention
       const void* dmid_op = dmid_;
-      VF_TRY(prepare_dy(c, dmid_, true, d_, R, d_, c.gout(B.o.b_off, w, i), defer ? X.dyT[2] : nullptr, &dmid_op, &dyT));
-      if (!(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.o, X.om, d_, dmid_op, d_, R, c.gout(B.o.w_off, w, i), dyT));
+      if (!together) VF_TRY(prepare_dy(c, dmid_, true, d_, R, d_, c.gout(B.o.b_off, w, i), defer ? X.dyT[2] : nullptr, &dmid_op, &dyT));
+      if (!together && !(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.o, X.om, d_, dmid_op, d_, R, c.gout(B.o.w_off, w, i), dyT));
       VF_TRY(lin_bwd_x(c, "gemm_dgrad", B.o, P, dmid_op, d_, R, tmp32_, d_, nullptr));   // d(om), fp32
       // dP = dO V^T ; dV = P^T dO ; dS = P (dP - rowsum(dP P)) ; dQ = dS K / sqrt(dh) ; dK = dS^T Q / sqrt(dh)
       if (mfma_attn_) {
@@ -330,8 +343,9 @@ class Encoder final : public Model {
                                           T_, dh_, T_, heads, nh_, scale, st));
       }
       const void* dqkv_op = dqkv_;
-      VF_TRY(prepare_dy(c, dqkv_, !bf16_, 3 * d_, R, 3 * d_, c.gout(B.qkv.b_off, w, i), defer ? X.dyT[3] : nullptr, &dqkv_op, &dyT));
-      if (!(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.qkv, X.a, d_, dqkv_, 3 * d_, R, c.gout(B.qkv.w_off, w, i), dyT));
+      if (!together) VF_TRY(prepare_dy(c, dqkv_, !bf16_, 3 * d_, R, 3 * d_, c.gout(B.qkv.b_off, w, i), defer ? X.dyT[3] : nullptr, &dqkv_op, &dyT));
+      if (!together && !(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.qkv, X.a, d_, dqkv_, 3 * d_, R, c.gout(B.qkv.w_off, w, i), dyT));
+      if (together) VF_KS(c, st, "gemm_wgrad", launch_gemm_f32_jobs(jobs, nullptr, LossNodes{}, nullptr, nullptr, st));
       VF_TRY(lin_bwd_x(c, "gemm_dgrad", B.qkv, P, dqkv_, 3 * d_, R, tmp32_, d_, nullptr));
       VF_KS(c, st, "layernorm_bwd", launch_layernorm_bwd(tmp32_, 1, 0, d_, X.hin, d_, nullptr, R, d_, P + B.ln1_g,
                                                     bf16_, X.mean1, X.rstd1, dmid_, dh_buf_, d_, red_,
@@ -348,6 +362,13 @@ class Encoder final : public Model {
   }
 
  private:
+  // The weight and bias gradient of an fp32 Linear layer with input `in` and output gradient dy (row pitch lddy, 0: N).
+  void add_jobs(const Ctx& c, F32Jobs* jobs, const Lin& L, const void* in, const void* dy, float w, int i, int64_t lddy = 0) const {
+    const float* g = static_cast<const float*>(dy);
+    const int64_t ld = lddy ? lddy : L.N;
+    jobs->job[jobs->count++] = {static_cast<const float*>(in), L.K, g, ld, c.gout(L.w_off, w, i), L.K, L.N};
+    jobs->job[jobs->count++] = {nullptr, 0, g, ld, c.gout(L.b_off, w, i), 0, L.N};
+  }
   // ---- operand views for the batched attention products (batch = sequence * heads + head) ------
   const void* at(const void* p, int64_t elems, bool is16) const {
     return static_cast<const char*>(p) + elems * (is16 ? 2 : 4);
@@ -376,8 +397,9 @@ class Encoder final : public Model {
 
   // out[R, N] = in[R, K] W + bias (+ residual); out is T (out_act) or fp32
   int lin_fwd(Ctx& c, const char* tag, const Lin& L, const float* P, const void* in, int64_t ldin, int R,
-              void* out, int64_t ldo, bool out_act, const float* residual) {
+              void* out, int64_t ldo, bool out_act, const float* residual, float* gelu_out = nullptr) {
     Epilogue ep;
+    if (gelu_out) { ep.gelu = 1; ep.act = gelu_out; ep.ldact = ldo; }
     ep.C = out; ep.ldc = ldo;
     ep.c_is_bf16 = out_act && bf16_;
     ep.bias = P + L.b_off; ep.bias_round_bf16 = bf16_;
@@ -502,8 +524,9 @@ class Encoder final : public Model {
 
   // dx[R, K] (fp32) = dy W^T.  With `split` the product may arrive as partial slabs.
   int lin_bwd_x(Ctx& c, const char* tag, const Lin& L, const float* P, const void* dy, int64_t lddy, int R,
-                float* dx, int64_t lddx, int* split) {
+                float* dx, int64_t lddx, int* split, const float* gelu_in = nullptr) {
     Epilogue ep;
+    if (gelu_in) { ep.gelu = 1; ep.gate = gelu_in; ep.ldg = lddx; }
     ep.C = dx; ep.ldc = lddx;
     int ns = 1;
     if (split) {

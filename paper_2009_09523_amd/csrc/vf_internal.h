@@ -63,11 +63,12 @@ struct Epilogue {
   int64_t ldc = 0;
   int c_is_bf16 = 0;             // store C as bf16 (RNE) instead of fp32
   int stream_c = 0;              // store C with the non-temporal hint (it is not kept in the L2s)
-  // fp32 products only: C is 0 where gate[m, n] <= 0 (ReLU backward); relu[m, n] = max(C, 0) beside C (ReLU forward)
+  // fp32 products only, ReLU or (gelu != 0) GELU: act[m, n] = f(C) beside C (forward); C times f'(gate[m, n]) (backward)
+  int gelu = 0;
   const float* gate = nullptr;
   int64_t ldg = 0;
-  float* relu = nullptr;
-  int64_t ldrelu = 0;
+  float* act = nullptr;
+  int64_t ldact = 0;
 };
 
 // BatchNorm + ReLU backward of whole nodes of 128 rows, taken inside the epilogue of the product that

@@ -274,7 +274,7 @@ class Mlp final : public Model {
       Epilogue ep;
       ep.C = zsrc; ep.ldc = L.ld;
       const bool relu = relu_in_product(L, split);
-      if (relu) { ep.relu = static_cast<float*>(L.a[q]); ep.ldrelu = L.ld; }
+      if (relu) { ep.act = static_cast<float*>(L.a[q]); ep.ldact = L.ld; }
       if (L.has_bias) { ep.bias = P + L.b_off; ep.bias_round_bf16 = bf16_; }
       if (bf16_)
         VF_KS(c, st, "gemm_fwd", launch_gemm_bf16(static_cast<const bf16_t*>(in), ldin, L.wtr, L.ldt, b, L.N, L.K,
