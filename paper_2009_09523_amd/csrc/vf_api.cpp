@@ -89,9 +89,11 @@ void release_streams(Ctx& c) {
                        &c.side_done[0], &c.side_done[1], &c.prep_done};
   for (hipEvent_t* e : evs)
     if (*e) { (void)hipEventDestroy(*e); *e = nullptr; }
-  for (hipEvent_t e : c.range_done)
-    if (e) (void)hipEventDestroy(e);
-  c.range_done.clear();
+  for (std::vector<hipEvent_t>* list : {&c.range_done, &c.piece_events}) {
+    for (hipEvent_t e : *list)
+      if (e) (void)hipEventDestroy(e);
+    list->clear();
+  }
   if (c.side) { (void)hipStreamDestroy(c.side); c.side = nullptr; }
 }
 
@@ -151,7 +153,10 @@ void drop_graph(Ctx& c) {
 // 3 = side(window i).  Each runs on one stream.
 int enqueue_part(Ctx& c, const StepArgs& a, int part, int idx, hipStream_t st) {
   if (part == 0) return c.model->prepare(c, a.params, st);
-  if (part == 1) return c.model->run_node_fwd(c, a, idx, st);
+  if (part == 1) {
+    VF_TRY(c.model->run_node_fwd(c, a, idx, st));
+    return c.model->finish_forward(c, a, idx, st);
+  }
   if (part == 2) return c.model->run_node_bwd(c, a, idx, st);
   const int i0 = idx * c.window;
   return c.model->run_nodes_side(c, a, i0, std::min(c.window, a.V - i0), st);
@@ -264,6 +269,16 @@ int enqueue_nodes(Ctx& c, const StepArgs& a, bool use_graph) {
   c.marking = !use_graph && !c.ranges.empty();
   const int nwin = (a.V + c.window - 1) / c.window;
   const int reach = std::max(1, std::min(2, c.copies() / c.window));
+  const bool pieces = !use_graph && c.fused && !c.piece_events.empty() && c.model->side_early(a);
+  c.early_unit = -1;
+  c.early = false;
+  // A forward part, the event that its backward part waits for, and what nothing waits for.
+  auto forward = [&](int i, int q) -> int {
+    if (use_graph) VF_TRY(run_part(c, a, true, 1, i, c.stream));
+    else VF_TRY(c.model->run_node_fwd(c, a, i, c.stream));
+    VF_HIP(hipEventRecord(c.fwd_done[q], c.stream));
+    return use_graph ? VF_OK : c.model->finish_forward(c, a, i, c.stream);
+  };
   // Side part i on the forward stream, behind forward part i+1: it reads tensor set i & 1, which
   // forward part i+2 -- enqueued after it on the same stream -- writes next, and what backward
   // part i left for it, which backward part i+2 overwrites only after forward part i+2.
@@ -272,9 +287,9 @@ int enqueue_nodes(Ctx& c, const StepArgs& a, bool use_graph) {
     for (int i = 0; i < a.V; ++i) {
       const int q = c.aset(i);
       if (i >= 2) VF_HIP(hipStreamWaitEvent(c.stream, c.bwd_done[q], 0));
-      VF_TRY(run_part(c, a, use_graph, 1, i, c.stream));
-      VF_HIP(hipEventRecord(c.fwd_done[q], c.stream));
+      VF_TRY(forward(i, q));
       VF_HIP(hipStreamWaitEvent(c.side, c.fwd_done[q], 0));
+      if (pieces && i == a.V - 1) c.early_unit = i;
       VF_TRY(run_part(c, a, use_graph, 2, i, c.side));
       VF_HIP(hipEventRecord(c.bwd_done[q], c.side));
       if (i >= 1) {
@@ -282,10 +297,12 @@ int enqueue_nodes(Ctx& c, const StepArgs& a, bool use_graph) {
         VF_TRY(run_part(c, a, use_graph, 3, i - 1, c.stream));
       }
     }
-    // join: the last backward part ends the second stream's work
+    // join: the last backward part ends the second stream's work (the last side part goes beside it if it can)
     c.last_side = c.bwd_done[c.aset(a.V - 1)];
-    VF_HIP(hipStreamWaitEvent(c.stream, c.last_side, 0));
+    if (c.early_unit < 0) VF_HIP(hipStreamWaitEvent(c.stream, c.last_side, 0));
     VF_TRY(run_part(c, a, use_graph, 3, a.V - 1, c.stream));
+    if (c.early_unit >= 0) VF_HIP(hipStreamWaitEvent(c.stream, c.last_side, 0));
+    c.early_unit = -1;
     return VF_OK;
   }
   for (int w = 0; w < nwin; ++w) {
@@ -297,11 +314,21 @@ int enqueue_nodes(Ctx& c, const StepArgs& a, bool use_graph) {
       const int q = c.aset(i);
       // the tensors of set q were last read by bwd(i-2)
       if (i >= 2) VF_HIP(hipStreamWaitEvent(c.stream, c.bwd_done[q], 0));
-      VF_TRY(run_part(c, a, use_graph, 1, i, c.stream));
-      VF_HIP(hipEventRecord(c.fwd_done[q], c.stream));
+      VF_TRY(forward(i, q));
       VF_HIP(hipStreamWaitEvent(c.side, c.fwd_done[q], 0));
+      if (pieces && i == a.V - 1) c.early_unit = i;
       VF_TRY(run_part(c, a, use_graph, 2, i, c.side));
       VF_HIP(hipEventRecord(c.bwd_done[q], c.side));
+    }
+    if (c.early_unit >= 0) {
+      // behind the side part of the window before (one gradient buffer, windows in order) and the backward parts of the
+      // window's other units
+      if (w > 0) VF_HIP(hipStreamWaitEvent(c.stream, c.side_done[(w - 1) & 1], 0));
+      if (i1 - i0 > 1) VF_HIP(hipStreamWaitEvent(c.stream, c.bwd_done[c.aset(a.V - 2)], 0));
+      VF_TRY(run_part(c, a, false, 3, w, c.stream));
+      c.early_unit = -1;
+      c.early = true;
+      return VF_OK;
     }
     // The window's weight gradients follow its backward parts on the second stream (a staged
     // node's gradient lives in the one staging vector that the next backward part writes again).
@@ -315,28 +342,35 @@ int enqueue_nodes(Ctx& c, const StepArgs& a, bool use_graph) {
   return VF_OK;
 }
 
-int update_stretch(Ctx& c, float* params, int64_t off, int64_t n) {
+int update_stretch(Ctx& c, float* params, int64_t off, int64_t n, hipStream_t st) {
   const vf_config& f = c.cfg;
   if (f.optimizer == VF_SGDM) {
-    VF_K(c, "optimizer", launch_sgdm(params + off, c.opt0 + off, c.gbuf + off, f.lr, f.momentum, n, c.stream));
+    VF_KS(c, st, "optimizer", launch_sgdm(params + off, c.opt0 + off, c.gbuf + off, f.lr, f.momentum, n, st));
     return VF_OK;
   }
   const double t = (double)(c.steps + 1);
   const float inv_c1 = (float)(1.0 / (1.0 - std::pow((double)f.beta1, t)));
   const float inv_c2 = (float)(1.0 / (1.0 - std::pow((double)f.beta2, t)));
-  VF_K(c, "optimizer", launch_adam(params + off, c.opt0 + off, c.opt1 + off, c.gbuf + off, f.lr, f.beta1, f.beta2,
-                                   f.adam_eps, inv_c1, inv_c2, n, c.stream));
+  VF_KS(c, st, "optimizer", launch_adam(params + off, c.opt0 + off, c.opt1 + off, c.gbuf + off, f.lr, f.beta1, f.beta2,
+                                   f.adam_eps, inv_c1, inv_c2, n, st));
   return VF_OK;
 }
 
 // The one update of a step (Section 3.2 step 5): elementwise, so it may go stretch by stretch,
 // each as soon as its gradient is complete.
 int enqueue_update(Ctx& c, float* params) {
-  if (!c.marking) return update_stretch(c, params, 0, c.P);
+  if (!c.marking) return update_stretch(c, params, 0, c.P, c.stream);
   c.marking = false;
   for (size_t k = 0; k < c.ranges.size(); ++k) {
-    VF_HIP(hipStreamWaitEvent(c.stream, c.range_done[k], 0));
-    VF_TRY(update_stretch(c, params, c.ranges[k].off, c.ranges[k].n));
+    // (early: the weight gradients still to come are on the first stream, and the backward part, which reads the
+    // parameters of the normalisations, is done on the second)
+    hipStream_t st = c.early ? c.side : c.stream;
+    VF_HIP(hipStreamWaitEvent(st, c.range_done[k], 0));
+    VF_TRY(update_stretch(c, params, c.ranges[k].off, c.ranges[k].n, st));
+  }
+  if (c.early) {
+    c.last_side = c.side_done[0];
+    VF_HIP(hipEventRecord(c.last_side, c.side));
   }
   VF_HIP(hipStreamWaitEvent(c.stream, c.last_side, 0));
   return VF_OK;
@@ -349,6 +383,18 @@ int copy_out(Ctx& c, const float* src, float* out, size_t count) {
 }
 
 }  // namespace
+
+int Ctx::piece_done(int unit, int k, hipStream_t st) {
+  if (unit != early_unit || k < 0 || k >= (int)piece_events.size()) return VF_OK;
+  VF_HIP(hipEventRecord(piece_events[k], st));
+  return VF_OK;
+}
+
+int Ctx::piece_wait(int unit, int k, hipStream_t st) {
+  if (unit != early_unit || k < 0 || k >= (int)piece_events.size()) return VF_OK;
+  VF_HIP(hipStreamWaitEvent(st, piece_events[k], 0));
+  return VF_OK;
+}
 
 int Ctx::mark_range(int k, hipStream_t st) {
   if (!marking || k < 0 || k >= (int)range_done.size()) return VF_OK;
@@ -424,8 +470,10 @@ int vf_init(const vf_config* cfg, vf_ctx** out) {
       if (e == hipSuccess) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
     c.model->update_ranges(&c.ranges);
     c.range_done.assign(c.ranges.size(), nullptr);
-    for (hipEvent_t& ev : c.range_done)
-      if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    c.piece_events.assign((size_t)c.model->pieces(), nullptr);
+    for (std::vector<hipEvent_t>* list : {&c.range_done, &c.piece_events})
+      for (hipEvent_t& ev : *list)
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (e != hipSuccess) {
       set_last_error("side stream set-up", e, __FILE__, __LINE__);
       release_streams(c);

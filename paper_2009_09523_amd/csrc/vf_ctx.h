@@ -114,6 +114,15 @@ class Model {
   // in which the last side part of a step completes their gradients; the model calls
   // Ctx::mark_range(k) at that point.  Empty: the gradient is complete when the side part ends.
   virtual void update_ranges(std::vector<UpdateRange>* out) const { out->clear(); }
+  // Two streams, launches made one by one, fused fold: nothing is left for the forward stream while the last unit's
+  // backward part runs, so the last window's side part goes there, piece by piece: the backward part of unit
+  // c.early_unit calls c.piece_done(k) when what piece k of the side part reads is written, the side part
+  // c.piece_wait(k) before it.  The number of pieces; 0: the side part follows the backward part.
+  virtual int pieces() const { return 0; }
+  // Whether that pays for this step.
+  virtual bool side_early(const StepArgs&) const { return true; }
+  // What of a unit's forward part nothing waits for (the step's loss bookkeeping), enqueued behind it.
+  virtual int finish_forward(Ctx&, const StepArgs&, int, hipStream_t) { return VF_OK; }
   // Largest fold window the side part can take (it must keep that many nodes' operands).
   virtual int max_window() const { return 1; }
   // How many consecutive nodes the passes take as one unit at most, given that one of them has `rows` rows (1: such a
@@ -236,6 +245,12 @@ struct Ctx {
   bool marking = false;          // this step's side part records range_done
   hipEvent_t last_side = nullptr;   // the event that ends the second stream's work of this step
   int mark_range(int k, hipStream_t st);
+
+  int early_unit = -1;           // the last unit, while its backward part and the last side part are enqueued beside each other
+  bool early = false;            // this step's update goes onto the second stream, behind the last backward part
+  std::vector<hipEvent_t> piece_events;
+  int piece_done(int unit, int k, hipStream_t st);
+  int piece_wait(int unit, int k, hipStream_t st);
 };
 
 // Debugging aid: with VF_SYNC_EACH set in the environment the host waits after every launch

@@ -185,6 +185,11 @@ class Encoder final : public Model {
   // backward part (the longer of the two parts) but as its side part, which the step enqueues on
   // the forward stream behind the next node's forward part.  The backward part leaves them the
   // transposed output gradients; the layers' inputs are still in the node's tensor set.
+  int pieces() const override { return supports_overlap() ? (int)blocks_.size() : 0; }   // one per block
+  // (the last unit's weight gradients beside its backward part, block by block: 3 x 8 sequences of 100, two blocks 512 wide
+  // 913 -> 822 us; 8 x 8 of 64, four blocks 256 wide 1390 -> 1222; 4 x 16 of 128, two blocks 768 wide 2759 -> 2670; one block
+  // only has its own first half of backward to run beside: 757 -> 800)
+  bool side_early(const StepArgs&) const override { return blocks_.size() > 1; }
   bool side_beside_forward(const Ctx& c) const override { return sets_ == 2 && c.overlap && c.fused; }
 
   int run_nodes_side(Ctx& c, const StepArgs& s, int i0, int count, hipStream_t st) override {
@@ -345,6 +350,7 @@ class Encoder final : public Model {
       const void* dqkv_op = dqkv_;
       if (!together) VF_TRY(prepare_dy(c, dqkv_, !bf16_, 3 * d_, R, 3 * d_, c.gout(B.qkv.b_off, w, i), defer ? X.dyT[3] : nullptr, &dqkv_op, &dyT));
       if (!together && !(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.qkv, X.a, d_, dqkv_, 3 * d_, R, c.gout(B.qkv.w_off, w, i), dyT));
+      VF_TRY(c.piece_done(i, l, st));                   // (the block's four output gradients are there)
       if (together) VF_KS(c, st, "gemm_wgrad", launch_gemm_f32_jobs(jobs, nullptr, LossNodes{}, nullptr, nullptr, st));
       VF_TRY(lin_bwd_x(c, "gemm_dgrad", B.qkv, P, dqkv_, 3 * d_, R, tmp32_, d_, nullptr));
       VF_KS(c, st, "layernorm_bwd", launch_layernorm_bwd(tmp32_, 1, 0, d_, X.hin, d_, nullptr, R, d_, P + B.ln1_g,
@@ -488,6 +494,7 @@ class Encoder final : public Model {
     for (int l = (int)blocks_.size() - 1; l >= 0; --l) {
       Block& B = blocks_[l];
       BlockActs& X = B.x[q];
+      VF_TRY(c.piece_wait(i, l, st));
       const Lin* lins[4] = {&B.w2, &B.w1, &B.o, &B.qkv};
       const void* ins[4] = {X.g, X.f, X.om, X.a};
       const int64_t ldins[4] = {f_, d_, d_, d_};

@@ -209,6 +209,7 @@ class Mlp final : public Model {
 
   int run_node_main(Ctx& c, const StepArgs& s, int i, hipStream_t st) override {
     VF_TRY(run_node_fwd(c, s, i, st));
+    VF_TRY(finish_forward(c, s, i, st));
     return run_node_bwd(c, s, i, st);
   }
 
@@ -296,10 +297,25 @@ class Mlp final : public Model {
     }
     wait_casts_ = false;
     if (stats.count) VF_KS(c, st, "bn_stats_finish", launch_bn_stats_finish(stats, s.group(i), cfg_.bn_momentum, st));
-    // loss bookkeeping of the whole step after the last node's rows are in: node losses and
-    // their weighted sum (Section 5.2), in node order (fp32: with the weight gradients)
-    if (i == s.V - 1 && bf16_) return reduce_losses(c, s, st);
     return VF_OK;
+  }
+
+  // Loss bookkeeping of the whole step after the last node's rows are in: node losses and their weighted sum (Section 5.2),
+  // in node order (fp32: with the weight gradients).
+  int finish_forward(Ctx& c, const StepArgs& s, int i, hipStream_t st) override {
+    return i == s.V - 1 && bf16_ ? reduce_losses(c, s, st) : VF_OK;
+  }
+  // One per layer: its output gradient and that one's transposed copy.
+  int pieces() const override { return bf16_ ? (int)layers_.size() : 0; }
+  // Beside each other the weight gradients fill what the input-gradient products, the BatchNorm passes and their launches
+  // leave idle, and the update moves behind the backward part.  Steps, one after the other | beside each other: 8 x 128
+  // 1024-2048^3-1000 372 | 333 us, 1024-4096^3-1000 647 | 635; 32 x 128 784-1000-500-10 413 | 344; 2 x 300 1024-4096^3-1000
+  // 895 | 861.  Not with fewer rows, where the events cost more (1 x 128 1024^4-1000 172 | 181) or the products take all
+  // compute units and the update loses its company (4 x 128 1024-4096^3-1000 549 | 569), and not with so many parameters
+  // that the weight gradients fill the chip for milliseconds (2048-8192^6-1000, 64 x 128: 15.8 | 16.1 ms).
+  bool side_early(const StepArgs& s) const override {
+    const int last = s.V - 1;
+    return P_ <= ((int64_t)128 << 20) && (s.sizes[last] >= 1024 || (s.V > 1 && s.count[last] == 1 && s.sizes[last] > 128));
   }
 
   static LossNodes loss_nodes(const StepArgs& s, int first) {
@@ -361,6 +377,7 @@ class Mlp final : public Model {
           VF_KS(c, st, "gemm_dgrad_bn", launch_gemm_bf16_bn_bwd(static_cast<const bf16_t*>(dz_in), L.ld, L.wnat, L.ldn, b, L.K,
                                                              kdim(L), fa, st));
           sums.job[sums.count++] = {Pv.sums, nullptr, nullptr, nullptr, gg, gb, Pv.N};
+          VF_TRY(c.piece_done(i, l - 1, st));
           continue;
         }
       }
@@ -382,6 +399,7 @@ class Mlp final : public Model {
                                      Pv.has_bn ? P + Pv.g_off : nullptr, Pv.has_bn ? P + Pv.be_off : nullptr,
                                      bf16_, Pv.mean[q], Pv.rstd[q], Pv.dz[0], Pv.ld, bf16_, bf16_ ? Pv.dzT + pc : nullptr, ldw_,
                                      gg, gb, st, tscale(c, s, i), s.group(i), s.rows_of(i)));
+      VF_TRY(c.piece_done(i, l - 1, st));
     }
     if (sums.count) VF_KS(c, st, "bn_sums_finish", launch_bn_sums_finish(sums, s.group(i), st));
     return VF_OK;
@@ -439,6 +457,7 @@ class Mlp final : public Model {
         GradOut go = c.gout(L.w_off, w, i0);
         if (!L.hidden)
           VF_KS(c, st, "bias_grad", launch_rowsum_bf16(L.dzT + pc, ldw_, L.N, rows, c.gout(L.b_off, w, i0), st));
+        if (L.hidden) VF_TRY(c.piece_wait(i0 + count - 1, l, st));
         Epilogue ep;
         ep.C = go.dst; ep.ldc = L.N; ep.alpha = go.alpha;
         if (go.accumulate) { ep.R = go.dst; ep.ldr = L.N; ep.beta = 1.f; }
@@ -464,6 +483,7 @@ class Mlp final : public Model {
         ep.C = go.dst; ep.ldc = L.N; ep.alpha = go.alpha;
         if (go.accumulate) { ep.R = go.dst; ep.ldr = L.N; ep.beta = 1.f; }
         const bf16_t* inT = (l == 0 ? xT_ : layers_[l - 1].aT) + pc;
+        if (L.hidden) VF_TRY(c.piece_wait(i, l, st));
         VF_KS(c, st, "gemm_wgrad", launch_gemm_bf16(inT, ldw_, L.dzT + pc, ldw_, L.K, L.N, b, 1, 0, ep, st));
         if (c.fused && i == i0 + count - 1) VF_TRY(layer_done(l));
       }
@@ -484,6 +504,7 @@ class Mlp final : public Model {
           fa.K[j] = s.sizes[i0 + j];
           fa.w[j] = s.w[i0 + j];
         }
+        if (L.hidden) VF_TRY(c.piece_wait(i0 + count - 1, l, st));
         VF_KS(c, st, "gemm_wgrad", launch_gemm_bf16_fold(fa, ldw_, L.K, L.N, c.gbuf + L.w_off, L.N, st));
         VF_TRY(layer_done(l));
       }
