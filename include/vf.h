@@ -154,7 +154,8 @@ typedef struct vf_config {
                                     many units of grouped nodes) are folded into the gradient
                                     buffer in one pass over it: nodes of one size (one weight
                                     b_i/B) as ONE product over all their rows, nodes of several
-                                    sizes (multiples of 8) as one product with the weights folded
+                                    sizes (multiples of 8, or with node_group > 1 nodes of any size
+                                    that go alone) as one product with the weights folded
                                     into the transposed output gradients, other sizes -- or any
                                     with VF_FLAG_ORDERED_FOLD -- as the chain of fused
                                     multiply-adds of the node-by-node fold (bitwise its result).

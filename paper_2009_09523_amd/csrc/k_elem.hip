@@ -119,11 +119,12 @@ __global__ __launch_bounds__(256) void cast_weight_kernel(const float* __restric
   }
 }
 
-// The same transpose for every node of a fold window (blockIdx.z = node).
-__global__ __launch_bounds__(256) void transpose_nodes_kernel(NodeList nl, int64_t ldi, int64_t ldo, int C) {
+// The same transpose for every node of a fold window (blockIdx.z = node).  pad: the columns past a node's rows, up to the
+// next multiple of 8, are written as 0.
+__global__ __launch_bounds__(256) void transpose_nodes_kernel(NodeList nl, int64_t ldi, int64_t ldo, int C, int pad) {
   __shared__ bf16_t tile[TS][TS + 2];
   const int j = blockIdx.z;
-  const int R = nl.rows[j];
+  const int R = nl.rows[j], W = pad ? (R + 7) & ~7 : R;
   const int r0 = blockIdx.y * TS, c0 = blockIdx.x * TS;
   if (r0 >= R) return;
   const bf16_t* __restrict__ in = nl.src[j];
@@ -132,13 +133,13 @@ __global__ __launch_bounds__(256) void transpose_nodes_kernel(NodeList nl, int64
 #pragma unroll
   for (int i = 0; i < TS; i += 8) {
     const int r = r0 + ty + i, c = c0 + tx;
-    if (r < R && c < C) tile[ty + i][tx] = in[(int64_t)r * ldi + c];
+    if (c < C) tile[ty + i][tx] = r < R ? in[(int64_t)r * ldi + c] : (bf16_t)0;
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < TS; i += 8) {
     const int c = c0 + ty + i, r = r0 + tx;
-    if (r < R && c < C) out[(int64_t)c * ldo + r] = tile[tx][ty + i];
+    if (r < W && c < C) out[(int64_t)c * ldo + r] = tile[tx][ty + i];
   }
 }
 
@@ -183,7 +184,7 @@ int launch_transpose_bf16_jobs(const TransposeJobs& tj, hipStream_t s) {
   return VF_OK;
 }
 
-int launch_transpose_nodes(const NodeList& nl, int64_t ldi, int64_t ldo, int C, hipStream_t s) {
+int launch_transpose_nodes(const NodeList& nl, int64_t ldi, int64_t ldo, int C, hipStream_t s, bool pad) {
   if (nl.count < 1 || nl.count > kFoldMax || C <= 0) return VF_EINVAL;
   int max_rows = 0;
   for (int j = 0; j < nl.count; ++j) {
@@ -191,7 +192,7 @@ int launch_transpose_nodes(const NodeList& nl, int64_t ldi, int64_t ldo, int C, 
     max_rows = nl.rows[j] > max_rows ? nl.rows[j] : max_rows;
   }
   dim3 grid((C + TS - 1) / TS, (max_rows + TS - 1) / TS, nl.count);
-  transpose_nodes_kernel<<<grid, 256, 0, s>>>(nl, ldi, ldo, C);
+  transpose_nodes_kernel<<<grid, 256, 0, s>>>(nl, ldi, ldo, C, pad);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }

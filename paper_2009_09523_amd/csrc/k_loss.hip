@@ -147,6 +147,10 @@ __global__ __launch_bounds__(256) void softmax_xent_kernel(const float* zp, int 
       if (dzT) dzT[(int64_t)c * ldt + r] = f32_to_bf16(d * tscale);
     }
   }
+  // the transposed copy's columns past the last row, up to the next multiple of 8: 0 (a window's nodes may be one contraction)
+  if (dzT && r == R - 1)
+    for (int q = R; q < ((R + 7) & ~7); ++q)
+      for (int c = threadIdx.x; c < C; c += 256) dzT[(int64_t)c * ldt + q] = 0;
   if (threadIdx.x == 0) rowloss[r] = logf(sum) + mx - zlabel;   // zlabel: visible after the reductions' barriers
 }
 

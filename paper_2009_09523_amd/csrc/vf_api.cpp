@@ -435,11 +435,13 @@ int vf_init(const vf_config* cfg, vf_ctx** out) {
   if (!h) return VF_ENOMEM;
   Ctx& c = h->c;
   c.cfg = *cfg;
-  // Units of 16 or 32 nodes: a fold window never needs more units than a batch has (the window's
-  // transposed operand copies are sized by window x largest unit).
+  // Units of 16 or 32 nodes: a fold window never needs more units than a batch has (the window's transposed operand copies
+  // are sized for that many units, or for a batch if that is less); nodes of more than 128 rows are units of their own in an MLP.
   if (c.cfg.node_group >= 16 && c.cfg.fold_window > 1) {
     const int64_t unit = (int64_t)c.cfg.max_node_size * c.cfg.node_group;
-    c.cfg.fold_window = (int32_t)std::max<int64_t>(1, std::min<int64_t>(c.cfg.fold_window, (c.cfg.max_batch + unit - 1) / unit));
+    int64_t units = (c.cfg.max_batch + unit - 1) / unit;
+    if (c.cfg.model_kind == VF_MLP && c.cfg.max_node_size > 128) units = (c.cfg.max_batch + 128) / 129;
+    c.cfg.fold_window = (int32_t)std::max<int64_t>(1, std::min<int64_t>(c.cfg.fold_window, units));
   }
   cfg = &c.cfg;
   c.stream = static_cast<hipStream_t>(cfg->stream);

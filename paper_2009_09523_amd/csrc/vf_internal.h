@@ -264,7 +264,7 @@ struct NodeList {
   int overwrite;
 };
 // dst[j][c*ldo + r] = src[j][r*ldi + c] for every node j (r < rows[j], c < C): k_elem.hip
-int launch_transpose_nodes(const NodeList& nl, int64_t ldi, int64_t ldo, int C, hipStream_t s);
+int launch_transpose_nodes(const NodeList& nl, int64_t ldi, int64_t ldo, int C, hipStream_t s, bool pad = false);
 // out[r] <- fma(w[count-1], S_{count-1}[r], ... fma(w[0], S_0[r], overwrite ? 0 : out[r])) with
 // S_j[r] = sum over c < rows[j] of src[j][r*ld + c], r < R (bias gradients of a window from the
 // transposed output gradients; the same chain as one launch per node): k_norm.hip

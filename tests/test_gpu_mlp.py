@@ -630,6 +630,29 @@ def test_units_of_whole_nodes_on_narrow_layers_match_the_oracle(name, dims, node
     check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=BENCH, fold_window=8, node_group=16), oracle_steps(wl, theta, x, y))
 
 
+@pytest.mark.parametrize("sizes", [(129, 300, 83), (257, 257), (512, 1, 131, 7), (1024, 130), (1025, 200)])
+@pytest.mark.parametrize("name", ["mlp_mid_bn_bf16", "mlp_mid_bf16"])
+def test_long_nodes_of_odd_sizes_in_a_window_match_the_oracle(name, sizes):
+    """Nodes of more than 128 rows in the launch configuration of units: each goes alone, its BatchNorm kernels hold up to
+    512 or 1024 rows in registers (1025: the kernel that walks them), and the window's weight gradients are one product
+    over operand copies padded with zeros to multiples of 8 (a second step finds the first one's rows there)."""
+    wl = dataclasses.replace(I.workload(name), dims=(72, 264, 136, 52), node_sizes=sizes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    ref = oracle_steps(wl, theta, x, y)
+    base = None
+    for flags in (BENCH, FUSED):
+        gpu = run_gpu(wl, theta, x, y, flags=flags, fold_window=8, node_group=32)
+        check_against_oracle(wl, gpu, ref)
+        base = base or gpu
+        assert gpu["G"].tobytes() == base["G"].tobytes()
+    back = sizes[::-1]                       # other columns, so that what was written before lies in the padding
+    both = run_gpu(wl, theta, x, y, flags=BENCH, fold_window=8, node_group=32, steps=2)
+    assert np.isfinite(both["G"]).all()
+    ref = oracle_steps(wl, theta, x, y, node_sizes=back)
+    check_against_oracle(wl, run_gpu(wl, theta, x, y, node_sizes=back, flags=BENCH, fold_window=8, node_group=32), ref)
+
+
 def test_node_groups_keep_the_workspace_independent_of_the_node_count():
     wl, theta, x, y = _case("mlp_mid_bn_bf16")
     few = run_gpu(wl, theta, x[:80], y[:80], node_sizes=[40, 40], flags=FUSED, node_group=4, max_node_size=40,
