@@ -147,24 +147,77 @@ __global__ __launch_bounds__(NT) void im2colT_kernel(const bf16_t* __restrict__ 
   }
 }
 
+// ---- operands of a weight gradient ------------------------------------------------------------------
+// colsT[(tap, c), r] = in[r shifted by the tap, c] (0 outside the image) and dyT[o, r] = dy[r, o] in one launch: 64 x 64
+// tiles through LDS, 16 bytes per lane on both sides, blockIdx.y over the column tiles of the patches and then of dy.  Every
+// lane finds the tap of its own eight channels (Cin / 8 chunks a tap, by a multiplication: `inv` = ceil(65536 / (Cin / 8))
+// is exact for the 288 chunks there are at most).  Columns past the last row, up to ld's multiple of 8, are 0.  Cin, Cout
+// % 8 == 0, Cin <= 256, 16-byte aligned rows.  (37632 positions, 40 to 40 channels: a transpose of the input, the patches
+// from it by windows and a transpose of dy were 3.4 + 7.5 + 4.2 us and two more gaps.)
+__global__ __launch_bounds__(NT) void conv_wgrad_operands_kernel(const bf16_t* __restrict__ x, int Cin,
+                                                                 const bf16_t* __restrict__ dy, int Cout, int rows, int H, int W,
+                                                                 bf16_t* __restrict__ colsT, bf16_t* __restrict__ dyT, int64_t ld,
+                                                                 int ptiles, int inv) {
+  __shared__ __attribute__((aligned(16))) bf16_t tile[64][kTransposePitch];
+  const bool patch = (int)blockIdx.y < ptiles;
+  const int r0 = blockIdx.x * 64, c0 = (patch ? blockIdx.y : blockIdx.y - ptiles) * 64;
+  const int C = patch ? 9 * Cin : Cout;
+  const int v = threadIdx.x & 7, row = threadIdx.x >> 3;       // 8 vectors per row, 32 rows per pass
+  const int kc = min(c0 + 8 * v, C - 8) >> 3;
+  const int tap = patch ? (kc * inv) >> 16 : 0, ch = 8 * kc - tap * Cin;
+  const int kh = (tap * 11) >> 5, kw = tap - 3 * kh;           // (tap / 3 for tap <= 15)
+  const int shift = (kh - 1) * W + (kw - 1);
+  u32x4 got[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = min(r0 + row + 32 * i, rows - 1);
+    bool inside = r0 + row + 32 * i < rows;
+    const bf16_t* src = dy + (int64_t)r * Cout + 8 * kc;
+    if (patch) {
+      const int line = r / W, w = r - line * W + kw - 1, h = line % H + kh - 1;
+      const bool in_image = h >= 0 && h < H && w >= 0 && w < W;
+      inside = inside && in_image;
+      src = x + (int64_t)(in_image ? r + shift : r) * Cin + ch;
+    }
+    got[i] = *reinterpret_cast<const u32x4*>(src);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) got[i][e] = inside ? got[i][e] : 0u;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *reinterpret_cast<uint32_t*>(&tile[row + 32 * i][8 * v + 2 * e]) = got[i][e];
+  __syncthreads();
+  bf16_t* __restrict__ out = patch ? colsT : dyT;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int col = (threadIdx.x >> 3) + 32 * i;               // output row = patch element or channel
+    const int rb = 8 * (threadIdx.x & 7);                      // eight positions -> one 16-byte vector
+    u32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (uint32_t)tile[rb + 2 * e][col] | ((uint32_t)tile[rb + 2 * e + 1][col] << 16);
+    if (c0 + col < C && r0 + rb < rows) *reinterpret_cast<u32x4*>(&out[(int64_t)(c0 + col) * ld + r0 + rb]) = o;
+  }
+}
+
 // ---- filter copies ----------------------------------------------------------------------------
 // nat[o, k] = bf16(Wf[o, k]) for k < 9*Cin (row pitch Kp; the padding stays as it is: zero);
 // flip[c, (2-kh)*3*Cout + (2-kw)*Cout + o] = bf16(Wf[o, kh, kw, c]): the filters of the input
 // gradient, which is the 3x3 convolution of the output gradient with the filters turned by 180
-// degrees and input/output channels exchanged (row pitch Kpf).
-__global__ __launch_bounds__(NT) void conv_weight_copies_kernel(const float* __restrict__ Wf, int Cout, int Cin,
-                                                                bf16_t* __restrict__ nat, int Kp,
-                                                                bf16_t* __restrict__ flip, int Kpf) {
-  const int K = 9 * Cin;
+// degrees and input/output channels exchanged (row pitch Kpf).  All layers in one launch (2.4 us each and the gaps between
+// them otherwise): blockIdx.y is the layer.
+__global__ __launch_bounds__(NT) void conv_weight_copies_kernel(ConvCopyJobs jobs) {
+  const ConvCopyJob& job = jobs.job[blockIdx.y];
+  const int Cin = job.Cin, Cout = job.Cout, K = 9 * Cin;
   const int idx = blockIdx.x * NT + threadIdx.x;
   if (idx >= Cout * K) return;
   const int o = idx / K, k = idx - o * K;
-  const bf16_t v = f32_to_bf16(Wf[idx]);
-  nat[(int64_t)o * Kp + k] = v;
-  if (flip) {
+  const bf16_t v = f32_to_bf16(job.Wf[idx]);
+  job.nat[(int64_t)o * job.Kp + k] = v;
+  if (job.flip) {
     const int tap = k / Cin, c = k - tap * Cin;
     const int kh = tap / 3, kw = tap - 3 * kh;
-    flip[(int64_t)c * Kpf + ((2 - kh) * 3 + (2 - kw)) * Cout + o] = v;
+    job.flip[(int64_t)c * job.Kpf + ((2 - kh) * 3 + (2 - kw)) * Cout + o] = v;
   }
 }
 
@@ -798,10 +851,32 @@ int launch_im2col3x3_transposed(const bf16_t* xT, int64_t ldx, int64_t rows, int
   return VF_OK;
 }
 
-int launch_conv_weight_copies(const float* Wf, int Cout, int Cin, bf16_t* nat, int Kp, bf16_t* flip, int Kpf,
-                              hipStream_t s) {
-  if (Cout <= 0 || Cin <= 0 || Kp < 9 * Cin || (flip && Kpf < 9 * Cout)) return VF_EINVAL;
-  conv_weight_copies_kernel<<<(unsigned)blocks((int64_t)Cout * 9 * Cin), NT, 0, s>>>(Wf, Cout, Cin, nat, Kp, flip, Kpf);
+int launch_conv_weight_copies(const ConvCopyJobs& jobs, hipStream_t s) {
+  if (jobs.count < 1 || jobs.count > kConvCopyJobs) return VF_EINVAL;
+  int64_t most = 0;
+  for (int j = 0; j < jobs.count; ++j) {
+    const ConvCopyJob& g = jobs.job[j];
+    if (!g.Wf || !g.nat || g.Cout <= 0 || g.Cin <= 0 || g.Kp < 9 * g.Cin || (g.flip && g.Kpf < 9 * g.Cout)) return VF_EINVAL;
+    most = std::max(most, (int64_t)g.Cout * 9 * g.Cin);
+  }
+  conv_weight_copies_kernel<<<dim3((unsigned)blocks(most), jobs.count), NT, 0, s>>>(jobs);
+  VF_LAUNCH_CHECK();
+  return VF_OK;
+}
+
+bool conv_wgrad_operands_fit(const bf16_t* x, int Cin, int Cout) {
+  return Cin > 0 && Cin % 8 == 0 && Cin <= 256 && Cout > 0 && Cout % 8 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+}
+
+int launch_conv_wgrad_operands(const bf16_t* x, int Cin, const bf16_t* dy, int Cout, int64_t rows, int H, int W, bf16_t* colsT,
+                               bf16_t* dyT, int64_t ld, hipStream_t s) {
+  if (!x || !dy || !colsT || !dyT || !conv_wgrad_operands_fit(x, Cin, Cout) || rows <= 0 || rows > 0x7fffff00 || H <= 0 || W <= 0 ||
+      rows % ((int64_t)H * W) || (ld & 7) || ld < ((rows + 7) & ~int64_t(7)) || (reinterpret_cast<uintptr_t>(dy) & 15) ||
+      (reinterpret_cast<uintptr_t>(colsT) & 15) || (reinterpret_cast<uintptr_t>(dyT) & 15))
+    return VF_EINVAL;
+  const int ptiles = (9 * Cin + 63) / 64, inv = (65536 + Cin / 8 - 1) / (Cin / 8);
+  const dim3 grid((unsigned)((rows + 63) / 64), ptiles + (Cout + 63) / 64);
+  conv_wgrad_operands_kernel<<<grid, NT, 0, s>>>(x, Cin, dy, Cout, (int)rows, H, W, colsT, dyT, ld, ptiles, inv);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }

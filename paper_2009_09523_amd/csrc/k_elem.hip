@@ -38,19 +38,21 @@ __global__ __launch_bounds__(256) void transpose_kernel(const TIN* __restrict__ 
 // out[c*ldo + r] = in[r*ldi + c] for bf16, 64x64 tiles, 16 bytes per lane on both sides (eight
 // lanes cover 128 contiguous bytes of an input row, and of an output row).  Loads go to clamped,
 // always valid addresses and come first, so both of a thread's loads are in flight together.
-// Requires C % 8 == 0, ldi % 8 == 0, ldo % 8 == 0, 16-byte aligned bases, and output rows that
-// may be written up to R rounded to 8 (the rows past R receive copies of row R-1).
+// Requires ldi % 8 == 0, ldi >= C rounded up to 8 (what lies there is read and dropped), ldo % 8 == 0, 16-byte aligned
+// bases, and output rows that may be written up to R rounded to 8 (the rows past R receive copies of row R-1).
 __device__ __forceinline__ void transpose64_body(const bf16_t* __restrict__ in, int64_t ldi,
                                                  bf16_t* __restrict__ out, int64_t ldo, int R, int C, int bx, int by) {
-  __shared__ __attribute__((aligned(16))) bf16_t tile[64][64 + 8];
+  __shared__ __attribute__((aligned(16))) bf16_t tile[64][kTransposePitch];
   const int r0 = by * 64, c0 = bx * 64;
   const int v = threadIdx.x & 7, row = threadIdx.x >> 3;     // 8 vectors per row, 32 rows per pass
   u32x4 x[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
-    x[i] = *reinterpret_cast<const u32x4*>(&in[(int64_t)min(r0 + row + 32 * i, R - 1) * ldi + min(c0 + 8 * v, C - 8)]);
+    x[i] = *reinterpret_cast<const u32x4*>(&in[(int64_t)min(r0 + row + 32 * i, R - 1) * ldi + min(c0 + 8 * v, ((C + 7) & ~7) - 8)]);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) *reinterpret_cast<u32x4*>(&tile[row + 32 * i][8 * v]) = x[i];
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *reinterpret_cast<uint32_t*>(&tile[row + 32 * i][8 * v + 2 * e]) = x[i][e];
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -76,32 +78,48 @@ __global__ __launch_bounds__(256) void transpose64_jobs_kernel(TransposeJobs tj)
   transpose64_body(tj.in[j], tj.ldi[j], tj.out[j], tj.ldo, tj.R, tj.C[j], blockIdx.x - first, blockIdx.y);
 }
 
-// fp32 [R, C] -> bf16 natural copy [R, ldn] and transposed copy [C, ldt], 64x64 tiles.
-// Every thread reads 16 bytes and writes 8 bytes at a time in both orientations.
-// Requires C % 4 == 0, ldi % 4 == 0, ldn % 4 == 0, ldt % 4 == 0 and 16-byte aligned bases.
-__global__ __launch_bounds__(256) void cast_weight_kernel(const float* __restrict__ in, int64_t ldi,
-                                                          bf16_t* __restrict__ nat, int64_t ldn,
-                                                          bf16_t* __restrict__ tr, int64_t ldt, int R, int C) {
+// fp32 [R, C] -> bf16 natural copy [R, ldn] and transposed copy [C, ldt], 64x64 tiles, of several matrices in one launch
+// (blockIdx.x runs over their tiles; up to 17 launches of 5 us otherwise).  Every thread reads 16 bytes and writes 8 bytes at a time in both
+// orientations; rows of C elements that are no multiple of 4, or unaligned, are read element by element (768 x 30522: 54 us by 32 x 32
+// tiles of single elements; with sixteen matrices of 28 million elements beside it 74 here).  Requires ldn, ldt % 4 == 0, ldn >= C rounded up to 4, ldt >= R rounded up to 4
+// (the padding receives zeros), nat and tr 8-byte aligned.
+__global__ __launch_bounds__(256) void cast_weight_kernel(CastJobs jobs) {
   __shared__ bf16_t tile[64][64 + 2];
-  const int q = threadIdx.x & 15, g = threadIdx.x >> 4;      // 16 quads per row, 16 row groups
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  // loads at clamped (always valid) positions first, all four in flight together (C % 4 == 0,
-  // so C - 4 starts a whole quad)
-  float4 vin[4];
+  int j = 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    vin[i] = load4_stream(&in[(int64_t)min(r0 + g + 16 * i, R - 1) * ldi + min(c0 + 4 * q, C - 4)]);
+  for (int i = 0; i < kCastJobs; ++i) j += (int)blockIdx.x >= jobs.end[i] ? 1 : 0;
+  const CastJob& job = jobs.job[j];
+  const int R = job.R, C = job.C;
+  const float* __restrict__ in = job.in;
+  const int t = (int)blockIdx.x - (j ? jobs.end[j - 1] : 0), tiles_c = (C + 63) / 64;
+  const int q = threadIdx.x & 15, g = threadIdx.x >> 4;      // 16 quads per row, 16 row groups
+  const int r0 = t / tiles_c * 64, c0 = t % tiles_c * 64;
+  // loads at clamped (always valid) positions first, all in flight together
+  float4 vin[4];
+  if (job.vec) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      vin[i] = load4_stream(&in[(int64_t)min(r0 + g + 16 * i, R - 1) * C + min(c0 + 4 * q, C - 4)]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* p = &in[(int64_t)min(r0 + g + 16 * i, R - 1) * C];
+      const int c = c0 + 4 * q;
+      vin[i] = make_float4(p[min(c, C - 1)], p[min(c + 1, C - 1)], p[min(c + 2, C - 1)], p[min(c + 3, C - 1)]);
+    }
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int rl = g + 16 * i, r = r0 + rl, c = c0 + 4 * q;
-    bf16_t h[4] = {0, 0, 0, 0};
+    const float v[4] = {vin[i].x, vin[i].y, vin[i].z, vin[i].w};
+    bf16_t h[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) h[u] = r < R && c + u < C ? f32_to_bf16(v[u]) : (bf16_t)0;
     if (r < R && c < C) {
-      const float4 v = vin[i];
-      h[0] = f32_to_bf16(v.x); h[1] = f32_to_bf16(v.y); h[2] = f32_to_bf16(v.z); h[3] = f32_to_bf16(v.w);
       uint2 pk;
       pk.x = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
       pk.y = (uint32_t)h[2] | ((uint32_t)h[3] << 16);
-      *reinterpret_cast<uint2*>(&nat[(int64_t)r * ldn + c]) = pk;
+      *reinterpret_cast<uint2*>(&job.nat[(int64_t)r * job.ldn + c]) = pk;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) tile[rl][4 * q + u] = h[u];
@@ -114,7 +132,7 @@ __global__ __launch_bounds__(256) void cast_weight_kernel(const float* __restric
       uint2 pk;
       pk.x = (uint32_t)tile[4 * q][cl] | ((uint32_t)tile[4 * q + 1][cl] << 16);
       pk.y = (uint32_t)tile[4 * q + 2][cl] | ((uint32_t)tile[4 * q + 3][cl] << 16);
-      *reinterpret_cast<uint2*>(&tr[(int64_t)c * ldt + r]) = pk;
+      *reinterpret_cast<uint2*>(&job.tr[(int64_t)c * job.ldt + r]) = pk;
     }
   }
 }
@@ -155,7 +173,7 @@ __global__ __launch_bounds__(256) void cast_kernel(const float* __restrict__ in,
 int launch_transpose_bf16(const bf16_t* in, int64_t ldi, bf16_t* out, int64_t ldo, int R, int C,
                           hipStream_t s) {
   if (R <= 0 || C <= 0) return VF_OK;
-  const bool wide = (C & 7) == 0 && (ldi & 7) == 0 && (ldo & 7) == 0 && ldo >= ((R + 7) & ~7) &&
+  const bool wide = ldi >= ((C + 7) & ~7) && (ldi & 7) == 0 && (ldo & 7) == 0 && ldo >= ((R + 7) & ~7) &&
                     (reinterpret_cast<uintptr_t>(in) & 15) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
   if (wide) {
     dim3 grid64((C + 63) / 64, (R + 63) / 64);
@@ -197,21 +215,31 @@ int launch_transpose_nodes(const NodeList& nl, int64_t ldi, int64_t ldo, int C, 
   return VF_OK;
 }
 
-int launch_cast_weight(const float* w, int R, int C, bf16_t* nat, int64_t ldn, bf16_t* tr,
-                       int64_t ldt, hipStream_t s) {
-  if (R <= 0 || C <= 0) return VF_OK;
-  const bool vec = (C & 3) == 0 && (ldn & 3) == 0 && (ldt & 3) == 0 &&
-                   (reinterpret_cast<uintptr_t>(w) & 15) == 0 && (reinterpret_cast<uintptr_t>(nat) & 7) == 0 &&
-                   (reinterpret_cast<uintptr_t>(tr) & 7) == 0;
-  if (vec) {
-    dim3 grid((C + 63) / 64, (R + 63) / 64);
-    cast_weight_kernel<<<grid, 256, 0, s>>>(w, C, nat, ldn, tr, ldt, R, C);
-  } else {
-    dim3 grid((C + TS - 1) / TS, (R + TS - 1) / TS);
-    transpose_kernel<float><<<grid, 256, 0, s>>>(w, C, tr, ldt, nat, ldn, R, C);
+int launch_cast_weights(CastJobs jobs, hipStream_t s) {
+  if (jobs.count < 1 || jobs.count > kCastJobs) return VF_EINVAL;
+  int64_t end = 0;
+  for (int j = 0; j < jobs.count; ++j) {
+    CastJob& g = jobs.job[j];
+    if (!g.in || !g.nat || !g.tr || g.R <= 0 || g.C <= 0 || (g.ldn & 3) || (g.ldt & 3) || g.ldn < ((g.C + 3) & ~3) ||
+        g.ldt < ((g.R + 3) & ~3) || (reinterpret_cast<uintptr_t>(g.nat) & 7) || (reinterpret_cast<uintptr_t>(g.tr) & 7))
+      return VF_EINVAL;
+    g.vec = (g.C & 3) == 0 && (reinterpret_cast<uintptr_t>(g.in) & 15) == 0;
+    end += (int64_t)((g.R + 63) / 64) * ((g.C + 63) / 64);
+    if (end > 0x7fffffff) return VF_EINVAL;
+    jobs.end[j] = (int)end;
   }
+  for (int j = jobs.count; j < kCastJobs; ++j) jobs.end[j] = 0x7fffffff;
+  cast_weight_kernel<<<(unsigned)end, 256, 0, s>>>(jobs);
   VF_LAUNCH_CHECK();
   return VF_OK;
+}
+
+int launch_cast_weight(const float* w, int R, int C, bf16_t* nat, int64_t ldn, bf16_t* tr, int64_t ldt, hipStream_t s) {
+  if (R <= 0 || C <= 0) return VF_OK;
+  CastJobs jobs{};
+  jobs.job[0] = {w, R, C, nat, ldn, tr, ldt, 0};
+  jobs.count = 1;
+  return launch_cast_weights(jobs, s);
 }
 
 int launch_cast_bf16(const float* in, int64_t ldi, bf16_t* out, int64_t ldo, int R, int C,

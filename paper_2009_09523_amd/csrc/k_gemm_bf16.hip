@@ -424,14 +424,16 @@ __device__ __forceinline__ int dl_swizzle(int r) { return (r & 7) ^ ((r >> 3) & 
 // tap of its own 16 bytes (chunk / (Cin / 8), by a multiplication: `inv` = ceil(65536 / (Cin / 8)) is exact
 // for the 288 chunks there are at most); chunks beyond 9 Cin are zeros in both operands.  At 37632
 // positions, 40 to 40 channels, writing and reading the patch matrix took 10.2 + 13.3 us; this takes 14.9.
-struct ConvOperand { int H, W, Cin; const bf16_t* zeros; int inv; int rows_on_x; };
+// `stats`: per row tile and column, the mean of what the tile stored and the sum of squared deviations from it (what a
+// BatchNorm over the positions starts from; read back by a kernel of its own they were 5.7 us behind a product of 13).
+struct ConvOperand { int H, W, Cin; const bf16_t* zeros; int inv; int rows_on_x; float* stats; };
 
 template <int NS, int CONV = 0, bool TAIL = false>
 __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                           const bf16_t* __restrict__ B, int64_t ldb,
                                                           int M, int N, int K, int kchunk,
                                                           int64_t slab_stride, Epilogue ep,
-                                                          ConvOperand cv = ConvOperand{0, 0, 0, nullptr, 0, 0}) {
+                                                          ConvOperand cv = ConvOperand{0, 0, 0, nullptr, 0, 0, nullptr}) {
   constexpr int TILE = 64 * BK;                 // elements of one operand tile (8 KB)
   constexpr int STAGE = 2 * TILE;
   constexpr int LPS = 4;                        // loads per lane and stage (2 for A, 2 for B)
@@ -564,6 +566,33 @@ __global__ __launch_bounds__(NT) void gemm_bf16_dl_kernel(const bf16_t* __restri
   f32x16 tiles[1][1];
   tiles[0][0] = acc;
   store_tiles<1, 1>(tiles, ep, cbase, blockIdx.z == 0, m0 + wm * 32, n0 + wn * 32, M, N, lane);
+  if (CONV && cv.stats) {
+    float* part = reinterpret_cast<float*>(lds);           // [2][wave][32]
+    const int first = m0 + wm * 32 + 4 * (lane >> 5);      // row of accumulator register 0
+    const float inv = 1.f / (float)min(64, M - m0);
+    float s = 0.f, q = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s += first + 8 * (r >> 2) + (r & 3) < M ? acc[r] : 0.f;
+    s += __shfl_xor(s, 32, 64);
+    __syncthreads();                                       // (the operand stages are read by all)
+    if (lane < 32) part[wave * 32 + lane] = s;
+    __syncthreads();
+    const int c = lane & 31;
+    const float mean = (part[wn * 32 + c] + part[(wn + 2) * 32 + c]) * inv;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float d = first + 8 * (r >> 2) + (r & 3) < M ? acc[r] - mean : 0.f;
+      q = fmaf(d, d, q);
+    }
+    q += __shfl_xor(q, 32, 64);
+    if (lane < 32) part[128 + wave * 32 + lane] = q;
+    __syncthreads();
+    if (wm == 0 && lane < 32 && n0 + wn * 32 + c < N) {
+      float* out = cv.stats + (int64_t)(m0 >> 6) * 2 * N + n0 + wn * 32 + c;
+      out[0] = mean;
+      out[N] = part[128 + wn * 32 + c] + part[128 + (wn + 2) * 32 + c];
+    }
+  }
 }
 
 // ---- wide LDS-direct variant: 256 x BN tiles, eight wavefronts ---------------------------------
@@ -2807,7 +2836,11 @@ int launch_conv3x3_bf16(const bf16_t* x, int64_t rows, int H, int W, int Cin, co
   // Column tiles of the same positions run side by side (they share the patches); a grid's second dimension ends at
   // 65535 row tiles (4.2 million positions), its first does not.
   const int64_t mtiles = (rows + 63) / 64;
-  ConvOperand cv{H, W, Cin, zeros, 0, mtiles > 65535};
+  ConvOperand cv{H, W, Cin, zeros, 0, mtiles > 65535, nullptr};
+  if (stats && stats_chunks && stats_rows && plain && !ep.R && mtiles <= 0x7fffffff) {
+    cv.stats = stats;
+    *stats_chunks = (int)mtiles; *stats_rows = 64;
+  }
   const dim3 grid = cv.rows_on_x ? dim3((unsigned)mtiles, (N + 63) / 64) : dim3((N + 63) / 64, (unsigned)mtiles);
   if (Cin % BK) {
     cv.inv = (65536 + Cin / 8 - 1) / (Cin / 8);

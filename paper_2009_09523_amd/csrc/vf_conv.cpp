@@ -91,11 +91,11 @@ class Conv final : public Model {
     a.request(&zeros_, (size_t)64);
     a.request(&colsT_, (size_t)kp_max * ldr_);
     a.request(&dyT_, (size_t)C_ * ldr_);
-    a.request(&inT_, (size_t)std::max(C_, cfg_.in_ch) * ldr_);
+    a.request(&inT_, (size_t)cfg_.in_ch * ldr_);
     a.request(&dy_, rows * C_);
     a.request(&gA_, rows * C_);
     a.request(&gB_, rows * C_);
-    a.request(&partial_, (size_t)std::max(conv_chunks_max(rows_max_), kConvStatsChunks) * 2 * C_);
+    a.request(&partial_, (size_t)std::max<int64_t>(conv_chunks_max(rows_max_), std::max<int64_t>(kConvStatsChunks, (rows_max_ + 63) / 64)) * 2 * C_);
     a.request(&sums_, (size_t)2 * C_);
     // contraction slabs of a weight gradient: up to wgrad_split from the product over the transposed
     // patch matrix, up to kDirectSplit per 64 x 64 channel block from the direct kernel
@@ -127,8 +127,14 @@ class Conv final : public Model {
   int prepare(Ctx& c, const float* params, hipStream_t st) override {
     // the element-wise kernels read gamma, beta and the statistics four at a time
     if (reinterpret_cast<uintptr_t>(params) & 15) return VF_EINVAL;
-    for (ConvLayer& L : layers_)
-      VF_KS(c, st, "cast_weight", launch_conv_weight_copies(params + L.w_off, L.C, L.Cin, L.wnat, L.Kp, L.wflip, L.Kpf, st));
+    for (size_t l = 0; l < layers_.size(); l += kConvCopyJobs) {
+      ConvCopyJobs jobs{};
+      for (size_t k = l; k < layers_.size() && jobs.count < kConvCopyJobs; ++k) {
+        const ConvLayer& L = layers_[k];
+        jobs.job[jobs.count++] = {params + L.w_off, L.C, L.Cin, L.wnat, L.Kp, L.wflip, L.Kpf};
+      }
+      VF_KS(c, st, "cast_weight", launch_conv_weight_copies(jobs, st));
+    }
     VF_KS(c, st, "cast_weight", launch_cast_weight(params + fc_w_off_, C_, cfg_.classes, fc_wnat_, ldz_, fc_wtr_, ldc_, st));
     return VF_OK;
   }
@@ -233,9 +239,13 @@ class Conv final : public Model {
       VF_KS(c, st, "fold_slabs", launch_fold_slabs(slabs_, split, slab, slab, c.gout(L.w_off, w, node), st));
       return VF_OK;
     }
-    VF_KS(c, st, "transpose", launch_transpose_bf16(L.in, L.Cin, inT_, ldr_, rows, L.Cin, st));
-    VF_KS(c, st, "im2col", launch_im2col3x3_transposed(inT_, ldr_, rows, H_, H_, L.Cin, colsT_, ldr_, st));
-    VF_KS(c, st, "transpose", launch_transpose_bf16(dy_, L.C, dyT_, ldr_, rows, L.C, st));
+    if (conv_wgrad_operands_fit(L.in, L.Cin, L.C)) {
+      VF_KS(c, st, "im2col", launch_conv_wgrad_operands(L.in, L.Cin, dy_, L.C, rows, H_, H_, colsT_, dyT_, ldr_, st));
+    } else {                 // (the first layer)
+      VF_KS(c, st, "transpose", launch_transpose_bf16(L.in, L.Cin, inT_, ldr_, rows, L.Cin, st));
+      VF_KS(c, st, "im2col", launch_im2col3x3_transposed(inT_, ldr_, rows, H_, H_, L.Cin, colsT_, ldr_, st));
+      VF_KS(c, st, "transpose", launch_transpose_bf16(dy_, L.C, dyT_, ldr_, rows, L.C, st));
+    }
     int split = wgrad_split(L, rows);
     const int slice = ((rows + split - 1) / split + 63) / 64 * 64;
     split = (rows + slice - 1) / slice;                       // no empty slice
@@ -318,7 +328,7 @@ class Conv final : public Model {
   bf16_t* zeros_ = nullptr;        // 128 bytes of 0: what the product kernel reads outside the image
   bf16_t* colsT_ = nullptr;        // [Kp, ldr]  patches transposed
   bf16_t* dyT_ = nullptr;          // [C, ldr]   output gradient transposed
-  bf16_t* inT_ = nullptr;          // [Cin, ldr] a layer's input transposed
+  bf16_t* inT_ = nullptr;          // [in_ch, ldr] the first layer's input transposed
   bf16_t* dy_ = nullptr;           // [rows, C]  gradient w.r.t. a convolution output
   float* gA_ = nullptr;            // [rows, C]  gradients w.r.t. activations (two, alternating)
   float* gB_ = nullptr;

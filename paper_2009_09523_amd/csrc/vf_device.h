@@ -70,6 +70,10 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Row pitch of the 64 x 64 bf16 tiles that are written by rows and read by columns: 33 words, so that the eight lanes that
+// read rows 8 k of a column pair meet on no bank (at 36 words four of them did).
+constexpr int kTransposePitch = 66;
+
 // Exact GELU and its derivative.
 __device__ __forceinline__ float gelu_f(float v) { return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f)); }
 __device__ __forceinline__ float gelu_df(float v) {

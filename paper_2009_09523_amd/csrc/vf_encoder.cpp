@@ -175,9 +175,14 @@ class Encoder final : public Model {
 
   int prepare(Ctx& c, const float* params, hipStream_t st) override {
     if (!bf16_) return VF_OK;
-    for (Lin* L : lins_)
-      VF_KS(c, st, "cast_weight", launch_cast_weight(params + L->w_off, L->K, L->N, L->wnat, L->ldn, L->wtr,
-                                                     L->ldt, st));
+    for (size_t l = 0; l < lins_.size(); l += kCastJobs) {
+      CastJobs jobs{};
+      for (size_t k = l; k < lins_.size() && jobs.count < kCastJobs; ++k) {
+        const Lin* L = lins_[k];
+        jobs.job[jobs.count++] = {params + L->w_off, L->K, L->N, L->wnat, L->ldn, L->wtr, L->ldt, 0};
+      }
+      VF_KS(c, st, "cast_weight", launch_cast_weights(jobs, st));
+    }
     return VF_OK;
   }
 

@@ -245,7 +245,7 @@ int launch_gemm_bf16_fold(const FoldArgs& fa, int64_t ld, int M, int N, float* C
 // 3x3 convolution (stride 1, zero padding 1) of a channels-last bf16 image stack x [rows, Cin],
 // rows = images*H*W, Cin % 64 == 0, with filters Wk [N, 9*Cin] (row pitch ldb), as a product
 // whose first operand is read straight from x; epilogue as launch_gemm_bf16.  zeros: 128 bytes
-// of device memory holding 0.  With `stats` (room for kConvStatsChunks * 2 * N floats) the kernel
+// of device memory holding 0.  With `stats` (room for max(kConvStatsChunks, rows / 64 rounded up) * 2 * N floats) the kernel
 // that takes the shape may also leave per-chunk, per-channel (mean, sum of squared deviations) of
 // what it stored, chunk k covering rows [k * *stats_rows, (k + 1) * *stats_rows): *stats_chunks
 // chunks (0: none were written), in the layout launch_bn2d_stats_finish reads.
@@ -289,6 +289,22 @@ int launch_transpose_bf16_jobs(const TransposeJobs& tj, hipStream_t s);
 int launch_transpose_bf16(const bf16_t* in, int64_t ldi, bf16_t* out, int64_t ldo, int R, int C,
                           hipStream_t s);
 // fp32 [R,C] (ld = C) -> bf16 natural copy [R, ldn] and transposed copy [C, ldt]
+struct CastJob {
+  const float* in;               // [R, C]
+  int R, C;
+  bf16_t* nat;                   // [R, ldn]
+  int64_t ldn;
+  bf16_t* tr;                    // [C, ldt]
+  int64_t ldt;
+  int vec;                       // (set by the launch)
+};
+constexpr int kCastJobs = 16;
+struct CastJobs {
+  int count;
+  int end[kCastJobs];            // tiles of a job and those before it (set by the launch)
+  CastJob job[kCastJobs];
+};
+int launch_cast_weights(CastJobs jobs, hipStream_t s);   // several matrices in one launch
 int launch_cast_weight(const float* w, int R, int C, bf16_t* nat, int64_t ldn, bf16_t* tr,
                        int64_t ldt, hipStream_t s);
 // fp32 [R,C] -> bf16 [R,C] with the given leading dimensions
@@ -340,8 +356,22 @@ int launch_im2col3x3_transposed(const bf16_t* xT, int64_t ldx, int64_t rows, int
                                 int64_t ldo, hipStream_t s);
 // bf16 copies of fp32 filters [Cout, 3, 3, Cin]: as they are (row pitch Kp) and, if flip != null,
 // turned by 180 degrees with the channel roles exchanged, [Cin, 3, 3, Cout] (row pitch Kpf)
-int launch_conv_weight_copies(const float* Wf, int Cout, int Cin, bf16_t* nat, int Kp, bf16_t* flip, int Kpf,
-                              hipStream_t s);
+struct ConvCopyJob {
+  const float* Wf;
+  int Cout, Cin;
+  bf16_t* nat;
+  int Kp;
+  bf16_t* flip;                  // or null
+  int Kpf;
+};
+constexpr int kConvCopyJobs = 16;
+struct ConvCopyJobs { ConvCopyJob job[kConvCopyJobs]; int count; };
+int launch_conv_weight_copies(const ConvCopyJobs& jobs, hipStream_t s);
+// Both operands of a weight gradient taken as a product over the positions: the transposed patch matrix [9 Cin, ld] of x and
+// the transposed dy [Cout, ld] (conv_wgrad_operands_fit: channels in multiples of 8, aligned).
+bool conv_wgrad_operands_fit(const bf16_t* x, int Cin, int Cout);
+int launch_conv_wgrad_operands(const bf16_t* x, int Cin, const bf16_t* dy, int Cout, int64_t rows, int H, int W, bf16_t* colsT,
+                               bf16_t* dyT, int64_t ld, hipStream_t s);
 // per-column mean and 1/sqrt(biased variance + eps) of y [rows, C]; moving statistics blended
 int launch_bn2d_stats(const float* y, int64_t rows, int C, float eps, float* partial, float* mean, float* rstd,
                       float* run_mean, float* run_var, float run_mix, hipStream_t s);
