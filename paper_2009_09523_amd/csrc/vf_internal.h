@@ -208,6 +208,28 @@ bool gemm_bf16_bn_fwd_takes(const bf16_t* A, int64_t lda, const bf16_t* B, int64
                             const BnFwdArgs& fa);
 int launch_gemm_bf16_bn_fwd(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int M, int N, int K,
                             const BnFwdArgs& fa, hipStream_t s);
+// One node of up to 128 rows: the bf16 product A [R, K] B^T (B [N, K], both contiguous along k, rows padded with zeros to
+// multiples of 8), the gradient at a layer's output, with the BatchNorm + ReLU (gamma null: ReLU) backward pass of that
+// layer in the same launch (k_node_bf16.hip): out = the bf16 gradient at z, outT its transposed copy times tscale, the
+// scale and shift (or bias) gradients.
+struct NodeBnArgs {
+  const float* gamma;            // or null
+  const float* beta;
+  int round_params;
+  const float* z;
+  int64_t ldz;
+  bf16_t* out;
+  int64_t ldo;
+  bf16_t* outT;                  // [N, ldt], 16-byte aligned columns
+  int64_t ldt;
+  const float* mean;
+  const float* rstd;
+  float tscale;
+  GradOut gout_g, gout_b;
+};
+bool node_bn_bwd_takes(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int R, int N, int K, const NodeBnArgs& f);
+int launch_node_bn_bwd(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int R, int N, int K, const NodeBnArgs& f,
+                       hipStream_t s);
 // What such products leave to do, for several layers of a unit in one launch (k_norm.hip).
 struct BnFinishJob {
   const float* src0;             // sums [nodes][2][C], or the per-node means [nodes][C] ...

@@ -383,6 +383,16 @@ class Mlp final : public Model {
           continue;
         }
       }
+      if (bf16_ && s.group(i) == 1) {
+        const bf16_t* dz = static_cast<const bf16_t*>(dz_in);
+        const NodeBnArgs f{Pv.has_bn ? P + Pv.g_off : nullptr, Pv.has_bn ? P + Pv.be_off : nullptr, 1, Pv.z[q], Pv.ld,
+                           static_cast<bf16_t*>(Pv.dz[0]), Pv.ld, Pv.dzT + pc, ldw_, Pv.mean[q], Pv.rstd[q], tscale(c, s, i), gg, gb};
+        if (node_bn_bwd_takes(dz, L.ld, L.wnat, L.ldn, b, L.K, kdim(L), f)) {
+          VF_KS(c, st, "gemm_dgrad_bn", launch_node_bn_bwd(dz, L.ld, L.wnat, L.ldn, b, L.K, kdim(L), f, st));
+          VF_TRY(c.piece_done(i, l - 1, st));
+          continue;
+        }
+      }
       if (!bf16_ && Pv.has_bn && s.group(i) == 1 && split == 1 && f32_bn_takes(b, L.K, L.N, L.ld, L.N, true)) {
         F32BnArgs f{P + Pv.g_off, P + Pv.be_off, cfg_.bn_eps, Pv.z[q], Pv.ld, static_cast<float*>(Pv.dz[0]), Pv.ld, Pv.mean[q],
                     Pv.rstd[q], nullptr, nullptr, 0.f, gg, gb};

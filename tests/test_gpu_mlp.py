@@ -653,6 +653,30 @@ def test_long_nodes_of_odd_sizes_in_a_window_match_the_oracle(name, sizes):
     check_against_oracle(wl, run_gpu(wl, theta, x, y, node_sizes=back, flags=BENCH, fold_window=8, node_group=32), ref)
 
 
+@pytest.mark.parametrize("name", ["mlp_mid_bn_bf16", "mlp_mid_bf16"])
+@pytest.mark.parametrize("dims,nodes", [((64, 40, 24, 7), (128, 97, 1)), ((1536, 33, 264, 16), (32, 31, 64)),
+                                        ((768, 520, 8, 100), (64, 33, 65)), ((384, 17, 384, 50), (128, 100, 16)),
+                                        ((1544, 64, 50), (32, 8))])
+def test_bf16_nodes_in_one_launch_per_product_match_the_oracle(name, dims, nodes):
+    """Nodes that go alone, with products short enough for the launch that takes BatchNorm / ReLU along (rows and columns at
+    and beside its tiles, contractions at its limits and one beyond, widths whose rows are padded): node by node in both folds,
+    as a graph, on two streams, and with the nodes' weights inside the transposed operand."""
+    wl = dataclasses.replace(I.workload(name), dims=dims, node_sizes=nodes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    ref = oracle_steps(wl, theta, x, y)
+    base = None
+    for flags in (FUSED | NO_GRAPH, FUSED, 0, BENCH):
+        gpu = run_gpu(wl, theta, x, y, flags=flags)
+        check_against_oracle(wl, gpu, ref)
+        base = base or gpu
+        assert gpu["G"].tobytes() == base["G"].tobytes(), flags
+    sizes = [24, 8, 32, 16]
+    wl = dataclasses.replace(wl, node_sizes=tuple(sizes))
+    x, y = I.make_batch(wl)
+    check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=FUSED, fold_window=4), oracle_steps(wl, theta, x, y))
+
+
 def test_node_groups_keep_the_workspace_independent_of_the_node_count():
     wl, theta, x, y = _case("mlp_mid_bn_bf16")
     few = run_gpu(wl, theta, x[:80], y[:80], node_sizes=[40, 40], flags=FUSED, node_group=4, max_node_size=40,
