@@ -419,12 +419,34 @@ __global__ __launch_bounds__(NT) void bn2d_apply_fwd_kernel(const float* __restr
   reinterpret_cast<uint2*>(a)[i] = pack4(o);
 }
 
+// Gradient of the mean over an image's HW positions: what every position of image r / HW receives.
+struct PoolGrad {
+  const float* dpooled;
+  int64_t ldd;
+  uint32_t HW;
+  __device__ __forceinline__ float4 at(uint32_t r, int c) const {
+    const float inv = 1.f / (float)HW;
+    const float4 d = *reinterpret_cast<const float4*>(&dpooled[(int64_t)(r / HW) * ldd + c]);
+    return make_float4(d.x * inv, d.y * inv, d.z * inv, d.w * inv);
+  }
+};
+__device__ __forceinline__ float4 param4(const float* p, int c, int round_params) {
+  float4 g = *reinterpret_cast<const float4*>(&p[c]);
+  if (round_params) { g.x = round_bf16(g.x); g.y = round_bf16(g.y); g.z = round_bf16(g.z); g.w = round_bf16(g.w); }
+  return g;
+}
+
 // Backward, step 1: per chunk and column, the sums over the chunk's rows of dpre and of
-// dpre * xhat, with dpre = da where the ReLU was open (its stored output a > 0) and
-// xhat = (y - mean) * rstd.  partial[(chunk*2 + 0)*C + c] = sum dpre, [.. + 1 ..] = sum dpre*xhat.
-__global__ __launch_bounds__(NT) void bn2d_bwd_partial_kernel(const float* __restrict__ da, const bf16_t* __restrict__ a,
+// dpre * xhat, with dpre = da where the ReLU was open and xhat = (y - mean) * rstd.  SKIP: another activation was added
+// before the ReLU, and where it was open shows in its stored output (a > 0); else in gamma * xhat + beta > 0, the same
+// expression the forward kernel has, and `a` is not read (16.8 of 84 MB at 131072 x 64).  POOL: da is the gradient of the
+// images' means, read as [images, C] and never written out (as a tensor it was a launch of 8 us and 33.5 MB to read twice).  partial[(chunk*2 + 0)*C + c] = sum dpre, [.. + 1 ..] = sum dpre*xhat.
+template <bool SKIP, bool POOL>
+__global__ __launch_bounds__(NT) void bn2d_bwd_partial_kernel(const float* __restrict__ da, PoolGrad pool, const bf16_t* __restrict__ a,
                                                               const float* __restrict__ y, int64_t rows, int C,
-                                                              int chunk, const float* __restrict__ mean,
+                                                              int chunk, const float* __restrict__ gamma,
+                                                              const float* __restrict__ beta, int round_params,
+                                                              const float* __restrict__ mean,
                                                               const float* __restrict__ rstd, float* __restrict__ partial) {
   extern __shared__ float4 red[];
   const Tall t = tall_shape(C, chunk);
@@ -435,26 +457,30 @@ __global__ __launch_bounds__(NT) void bn2d_bwd_partial_kernel(const float* __res
   const int64_t base = r0 * C + 4 * g;
   const float4 m = *reinterpret_cast<const float4*>(&mean[4 * g]);
   const float4 rs = *reinterpret_cast<const float4*>(&rstd[4 * g]);
+  float4 gm = make_float4(0.f, 0.f, 0.f, 0.f), bt = gm;
+  if (!SKIP) { gm = param4(gamma, 4 * g, round_params); bt = param4(beta, 4 * g, round_params); }
   float4 sb = make_float4(0.f, 0.f, 0.f, 0.f), sg = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int p0 = 0; p0 < t.passes; p0 += PB) {
     float4 d[PB], v[PB];
     uint2 o2[PB];
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
-      const int64_t at = base + (int64_t)min(lane + (p0 + u) * t.rl, n - 1) * C;
-      d[u] = *reinterpret_cast<const float4*>(&da[at]);
+      const int row = min(lane + (p0 + u) * t.rl, n - 1);
+      const int64_t at = base + (int64_t)row * C;
+      d[u] = POOL ? pool.at((uint32_t)(r0 + row), 4 * g) : *reinterpret_cast<const float4*>(&da[at]);
       v[u] = *reinterpret_cast<const float4*>(&y[at]);
-      o2[u] = *reinterpret_cast<const uint2*>(&a[at]);
+      if (SKIP) o2[u] = *reinterpret_cast<const uint2*>(&a[at]);
     }
 #pragma unroll
     for (int u = 0; u < PB; ++u)
       if (active && p0 + u < t.passes && lane + (p0 + u) * t.rl < n) {
-        const float4 o = unpack4(o2[u]);
+        const float4 xh = make_float4((v[u].x - m.x) * rs.x, (v[u].y - m.y) * rs.y, (v[u].z - m.z) * rs.z, (v[u].w - m.w) * rs.w);
+        const float4 o = SKIP ? unpack4(o2[u]) : make_float4(fmaf(gm.x, xh.x, bt.x), fmaf(gm.y, xh.y, bt.y), fmaf(gm.z, xh.z, bt.z), fmaf(gm.w, xh.w, bt.w));
         const float dx = o.x > 0.f ? d[u].x : 0.f, dy = o.y > 0.f ? d[u].y : 0.f;
         const float dz = o.z > 0.f ? d[u].z : 0.f, dw = o.w > 0.f ? d[u].w : 0.f;
         sb.x += dx; sb.y += dy; sb.z += dz; sb.w += dw;
-        sg.x = fmaf(dx, (v[u].x - m.x) * rs.x, sg.x); sg.y = fmaf(dy, (v[u].y - m.y) * rs.y, sg.y);
-        sg.z = fmaf(dz, (v[u].z - m.z) * rs.z, sg.z); sg.w = fmaf(dw, (v[u].w - m.w) * rs.w, sg.w);
+        sg.x = fmaf(dx, xh.x, sg.x); sg.y = fmaf(dy, xh.y, sg.y);
+        sg.z = fmaf(dz, xh.z, sg.z); sg.w = fmaf(dw, xh.w, sg.w);
       }
   }
   const float4 tb = lanes_sum(sb, red, g, lane, t);
@@ -507,24 +533,32 @@ __global__ __launch_bounds__(NTF) void bn2d_bwd_finish_kernel(const float* __res
 // Step 3: dy = gamma * rstd * (dpre - sum_b/R - xhat * sum_g/R), stored bf16 (operand of the
 // backward products); with keep_dpre the masked gradient dpre replaces da (it also flows through
 // the skip connection).
-__global__ __launch_bounds__(NT) void bn2d_bwd_apply_kernel(float* __restrict__ da, const bf16_t* __restrict__ a,
+template <bool SKIP, bool POOL>
+__global__ __launch_bounds__(NT) void bn2d_bwd_apply_kernel(float* __restrict__ da, PoolGrad pool, const bf16_t* __restrict__ a,
                                                             const float* __restrict__ y, int64_t n4, int C, float inv_rows,
-                                                            const float* __restrict__ gamma, int round_params,
+                                                            const float* __restrict__ gamma, const float* __restrict__ beta, int round_params,
                                                             const float* __restrict__ mean, const float* __restrict__ rstd,
                                                             const float* __restrict__ sums, int keep_dpre,
                                                             bf16_t* __restrict__ dy) {
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
   if (i >= n4) return;
-  const int c = 4 * split_index((uint32_t)C >> 2).r;
-  const float4 d = reinterpret_cast<const float4*>(da)[i];
+  const Split at = split_index((uint32_t)C >> 2);
+  const int c = 4 * at.r;
+  const float4 d = POOL ? pool.at((uint32_t)at.q, c) : reinterpret_cast<const float4*>(da)[i];
   const float4 v = reinterpret_cast<const float4*>(y)[i];
-  const float4 o = unpack4(reinterpret_cast<const uint2*>(a)[i]);
-  float4 g = *reinterpret_cast<const float4*>(&gamma[c]);
+  const float4 g = param4(gamma, c, round_params);
   const float4 m = *reinterpret_cast<const float4*>(&mean[c]);
   const float4 r = *reinterpret_cast<const float4*>(&rstd[c]);
   const float4 sb = *reinterpret_cast<const float4*>(&sums[c]);
   const float4 sg = *reinterpret_cast<const float4*>(&sums[C + c]);
-  if (round_params) { g.x = round_bf16(g.x); g.y = round_bf16(g.y); g.z = round_bf16(g.z); g.w = round_bf16(g.w); }
+  float4 o;
+  if (SKIP) {
+    o = unpack4(reinterpret_cast<const uint2*>(a)[i]);
+  } else {
+    const float4 bt = param4(beta, c, round_params);
+    o = make_float4(fmaf(g.x, (v.x - m.x) * r.x, bt.x), fmaf(g.y, (v.y - m.y) * r.y, bt.y), fmaf(g.z, (v.z - m.z) * r.z, bt.z),
+                    fmaf(g.w, (v.w - m.w) * r.w, bt.w));
+  }
   float4 dp;
   dp.x = o.x > 0.f ? d.x : 0.f; dp.y = o.y > 0.f ? d.y : 0.f;
   dp.z = o.z > 0.f ? d.z : 0.f; dp.w = o.w > 0.f ? d.w : 0.f;
@@ -571,17 +605,6 @@ __global__ __launch_bounds__(NT) void avgpool_fwd_kernel(const bf16_t* __restric
   }
 }
 
-// da[n, p, c] = dpooled[n, c] / HW.
-__global__ __launch_bounds__(NT) void avgpool_bwd_kernel(const float* __restrict__ dpooled, int64_t ldd, int HW, int C,
-                                                         int64_t n4, float* __restrict__ da) {
-  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  if (i >= n4) return;
-  const Split at = split_index((uint32_t)C >> 2);          // position among all images' and column group
-  const int64_t img = (uint32_t)at.q / (uint32_t)HW;
-  const float inv = 1.f / (float)HW;
-  const float4 d = *reinterpret_cast<const float4*>(&dpooled[img * ldd + 4 * at.r]);
-  reinterpret_cast<float4*>(da)[i] = make_float4(d.x * inv, d.y * inv, d.z * inv, d.w * inv);
-}
 
 // ---- contraction slabs folded into a gradient ----------------------------------------------------
 // out[p] (+)= alpha * (slab_0[p] + slab_1[p] + ...), slabs in order.
@@ -913,18 +936,27 @@ int launch_bn2d_apply_fwd(const float* y, int64_t rows, int C, const float* gamm
   return VF_OK;
 }
 
-int launch_bn2d_bwd(float* da, const bf16_t* a, const float* y, int64_t rows, int C, const float* gamma,
-                    int round_params, const float* mean, const float* rstd, float* partial, float* sums,
-                    int keep_dpre, bf16_t* dy, GradOut gout_g, GradOut gout_b, hipStream_t s) {
-  if (rows <= 0 || !tall_ok(C) || !partial || !sums) return VF_EINVAL;
+int launch_bn2d_bwd(float* da, const float* dpooled, int64_t ldd, int HW, const bf16_t* a, const float* y, int64_t rows, int C,
+                    const float* gamma, const float* beta, int round_params, const float* mean, const float* rstd, float* partial,
+                    float* sums, int keep_dpre, bf16_t* dy, GradOut gout_g, GradOut gout_b, hipStream_t s) {
+  if (rows <= 0 || rows > 0x7fffffff || !tall_ok(C) || !partial || !sums || (!dpooled && !da) || (keep_dpre && !da)) return VF_EINVAL;
+  if (dpooled && (HW <= 0 || ldd < C || (ldd & 3))) return VF_EINVAL;
   const int nchunk = conv_chunks(rows);
-  bn2d_bwd_partial_kernel<<<nchunk, NT, tall_lds(C), s>>>(da, a, y, rows, C, chunk_rows(rows), mean, rstd, partial);
-  VF_LAUNCH_CHECK();
-  bn2d_bwd_finish_kernel<<<(C + FIN_COLS - 1) / FIN_COLS, NTF, 0, s>>>(partial, nchunk, C, sums, gout_g, gout_b);
-  VF_LAUNCH_CHECK();
+  const PoolGrad pool{dpooled, ldd, (uint32_t)HW};
   const int64_t n4 = rows * C / 4;
-  bn2d_bwd_apply_kernel<<<(unsigned)blocks(n4), NT, 0, s>>>(da, a, y, n4, C, 1.0f / (float)rows, gamma, round_params,
-                                                            mean, rstd, sums, keep_dpre, dy);
+#define VF_BN2D(SK, PO)                                                                                                         \
+  do {                                                                                                                          \
+    bn2d_bwd_partial_kernel<SK, PO><<<nchunk, NT, tall_lds(C), s>>>(da, pool, a, y, rows, C, chunk_rows(rows), gamma, beta,     \
+                                                                    round_params, mean, rstd, partial);                         \
+    VF_LAUNCH_CHECK();                                                                                                          \
+    bn2d_bwd_finish_kernel<<<(C + FIN_COLS - 1) / FIN_COLS, NTF, 0, s>>>(partial, nchunk, C, sums, gout_g, gout_b);             \
+    VF_LAUNCH_CHECK();                                                                                                          \
+    bn2d_bwd_apply_kernel<SK, PO><<<(unsigned)blocks(n4), NT, 0, s>>>(da, pool, a, y, n4, C, 1.0f / (float)rows, gamma, beta,   \
+                                                                      round_params, mean, rstd, sums, keep_dpre, dy);           \
+  } while (0)
+  if (a) { if (dpooled) VF_BN2D(true, true); else VF_BN2D(true, false); }
+  else   { if (dpooled) VF_BN2D(false, true); else VF_BN2D(false, false); }
+#undef VF_BN2D
   VF_LAUNCH_CHECK();
   return VF_OK;
 }
@@ -932,14 +964,6 @@ int launch_bn2d_bwd(float* da, const bf16_t* a, const float* y, int64_t rows, in
 int launch_avgpool_fwd(const bf16_t* a, int n_img, int HW, int C, bf16_t* pooled, int64_t ldp, hipStream_t s) {
   if (n_img <= 0 || HW <= 0 || !tall_ok(C) || ldp < C || (ldp & 3)) return VF_EINVAL;
   avgpool_fwd_kernel<<<n_img, NT, tall_lds(C), s>>>(a, HW, C, pooled, ldp);
-  VF_LAUNCH_CHECK();
-  return VF_OK;
-}
-
-int launch_avgpool_bwd(const float* dpooled, int64_t ldd, int n_img, int HW, int C, float* da, hipStream_t s) {
-  if (n_img <= 0 || HW <= 0 || !tall_ok(C) || ldd < C || (ldd & 3) || (int64_t)n_img * HW > 0x7fffffff) return VF_EINVAL;
-  const int64_t n4 = (int64_t)n_img * HW * C / 4;
-  avgpool_bwd_kernel<<<(unsigned)blocks(n4), NT, 0, s>>>(dpooled, ldd, HW, C, n4, da);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }

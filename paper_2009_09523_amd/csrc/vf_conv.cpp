@@ -270,10 +270,12 @@ class Conv final : public Model {
     return VF_OK;
   }
 
-  int bn_bwd(Ctx& c, ConvLayer& L, float* da, int rows, int keep_dpre, const float* P, float w, int node,
+  // `pooled`: the layer's output is the last one, whose gradient is that of the images' means.
+  int bn_bwd(Ctx& c, ConvLayer& L, float* da, int rows, bool skip, bool pooled, const float* P, float w, int node,
              hipStream_t st) {
-    VF_KS(c, st, "bn_bwd", launch_bn2d_bwd(da, L.a, L.y, rows, L.C, P + L.g_off, 1, L.mean, L.rstd, partial_, sums_,
-                                           keep_dpre, dy_, c.gout(L.g_off, w, node), c.gout(L.be_off, w, node), st));
+    VF_KS(c, st, "bn_bwd", launch_bn2d_bwd(da, pooled ? dpooled_ : nullptr, ldc_, HW_, skip ? L.a : nullptr, L.y, rows, L.C,
+                                           P + L.g_off, P + L.be_off, 1, L.mean, L.rstd, partial_, sums_, skip ? 1 : 0,
+                                           dy_, c.gout(L.g_off, w, node), c.gout(L.be_off, w, node), st));
     return VF_OK;
   }
 
@@ -298,20 +300,19 @@ class Conv final : public Model {
       if (go.accumulate) { ep.R = go.dst; ep.ldr = cfg_.classes; ep.beta = 1.f; }
       VF_KS(c, st, "gemm_wgrad", launch_gemm_bf16(pooledT_, ldb_, dzT_, ldb_, C_, cfg_.classes, b, 1, 0, ep, st));
     }
-    VF_KS(c, st, "avgpool", launch_avgpool_bwd(dpooled_, ldc_, b, HW_, C_, gA_, st));
     for (int blk = cfg_.n_blocks - 1; blk >= 0; --blk) {
       ConvLayer& L1 = layers_[1 + 2 * blk];
       ConvLayer& L2 = layers_[2 + 2 * blk];
-      // gA_: gradient w.r.t. the block's output; afterwards (keep_dpre) w.r.t. the sum before its ReLU,
+      // gA_: gradient w.r.t. the block's output (of the last block: dpooled_ instead); afterwards w.r.t. the sum before its ReLU,
       // which is also what flows through the skip connection
-      VF_TRY(bn_bwd(c, L2, gA_, rows, 1, P, w, i, st));
+      VF_TRY(bn_bwd(c, L2, gA_, rows, true, blk == cfg_.n_blocks - 1, P, w, i, st));
       VF_TRY(conv_wgrad(c, L2, rows, w, i, st));
       VF_TRY(conv_dgrad(c, L2, rows, gB_, nullptr, st));
-      VF_TRY(bn_bwd(c, L1, gB_, rows, 0, P, w, i, st));
+      VF_TRY(bn_bwd(c, L1, gB_, rows, false, false, P, w, i, st));
       VF_TRY(conv_wgrad(c, L1, rows, w, i, st));
       VF_TRY(conv_dgrad(c, L1, rows, gA_, gA_, st));          // through the convolutions + through the skip
     }
-    VF_TRY(bn_bwd(c, layers_[0], gA_, rows, 0, P, w, i, st));
+    VF_TRY(bn_bwd(c, layers_[0], gA_, rows, false, cfg_.n_blocks == 0, P, w, i, st));
     VF_TRY(conv_wgrad(c, layers_[0], rows, w, i, st));
     return VF_OK;
   }

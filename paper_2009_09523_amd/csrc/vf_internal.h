@@ -404,13 +404,13 @@ int launch_bn2d_stats_finish(const float* partial, int nchunk, int rows_per_chun
 // a = relu(gamma * (y - mean) * rstd + beta (+ skip)) as bf16
 int launch_bn2d_apply_fwd(const float* y, int64_t rows, int C, const float* gamma, const float* beta, int round_params,
                           const float* mean, const float* rstd, const bf16_t* skip, bf16_t* a, hipStream_t s);
-// backward of the above given da (gradient w.r.t. a): dgamma, dbeta into the gradient; dy (bf16)
-// the gradient w.r.t. y; with keep_dpre, da is replaced by the gradient w.r.t. the ReLU's input
-int launch_bn2d_bwd(float* da, const bf16_t* a, const float* y, int64_t rows, int C, const float* gamma,
-                    int round_params, const float* mean, const float* rstd, float* partial, float* sums,
-                    int keep_dpre, bf16_t* dy, GradOut gout_g, GradOut gout_b, hipStream_t s);
+// backward of the above given da (gradient w.r.t. a; with dpooled instead the gradient of the means over HW positions,
+// [images, ldd]): dgamma, dbeta into the gradient; dy (bf16) the gradient w.r.t. y; with keep_dpre, da receives the
+// gradient w.r.t. the ReLU's input.  a: the stored output where a skip was added, else null
+int launch_bn2d_bwd(float* da, const float* dpooled, int64_t ldd, int HW, const bf16_t* a, const float* y, int64_t rows, int C,
+                    const float* gamma, const float* beta, int round_params, const float* mean, const float* rstd, float* partial,
+                    float* sums, int keep_dpre, bf16_t* dy, GradOut gout_g, GradOut gout_b, hipStream_t s);
 int launch_avgpool_fwd(const bf16_t* a, int n_img, int HW, int C, bf16_t* pooled, int64_t ldp, hipStream_t s);
-int launch_avgpool_bwd(const float* dpooled, int64_t ldd, int n_img, int HW, int C, float* da, hipStream_t s);
 // dW[o, (kh, kw, c)] = sum over positions of dy[r, o] * x[r + (kh-1) W + (kw-1), c] (0 outside the
 // image) straight from dy [rows, Cout] and x [rows, Cin] (bf16, channels last), as up to max_split
 // slabs [Cout, 9 Cin] (slab_stride floats apart) of partial sums over slices of the positions, to
