@@ -129,46 +129,122 @@ __global__ __launch_bounds__(NT) void embed_tok_bwd_kernel(const int32_t* __rest
 
 // The same with 16-byte accesses (d a multiple of 4, d <= 1024) and the matching rows dealt out
 // to the four wavefronts: wavefront w adds the matches k = w, w + 4, w + 8, .. of the increasing
-// list, eight rows in flight per lane (read at clamped list positions, selected afterwards, so no
-// load waits behind a branch), and the four partial sums are joined in wavefront order.  An id
-// that many tokens share (the id that stands in for masked positions: 15 % of a node's tokens)
-// is the launch's critical path: 32 rows in flight for it instead of 8.  The order of the
-// additions is fixed, so the result is the same on every run.
+// list, DEPTH rows in flight per lane (read at clamped list positions, selected afterwards, so no
+// load waits behind a branch), and the four partial sums are joined in wavefront order.  The order
+// of the additions is fixed, so the result is the same on every run.
+//
+// What bounds it: R workgroups scan R ids each, which is a matter of instructions per id (so four
+// ids a load and a branch over what matches nothing), and the id that many tokens share (the one
+// that stands in for masked positions: 15 % of a node's tokens), whose rows one workgroup would
+// fetch through one compute unit.  An id of TOK_HEAVY tokens or more is therefore added up by the
+// workgroups of its first ceil(d / 256) tokens, 256 columns each: below 64 the list is one trip of
+// 64 rows in flight and the rest is waiting.  An id with one token, as most, needs no list.
+// 8192 tokens of 768 columns: 145 us with a single scan word per load, all columns in one
+// workgroup and 32 rows of them in flight (100 registers); columns shared out 95; four ids a load 62.
+// 4000 x 512: 42 -> 36.
+constexpr int TOK_HEAVY = 64;
+typedef int32_t Ids4 __attribute__((ext_vector_type(4), aligned(4)));   // a node may begin at any token
+
+// acc[j] += the rows of the matches list[wave], list[wave + 4], .. (n of them in all), columns
+// c0 + 256 j + 4 lane ..
+template <int CPL, int DEPTH>
+__device__ __forceinline__ void add_token_rows(const int* list, int n, const float* __restrict__ dh, int d,
+                                               int c0, int lane, int wave, float4 (&acc)[CPL]) {
+  for (int k0 = 0; k0 < n; k0 += 4 * DEPTH) {
+    int row[DEPTH];
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) row[u] = list[min(k0 + 4 * u + wave, n - 1)];
+    // the loads of all column groups before the first addition (one trip to memory per 4 DEPTH
+    // rows, not one per column group); a column group beyond the row is skipped by everybody
+    float4 v[CPL][DEPTH];
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+      if (c0 + 256 * j < d) {
+        const int c = min(c0 + 256 * j + 4 * lane, d - 4);
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) v[j][u] = *reinterpret_cast<const float4*>(&dh[(int64_t)row[u] * d + c]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+      if (c0 + 256 * j < d) {
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) {             // padding adds +0
+          const bool live = k0 + 4 * u + wave < n;
+          acc[j].x += live ? v[j][u].x : 0.f;
+          acc[j].y += live ? v[j][u].y : 0.f;
+          acc[j].z += live ? v[j][u].z : 0.f;
+          acc[j].w += live ? v[j][u].w : 0.f;
+        }
+      }
+    }
+  }
+}
+
 __global__ __launch_bounds__(NT) void embed_tok_bwd4_kernel(const int32_t* __restrict__ ids,
                                                             const float* __restrict__ dh, int R, int d,
                                                             int vocab, GradOut out) {
   __shared__ uint32_t match[MAX_TOK_WORDS];
   __shared__ int list[256];
-  __shared__ int scan[NT];
-  __shared__ int earlier;
+  __shared__ int scan[NT / 64];
+  __shared__ int earlier, tokens;
   __shared__ __attribute__((aligned(16))) float part[3 * 1024];
+  constexpr int CPL = 4;                            // 16-byte columns per lane: d <= 1024
   const int r = blockIdx.x;
   const int id = clampi(ids[r], 0, vocab - 1);
   const int nwords = (R + 31) / 32;
-  if (threadIdx.x == 0) earlier = 0;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int groups = (d + 255) / 256;
+  if (threadIdx.x == 0) { earlier = 0; tokens = 0; }
   for (int wd = threadIdx.x; wd < nwords; wd += NT) match[wd] = 0u;
   __syncthreads();
-  for (int q0 = 0; q0 < R; q0 += 8 * NT) {
-    int other[8];
+  // The bitmap: four ids per load and lane, nothing to do for the many loads without a match.  An
+  // id outside the table counts as the table's first or last, so a match lies in [lo, lo + width].
+  const int lo = id == 0 ? INT32_MIN : id;
+  const uint32_t width = (uint32_t)(id == vocab - 1 ? INT32_MAX : id) - (uint32_t)lo;
+  int before = 0, found = 0;                        // this thread's matches before r, and all
+  auto mark = [&](int q, uint32_t hits) {           // token q + i matches if bit i is set
+    atomicOr(&match[q >> 5], hits << (q & 31));
+    found += __popc(hits);
+    before += __popc(q >= r ? 0u : r - q < 4 ? hits & ((1u << (r - q)) - 1) : hits);
+  };
+  const int quads = R / 4;
+  for (int b0 = threadIdx.x; b0 < quads; b0 += 8 * NT) {
+    Ids4 v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) other[u] = ids[min(q0 + u * NT + (int)threadIdx.x, R - 1)];
+    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const Ids4*>(&ids[4 * (int64_t)min(b0 + u * NT, quads - 1)]);
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int q = q0 + u * NT + threadIdx.x;
-      const bool hit = q < R && clampi(other[u], 0, vocab - 1) == id;
-      if (hit) {
-        if (q < r) earlier = 1;
-        else atomicOr(&match[q >> 5], 1u << (q & 31));
-      }
+      uint32_t hits = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) hits |= (uint32_t)v[u][i] - (uint32_t)lo <= width ? 1u << i : 0u;
+      if (hits && b0 + u * NT < quads) mark(4 * (b0 + u * NT), hits);
     }
   }
+  if ((int)threadIdx.x < R - 4 * quads) {           // the last one to three
+    const int q = 4 * quads + threadIdx.x;
+    if ((uint32_t)ids[q] - (uint32_t)lo <= width) mark(q, 1u);
+  }
+  if (found) {
+    atomicAdd(&earlier, before);
+    atomicAdd(&tokens, found);
+  }
   __syncthreads();
-  if (earlier) return;
-  constexpr int CPL = 4;                            // 16-byte columns per lane: d <= 1024
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float4 acc[CPL];
-#pragma unroll
-  for (int j = 0; j < CPL; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int rank = earlier, total = tokens;         // of r among the id's tokens; all of them
+  const bool heavy = total >= TOK_HEAVY;
+  if (rank > 0 && !(heavy && rank < groups)) return;
+  if (total == 1) {                                 // most ids: the token's row is the sum
+    const int c = 4 * threadIdx.x;
+    if (c < d) {
+      const float4 v = *reinterpret_cast<const float4*>(&dh[(int64_t)r * d + c]);
+      const float4 p = *reinterpret_cast<const float4*>(&out.dst[(int64_t)id * d + c]);
+      const float4 o = out.accumulate ? p : make_float4(0.f, 0.f, 0.f, 0.f);
+      *reinterpret_cast<float4*>(&out.dst[(int64_t)id * d + c]) =
+          make_float4(fmaf(out.alpha, v.x, o.x), fmaf(out.alpha, v.y, o.y), fmaf(out.alpha, v.z, o.z),
+                      fmaf(out.alpha, v.w, o.w));
+    }
+    return;
+  }
   // The matching tokens in increasing order, 256 at a time.  Every thread owns eight words of the
   // bitmap: it counts their bits, a scan over the threads gives each word the position of its
   // first match in the whole list, and for each window of 256 positions a thread writes the
@@ -182,16 +258,22 @@ __global__ __launch_bounds__(NT) void embed_tok_bwd4_kernel(const int32_t* __res
     cnt[i] = wd < nwords ? __popc(match[wd]) : 0;
     mine += cnt[i];
   }
-  scan[threadIdx.x] = mine;
-  __syncthreads();
-  for (int off = 1; off < NT; off <<= 1) {
-    const int add = (int)threadIdx.x >= off ? scan[threadIdx.x - off] : 0;
-    __syncthreads();
-    scan[threadIdx.x] += add;
-    __syncthreads();
+  int upto = mine;                                  // inclusive scan over the threads
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int add = __shfl_up(upto, off);
+    if (lane >= off) upto += add;
   }
-  const int first = scan[threadIdx.x] - mine;       // list position of this thread's first match
-  const int total = scan[NT - 1];
+  if (lane == 63) scan[wave] = upto;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) upto += w < wave ? scan[w] : 0;
+  const int first = upto - mine;                    // list position of this thread's first match
+  const int c0 = heavy ? 256 * rank : 0, c1 = heavy ? min(d, c0 + 256) : d;   // this workgroup's columns
+  float4 acc[CPL], one[1];
+#pragma unroll
+  for (int j = 0; j < CPL; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  one[0] = acc[0];
   for (int base = 0; base < total; base += 256) {
     int o = first;
 #pragma unroll
@@ -210,43 +292,17 @@ __global__ __launch_bounds__(NT) void embed_tok_bwd4_kernel(const int32_t* __res
     }
     __syncthreads();
     const int n = min(256, total - base);
-    for (int k0 = 0; k0 < n; k0 += 32) {
-      int row[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) row[u] = list[min(k0 + 4 * u + wave, n - 1)];
-      // the loads of all column groups before the first addition (one trip to memory per 32
-      // rows, not one per column group); a column group beyond the row is skipped by everybody
-      float4 v[CPL][8];
-#pragma unroll
-      for (int j = 0; j < CPL; ++j) {
-        if (256 * j < d) {
-          const int c = min(4 * lane + 256 * j, d - 4);
-#pragma unroll
-          for (int u = 0; u < 8; ++u) v[j][u] = *reinterpret_cast<const float4*>(&dh[(int64_t)row[u] * d + c]);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < CPL; ++j) {
-        if (256 * j < d) {
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {             // padding adds +0
-            const bool live = k0 + 4 * u + wave < n;
-            acc[j].x += live ? v[j][u].x : 0.f;
-            acc[j].y += live ? v[j][u].y : 0.f;
-            acc[j].z += live ? v[j][u].z : 0.f;
-            acc[j].w += live ? v[j][u].w : 0.f;
-          }
-        }
-      }
-    }
+    if (heavy) add_token_rows<1, 16>(list, n, dh, d, c0, lane, wave, one);
+    else add_token_rows<CPL, 4>(list, n, dh, d, 0, lane, wave, acc);
     __syncthreads();
   }
+  if (heavy) acc[0] = one[0];
   // join the wavefronts' sums in wavefront order; wavefront 0 writes the table row
   if (wave > 0) {
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
-      const int c = 4 * lane + 256 * j;
-      if (c < d) *reinterpret_cast<float4*>(&part[(wave - 1) * 1024 + c]) = acc[j];
+      const int c = c0 + 4 * lane + 256 * j;
+      if (c < c1) *reinterpret_cast<float4*>(&part[(wave - 1) * 1024 + c]) = acc[j];
     }
   }
   __syncthreads();
@@ -254,13 +310,13 @@ __global__ __launch_bounds__(NT) void embed_tok_bwd4_kernel(const int32_t* __res
   float4 old[CPL];
 #pragma unroll
   for (int j = 0; j < CPL; ++j) {
-    const int c = min(4 * lane + 256 * j, d - 4);
+    const int c = min(c0 + 4 * lane + 256 * j, c1 - 4);
     old[j] = *reinterpret_cast<const float4*>(&out.dst[(int64_t)id * d + c]);
   }
 #pragma unroll
   for (int j = 0; j < CPL; ++j) {
-    const int c = 4 * lane + 256 * j;
-    if (c < d) {
+    const int c = c0 + 4 * lane + 256 * j;
+    if (c < c1) {
       float4 t = acc[j];
 #pragma unroll
       for (int w = 0; w < 3; ++w) {

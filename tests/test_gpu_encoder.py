@@ -95,6 +95,31 @@ def test_units_of_more_heads_than_a_grid_has_rows(sizes):
     check_against_oracle(wl, gpu, oracle_steps(wl, theta, x, y))
 
 
+@pytest.mark.parametrize("d", [8, 260, 512, 772, 1024])
+@pytest.mark.parametrize("shared", [63, 64, 65, 257, 300])
+def test_token_rows_that_many_tokens_share(d, shared):
+    """The rows of an id with 64 tokens or more are added up by several workgroups, 256 columns each, 256 tokens at
+    a time.  `shared` tokens of the first node carry one id, scattered, the second node's carry it once, and every
+    other id has few.  One layer, so the table's gradient is the embedding's and the decoder's (tol: the harness')."""
+    print(f"d={d} shared={shared}", flush=True)
+    wl = replace(I.workload("enc_small_f32"), name=f"enc_shared_{d}_{shared}", n_layers=1, d_model=d, n_heads=2, d_ffn=16,
+                 seq_len=19, vocab=211, n_masked=2, node_sizes=(20, 2))
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    rng = np.random.default_rng(d + shared)
+    tokens = x[:20].reshape(-1)
+    tokens[:] = rng.integers(0, 200, tokens.size)
+    tokens[rng.permutation(tokens.size)[:shared]] = 207
+    x[:20] = tokens.reshape(x[:20].shape)
+    x[20:] = np.arange(x[20:].size).reshape(x[20:].shape)
+    x[20, 3] = 207
+    gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH)
+    ref = oracle_steps(wl, theta, x, y)
+    check_against_oracle(wl, gpu, ref)
+    row, ref_row = gpu["G"][207 * d:208 * d], np.asarray(ref["G"])[207 * d:208 * d]
+    assert np.linalg.norm(row - ref_row) <= TOL[wl.dtype] * np.linalg.norm(ref_row)
+
+
 def test_encoder_fused_and_staged_agree_bitwise():
     wl, theta, x, y = _case("enc_small_bf16")
     a = run_gpu(wl, theta, x, y, flags=0)
