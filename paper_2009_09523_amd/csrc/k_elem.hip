@@ -82,12 +82,14 @@ __global__ __launch_bounds__(256) void transpose64_jobs_kernel(TransposeJobs tj)
 // (blockIdx.x runs over their tiles; up to 17 launches of 5 us otherwise).  Every thread reads 16 bytes and writes 8 bytes at a time in both
 // orientations; rows of C elements that are no multiple of 4, or unaligned, are read element by element (768 x 30522: 54 us by 32 x 32
 // tiles of single elements; with sixteen matrices of 28 million elements beside it 74 here).  Requires ldn, ldt % 4 == 0, ldn >= C rounded up to 4, ldt >= R rounded up to 4
-// (the padding receives zeros), nat and tr 8-byte aligned.
-__global__ __launch_bounds__(256) void cast_weight_kernel(CastJobs jobs) {
+// (the padding receives zeros), nat and tr 8-byte aligned.  MAX is 1 where a matrix goes alone (an MLP's layers): the list of
+// sixteen is 1.1 KB of arguments, which cost the host 1 us a launch (98 rows of seven layers, bound by launches: 293 | 287 us).
+template <int MAX>
+__global__ __launch_bounds__(256) void cast_weight_kernel(CastJobList<MAX> jobs) {
   __shared__ bf16_t tile[64][64 + 2];
   int j = 0;
 #pragma unroll
-  for (int i = 0; i < kCastJobs; ++i) j += (int)blockIdx.x >= jobs.end[i] ? 1 : 0;
+  for (int i = 0; i < MAX && MAX > 1; ++i) j += (int)blockIdx.x >= jobs.end[i] ? 1 : 0;
   const CastJob& job = jobs.job[j];
   const int R = job.R, C = job.C;
   const float* __restrict__ in = job.in;
@@ -215,8 +217,9 @@ int launch_transpose_nodes(const NodeList& nl, int64_t ldi, int64_t ldo, int C, 
   return VF_OK;
 }
 
-int launch_cast_weights(CastJobs jobs, hipStream_t s) {
-  if (jobs.count < 1 || jobs.count > kCastJobs) return VF_EINVAL;
+template <int MAX>
+static int launch_cast_list(CastJobList<MAX>& jobs, hipStream_t s) {
+  if (jobs.count < 1 || jobs.count > MAX) return VF_EINVAL;
   int64_t end = 0;
   for (int j = 0; j < jobs.count; ++j) {
     CastJob& g = jobs.job[j];
@@ -228,18 +231,20 @@ int launch_cast_weights(CastJobs jobs, hipStream_t s) {
     if (end > 0x7fffffff) return VF_EINVAL;
     jobs.end[j] = (int)end;
   }
-  for (int j = jobs.count; j < kCastJobs; ++j) jobs.end[j] = 0x7fffffff;
-  cast_weight_kernel<<<(unsigned)end, 256, 0, s>>>(jobs);
+  for (int j = jobs.count; j < MAX; ++j) jobs.end[j] = 0x7fffffff;
+  cast_weight_kernel<MAX><<<(unsigned)end, 256, 0, s>>>(jobs);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }
 
+int launch_cast_weights(CastJobs jobs, hipStream_t s) { return launch_cast_list(jobs, s); }
+
 int launch_cast_weight(const float* w, int R, int C, bf16_t* nat, int64_t ldn, bf16_t* tr, int64_t ldt, hipStream_t s) {
   if (R <= 0 || C <= 0) return VF_OK;
-  CastJobs jobs{};
+  CastJobList<1> jobs{};
   jobs.job[0] = {w, R, C, nat, ldn, tr, ldt, 0};
   jobs.count = 1;
-  return launch_cast_weights(jobs, s);
+  return launch_cast_list(jobs, s);
 }
 
 int launch_cast_bf16(const float* in, int64_t ldi, bf16_t* out, int64_t ldo, int R, int C,

@@ -320,12 +320,14 @@ struct CastJob {
   int64_t ldt;
   int vec;                       // (set by the launch)
 };
-constexpr int kCastJobs = 16;
-struct CastJobs {
+template <int MAX>
+struct CastJobList {
   int count;
-  int end[kCastJobs];            // tiles of a job and those before it (set by the launch)
-  CastJob job[kCastJobs];
+  int end[MAX];                  // tiles of a job and those before it (set by the launch)
+  CastJob job[MAX];
 };
+constexpr int kCastJobs = 16;
+using CastJobs = CastJobList<kCastJobs>;
 int launch_cast_weights(CastJobs jobs, hipStream_t s);   // several matrices in one launch
 int launch_cast_weight(const float* w, int R, int C, bf16_t* nat, int64_t ldn, bf16_t* tr,
                        int64_t ldt, hipStream_t s);

@@ -131,3 +131,21 @@ def test_stage_loop_of_the_direct_kernel_goes_from_the_wait_to_the_barrier(gemm_
         assert not [i for i in ins if i.startswith("v_readfirstlane")], name
         wait = [k for k, i in enumerate(ins) if i.startswith("s_waitcnt") and "vmcnt" in i][0]
         assert ins[wait + 1].startswith("s_barrier") and "lgkmcnt(0)" in ins[wait], (name, ins[wait:wait + 4])
+
+
+def test_a_weight_copy_alone_does_not_carry_a_job_list(tmp_path):
+    """An MLP copies its weights layer by layer, one launch each, and its small steps are bound by the launches: with the
+    list of sixteen jobs among their arguments (1.1 KB a launch) a step of seven layers took 293 us instead of 287."""
+    from paper_2009_09523_amd import build as vfbuild
+    if not os.path.exists(vfbuild.HIPCC):
+        pytest.skip("hipcc not available")
+    out = tmp_path / "k_elem.s"
+    cmd = [vfbuild.HIPCC, *vfbuild.FLAGS, "-x", "hip", "--cuda-device-only", "-S", os.path.join(vfbuild.CSRC, "k_elem.hip"), "-o", str(out)]
+    assert subprocess.run(cmd, capture_output=True).returncode == 0
+    sizes = []
+    for entry in re.split(r"\n  - \.", out.read_text().split("amdhsa.kernels:")[1]):
+        if re.search(r"\.name: +\S*cast_weight_kernel", entry):
+            explicit = [(int(o), int(z)) for o, z, kind in
+                        re.findall(r"\.offset: +(\d+)\s+\.size: +(\d+)\s+\.value_kind: +(\w+)", entry) if not kind.startswith("hidden")]
+            sizes.append(max(o + z for o, z in explicit))
+    assert len(sizes) == 2 and min(sizes) <= 128, sizes
