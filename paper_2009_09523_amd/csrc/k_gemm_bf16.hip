@@ -2837,7 +2837,13 @@ int launch_conv3x3_bf16(const bf16_t* x, int64_t rows, int H, int W, int Cin, co
   // 65535 row tiles (4.2 million positions), its first does not.
   const int64_t mtiles = (rows + 63) / 64;
   ConvOperand cv{H, W, Cin, zeros, 0, mtiles > 65535, nullptr};
-  if (stats && stats_chunks && stats_rows && plain && !ep.R && mtiles <= 0x7fffffff) {
+  // Many positions of few channels: the finish kernel, a workgroup per eight channels, joins 64 chunks a lane and more, and a
+  // pass over so narrow an output costs less.  Steps of one block, us with the
+  // pass | with the epilogue: 16 channels of 65536 positions 247 | 241, of 131072 332 | 333, of 4.2 million 7406 | 7774; 40
+  // of 131072 457 | 459, of 4.2 million 12578 | 12765; 56 of 4.2 million 15907 | 15943, 72 of 524288 3387 | 3401; 128 of
+  // 4.2 million 27999 | 27477.
+  const bool few_chunks = N >= 64 || rows <= 65536;
+  if (stats && stats_chunks && stats_rows && plain && !ep.R && few_chunks) {
     cv.stats = stats;
     *stats_chunks = (int)mtiles; *stats_rows = 64;
   }

@@ -84,15 +84,29 @@ def test_channel_counts_that_are_multiples_of_eight(width, img, sizes):
     check_against_oracle(wl, gpu, ref)
 
 
-def test_more_row_tiles_than_a_grids_second_dimension():
-    """A node of 4.3 million positions (66560 tiles of 64).  Its 1040 images are 8 images 130 times over, so statistics,
-    loss and gradient (means over the node) are those of the 8 images."""
-    few = replace(I.workload("conv_tiny_bf16"), name="conv_w16_img64", img=64, width=16, node_sizes=(8,))
-    many = replace(few, name="conv_w16_img64_many", node_sizes=(1040,))
+@pytest.mark.parametrize("width", [16, 72])
+def test_more_row_tiles_than_a_grids_second_dimension(width):
+    """A node of 4.3 million positions (66560 tiles of 64); the statistics come from a pass of their own (16 channels) and
+    from the product's epilogue (72).  Its 1040 images are 8 images 130 times over, so statistics, loss and gradient (means
+    over the node) are those of the 8 images."""
+    print(f"width={width}", flush=True)
+    few = replace(I.workload("conv_tiny_bf16"), name=f"conv_w{width}_img64", img=64, width=width, node_sizes=(8,))
+    many = replace(few, name=f"conv_w{width}_img64_many", node_sizes=(1040,))
     theta = I.make_params(few, jitter=0.1)
     x, y = I.make_batch(few)
     gpu = run_gpu(many, theta, np.tile(x, (130, 1, 1, 1)), np.tile(y, 130), flags=FUSED | NO_GRAPH)
     check_against_oracle(few, gpu, oracle_steps(few, theta, x, y))
+
+
+@pytest.mark.parametrize("width", [16, 56])
+def test_statistics_of_few_channels_beside_the_limit_on_positions(width):
+    """Below 64 channels a node of 65536 positions has its statistics from the product's epilogue, the next larger one from
+    a pass of its own."""
+    print(f"width={width}", flush=True)
+    wl = replace(I.workload("conv_tiny_bf16"), name=f"conv_limit_w{width}", img=32, width=width, node_sizes=(64, 65))
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH), oracle_steps(wl, theta, x, y))
 
 
 @pytest.mark.parametrize("width,pitch", [(64, 32), (24, 32), (8, 72)])
