@@ -711,9 +711,16 @@ static bool near32(bool kc, int64_t ld, int rows, int K) {
 // only, so with long contractions of many rows its few workgroups cost more than the BatchNorm launch they save.  Steps of
 // K-N-N-10 networks of three nodes, launches apart | fused (us): 16 rows, N = 64, K = 1000 115 | 86; 32 rows, N = 1000,
 // K = 1000 193 | 180; 64 rows, N = 256, K = 256 124 | 104, K = 512 111 | 118; 100 rows, N = 500, K = 64 131 | 129, K = 256 136 | 171.
+// And while the columns are not so many that a compute unit has several workgroups, each reading all rows again (rows times
+// columns; forward, where the columns are strided, also columns times contraction).  Forward, K-N-10, three nodes: 8 rows,
+// K = 1024, N = 8192 216 | 199, N = 16384 304 | 316; 64 rows, K = 256, N = 16384 222 | 219; 128 rows, K = 128, N = 8192
+// 150 | 148, N = 16384 226 | 242.  Backward, 64-N-K: 8 rows, K = 1024, N = 16384 403 | 392; 96 rows, K = 170, N = 16384
+// 354 | 324; 128 rows, K = 128, N = 16384 318 | 319.
 bool f32_bn_takes(int R, int N, int K, int64_t lda, int64_t ldb, bool backward) {
   if (R < 1 || R > 128 || N < 1 || K < 1) return false;
-  return (int64_t)((R + 31) / 32 * 32) * K <= (R <= 32 ? 32768 : 16384) && near32(true, lda, R, K) && near32(backward, ldb, N, K);
+  const int64_t rows = (R + 31) / 32 * 32;
+  if (rows * N > (backward ? 3 << 19 : 1 << 20) || (!backward && (int64_t)N * K > 1 << 23)) return false;
+  return rows * K <= (R <= 32 ? 32768 : 16384) && near32(true, lda, R, K) && near32(backward, ldb, N, K);
 }
 
 int launch_gemm_f32_bn(const float* A, int64_t lda, const float* B, int64_t ldb, int R, int N, int K, bool backward,

@@ -68,6 +68,22 @@ def test_f32_fused_launches_at_their_edges(name, dims, nodes):
     check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=FUSED, node_group=4), ref)
 
 
+@pytest.mark.parametrize("name,dims,rows,tag,taken", [
+    ("mlp_small_bn_f32", (64, 8192, 10), 128, "gemm_fwd_bn", True), ("mlp_small_bn_f32", (64, 8193, 10), 128, "gemm_fwd_bn", False),
+    ("mlp_small_bn_f32", (1024, 8192, 10), 8, "gemm_fwd_bn", True), ("mlp_small_bn_f32", (1024, 8193, 10), 8, "gemm_fwd_bn", False),
+    ("mlp_small_bn_f32", (24, 12288, 20), 128, "gemm_dgrad_bn", True), ("mlp_small_bn_f32", (24, 12289, 20), 128, "gemm_dgrad_bn", False)])
+def test_one_launch_per_product_only_up_to_so_many_columns(name, dims, rows, tag, taken):
+    """A workgroup of the launches that take BatchNorm along reads all rows of its node for 16 columns: on wide layers that
+    is slower than the launches apart, and they go apart."""
+    print(f"{name} dims={dims} rows={rows}", flush=True)
+    wl = dataclasses.replace(I.workload(name), dims=dims, node_sizes=(rows,))
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH, profile=True)
+    assert (tag in gpu["launches"]) == taken, sorted(gpu["launches"])
+    check_against_oracle(wl, gpu, oracle_steps(wl, theta, x, y))
+
+
 @pytest.mark.parametrize("dims,rows", [((31, 2051, 33), 1100), ((99, 2051, 100), 1100), ((130, 2051, 131), 1100), ((260, 2051, 204), 1100),
                                        ((700, 2051, 321), 1100), ((131, 2051, 260), 2100), ((81, 2100, 97), 2100),
                                        ((100, 4100, 129), 4200), ((129, 4100, 256), 4200), ((2051, 1101, 10), 24),

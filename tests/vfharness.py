@@ -27,8 +27,9 @@ def to_device_batch(wl, x, y, device="cuda"):
 
 
 def run_gpu(wl, theta, x, y, node_sizes=None, flags=0, steps=1, max_node_size=None, max_nodes=None,
-            max_batch=None, fold_window=0, node_group=0):
-    """Runs `steps` vf_step calls on the same batch; returns the results of the last one."""
+            max_batch=None, fold_window=0, node_group=0, profile=False):
+    """Runs `steps` vf_step calls on the same batch; returns the results of the last one (profile: and which launches
+    they made, by tag)."""
     import torch
     import paper_2009_09523_amd as vf
     from paper_2009_09523_amd.binding import config_from_workload
@@ -43,12 +44,15 @@ def run_gpu(wl, theta, x, y, node_sizes=None, flags=0, steps=1, max_node_size=No
     params = torch.from_numpy(theta.astype(np.float32)).cuda()
     xt, yt = to_device_batch(wl, x, y)
     torch.cuda.synchronize()
+    if profile:
+        eng.profile_start()
     for _ in range(steps):
         eng.step(params, xt, yt, sizes)
+    launches = eng.profile_stop() if profile else {}
     G = torch.empty_like(params)
     eng.grads(G)
     out = {"G": G.cpu().numpy(), "loss": eng.loss(), "node_losses": eng.node_losses(len(sizes)),
-           "t": eng.step_count, "workspace_bytes": eng.workspace_bytes, "streams": eng.streams}
+           "t": eng.step_count, "launches": launches, "workspace_bytes": eng.workspace_bytes, "streams": eng.streams}
     s0 = torch.empty_like(params)
     eng.opt_state(0, s0)
     out["s0"] = s0.cpu().numpy()
