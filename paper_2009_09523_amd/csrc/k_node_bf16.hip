@@ -180,11 +180,17 @@ __global__ __launch_bounds__(NTN) void gemm_bf16_node_kernel(const bf16_t* __res
 // K = 256 232 | 200; 32 rows, N = 512, K = 1024 249 | 224; 64 rows, N = 512, K = 256 220 | 196; 128 rows, N = 512, K = 256
 // 228 | 210, N = 256, K = 1024 240 | 248, N = K = 4096 656 | 728.
 constexpr int64_t kNodeWork = 49152;
+// Rows times columns, and columns times contraction, up to which it does: beyond, a compute unit has several workgroups.
+// 64-N-K, four nodes: 32 rows, K = 768, N = 8192 346 | 332, N = 16384 406 | 407, K = 1536 496 | 489, 632 | 656; 64 rows,
+// K = 384, N = 8192 206 | 201, N = 16384 326 | 331; 128 rows, K = 384, N = 4096 191 | 185, N = 8192 231 | 241, N = 16384
+// 303 | 339.
+constexpr int64_t kNodeOut = 1 << 19, kNodeWeights = 1 << 24;
 
 bool node_bn_bwd_takes(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int R, int N, int K, const NodeBnArgs& f) {
   if (R < 1 || R > 128 || N < 1 || K < 1 || !A || !B || !f.z || !f.out || !f.outT) return false;
   const int64_t K8 = (K + 7) & ~7;
-  if ((R + 31) / 32 * 32 * K8 > kNodeWork) return false;
+  const int64_t rows = (R + 31) / 32 * 32;
+  if (rows * K8 > kNodeWork || rows * N > kNodeOut || N * K8 > kNodeWeights) return false;
   if ((lda & 7) || (ldb & 7) || lda < K8 || ldb < K8 || (f.ldt & 7) || f.ldt < ((R + 7) & ~7)) return false;
   auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   if (!al(A) || !al(B) || !al(f.outT)) return false;

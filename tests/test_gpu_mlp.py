@@ -71,7 +71,10 @@ def test_f32_fused_launches_at_their_edges(name, dims, nodes):
 @pytest.mark.parametrize("name,dims,rows,tag,taken", [
     ("mlp_small_bn_f32", (64, 8192, 10), 128, "gemm_fwd_bn", True), ("mlp_small_bn_f32", (64, 8193, 10), 128, "gemm_fwd_bn", False),
     ("mlp_small_bn_f32", (1024, 8192, 10), 8, "gemm_fwd_bn", True), ("mlp_small_bn_f32", (1024, 8193, 10), 8, "gemm_fwd_bn", False),
-    ("mlp_small_bn_f32", (24, 12288, 20), 128, "gemm_dgrad_bn", True), ("mlp_small_bn_f32", (24, 12289, 20), 128, "gemm_dgrad_bn", False)])
+    ("mlp_small_bn_f32", (24, 12288, 20), 128, "gemm_dgrad_bn", True), ("mlp_small_bn_f32", (24, 12289, 20), 128, "gemm_dgrad_bn", False),
+    ("mlp_mid_bn_bf16", (64, 4096, 40), 97, "gemm_dgrad_bn", True), ("mlp_mid_bn_bf16", (64, 4097, 40), 97, "gemm_dgrad_bn", False),
+    ("mlp_mid_bf16", (16, 10922, 1536), 8, "gemm_dgrad_bn", True), ("mlp_mid_bf16", (16, 10923, 1536), 8, "gemm_dgrad_bn", False),
+    ("mlp_mid_bf16", (24, 16384, 20), 32, "gemm_dgrad_bn", True), ("mlp_mid_bf16", (24, 16388, 20), 32, "gemm_dgrad_bn", False)])
 def test_one_launch_per_product_only_up_to_so_many_columns(name, dims, rows, tag, taken):
     """A workgroup of the launches that take BatchNorm along reads all rows of its node for 16 columns: on wide layers that
     is slower than the launches apart, and they go apart."""
