@@ -310,14 +310,29 @@ class Mlp final : public Model {
   // One per layer: its output gradient and that one's transposed copy.
   int pieces() const override { return bf16_ ? (int)layers_.size() : 0; }
   // Beside each other the weight gradients fill what the input-gradient products, the BatchNorm passes and their launches
-  // leave idle, and the update moves behind the backward part.  Steps, one after the other | beside each other: 8 x 128
-  // 1024-2048^3-1000 372 | 333 us, 1024-4096^3-1000 647 | 635; 32 x 128 784-1000-500-10 413 | 344; 2 x 300 1024-4096^3-1000
-  // 895 | 861.  Not with fewer rows, where the events cost more (1 x 128 1024^4-1000 172 | 181) or the products take all
-  // compute units and the update loses its company (4 x 128 1024-4096^3-1000 549 | 569), and not with so many parameters
-  // that the weight gradients fill the chip for milliseconds (2048-8192^6-1000, 64 x 128: 15.8 | 16.1 ms).
+  // leave idle, and the update moves behind the backward part; it costs a pair of events a layer.  Steps, one after the
+  // other | beside each other (us), of some 400 measured with one to six hidden layers:
+  //  * not with so many parameters that the weight gradients fill the chip by themselves: 2048-6144^2-1000 (57 M) 8 x 128
+  //    821 | 783, 32 x 128 1916 | 1966; 1024-6144^3-10 (82 M) 64 x 128 5079 | 5307; 2048-8192^6-1000 15507 | 15824.
+  //  * a node that goes alone: with enough of weight gradients to hide.  2 x 256 256-256^2-10 212 | 221, 1024-1536^4-1000
+  //    357 | 350, 4 x 300 1024-2048^2-100 (2.0e9 rows x parameters) 368 | 375, 1024-6144-512-1000 (3.0e9) 430 | 405, 3 x 700
+  //    784-2048-100 (1.3e9) 232 | 243, 1024-1536^2-100 (2.9e9) 344 | 328; alone in its step 1 x 1024 1024-768-10 127 | 136,
+  //    784-256-1024^2-10 (1.6e9) 212 | 205, 1024^4-1000 225 | 220, but below 1024 rows 1 x 256 1024-4096^3-1000 461 | 476.
+  //  * a unit of several, from 1024 rows on (below, the products take all compute units and the update loses its company: 4 x
+  //    128 1024-4096^3-1000 549 | 569): whole nodes of 128 rows on the 128 x 128 tiles with the BatchNorm passes, whose
+  //    steps of small networks have little else (16 x 128 256^3-10 186 | 192, 64-512^4-10 299 | 269; two units, 48 x 128
+  //    256-4096-10 380 | 400, 784-256-1024^2-10 518 | 516, six layers of 256 641 | 610), others always (24 x 100 64-256-100
+  //    182 | 163, 256^3-10 284 | 230) but for two units of the very smallest (64 x 64 64-256-100 264 | 275).
   bool side_early(const StepArgs& s) const override {
-    const int last = s.V - 1;
-    return P_ <= ((int64_t)128 << 20) && (s.sizes[last] >= 1024 || (s.V > 1 && s.count[last] == 1 && s.sizes[last] > 128));
+    const int last = s.V - 1, rows = s.sizes[last];
+    if (P_ > (int64_t)64 << 20) return false;
+    if (s.count[last] == 1 && rows > 128) return (s.V > 1 ? rows * P_ >= 2100000000 : rows >= 1024 && rows * P_ >= 1400000000);
+    if (rows < 1024) return false;
+    bool whole = true;
+    for (int n = 0; n < s.count[last] && whole; ++n) whole = s.rows_of(last)[n] == 128;
+    for (const Layer& L : layers_) whole = whole && (!L.hidden || L.N % 128 == 0);
+    if (!whole) return s.V == 1 || P_ >= 1 << 16;
+    return P_ >= (s.V > 1 && layers_.size() < 6 ? 3 << 19 : 1 << 19);
   }
 
   static LossNodes loss_nodes(const StepArgs& s, int first) {

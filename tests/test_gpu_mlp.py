@@ -696,6 +696,26 @@ def test_bf16_nodes_in_one_launch_per_product_match_the_oracle(name, dims, nodes
     check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=FUSED, fold_window=4), oracle_steps(wl, theta, x, y))
 
 
+@pytest.mark.parametrize("dims,nodes,window", [((64, 256, 264, 24), (100,) * 11, 8), ((64, 256, 264, 24), (100,) * 44, 1),
+                                               ((64, 256, 264, 24), (100,) * 44, 8), ((256, 512, 1024, 24), (128,) * 9, 8),
+                                               ((512, 1536, 1536, 100), (131, 613, 700), 1), ((512, 1536, 1536, 100), (131, 613, 700), 2),
+                                               ((512, 1536, 1536, 100), (131, 613, 700), 8)])
+def test_last_units_weight_gradients_beside_its_backward_part(dims, nodes, window):
+    """Steps large enough for it (rows of the last unit, parameters) with two streams: one unit, two in one window and in two,
+    lone nodes with one window before and with other units of the window before.  The oracle's result, and the bits of
+    one stream, in a second step from the first one's state too."""
+    wl = dataclasses.replace(I.workload("mlp_mid_bn_bf16"), dims=dims, node_sizes=nodes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    one = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH, fold_window=window, node_group=32)
+    check_against_oracle(wl, one, oracle_steps(wl, theta, x, y))
+    for steps in (1, 2):
+        one = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH, fold_window=window, node_group=32, steps=steps)
+        two = run_gpu(wl, theta, x, y, flags=BENCH, fold_window=window, node_group=32, steps=steps)
+        assert two["G"].tobytes() == one["G"].tobytes() and two["theta"].tobytes() == one["theta"].tobytes()
+        assert two["s0"].tobytes() == one["s0"].tobytes()
+
+
 def test_node_groups_keep_the_workspace_independent_of_the_node_count():
     wl, theta, x, y = _case("mlp_mid_bn_bf16")
     few = run_gpu(wl, theta, x[:80], y[:80], node_sizes=[40, 40], flags=FUSED, node_group=4, max_node_size=40,
