@@ -654,7 +654,7 @@ def test_units_of_whole_nodes_on_narrow_layers_match_the_oracle(name, dims, node
 def test_long_nodes_of_odd_sizes_in_a_window_match_the_oracle(name, sizes):
     """Nodes of more than 128 rows in the launch configuration of units: each goes alone, its BatchNorm kernels hold up to
     512 or 1024 rows in registers (1025: the kernel that walks them), and the window's weight gradients are one product
-    over operand copies padded with zeros to multiples of 8 (a second step finds the first one's rows there)."""
+    over operand copies padded with zeros to multiples of 8."""
     wl = dataclasses.replace(I.workload(name), dims=(72, 264, 136, 52), node_sizes=sizes)
     theta = I.make_params(wl, jitter=0.1)
     x, y = I.make_batch(wl)
@@ -665,11 +665,55 @@ def test_long_nodes_of_odd_sizes_in_a_window_match_the_oracle(name, sizes):
         check_against_oracle(wl, gpu, ref)
         base = base or gpu
         assert gpu["G"].tobytes() == base["G"].tobytes()
-    back = sizes[::-1]                       # other columns, so that what was written before lies in the padding
+    back = sizes[::-1]
     both = run_gpu(wl, theta, x, y, flags=BENCH, fold_window=8, node_group=32, steps=2)
     assert np.isfinite(both["G"]).all()
     ref = oracle_steps(wl, theta, x, y, node_sizes=back)
     check_against_oracle(wl, run_gpu(wl, theta, x, y, node_sizes=back, flags=BENCH, fold_window=8, node_group=32), ref)
+
+
+@pytest.mark.parametrize("window", [2, 8])
+@pytest.mark.parametrize("flags", [FUSED | NO_GRAPH, BENCH, FUSED])
+@pytest.mark.parametrize("name", ["mlp_mid_bn_bf16", "mlp_mid_bf16"])
+def test_padding_of_packed_windows_after_steps_of_other_node_sizes(name, flags, window):
+    """One step object, one partition after the other, chosen so that the columns that pad a node's copies (to a multiple of
+    8) hold live rows of a step before: 129..135, 436..439 and 954..959 of the second partition, 514..519 and 649..655 of the
+    third, all inside nodes of the first.  Each step's gradient has the bits of a step object that has seen nothing else.
+    (The bias gradient of the last layer is a sum over the padded copies of one operand, so a missing zero shows there; in a
+    weight gradient both operands would have to lack it.)"""
+    import torch
+    import paper_2009_09523_amd as vf
+    from paper_2009_09523_amd.binding import config_from_workload
+    from vfharness import to_device_batch
+    print(f"{name} flags={flags} window={window}", flush=True)
+    wl = dataclasses.replace(I.workload(name), dims=(72, 264, 136, 52), node_sizes=(512, 131, 312))
+    splits = [(512, 131, 312), (129, 300, 514), (514, 129, 300), (512, 131, 312)]
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    xt, yt = to_device_batch(wl, x, y)
+
+    def engine():
+        return vf.VirtualNodeStep(config_from_workload(wl, flags=flags, stream=torch.cuda.Stream(), fold_window=window, node_group=32,
+                                                       max_node_size=514, max_nodes=3, max_batch=955))
+
+    def gradient(eng, p, sizes):
+        torch.cuda.synchronize()
+        eng.step(p, xt[:sum(sizes)], yt[:sum(sizes)], list(sizes))
+        G = torch.empty_like(p)
+        eng.grads(G)
+        torch.cuda.synchronize()
+        return G.cpu().numpy()
+
+    one, p = engine(), torch.from_numpy(theta.astype(np.float32)).cuda()
+    for sizes in splits:
+        alone, before = engine(), p.clone()
+        theta_in, b = before.cpu().numpy(), sum(sizes)
+        G = gradient(one, p, sizes)
+        assert G.tobytes() == gradient(alone, before, sizes).tobytes(), sizes
+        alone.close()
+    one.close()
+    ref = O.oracle_step(dataclasses.replace(wl, node_sizes=sizes), theta_in, x[:b], y[:b], node_sizes=list(sizes))
+    assert np.linalg.norm(G - ref["G"]) <= TOL[wl.dtype] * np.linalg.norm(ref["G"])
 
 
 @pytest.mark.parametrize("name", ["mlp_mid_bn_bf16", "mlp_mid_bf16"])
@@ -678,8 +722,8 @@ def test_long_nodes_of_odd_sizes_in_a_window_match_the_oracle(name, sizes):
                                         ((1544, 64, 50), (32, 8))])
 def test_bf16_nodes_in_one_launch_per_product_match_the_oracle(name, dims, nodes):
     """Nodes that go alone, with products short enough for the launch that takes BatchNorm / ReLU along (rows and columns at
-    and beside its tiles, contractions at its limits and one beyond, widths whose rows are padded): node by node in both folds,
-    as a graph, on two streams, and with the nodes' weights inside the transposed operand."""
+    and beside its tiles, widths whose rows are padded): node by node in both folds, as a graph, on two streams, and with the
+    nodes' weights inside the transposed operand.  (A backward product's contraction is its layer's output width.)"""
     wl = dataclasses.replace(I.workload(name), dims=dims, node_sizes=nodes)
     theta = I.make_params(wl, jitter=0.1)
     x, y = I.make_batch(wl)
@@ -694,6 +738,22 @@ def test_bf16_nodes_in_one_launch_per_product_match_the_oracle(name, dims, nodes
     wl = dataclasses.replace(wl, node_sizes=tuple(sizes))
     x, y = I.make_batch(wl)
     check_against_oracle(wl, run_gpu(wl, theta, x, y, flags=FUSED, fold_window=4), oracle_steps(wl, theta, x, y))
+
+
+@pytest.mark.parametrize("name", ["mlp_mid_bn_bf16", "mlp_mid_bf16"])
+@pytest.mark.parametrize("dims,nodes", [((24, 40, 1536, 1544), (32, 8)), ((24, 48, 768, 776), (64, 33)), ((24, 17, 384, 392), (128, 100)),
+                                        ((24, 33, 1100, 1552), (32, 31))])
+def test_bf16_node_launch_beside_its_limit_on_the_contraction(name, dims, nodes):
+    """The longest contraction that the launch with the backward pass takes for so many rows, and the next longer one, which
+    goes apart: three groups a wavefront (two in flight and an odd one), the last of them ragged (1100)."""
+    print(f"{name} dims={dims} nodes={nodes}", flush=True)
+    wl = dataclasses.replace(I.workload(name), dims=dims, node_sizes=nodes)
+    theta = I.make_params(wl, jitter=0.1)
+    x, y = I.make_batch(wl)
+    gpu = run_gpu(wl, theta, x, y, flags=FUSED | NO_GRAPH, profile=True)
+    assert {"gemm_dgrad_bn", "gemm_dgrad", "bn_relu_bwd"} <= set(gpu["launches"]), sorted(gpu["launches"])
+    check_against_oracle(wl, gpu, oracle_steps(wl, theta, x, y))
+    assert run_gpu(wl, theta, x, y, flags=0)["G"].tobytes() == gpu["G"].tobytes()
 
 
 @pytest.mark.parametrize("dims,nodes,window", [((64, 256, 264, 24), (100,) * 11, 8), ((64, 256, 264, 24), (100,) * 44, 1),
