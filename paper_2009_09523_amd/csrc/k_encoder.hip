@@ -803,10 +803,9 @@ __global__ __launch_bounds__(NT) void dy_bf16_prepare_kernel(const bf16_t* __res
 
 // ---- GELU (exact; gelu_f, gelu_df: vf_device.h) ------------------------------------------------
 // The pre-activation u is what a Linear layer put out: fp32 in every workload (only operands of
-// contractions are bf16).  T is the type of the GELU output (the next Linear layer's operand) and
-// of the gradient du handed to the backward products.
-template <typename T>
-__global__ __launch_bounds__(NT) void gelu_fwd_kernel(const float* __restrict__ u, T* __restrict__ g, int64_t n) {
+// contractions are bf16); the GELU output (the next Linear layer's operand) and the gradient du handed to the backward
+// products are bf16 here.  (fp32 encoders have GELU in the epilogues of their products.)
+__global__ __launch_bounds__(NT) void gelu_fwd_kernel(const float* __restrict__ u, bf16_t* __restrict__ g, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * NT;
   for (; i < n; i += stride) store_f(&g[i], gelu_f(u[i]));
@@ -844,9 +843,8 @@ __global__ __launch_bounds__(NT) void gelu_bwd8_kernel(const float4* __restrict_
   }
 }
 
-template <typename T>
 __global__ __launch_bounds__(NT) void gelu_bwd_kernel(const float* __restrict__ dg, const float* __restrict__ u,
-                                                      T* __restrict__ du, int64_t n) {
+                                                      bf16_t* __restrict__ du, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * NT;
   for (; i < n; i += stride) store_f(&du[i], dg[i] * gelu_df(u[i]));
@@ -1056,30 +1054,28 @@ int launch_dy_prepare(const void* dy, int dy_is_f32, int64_t ldi, int R, int C, 
   return VF_OK;
 }
 
-int launch_gelu_fwd(const float* u, void* g, int g_is_bf16, int64_t n, hipStream_t s) {
+int launch_gelu_fwd(const float* u, bf16_t* g, int64_t n, hipStream_t s) {
   if (n <= 0) return VF_OK;
-  if (g_is_bf16 && (n & 7) == 0 && ((reinterpret_cast<uintptr_t>(u) | reinterpret_cast<uintptr_t>(g)) & 15) == 0) {
-    gelu_fwd8_kernel<<<blocks_for(n / 8), NT, 0, s>>>(reinterpret_cast<const float4*>(u), static_cast<uint4*>(g), n / 8);
+  if ((n & 7) == 0 && ((reinterpret_cast<uintptr_t>(u) | reinterpret_cast<uintptr_t>(g)) & 15) == 0) {
+    gelu_fwd8_kernel<<<blocks_for(n / 8), NT, 0, s>>>(reinterpret_cast<const float4*>(u), reinterpret_cast<uint4*>(g), n / 8);
     VF_LAUNCH_CHECK();
     return VF_OK;
   }
-  if (g_is_bf16) gelu_fwd_kernel<bf16_t><<<blocks_for(n), NT, 0, s>>>(u, static_cast<bf16_t*>(g), n);
-  else           gelu_fwd_kernel<float><<<blocks_for(n), NT, 0, s>>>(u, static_cast<float*>(g), n);
+  gelu_fwd_kernel<<<blocks_for(n), NT, 0, s>>>(u, g, n);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }
 
-int launch_gelu_bwd(const float* dg, const float* u, void* du, int du_is_bf16, int64_t n, hipStream_t s) {
+int launch_gelu_bwd(const float* dg, const float* u, bf16_t* du, int64_t n, hipStream_t s) {
   if (n <= 0) return VF_OK;
-  if (du_is_bf16 && (n & 7) == 0 &&
+  if ((n & 7) == 0 &&
       ((reinterpret_cast<uintptr_t>(u) | reinterpret_cast<uintptr_t>(du) | reinterpret_cast<uintptr_t>(dg)) & 15) == 0) {
     gelu_bwd8_kernel<<<blocks_for(n / 8), NT, 0, s>>>(reinterpret_cast<const float4*>(dg), reinterpret_cast<const float4*>(u),
-                                                      static_cast<uint4*>(du), n / 8);
+                                                      reinterpret_cast<uint4*>(du), n / 8);
     VF_LAUNCH_CHECK();
     return VF_OK;
   }
-  if (du_is_bf16) gelu_bwd_kernel<bf16_t><<<blocks_for(n), NT, 0, s>>>(dg, u, static_cast<bf16_t*>(du), n);
-  else            gelu_bwd_kernel<float><<<blocks_for(n), NT, 0, s>>>(dg, u, static_cast<float*>(du), n);
+  gelu_bwd_kernel<<<blocks_for(n), NT, 0, s>>>(dg, u, du, n);
   VF_LAUNCH_CHECK();
   return VF_OK;
 }

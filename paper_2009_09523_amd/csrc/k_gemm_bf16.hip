@@ -1176,9 +1176,8 @@ __device__ __forceinline__ void bn_bwd_tile(f32x4 (&acc)[4][8], const BnBwdArgs&
       rstd = *reinterpret_cast<const f32x4*>(&fa.rstd[(int64_t)node * N + c]);
       g = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
       b = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
-      if (fa.round_params)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { g[e] = round_bf16(g[e]); b[e] = round_bf16(b[e]); }
+      for (int e = 0; e < 4; ++e) { g[e] = round_bf16(g[e]); b[e] = round_bf16(b[e]); }
     }
   };
 
@@ -1315,14 +1314,13 @@ __device__ __forceinline__ void bn_fwd_tile(f32x4 (&acc)[4][8], const BnFwdArgs&
     if (bn) {
       g = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
       b = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
-      if (fa.round_params)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { g[e] = round_bf16(g[e]); b[e] = round_bf16(b[e]); }
+      for (int e = 0; e < 4; ++e) { g[e] = round_bf16(g[e]); b[e] = round_bf16(b[e]); }
     } else if (fa.bias) {
       f32x4 bias = *reinterpret_cast<const f32x4*>(&fa.bias[c]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float bb = fa.round_params ? round_bf16(bias[e]) : bias[e];
+        const float bb = round_bf16(bias[e]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i][j][e] = fmaf(1.f, acc[i][j][e], bb);   // (the product epilogue's own form)
       }
@@ -1661,9 +1659,8 @@ __device__ __forceinline__ void mid_bn_bwd(f32x4 (&acc)[4][4], f32x4 (&z)[4][4],
       rstd[j] = *reinterpret_cast<const f32x4*>(&fa.rstd[(int64_t)node * N + c]);
       g[j] = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
       b = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
-      if (fa.round_params)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[e] = round_bf16(b[e]); }
+      for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[e] = round_bf16(b[e]); }
     }
     sg[j] = sb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1734,14 +1731,13 @@ __device__ __forceinline__ void mid_bn_fwd(f32x4 (&acc)[4][4], const BnFwdArgs& 
     if (bn) {
       g[j] = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
       b[j] = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
-      if (fa.round_params)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[j][e] = round_bf16(b[j][e]); }
+      for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[j][e] = round_bf16(b[j][e]); }
     } else if (fa.bias) {
       const f32x4 bias = *reinterpret_cast<const f32x4*>(&fa.bias[c]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float bb = fa.round_params ? round_bf16(bias[e]) : bias[e];
+        const float bb = round_bf16(bias[e]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i][j][e] = fmaf(1.f, acc[i][j][e], bb);   // (the product epilogue's own form)
       }

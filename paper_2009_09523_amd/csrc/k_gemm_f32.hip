@@ -633,9 +633,9 @@ int launch_operands(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
   auto tiles = [&](int t) { return (int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.nsplit; };
   const int K = g.K / g.nsplit;
   const int64_t t64 = tiles(64);
-  if constexpr (VEC == 2)
+  if constexpr (VEC == 2) {
     if (t64 >= 512 || tiles(32) > 1024) return launch_operands<AKC, BKC, 0>(g, ep, s);   // (what was measured above)
-  if (t64 > 512) {
+  } else if (t64 > 512) {
     constexpr bool along_k = AKC && BKC, scalar_k = !VEC && (AKC || BKC);
     const bool scalar_tiled = along_k ? (t64 >= 1536 || (K > (t64 < 1024 ? 112 : 80) && K <= (t64 < 1024 ? 256 : 640)))
                                       : t64 >= 4096 && (K <= 640 || t64 >= 8192);
@@ -649,13 +649,15 @@ int launch_operands(const F32Shape& g, const Epilogue& ep, hipStream_t s) {
     if (!along_k && !scalar_k && K <= (t64 < 1024 ? 256 : 512)) return launch_tile<32, 1, 1, 1, AKC, BKC, VEC>(g, ep, s);
     return launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
   }
-  if (t64 == 512)
-    return K <= 32 ? launch_tile<32, 1, 1, 1, AKC, BKC, VEC>(g, ep, s) : launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
-  if (tiles(32) > 1024) {      // (up to 512 tiles of 64 x 64: the same two reasons, tiled | 32/4 | taken)
-    // rows  1210 x 1300 x 8: 10.6 | 12.1 | tiled      k  1210 x 1300 x 255: 43 | 58 | 32x64/1 37   x 1025: 220 | 149 | 111
-    if (!AKC && !BKC && K <= 16)
-      return launch_tiled(g.A, 1, g.lda, g.B, 1, g.ldb, g.M, g.N, g.K, g.nsplit, g.slab, ep, s);
-    if (AKC && BKC && !VEC && K > 128) return launch_tile<32, 1, 2, 1, AKC, BKC, VEC>(g, ep, s);
+  if constexpr (VEC != 2) {
+    if (t64 == 512)
+      return K <= 32 ? launch_tile<32, 1, 1, 1, AKC, BKC, VEC>(g, ep, s) : launch_tile<32, 2, 2, 4, AKC, BKC, VEC>(g, ep, s);
+    if (tiles(32) > 1024) {    // (up to 512 tiles of 64 x 64: the same two reasons, tiled | 32/4 | taken)
+      // rows  1210 x 1300 x 8: 10.6 | 12.1 | tiled      k  1210 x 1300 x 255: 43 | 58 | 32x64/1 37   x 1025: 220 | 149 | 111
+      if (!AKC && !BKC && K <= 16)
+        return launch_tiled(g.A, 1, g.lda, g.B, 1, g.ldb, g.M, g.N, g.K, g.nsplit, g.slab, ep, s);
+      if (AKC && BKC && !VEC && K > 128) return launch_tile<32, 1, 2, 1, AKC, BKC, VEC>(g, ep, s);
+    }
   }
   if (tiles(16) <= (K <= 128 ? 1024 : 512))
     return K >= 512 ? launch_tile<16, 1, 1, 16, AKC, BKC, VEC>(g, ep, s) : launch_tile<16, 1, 1, 4, AKC, BKC, VEC>(g, ep, s);

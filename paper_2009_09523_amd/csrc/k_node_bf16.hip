@@ -51,9 +51,8 @@ __global__ __launch_bounds__(NTN) void gemm_bf16_node_kernel(const bf16_t* __res
   const bool bn = f.gamma != nullptr;
   float g = 1.f, b = 0.f, mean = 0.f, rstd = 1.f;
   if (bn) {
-    g = f.gamma[nc]; b = f.beta[nc];
+    g = round_bf16(f.gamma[nc]); b = round_bf16(f.beta[nc]);
     mean = f.mean[nc]; rstd = f.rstd[nc];
-    if (f.round_params) { g = round_bf16(g); b = round_bf16(b); }
   }
 #pragma unroll
   for (int p = 0; p < PER; ++p) {

@@ -250,7 +250,7 @@ class Encoder final : public Model {
       VF_KS(c, st, "layernorm_fwd", launch_layernorm_fwd(X.hmid, d_, nullptr, R, d_, P + B.ln2_g, P + B.ln2_b, bf16_,
                                                     cfg_.ln_eps, X.f, d_, bf16_, X.mean2, X.rstd2, st));
       VF_TRY(lin_fwd(c, "gemm_fwd", B.w1, P, X.f, d_, R, X.u, f_, false, nullptr, bf16_ ? nullptr : static_cast<float*>(X.g)));
-      if (bf16_) VF_KS(c, st, "gelu_fwd", launch_gelu_fwd(X.u, X.g, bf16_, (int64_t)R * f_, st));   // (fp32: in the product's epilogue)
+      if (bf16_) VF_KS(c, st, "gelu_fwd", launch_gelu_fwd(X.u, static_cast<bf16_t*>(X.g), (int64_t)R * f_, st));   // (fp32: in the product's epilogue)
       VF_TRY(lin_fwd(c, "gemm_fwd", B.w2, P, X.g, f_, R, hnext, d_, false, X.hmid));
     }
     VF_KS(c, st, "layernorm_fwd", launch_layernorm_fwd(H.hlast, d_, H.rowidx, Rm, d_, P + lnf_g_, P + lnf_b_, bf16_,
@@ -323,7 +323,7 @@ class Encoder final : public Model {
       if (!together) VF_TRY(prepare_dy(c, dh_buf_, true, d_, R, d_, c.gout(B.w2.b_off, w, i), defer ? X.dyT[0] : nullptr, &dh_op, &dyT));
       if (!together && !(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.w2, X.g, f_, dh_op, d_, R, c.gout(B.w2.w_off, w, i), dyT));
       VF_TRY(lin_bwd_x(c, "gemm_dgrad", B.w2, P, dh_op, d_, R, bf16_ ? tmp32_ : static_cast<float*>(du_), f_, nullptr, bf16_ ? nullptr : X.u));
-      if (bf16_) VF_KS(c, st, "gelu_bwd", launch_gelu_bwd(tmp32_, X.u, du_, bf16_, (int64_t)R * f_, st));
+      if (bf16_) VF_KS(c, st, "gelu_bwd", launch_gelu_bwd(tmp32_, X.u, static_cast<bf16_t*>(du_), (int64_t)R * f_, st));
       const void* du_op = du_;
       if (!together) VF_TRY(prepare_dy(c, du_, !bf16_, f_, R, f_, c.gout(B.w1.b_off, w, i), defer ? X.dyT[1] : nullptr, &du_op, &dyT));
       if (!together && !(defer && dyT)) VF_TRY(lin_bwd_w(c, "gemm_wgrad", B.w1, X.f, d_, du_, f_, R, c.gout(B.w1.w_off, w, i), dyT));

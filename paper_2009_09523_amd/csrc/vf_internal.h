@@ -82,7 +82,6 @@ struct BnBwdArgs {
   const float* rstd = nullptr;
   const float* gamma = nullptr;  // [N], or null: ReLU only
   const float* beta = nullptr;
-  int round_params = 0;          // gamma, beta rounded to bf16 first
   bf16_t* dz = nullptr;          // [M, N]
   int64_t lddz = 0;
   bf16_t* dzT = nullptr;         // [N, ldt]: column = row of the unit, values times tscale
@@ -102,7 +101,6 @@ struct BnFwdArgs {
   const float* gamma = nullptr;  // [N], or null: bias + ReLU only
   const float* beta = nullptr;
   const float* bias = nullptr;   // [N] or null (layers without BatchNorm)
-  int round_params = 0;          // gamma, beta, bias rounded to bf16 first
   float eps = 0.f;
   bf16_t* a = nullptr;           // activation [M, N]
   int64_t lda = 0;
@@ -215,7 +213,6 @@ int launch_gemm_bf16_bn_fwd(const bf16_t* A, int64_t lda, const bf16_t* B, int64
 struct NodeBnArgs {
   const float* gamma;            // or null
   const float* beta;
-  int round_params;
   const float* z;
   int64_t ldz;
   bf16_t* out;
@@ -533,10 +530,10 @@ bool dy_prepare_fits(int dy_is_f32, int64_t ldi, int64_t ldn, int64_t ldt, int R
 int launch_dy_prepare(const void* dy, int dy_is_f32, int64_t ldi, int R, int C, bf16_t* nat, int64_t ldn,
                       bf16_t* tr, int64_t ldt, float* scratch, GradOut out, hipStream_t s,
                       FinishList* defer = nullptr);
-// exact GELU: g = 0.5 u (1 + erf(u / sqrt 2));  u fp32 (a Linear layer's output), g T
-int launch_gelu_fwd(const float* u, void* g, int g_is_bf16, int64_t n, hipStream_t s);
-// du = dg * (Phi(u) + u phi(u));  dg and u fp32, du T
-int launch_gelu_bwd(const float* dg, const float* u, void* du, int du_is_bf16, int64_t n, hipStream_t s);
+// exact GELU: g = 0.5 u (1 + erf(u / sqrt 2));  u fp32 (a Linear layer's output)
+int launch_gelu_fwd(const float* u, bf16_t* g, int64_t n, hipStream_t s);
+// du = dg * (Phi(u) + u phi(u));  dg and u fp32
+int launch_gelu_bwd(const float* dg, const float* u, bf16_t* du, int64_t n, hipStream_t s);
 // row softmax in place over fp32 S [rows, n] -> P written as T to p (and nothing else)
 int launch_softmax_rows(const float* S, void* P, int p_is_bf16, int64_t rows, int n, hipStream_t s);
 // dS = P * (dP - sum_j dP*P) in place over dP (fp32); P is T
