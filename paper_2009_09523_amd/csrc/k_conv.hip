@@ -412,10 +412,10 @@ __global__ __launch_bounds__(NT) void bn2d_apply_fwd_kernel(const float* __restr
     b.x = round_bf16(b.x); b.y = round_bf16(b.y); b.z = round_bf16(b.z); b.w = round_bf16(b.w);
   }
   float4 o;
-  o.x = fmaxf(fmaf(g.x, (v.x - m.x) * r.x, b.x) + s.x, 0.f);
-  o.y = fmaxf(fmaf(g.y, (v.y - m.y) * r.y, b.y) + s.y, 0.f);
-  o.z = fmaxf(fmaf(g.z, (v.z - m.z) * r.z, b.z) + s.z, 0.f);
-  o.w = fmaxf(fmaf(g.w, (v.w - m.w) * r.w, b.w) + s.w, 0.f);
+  o.x = fmaxf(bn_pre(g.x, (v.x - m.x) * r.x, b.x) + s.x, 0.f);
+  o.y = fmaxf(bn_pre(g.y, (v.y - m.y) * r.y, b.y) + s.y, 0.f);
+  o.z = fmaxf(bn_pre(g.z, (v.z - m.z) * r.z, b.z) + s.z, 0.f);
+  o.w = fmaxf(bn_pre(g.w, (v.w - m.w) * r.w, b.w) + s.w, 0.f);
   reinterpret_cast<uint2*>(a)[i] = pack4(o);
 }
 
@@ -475,7 +475,7 @@ __global__ __launch_bounds__(NT) void bn2d_bwd_partial_kernel(const float* __res
     for (int u = 0; u < PB; ++u)
       if (active && p0 + u < t.passes && lane + (p0 + u) * t.rl < n) {
         const float4 xh = make_float4((v[u].x - m.x) * rs.x, (v[u].y - m.y) * rs.y, (v[u].z - m.z) * rs.z, (v[u].w - m.w) * rs.w);
-        const float4 o = SKIP ? unpack4(o2[u]) : make_float4(fmaf(gm.x, xh.x, bt.x), fmaf(gm.y, xh.y, bt.y), fmaf(gm.z, xh.z, bt.z), fmaf(gm.w, xh.w, bt.w));
+        const float4 o = SKIP ? unpack4(o2[u]) : make_float4(bn_pre(gm.x, xh.x, bt.x), bn_pre(gm.y, xh.y, bt.y), bn_pre(gm.z, xh.z, bt.z), bn_pre(gm.w, xh.w, bt.w));
         const float dx = o.x > 0.f ? d[u].x : 0.f, dy = o.y > 0.f ? d[u].y : 0.f;
         const float dz = o.z > 0.f ? d[u].z : 0.f, dw = o.w > 0.f ? d[u].w : 0.f;
         sb.x += dx; sb.y += dy; sb.z += dz; sb.w += dw;
@@ -556,17 +556,17 @@ __global__ __launch_bounds__(NT) void bn2d_bwd_apply_kernel(float* __restrict__ 
     o = unpack4(reinterpret_cast<const uint2*>(a)[i]);
   } else {
     const float4 bt = param4(beta, c, round_params);
-    o = make_float4(fmaf(g.x, (v.x - m.x) * r.x, bt.x), fmaf(g.y, (v.y - m.y) * r.y, bt.y), fmaf(g.z, (v.z - m.z) * r.z, bt.z),
-                    fmaf(g.w, (v.w - m.w) * r.w, bt.w));
+    o = make_float4(bn_pre(g.x, (v.x - m.x) * r.x, bt.x), bn_pre(g.y, (v.y - m.y) * r.y, bt.y), bn_pre(g.z, (v.z - m.z) * r.z, bt.z),
+                    bn_pre(g.w, (v.w - m.w) * r.w, bt.w));
   }
   float4 dp;
   dp.x = o.x > 0.f ? d.x : 0.f; dp.y = o.y > 0.f ? d.y : 0.f;
   dp.z = o.z > 0.f ? d.z : 0.f; dp.w = o.w > 0.f ? d.w : 0.f;
   float4 out;
-  out.x = g.x * r.x * (dp.x - sb.x * inv_rows - (v.x - m.x) * r.x * sg.x * inv_rows);
-  out.y = g.y * r.y * (dp.y - sb.y * inv_rows - (v.y - m.y) * r.y * sg.y * inv_rows);
-  out.z = g.z * r.z * (dp.z - sb.z * inv_rows - (v.z - m.z) * r.z * sg.z * inv_rows);
-  out.w = g.w * r.w * (dp.w - sb.w * inv_rows - (v.w - m.w) * r.w * sg.w * inv_rows);
+  out.x = bn_dz(g.x * r.x, dp.x, (v.x - m.x) * r.x, sg.x, sb.x, inv_rows);
+  out.y = bn_dz(g.y * r.y, dp.y, (v.y - m.y) * r.y, sg.y, sb.y, inv_rows);
+  out.z = bn_dz(g.z * r.z, dp.z, (v.z - m.z) * r.z, sg.z, sb.z, inv_rows);
+  out.w = bn_dz(g.w * r.w, dp.w, (v.w - m.w) * r.w, sg.w, sb.w, inv_rows);
   reinterpret_cast<uint2*>(dy)[i] = pack4(out);
   if (keep_dpre) reinterpret_cast<float4*>(da)[i] = dp;
 }

@@ -1214,7 +1214,7 @@ __device__ __forceinline__ void bn_bwd_tile(f32x4 (&acc)[4][8], const BnBwdArgs&
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float xhat = (zz[i][e] - mean[e]) * rstd[e];
-        const float pre = bn ? fmaf(g[e], xhat, b[e]) : zz[i][e];
+        const float pre = bn ? bn_pre(g[e], xhat, b[e]) : zz[i][e];
         const float dr = pre > 0.f ? acc[i][j][e] : 0.f;
         acc[i][j][e] = dr;
         zz[i][e] = xhat;
@@ -1246,7 +1246,7 @@ __device__ __forceinline__ void bn_bwd_tile(f32x4 (&acc)[4][8], const BnBwdArgs&
         const float dr = acc[i][j][e];
         if (bn) {
           const float kk = g[e] * rstd[e];
-          v[e] = kk * (dr - sb[e] * invR - zz[i][e] * sg[e] * invR);
+          v[e] = bn_dz(kk, dr, zz[i][e], sg[e], sb[e], invR);
         } else {
           v[e] = dr;
         }
@@ -1373,7 +1373,7 @@ __device__ __forceinline__ void bn_fwd_tile(f32x4 (&acc)[4][8], const BnFwdArgs&
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float zz = acc[i][j][e];
-        v[e] = bn ? fmaxf(fmaf(g[e], (zz - mean[e]) * rstd[e], b[e]), 0.f) : fmaxf(zz, 0.f);
+        v[e] = bn ? fmaxf(bn_pre(g[e], (zz - mean[e]) * rstd[e], b[e]), 0.f) : fmaxf(zz, 0.f);
       }
       uint2 pk;
       pk.x = f32x2_to_bf16x2(v[0], v[1]);
@@ -1668,7 +1668,7 @@ __device__ __forceinline__ void mid_bn_bwd(f32x4 (&acc)[4][4], f32x4 (&z)[4][4],
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float xhat = (z[i][j][e] - mean[e]) * rstd[j][e];
-        const float pre = bn ? fmaf(g[j][e], xhat, b[e]) : z[i][j][e];
+        const float pre = bn ? bn_pre(g[j][e], xhat, b[e]) : z[i][j][e];
         const float dr = pre > 0.f ? acc[i][j][e] : 0.f;
         acc[i][j][e] = dr;
         z[i][j][e] = xhat;
@@ -1701,7 +1701,7 @@ __device__ __forceinline__ void mid_bn_bwd(f32x4 (&acc)[4][4], f32x4 (&z)[4][4],
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float dr = acc[i][j][e], kk = g[j][e] * rstd[j][e];
-        v[e] = bn ? kk * (dr - sb[j][e] * invR - z[i][j][e] * sg[j][e] * invR) : dr;
+        v[e] = bn ? bn_dz(kk, dr, z[i][j][e], sg[j][e], sb[j][e], invR) : dr;
       }
       uint2 pk, pt;
       pk.x = f32x2_to_bf16x2(v[0], v[1]); pk.y = f32x2_to_bf16x2(v[2], v[3]);
@@ -1798,7 +1798,7 @@ __device__ __forceinline__ void mid_bn_fwd(f32x4 (&acc)[4][4], const BnFwdArgs& 
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float zz = acc[i][j][e];
-        v[e] = bn ? fmaxf(fmaf(g[j][e], (zz - mean[j][e]) * rstd[j][e], b[j][e]), 0.f) : fmaxf(zz, 0.f);
+        v[e] = bn ? fmaxf(bn_pre(g[j][e], (zz - mean[j][e]) * rstd[j][e], b[j][e]), 0.f) : fmaxf(zz, 0.f);
       }
       out[i][j].x = f32x2_to_bf16x2(v[0], v[1]); out[i][j].y = f32x2_to_bf16x2(v[2], v[3]);
       mid_put_transposed(out[i][j], tT, i, j, lr, lq);

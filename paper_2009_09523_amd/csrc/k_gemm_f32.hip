@@ -321,7 +321,7 @@ __global__ __launch_bounds__(BN_NW * 64) void gemm_f32_bn_kernel(const float* __
     for (int p = 0; p < PER; ++p)
       if (mine && mm[p] < R) {
         f.z[(int64_t)mm[p] * f.ldz + n] = v[p];
-        f.out[(int64_t)mm[p] * f.ldo + n] = fmaxf(fmaf(g, (v[p] - mean) * rstd, b), 0.f);
+        f.out[(int64_t)mm[p] * f.ldo + n] = fmaxf(bn_pre(g, (v[p] - mean) * rstd, b), 0.f);
       }
     return;
   }
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(BN_NW * 64) void gemm_f32_bn_kernel(const float* __
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
     const float xhat = (zz[p] - mean) * rstd;
-    const bool on = mm[p] < R && fmaf(g, xhat, b) > 0.f;
+    const bool on = mm[p] < R && bn_pre(g, xhat, b) > 0.f;
     zz[p] = mm[p] < R ? xhat : 0.f;
     v[p] = on ? v[p] : 0.f;
     sg = fmaf(v[p], zz[p], sg);
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(BN_NW * 64) void gemm_f32_bn_kernel(const float* __
   const float invR = 1.0f / (float)R, kk = g * rstd;
 #pragma unroll
   for (int p = 0; p < PER; ++p)
-    if (mine && mm[p] < R) f.out[(int64_t)mm[p] * f.ldo + n] = kk * (v[p] - sb * invR - zz[p] * sg * invR);
+    if (mine && mm[p] < R) f.out[(int64_t)mm[p] * f.ldo + n] = bn_dz(kk, v[p], zz[p], sg, sb, invR);
 }
 
 // ---- the last layer's product with the loss -------------------------------------------------------------

@@ -140,7 +140,7 @@ __global__ __launch_bounds__(NTN) void gemm_bf16_node_kernel(const bf16_t* __res
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
     const float xhat = (zz[p] - mean) * rstd;
-    const float pre = bn ? fmaf(g, xhat, b) : zz[p];
+    const float pre = bn ? bn_pre(g, xhat, b) : zz[p];
     const bool on = mm[p] < R;
     v[p] = on && pre > 0.f ? v[p] : 0.f;
     zz[p] = on ? xhat : 0.f;
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(NTN) void gemm_bf16_node_kernel(const bf16_t* __res
   for (int p = 0; p < PER; ++p) {
     float d = 0.f;
     if (mm[p] < R) {
-      d = bn ? kk * (v[p] - sb * invR - zz[p] * sg * invR) : v[p];
+      d = bn ? bn_dz(kk, v[p], zz[p], sg, sb, invR) : v[p];
       if (mine) f.out[(int64_t)mm[p] * f.ldo + n] = f32_to_bf16(d);
     }
     tile[lr][mm[p]] = f32_to_bf16(d * f.tscale);

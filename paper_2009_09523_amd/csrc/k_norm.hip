@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void bn_relu_fwd_kernel(const float* zp, int64
         float v = 0.f;
         if (live && r < R) {
           float zz = SMALL ? zr[n][k] : z[(int64_t)r * ldz + c];
-          v = bn ? fmaxf(fmaf(g, (zz - mean) * rstd, b), 0.f) : fmaxf(zz, 0.f);
+          v = bn ? fmaxf(bn_pre(g, (zz - mean) * rstd, b), 0.f) : fmaxf(zz, 0.f);
           store_f(&a[(int64_t)(rb + r) * lda + c], v);
         }
         if (aT) tile[tx][rl] = f32_to_bf16(v);
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void bn_relu_bwd_kernel(float* __restrict__ da
         const int r = ty + RL * k;
         const float zz = xr[n][k];
         const float xhat = (zz - mean[n]) * rstd[n];
-        const float pre = bn ? fmaf(g, xhat, b) : zz;
+        const float pre = bn ? bn_pre(g, xhat, b) : zz;
         const bool on = live && r < R;
         xr[n][k] = on ? xhat : 0.f;
         dr[n][k] = (on && pre > 0.f) ? dr[n][k] : 0.f;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256) void bn_relu_bwd_kernel(float* __restrict__ da
       for (int r = ty; r < R; r += RL) {
         float zz = z[(int64_t)r * ldz + c];
         float xhat = (zz - mean[n]) * rstd[n];
-        float pre = bn ? fmaf(g, xhat, b) : zz;
+        float pre = bn ? bn_pre(g, xhat, b) : zz;
         float d = sum_slabs<NS>(dap, slab, (int64_t)r * ldda + c);
         float dout = pre > 0.f ? d : 0.f;
         dap[(int64_t)r * ldda + c] = dout;   // keep the reduced, masked value in slab 0
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(256) void bn_relu_bwd_kernel(float* __restrict__ da
             xhat = (z[(int64_t)r * ldz + c] - mean[n]) * rstd[n];
             dout = dap[(int64_t)r * ldda + c];           // written by this thread in pass 1
           }
-          v = bn ? kk * (dout - sb * invR - xhat * sg * invR) : dout;
+          v = bn ? bn_dz(kk, dout, xhat, sg, sb, invR) : dout;
           store_f(&dz[(int64_t)(rb + r) * lddz + c], v);
         }
         if (dzT) tile[tx][rl] = f32_to_bf16(v * tscale);
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(TNT) void bn_relu_fwd_tall_kernel(const float* zp, 
     const int r = ty + TRL * k;
     float v = 0.f;
     if (live && r < R) {
-      v = bn ? fmaxf(fmaf(g, (zr[k] - mean) * rstd, b), 0.f) : fmaxf(zr[k], 0.f);
+      v = bn ? fmaxf(bn_pre(g, (zr[k] - mean) * rstd, b), 0.f) : fmaxf(zr[k], 0.f);
       store_f(&a[(int64_t)r * lda + c], v);
     }
     if (aT) tile[tx][r] = f32_to_bf16(v);
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(TNT) void bn_relu_bwd_tall_kernel(const float* __re
   for (int k = 0; k < RPL; ++k) {
     const bool on = ty + TRL * k < R;
     const float xhat = (xr[k] - mean) * rstd;
-    const float pre = bn ? fmaf(g, xhat, b) : xr[k];
+    const float pre = bn ? bn_pre(g, xhat, b) : xr[k];
     xr[k] = on ? xhat : 0.f;
     dr[k] = (on && pre > 0.f) ? dr[k] : 0.f;
     sg = fmaf(dr[k], xr[k], sg);
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(TNT) void bn_relu_bwd_tall_kernel(const float* __re
     const int r = ty + TRL * k;
     float v = 0.f;
     if (live && r < R) {
-      v = bn ? kk * (dr[k] - sb * invR - xr[k] * sg * invR) : dr[k];
+      v = bn ? bn_dz(kk, dr[k], xr[k], sg, sb, invR) : dr[k];
       store_f(&dz[(int64_t)r * lddz + c], v);
     }
     if (dzT) tile[tx][r] = f32_to_bf16(v * tscale);
@@ -597,7 +597,7 @@ __global__ __launch_bounds__((GroupShape<G, SGP>::THREADS)) void bn_relu_fwd_gro
       const int r = ty + RL * k;
       float v = 0.f;
       if (live && r < R) {
-        v = bn ? fmaxf(fmaf(g, (zr[q][k] - mean) * rstd, b), 0.f) : fmaxf(zr[q][k], 0.f);
+        v = bn ? fmaxf(bn_pre(g, (zr[q][k] - mean) * rstd, b), 0.f) : fmaxf(zr[q][k], 0.f);
         a[(int64_t)(rb + r) * lda + c] = f32_to_bf16(v);
       }
       if (aT) tile[sub][tx][r] = f32_to_bf16(v);
@@ -673,7 +673,7 @@ __global__ __launch_bounds__((GroupShape<G, SGP>::THREADS)) void bn_relu_bwd_gro
       const int r = ty + RL * k;
       const float zz = xr[q][k];
       const float xhat = (zz - mean[q]) * rstd[q];
-      const float pre = bn ? fmaf(g, xhat, b) : zz;
+      const float pre = bn ? bn_pre(g, xhat, b) : zz;
       const bool on = live && r < R;
       xr[q][k] = on ? xhat : 0.f;
       dr[q][k] = (on && pre > 0.f) ? dr[q][k] : 0.f;
@@ -689,7 +689,7 @@ __global__ __launch_bounds__((GroupShape<G, SGP>::THREADS)) void bn_relu_bwd_gro
       const int r = ty + RL * k;
       float v = 0.f;
       if (live && r < R) {
-        v = bn ? kk * (dr[q][k] - sb * invR - xr[q][k] * sg * invR) : dr[q][k];
+        v = bn ? bn_dz(kk, dr[q][k], xr[q][k], sg, sb, invR) : dr[q][k];
         dz[(int64_t)(rb + r) * lddz + c] = f32_to_bf16(v);
       }
       if (dzT) tile[sub][tx][r] = f32_to_bf16(v * tscale);
@@ -826,8 +826,8 @@ __global__ __launch_bounds__((GroupShape<G, SGP>::THREADS)) void bn_relu_fwd_pai
       const int r = ty + RL * k;
       float vx = 0.f, vy = 0.f;
       if (live && r < R) {
-        vx = bn ? fmaxf(fmaf(g.x, (zr[q][k].x - mean.x) * rstd.x, b.x), 0.f) : fmaxf(zr[q][k].x, 0.f);
-        vy = bn ? fmaxf(fmaf(g.y, (zr[q][k].y - mean.y) * rstd.y, b.y), 0.f) : fmaxf(zr[q][k].y, 0.f);
+        vx = bn ? fmaxf(bn_pre(g.x, (zr[q][k].x - mean.x) * rstd.x, b.x), 0.f) : fmaxf(zr[q][k].x, 0.f);
+        vy = bn ? fmaxf(bn_pre(g.y, (zr[q][k].y - mean.y) * rstd.y, b.y), 0.f) : fmaxf(zr[q][k].y, 0.f);
         *reinterpret_cast<uint32_t*>(&a[(int64_t)(rb + r) * lda + c]) = (uint32_t)f32_to_bf16(vx) | ((uint32_t)f32_to_bf16(vy) << 16);
       }
       if (aT) { tile[sub][2 * tx][r] = f32_to_bf16(vx); tile[sub][2 * tx + 1][r] = f32_to_bf16(vy); }
@@ -909,7 +909,7 @@ __global__ __launch_bounds__((GroupShape<G, SGP>::THREADS)) void bn_relu_bwd_pai
       {
         const float zz = xr[q][k].x;
         const float xhat = (zz - mean[q].x) * rstd[q].x;
-        const float pre = bn ? fmaf(g.x, xhat, b.x) : zz;
+        const float pre = bn ? bn_pre(g.x, xhat, b.x) : zz;
         xr[q][k].x = on ? xhat : 0.f;
         dr[q][k].x = (on && pre > 0.f) ? dr[q][k].x : 0.f;
         sg.x = fmaf(dr[q][k].x, xr[q][k].x, sg.x);
@@ -918,7 +918,7 @@ __global__ __launch_bounds__((GroupShape<G, SGP>::THREADS)) void bn_relu_bwd_pai
       {
         const float zz = xr[q][k].y;
         const float xhat = (zz - mean[q].y) * rstd[q].y;
-        const float pre = bn ? fmaf(g.y, xhat, b.y) : zz;
+        const float pre = bn ? bn_pre(g.y, xhat, b.y) : zz;
         xr[q][k].y = on ? xhat : 0.f;
         dr[q][k].y = (on && pre > 0.f) ? dr[q][k].y : 0.f;
         sg.y = fmaf(dr[q][k].y, xr[q][k].y, sg.y);
@@ -937,8 +937,8 @@ __global__ __launch_bounds__((GroupShape<G, SGP>::THREADS)) void bn_relu_bwd_pai
       const int r = ty + RL * k;
       float vx = 0.f, vy = 0.f;
       if (live && r < R) {
-        vx = bn ? kk.x * (dr[q][k].x - sb.x * invR - xr[q][k].x * sg.x * invR) : dr[q][k].x;
-        vy = bn ? kk.y * (dr[q][k].y - sb.y * invR - xr[q][k].y * sg.y * invR) : dr[q][k].y;
+        vx = bn ? bn_dz(kk.x, dr[q][k].x, xr[q][k].x, sg.x, sb.x, invR) : dr[q][k].x;
+        vy = bn ? bn_dz(kk.y, dr[q][k].y, xr[q][k].y, sg.y, sb.y, invR) : dr[q][k].y;
         *reinterpret_cast<uint32_t*>(&dz[(int64_t)(rb + r) * lddz + c]) = (uint32_t)f32_to_bf16(vx) | ((uint32_t)f32_to_bf16(vy) << 16);
       }
       if (dzT) { tile[sub][2 * tx][r] = f32_to_bf16(vx * tscale); tile[sub][2 * tx + 1][r] = f32_to_bf16(vy * tscale); }

@@ -70,6 +70,14 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// BatchNorm of one entry with normalised value xhat = (z - mean) * rstd, for every kernel that takes it: what ReLU receives,
+// and the gradient at z from the masked gradient dr behind it and the column's sums over the node's rows (invR = 1 / rows)
+// of dr * xhat (sg) and of dr (sb); kk = gamma * rstd.
+__device__ __forceinline__ float bn_pre(float gamma, float xhat, float beta) { return fmaf(gamma, xhat, beta); }
+__device__ __forceinline__ float bn_dz(float kk, float dr, float xhat, float sg, float sb, float invR) {
+  return kk * (dr - sb * invR - xhat * sg * invR);
+}
+
 // Row pitch of the 64 x 64 bf16 tiles that are written by rows and read by columns: 33 words, so that the eight lanes that
 // read rows 8 k of a column pair meet on no bank (at 36 words four of them did).
 constexpr int kTransposePitch = 66;
