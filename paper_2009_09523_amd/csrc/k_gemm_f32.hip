@@ -58,7 +58,7 @@ struct Operand {
       off[t] = r0 + r < nrows ? (KC ? (uint32_t)r * pitch + (uint32_t)kl * 4u : (uint32_t)r * 4u + (uint32_t)kl * pitch) : kOutside;
     }
   }
-  // The group of contraction elements k0 .. k0 + GU * CK - 1 (k0 the same for the whole wavefront).
+  // The group of contraction elements k0 .. k0 + G * CK - 1 (k0 the same for the whole wavefront).
   __device__ __forceinline__ void load(float (&v)[G][T][4], int k0) const {
     const int left = K - k0 - kl;                        // elements of this lane from its first one on
     // (a chunk that starts past the end: nothing is fetched, and its scalar offset stays inside the buffer, so that

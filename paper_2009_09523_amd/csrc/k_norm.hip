@@ -11,7 +11,8 @@
 // Shape: a workgroup owns CB = 16 columns and all rows; 256 threads = 16 columns x 16 row
 // lanes, so a 4096-wide layer gives 256 workgroups (one per compute unit).  For nodes of up
 // to RPT*16 = 128 rows every thread keeps its rows in registers and global memory is read
-// exactly once; larger nodes re-read the reduced values.
+// exactly once; nodes of up to 1024 rows do the same with 1024 threads (bn_relu_*_tall_kernel), still
+// larger ones re-read the reduced values.
 #include <algorithm>
 #include <cstdlib>
 

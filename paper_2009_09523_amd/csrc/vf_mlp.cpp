@@ -29,12 +29,11 @@ struct Layer {
   // T [max_b, ld]: gradient w.r.t. z.  Two sets only for the last layer (the softmax of the
   // forward part writes it); the hidden layers' are written and read by the backward part.
   void* dz[2] = {nullptr, nullptr};
-  // Weight-gradient operands, transposed: one wide matrix [N, ldw] each, in which node i owns
-  // the columns of copy Ctx::slot(i) (Mlp::cols), its rows contiguous along the matrix row.  So
-  // the operands of a whole fold window are still there when its weight gradients are taken in
-  // one pass, or (two streams) the second stream can read node i's operands while the first
-  // produces those of node i+1; and the nodes of a window (join_kind) lie side by side, one
-  // long contraction.
+  // Weight-gradient operands, transposed: one wide matrix [N, ldw] each, in which a unit's rows are consecutive columns
+  // (Mlp::cols): the units of a fold window one behind the other at multiples of 8, with windows of one unit two copies
+  // side by side (Ctx::slot).  So the operands of a whole window are still there when its weight gradients are taken in
+  // one pass, as one long contraction where they may be (join_kind), or (two streams) the second stream can read unit i's
+  // operands while the first produces those of unit i+1.
   bf16_t* aT = nullptr;      // a transposed
   bf16_t* dzT = nullptr;     // dz transposed
 };
