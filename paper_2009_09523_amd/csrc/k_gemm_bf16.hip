@@ -1134,6 +1134,12 @@ __device__ __forceinline__ void store_tiles16_row(const f32x4 (&acc)[8], const E
 // through LDS (the lower rows first), one group of 16 columns at a time.  A lane holds four consecutive columns of a row, so dz leaves in
 // 8-byte stores; the transposed copy goes through LDS (per wavefront 128 columns x 64 rows) and
 // leaves in 16-byte stores of eight rows.  LDS: the sums at 0 (8 KB), the transposed tiles behind.
+// Whether gamma and beta are rounded is an argument though it is always set: without that branch the
+// compiler orders a group's requests and waits otherwise, here and in bn_fwd_tile, and the tiles take
+// longer.  64 x 128 rows on 2048-8192^6-1000: 15.19 ms a step with it, 15.39 without; rounded only in the
+// group that uses them 15.4, with the parameters requested before the pre-activations too 15.33, and with
+// an instantiation for layers without BatchNorm it spills.
+
 // Sum over the 16 lanes of a row (lanes 16 k .. 16 k + 15), to all of them, by data-parallel-primitive
 // moves: neighbours, pairs, the quad's mirror image in its half row, the half row's in the row.  Both
 // partners of an exchange add the same two values, so every lane ends with the same bits.
@@ -1176,8 +1182,9 @@ __device__ __forceinline__ void bn_bwd_tile(f32x4 (&acc)[4][8], const BnBwdArgs&
       rstd = *reinterpret_cast<const f32x4*>(&fa.rstd[(int64_t)node * N + c]);
       g = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
       b = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
+      if (fa.round_params)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { g[e] = round_bf16(g[e]); b[e] = round_bf16(b[e]); }
+        for (int e = 0; e < 4; ++e) { g[e] = round_bf16(g[e]); b[e] = round_bf16(b[e]); }
     }
   };
 
@@ -1314,13 +1321,14 @@ __device__ __forceinline__ void bn_fwd_tile(f32x4 (&acc)[4][8], const BnFwdArgs&
     if (bn) {
       g = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
       b = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
+      if (fa.round_params)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { g[e] = round_bf16(g[e]); b[e] = round_bf16(b[e]); }
+        for (int e = 0; e < 4; ++e) { g[e] = round_bf16(g[e]); b[e] = round_bf16(b[e]); }
     } else if (fa.bias) {
       f32x4 bias = *reinterpret_cast<const f32x4*>(&fa.bias[c]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float bb = round_bf16(bias[e]);
+        const float bb = fa.round_params ? round_bf16(bias[e]) : bias[e];
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i][j][e] = fmaf(1.f, acc[i][j][e], bb);   // (the product epilogue's own form)
       }
@@ -1659,8 +1667,9 @@ __device__ __forceinline__ void mid_bn_bwd(f32x4 (&acc)[4][4], f32x4 (&z)[4][4],
       rstd[j] = *reinterpret_cast<const f32x4*>(&fa.rstd[(int64_t)node * N + c]);
       g[j] = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
       b = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
+      if (fa.round_params)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[e] = round_bf16(b[e]); }
+        for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[e] = round_bf16(b[e]); }
     }
     sg[j] = sb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1731,13 +1740,14 @@ __device__ __forceinline__ void mid_bn_fwd(f32x4 (&acc)[4][4], const BnFwdArgs& 
     if (bn) {
       g[j] = *reinterpret_cast<const f32x4*>(&fa.gamma[c]);
       b[j] = *reinterpret_cast<const f32x4*>(&fa.beta[c]);
+      if (fa.round_params)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[j][e] = round_bf16(b[j][e]); }
+        for (int e = 0; e < 4; ++e) { g[j][e] = round_bf16(g[j][e]); b[j][e] = round_bf16(b[j][e]); }
     } else if (fa.bias) {
       const f32x4 bias = *reinterpret_cast<const f32x4*>(&fa.bias[c]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float bb = round_bf16(bias[e]);
+        const float bb = fa.round_params ? round_bf16(bias[e]) : bias[e];
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i][j][e] = fmaf(1.f, acc[i][j][e], bb);   // (the product epilogue's own form)
       }

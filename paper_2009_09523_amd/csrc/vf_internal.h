@@ -82,6 +82,7 @@ struct BnBwdArgs {
   const float* rstd = nullptr;
   const float* gamma = nullptr;  // [N], or null: ReLU only
   const float* beta = nullptr;
+  int round_params = 0;          // gamma, beta rounded to bf16 first (always set; a constant it was slower: see bn_bwd_tile)
   bf16_t* dz = nullptr;          // [M, N]
   int64_t lddz = 0;
   bf16_t* dzT = nullptr;         // [N, ldt]: column = row of the unit, values times tscale
@@ -101,6 +102,7 @@ struct BnFwdArgs {
   const float* gamma = nullptr;  // [N], or null: bias + ReLU only
   const float* beta = nullptr;
   const float* bias = nullptr;   // [N] or null (layers without BatchNorm)
+  int round_params = 0;          // gamma, beta, bias rounded to bf16 first (as above)
   float eps = 0.f;
   bf16_t* a = nullptr;           // activation [M, N]
   int64_t lda = 0;

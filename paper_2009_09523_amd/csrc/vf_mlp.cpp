@@ -251,6 +251,7 @@ class Mlp final : public Model {
         ff.z = L.z[q]; ff.ldz = L.ld;
         if (L.has_bn) { ff.gamma = P + L.g_off; ff.beta = P + L.be_off; }
         else if (L.has_bias) ff.bias = P + L.b_off;
+        ff.round_params = bf16_;
         ff.eps = cfg_.bn_eps;
         ff.a = static_cast<bf16_t*>(L.a[q]); ff.lda = L.ld;
         ff.aT = L.aT + pc; ff.ldt = ldw_;
@@ -385,6 +386,7 @@ class Mlp final : public Model {
         fa.z = Pv.z[q]; fa.ldz = Pv.ld;
         fa.mean = Pv.mean[q]; fa.rstd = Pv.rstd[q];
         fa.gamma = Pv.has_bn ? P + Pv.g_off : nullptr; fa.beta = Pv.has_bn ? P + Pv.be_off : nullptr;
+        fa.round_params = bf16_;
         fa.dz = static_cast<bf16_t*>(Pv.dz[0]); fa.lddz = Pv.ld;
         fa.dzT = Pv.dzT + pc; fa.ldt = ldw_;
         fa.tscale = tscale(c, s, i);

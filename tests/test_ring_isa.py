@@ -133,6 +133,17 @@ def test_stage_loop_of_the_direct_kernel_goes_from_the_wait_to_the_barrier(gemm_
         assert ins[wait + 1].startswith("s_barrier") and "lgkmcnt(0)" in ins[wait], (name, ins[wait:wait + 4])
 
 
+def test_batchnorm_tiles_wait_for_a_groups_parameters_behind_a_branch(gemm_asm):
+    """Eight column groups of the 256 x 256 tile that ends in the BatchNorm backward pass: the rounding of their parameters
+    stands behind a branch each.  Without it the compiler orders the groups' requests otherwise, and the launch of
+    4096 x 8192 x 8192 takes 615 us instead of 601."""
+    bodies = ["\n".join(filter(None, (raw.split(";")[0].strip() for _, raw in body)))
+              for name, body in R.split_kernels(gemm_asm).items() if "gemm_bf16_wide_line16_kernelILi1E" in name]
+    assert len(bodies) == 1
+    waits = re.findall(r"s_cbranch_(?:scc[01]|vccn?z) \S+\n(?:\.LBB\S+\n)?s_waitcnt vmcnt\(\d+\)\nv_cvt_pk_bf16_f32", bodies[0])
+    assert len(waits) == 8, len(waits)
+
+
 def test_a_weight_copy_alone_does_not_carry_a_job_list(tmp_path):
     """An MLP copies its weights layer by layer, one launch each, and its small steps are bound by the launches: with the
     list of sixteen jobs among their arguments (1.1 KB a launch) a step of seven layers took 293 us instead of 287."""
