@@ -759,10 +759,12 @@ def test_bf16_node_launch_beside_its_limit_on_the_contraction(name, dims, nodes)
 @pytest.mark.parametrize("dims,nodes,window", [((64, 256, 264, 24), (100,) * 11, 8), ((64, 256, 264, 24), (100,) * 44, 1),
                                                ((64, 256, 264, 24), (100,) * 44, 8), ((256, 512, 1024, 24), (128,) * 9, 8),
                                                ((512, 1536, 1536, 100), (131, 613, 700), 1), ((512, 1536, 1536, 100), (131, 613, 700), 2),
-                                               ((512, 1536, 1536, 100), (131, 613, 700), 8)])
+                                               ((512, 1536, 1536, 100), (131, 613, 700), 8), ((40, 64, 72, 10), (1025,), 8),
+                                               ((40, 64, 72, 10), (300, 1300), 8), ((40, 64, 72, 10), (1041, 1025), 1)])
 def test_last_units_weight_gradients_beside_its_backward_part(dims, nodes, window):
     """Steps large enough for it (rows of the last unit, parameters) with two streams: one unit, two in one window and in two,
-    lone nodes with one window before and with other units of the window before.  The oracle's result, and the bits of
+    lone nodes with one window before and with other units of the window before, and small networks with a last node of more
+    rows than the BatchNorm kernels keep in registers.  The oracle's result, and the bits of
     one stream, in a second step from the first one's state too."""
     wl = dataclasses.replace(I.workload("mlp_mid_bn_bf16"), dims=dims, node_sizes=nodes)
     theta = I.make_params(wl, jitter=0.1)
