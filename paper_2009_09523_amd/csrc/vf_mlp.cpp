@@ -313,15 +313,18 @@ class Mlp final : public Model {
   // Beside each other the weight gradients fill what the input-gradient products, the BatchNorm passes and their launches
   // leave idle, and the update moves behind the backward part; it costs a pair of events a layer.  Steps, one after the
   // other | beside each other (us), of some 400 measured with one to six hidden layers:
-  //  * not with so many parameters that the weight gradients fill the chip by themselves: 2048-6144^2-1000 (57 M) 8 x 128
-  //    821 | 783, 32 x 128 1916 | 1966; 1024-6144^3-10 (82 M) 64 x 128 5079 | 5307; 2048-8192^6-1000 15507 | 15824.
+  //  * not with so many parameters that the weight gradients fill the chip by themselves: 2048-8192^6-1000 (361 M) 15507 |
+  //    15824; units of whole nodes of 128 rows reach that earlier the more rows they have: 1024-6144^3-10 (82 M) 8 x 128 1168 |
+  //    1092, 20 x 128 1924 | 1908 (1024-5120^4-1000, 89 M: 2400 | 2303), 24 x 128 2293 | 2416 (2562 | 2513), 32 x 128 2708 | 2908, 64
+  //    x 128 5079 | 5307, but 8192-8192-10 (67 M) 32 x 128 1429 | 1408; others do not: 16 x 100 1686 | 1591, 1024-5120^4-1000 48 x
+  //    100 4370 | 4088.
   //  * a node that goes alone: with enough of weight gradients to hide.  2 x 256 256-256^2-10 212 | 221, 1024-1536^4-1000
   //    357 | 350, 4 x 300 1024-2048^2-100 (2.0e9 rows x parameters) 368 | 375, 1024-6144-512-1000 (3.0e9) 430 | 405, 3 x 700
   //    784-2048-100 (1.3e9) 232 | 243, 1024-1536^2-100 (2.9e9) 344 | 328; alone in its step 1 x 1024 1024-768-10 127 | 136,
   //    784-256-1024^2-10 (1.6e9) 212 | 205, 1024^4-1000 225 | 220, but below 1024 rows 1 x 256 1024-4096^3-1000 461 | 476.
   //    From 1025 rows on always: the kernels that walk such a node's rows leave most of the chip idle (64-64-64-10 2 x 1025 397
   //    | 371, 64-128-10 3 x 4096 931 | 827, without BatchNorm 871 | 758, 784-300-100-10 1 x 1025 306 | 299; 64^5-10 1 x 1025
-  //    584 | 592, of 144 such steps the one that loses most).  Up to 128 Mi parameters, its products leave compute units idle:
+  //    584 | 592, of 144 such steps the one that loses most).  Of many parameters:
   //    1024-6144^3-10 1 x 1024 1175 | 1093, 2 x 1300 2918 | 2679, 3 x 513 1889 | 1851, but 2 x 4096 6983 | 7206; 2048-8192^2-1000
   //    (92 M) 1 x 1025 1590 | 1486, 2 x 4096 6002 | 5963, 1 x 1024 1152 | 1170.
   //  * a unit of several, from 1024 rows on (below, the products take all compute units and the update loses its company: 4 x
@@ -331,15 +334,15 @@ class Mlp final : public Model {
   //    182 | 163, 256^3-10 284 | 230) but for two units of the very smallest (64 x 64 64-256-100 264 | 275).
   bool side_early(const StepArgs& s) const override {
     const int last = s.V - 1, rows = s.sizes[last];
-    const bool alone = s.count[last] == 1 && rows > 128;
-    if (P_ > (int64_t)(alone ? 128 : 64) << 20) return false;
-    if (alone)
+    if (P_ > (int64_t)128 << 20) return false;
+    if (s.count[last] == 1 && rows > 128)
       return rows > 1024 || (s.V > 1 ? rows * P_ >= 2100000000 : rows == 1024 && rows * P_ >= 1400000000);
     if (rows < 1024) return false;
     bool whole = true;
     for (int n = 0; n < s.count[last] && whole; ++n) whole = s.rows_of(last)[n] == 128;
     for (const Layer& L : layers_) whole = whole && (!L.hidden || L.N % 128 == 0);
     if (!whole) return s.V == 1 || P_ >= 1 << 16;
+    if (rows > 2560 && P_ > (int64_t)64 << 20) return false;
     return P_ >= (s.V > 1 && layers_.size() < 6 ? 3 << 19 : 1 << 19);
   }
 
